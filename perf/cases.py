@@ -15,6 +15,7 @@ in its usual state.  Keys, values and queries are N(0,1), as in the package's wo
 """
 import math
 
+import numpy as np
 import torch
 
 from paper_2406_17808_amd import binding as B
@@ -156,17 +157,37 @@ def _step_inputs(c, gen):
     return tuple(_normal(c, gen, (b, h, d)) for h in (c["hq"], c["hkv"], c["hkv"]))
 
 
+def _inputs(c, cfg, seed):
+    """Everything that is drawn for a case, in a fixed order: the caches' contents, the tokens of the calls that
+    are made before the first timed one (per cache), and those of the timed ones."""
+    gen = torch.Generator(device=DEVICE)
+    gen.manual_seed(int(seed))
+    if c["kind"] == "prompt":
+        return {"tokens": _chunk_inputs(c, gen, c["context"])}
+    got = {"held": [_used_cache(c, cfg, gen) for _ in range(c["layers"])]}
+    # tokens to come: taken in turn, so that successive calls bring other tokens
+    if c["kind"] != "decode":
+        got["chunks"] = [_chunk_inputs(c, gen, c["chunk"]) for _ in range(4)]
+    if c["steps"]:
+        got["tokens"] = [_step_inputs(c, gen) for _ in range(max(32, c["steps"]))]
+    # the stream just before the first pass: ring heads away from slot 0 and off the tile grid
+    first = max(1, c["max_chunk"] - c["sinks"]) if c["max_chunk"] > 1 else 0
+    sizes = ([first] if first else []) + ([c["chunk"]] if c["kind"] == "chunk" else [])
+    got["before"] = [[_chunk_inputs(c, gen, n) for n in sizes] for _ in range(c["layers"])]
+    got["steps_before"] = 0 if c["kind"] == "chunk" else 37 if c["max_chunk"] == 1 else 5
+    return got
+
+
 def prepare(case, seed):
     c = dict(BASE, **case)
     cfg = _config(c)
-    gen = torch.Generator(device=DEVICE)
-    gen.manual_seed(int(seed))
+    got = _inputs(c, cfg, seed)
     state = {"case": c, "cfg": cfg, "at": 0}
     if c["kind"] == "prompt":
-        state["tokens"] = _chunk_inputs(c, gen, c["context"])
+        state["tokens"] = got["tokens"]
         state["out"] = torch.empty_like(state["tokens"][0])
         return state
-    held = [_used_cache(c, cfg, gen) for _ in range(c["layers"])]
+    held = got.pop("held")
     if c["layers"] > 1:
         state["owner"] = CascadeKVLayers(cfg, c["layers"], DEVICE, [h[0] for h in held])
         caches = state["owner"].layers
@@ -175,23 +196,17 @@ def prepare(case, seed):
     state["caches"] = caches
     torch.cuda.synchronize()
     del held
-    # tokens to come: taken in turn, so that successive calls bring other tokens
     if c["kind"] != "decode":
-        state["chunks"] = [_chunk_inputs(c, gen, c["chunk"]) for _ in range(4)]
+        state["chunks"] = got["chunks"]
         state["chunk_out"] = torch.empty_like(state["chunks"][0][0])
     if c["steps"]:
-        state["tokens"] = [_step_inputs(c, gen) for _ in range(max(32, c["steps"]))]
+        state["tokens"] = got["tokens"]
         state["step_outs"] = [[torch.empty_like(state["tokens"][0][0]) for _ in range(c["steps"])] for _ in caches]
-    # the stream just before the first pass: ring heads away from slot 0 and off the tile grid
-    first = max(1, c["max_chunk"] - c["sinks"]) if c["max_chunk"] > 1 else 0
-    for cache in caches:
-        if first:
-            cache.prefill_chunk(*_chunk_inputs(c, gen, first))
-        if c["kind"] == "chunk":
-            cache.prefill_chunk(*_chunk_inputs(c, gen, c["chunk"]))
-        else:
-            for i in range(37 if c["max_chunk"] == 1 else 5):
-                cache.decode_step(*state["tokens"][i % 32])
+    for cache, before in zip(caches, got["before"]):
+        for chunk in before:
+            cache.prefill_chunk(*chunk)
+        for i in range(got["steps_before"]):
+            cache.decode_step(*state["tokens"][i % 32])
     torch.cuda.synchronize()
     return state
 
@@ -250,6 +265,179 @@ def work(case):
         calls = [call(n, c["chunk"])] if c["kind"] != "decode" else []
         calls += [call(min(slots, n + c["chunk"]), 1)] * (c["steps"] * c["layers"])
     return {"bytes": float(sum(x[0] for x in calls)), "flops": float(sum(x[1] for x in calls))}
+
+
+class _Exact:
+    """The cache in 64 bits, for all sequences and KV heads at once: rows are columns of a token table, the sub-caches are
+    lists of row numbers [capacity, batch * KV heads] (all heads hold equally many items)."""
+
+    def __init__(self, c, held=None):
+        self.c = c
+        self.bh = c["batch"] * c["hkv"]
+        caps = [c["sinks"]] + [c["size"]] * c["cascades"]
+        self.rows = [np.zeros((max(x, 1), self.bh), np.int64) for x in caps]
+        self.cap, self.n, self.head, self.t = caps, [0] * len(caps), [0] * len(caps), 0
+        self.k, self.v, self.total = [], [], 0
+        self.mu = np.zeros((0, self.bh))
+        if held is not None:
+            init, (k, v, mu, _) = held
+            self._table(k.flatten(0, 1), v.flatten(0, 1), mu.flatten(0, 1).double().cpu().numpy().T)
+            counts, at = [int(x) for x in init.counts[:len(caps)]], 0
+            for part in [0] + list(range(len(caps) - 1, 0, -1)):
+                self.n[part] = counts[part]
+                self.rows[part][:counts[part]] = np.arange(at, at + counts[part])[:, None]
+                at += counts[part]
+            self.t = int(init.t)
+
+    def _table(self, k, v, mu):      # [batch * KV heads, rows, d]
+        self.k.append(k)
+        self.v.append(v)
+        if len(self.k) > 8:
+            self.k, self.v = [torch.cat(self.k, 1)], [torch.cat(self.v, 1)]
+        self.mu = np.concatenate([self.mu, mu])
+        self.total += k.shape[1]
+
+    def order(self):
+        """Rows in cache order [count, batch * KV heads]: sinks, last cascade oldest to newest, ..., first cascade."""
+        got = []
+        for part in [0] + list(range(len(self.cap) - 1, 0, -1)):
+            at = (self.head[part] + np.arange(self.n[part])) % max(self.cap[part], 1)
+            got.append(self.rows[part][at])
+        return np.concatenate(got)
+
+    def insert(self, row):
+        """Alg. 2 for one token (row: its number in the table)."""
+        x = np.full(self.bh, row)
+        if self.n[0] < self.cap[0]:
+            self.rows[0][self.n[0]] = x
+            self.n[0] += 1
+            return
+        t = self.t
+        self.t += 1
+        for i in range(1, len(self.cap)):
+            rows, cap = self.rows[i], self.cap[i]
+            if self.n[i] < cap:
+                rows[(self.head[i] + self.n[i]) % cap] = x
+                self.n[i] += 1
+                return
+            newest = (self.head[i] + cap - 1) % cap
+            if t % (1 << (i - 1)):
+                there = rows[newest]
+                rows[newest] = np.where(self.mu[x, np.arange(self.bh)] > self.mu[there, np.arange(self.bh)], x, there)
+                return
+            oldest = rows[self.head[i]].copy()
+            rows[self.head[i]] = x
+            self.head[i] = (self.head[i] + 1) % cap
+            x = oldest
+
+    def _rotated(self, x, first):      # [n, ..., d], the n rows at positions first, first + 1, ...
+        d = self.c["d"]
+        theta = self.c["base"] ** (-2.0 * torch.arange(d // 2, device=DEVICE, dtype=torch.float64) / d)
+        a = (first + torch.arange(x.shape[0], device=DEVICE, dtype=torch.float64))[:, None] * theta
+        a = a.reshape((x.shape[0],) + (1,) * (x.dim() - 2) + (d // 2,))
+        lo, hi = x[..., :d // 2], x[..., d // 2:]
+        return torch.cat([lo * torch.cos(a) - hi * torch.sin(a), hi * torch.cos(a) + lo * torch.sin(a)], -1)
+
+    def chunk(self, q, k, v, want):
+        """One call with n tokens, q [batch, n, hq, d]: outputs [batch, n, hq, d] (if wanted), scores and insertions."""
+        c = self.c
+        n, g, d, beta = q.shape[1], c["hq"] // c["hkv"], c["d"], float(np.float32(c["beta"]))
+        order = self.order()
+        m = len(order)
+        old_k, old_v = (torch.cat(x, 1) if x else None for x in (self.k, self.v))
+        if m:
+            self.k, self.v = [old_k], [old_v]
+        at = torch.from_numpy(order).to(DEVICE)
+        out = torch.empty(q.shape, device=DEVICE, dtype=torch.float64) if want else None
+        weight = (1.0 - beta) * beta ** torch.arange(n - 1, -1, -1, device=DEVICE, dtype=torch.float64)
+        delta = torch.empty((m + n, self.bh), device=DEVICE, dtype=torch.float64)
+        rows = max(1, min(n, (1 << 26) // (g * (m + n))))
+        for s in range(self.bh):
+            b, h = divmod(s, c["hkv"])
+            heads = slice(h * g, (h + 1) * g)
+            keys, vals = k[b, :, h].double(), v[b, :, h].double()
+            if m:
+                keys, vals = torch.cat([old_k[s][at[:, s]].double(), keys]), torch.cat([old_v[s][at[:, s]].double(), vals])
+            keys = self._rotated(keys, 0)
+            got = torch.zeros((g, m + n), device=DEVICE, dtype=torch.float64)
+            for a in range(0, n, rows):
+                e = min(a + rows, n)
+                x = self._rotated(q[b, a:e, heads].double(), m + a).transpose(0, 1).reshape(g * (e - a), d)
+                p = (x @ keys[:m + e].T).mul_(1.0 / math.sqrt(d)).reshape(g, e - a, m + e)
+                p[:, :, m + a:] += torch.full((e - a, e - a), -math.inf, device=DEVICE, dtype=torch.float64).triu(1)
+                p -= p.amax(-1, keepdim=True)
+                p.exp_()
+                p /= p.sum(-1, keepdim=True)
+                for i in range(g):
+                    got[i, :m + e] += weight[a:e] @ p[i]
+                if want:
+                    o = p.reshape(g * (e - a), m + e) @ vals[:m + e]
+                    out[b, a:e, heads] = o.reshape(g, e - a, d).transpose(0, 1)
+            delta[:, s] = got.mean(0) if c["mean"] else got.amax(0)
+        if c["homogeneous"]:
+            each = delta.reshape(m + n, c["batch"], c["hkv"])
+            one = each.mean(2, keepdim=True) if c["mean"] else each.amax(2, keepdim=True)
+            delta = one.expand_as(each).reshape(m + n, self.bh)
+        delta = delta.cpu().numpy()
+        heads = np.arange(self.bh)[None]
+        self.mu[order, heads] = self.mu[order, heads] * beta ** n + delta[:m]
+        first = self.total
+        self._table(k.transpose(1, 2).flatten(0, 1), v.transpose(1, 2).flatten(0, 1), delta[m:])
+        for i in range(n):
+            self.insert(first + i)
+        self._drop_unused()
+        return out
+
+    def _drop_unused(self):
+        """Rows that no head holds any longer leave the table when it has grown to twice what is held."""
+        if self.total < 2 * (sum(self.n) + 4096):
+            return
+        keep = np.unique(self.order())
+        number = np.zeros(self.total, np.int64)
+        number[keep] = np.arange(len(keep))
+        at = torch.from_numpy(keep).to(DEVICE)
+        self.k, self.v = [torch.cat(self.k, 1)[:, at]], [torch.cat(self.v, 1)[:, at]]
+        self.mu, self.total = self.mu[keep], len(keep)
+        for part, rows in enumerate(self.rows):
+            held = (self.head[part] + np.arange(self.n[part])) % max(self.cap[part], 1)
+            rows[held] = number[rows[held]]
+
+    def scores(self):
+        return self.mu[self.order(), np.arange(self.bh)[None]].T.reshape(self.c["batch"], self.c["hkv"], -1)
+
+
+def exact(case, seed):
+    """The first pass in 64 bits.  None where the scores are approximations by definition (single pass), for the
+    host's view of which token sits where (whole numbers), and for the largest batches, which take minutes."""
+    c = dict(BASE, **case)
+    calls = c["layers"] * (40 if c["kind"] == "decode" and c["max_chunk"] == 1 else 10)
+    if c["single_pass"] or c["batch"] * c["hkv"] * (c["sinks"] + c["cascades"] * c["size"]) * calls > 1e8:
+        return None
+    cfg = _config(c)
+    got = _inputs(c, cfg, seed)
+    if c["kind"] == "prompt":
+        x, outs = _Exact(c), []
+        for a in range(0, c["context"], c["chunk"]):
+            outs.append(x.chunk(*(y[:, a:a + c["chunk"]] for y in got["tokens"]), True))
+        return torch.cat(outs, 1)
+    layers = []
+    for held, before in zip(got["held"], got["before"]):
+        x = _Exact(c, held)
+        for chunk in before:
+            x.chunk(*chunk, False)
+        for i in range(got["steps_before"]):
+            x.chunk(*(y[:, None] for y in got["tokens"][i % 32]), False)
+        layers.append(x)
+    outs = []
+    if c["kind"] != "decode":
+        outs.append(layers[0].chunk(*got["chunks"][0], True))
+    for i in range(c["steps"]):
+        outs += [x.chunk(*(y[:, None] for y in got["tokens"][i]), True)[:, 0] for x in layers]
+    if c["kind"] == "turn":
+        mu = layers[0].scores()
+        full = c["sinks"] + c["cascades"] * c["size"]
+        outs += [None, mu if mu.shape[2] == full else None, None]
+    return outs
 
 
 def tolerance(case):
