@@ -237,16 +237,16 @@ def decode_bench(args, torch, B):
     # algorithmic bytes of a step: every cached K and V row once, scores read and written once
     bytes_step = BH * slots * (2 * d * 2 + 8)
     qk_ms, qk_n = prof["decode_qk"]
-    k_bytes = BH * slots * d * 2
+    kv_bytes = BH * slots * d * 4
     res = {
         "decode_step_us": dt / steps * 1e6, "decode_steps": steps, "decode_tokens_per_s": wl.batch * steps / dt,
         "decode_hbm_frac": bytes_step / (dt / steps) / HBM_PEAK,
         "decode_kernel_us": {k: v[0] / max(v[1], 1) * 1e3 for k, v in prof2.items() if v[1]},
-        "roofline_decode": {"bound": "hbm", "kernel": "decode_qk_stream_kernel", "achieved": k_bytes / (qk_ms / 1e3 / max(qk_n, 1)) / 1e9,
+        "roofline_decode": {"bound": "hbm", "kernel": "decode_attend_kernel", "achieved": kv_bytes / (qk_ms / 1e3 / max(qk_n, 1)) / 1e9,
                             "peak": HBM_PEAK / 1e9, "unit": "GB/s",
-                            "frac": k_bytes / (qk_ms / 1e3 / max(qk_n, 1)) / HBM_PEAK,
-                            "traffic": stored_traffic("decode_qk_stream_kernel_decode_b32_hbm_traffic.json"),
-                            "traffic_source": "profiles/decode_qk_stream_kernel_decode_b32_hbm_traffic.json (rocprofv3 --pmc runs, not this run)"},
+                            "frac": kv_bytes / (qk_ms / 1e3 / max(qk_n, 1)) / HBM_PEAK,
+                            "traffic": stored_traffic("decode_attend_kernel_decode_b32_hbm_traffic.json"),
+                            "traffic_source": "profiles/decode_attend_kernel_decode_b32_hbm_traffic.json (rocprofv3 --pmc runs, not this run)"},
     }
     cache.close()
     return res
@@ -311,18 +311,14 @@ def main():
     if not args.no_decode:
         line.update(decode_bench(args, torch, B))
         if ceilings is not None:
-            # the dominant decode kernel writes one byte of logits for every sixteen of keys it reads: next to
-            # the plain streaming reads, the ceiling of that very mix (rate of the bytes read, as `achieved` is
-            # the rate of the key bytes)
+            # the dominant decode kernel writes one byte of logits for every 32 of keys and values it reads: next to
+            # the plain streaming reads, the ceiling with one byte stored for every sixteen read (rate of the bytes
+            # read, as `achieved` is the rate of the K and V bytes)
             rd = max(ceilings["hbm_read_gb_s"], ceilings["hbm_read_regions_gb_s"])
             line["roofline_decode"]["frac_of_measured_read"] = line["roofline_decode"]["achieved"] / rd
             line["roofline_decode"]["frac_of_measured_read_with_stores"] = (line["roofline_decode"]["achieved"]
                                                                             / ceilings["hbm_read_with_1_16_stores_gb_s"])
             line["decode_frac_of_measured_read"] = line["decode_hbm_frac"] * HBM_PEAK / 1e9 / rd
-            # the whole step against its two passes as traffic alone (a read with stores, then a plain read,
-            # alternating): bytes of K and V read per second over the measured rate of that pair
-            kv_rate = 2 * line["roofline_decode"]["achieved"] * (line["decode_kernel_us"]["decode_qk"] / line["decode_step_us"])
-            line["decode_frac_of_measured_two_pass_read"] = kv_rate / ceilings["hbm_two_pass_read_gb_s"]
     print(json.dumps(line))
 
 

@@ -265,9 +265,9 @@ enum {
     CASCADE_K_ATTENTION = 1,   /* chunk attention (QK^T, softmax, PV) */
     CASCADE_K_SCORES = 2,      /* exact EMA score sums */
     CASCADE_K_UPDATE = 3,      /* cascade plan + row moves */
-    CASCADE_K_DECODE_QK = 4,
-    CASCADE_K_DECODE_PV = 5,
-    CASCADE_K_DECODE_FINISH = 6,
+    CASCADE_K_DECODE_QK = 4,   /* decode: the pass over K and V */
+    CASCADE_K_DECODE_PV = 5,   /* decode: the scores' EMA step, where it is a launch of its own (homogeneous heads, keep_update_scores) */
+    CASCADE_K_DECODE_FINISH = 6, /* decode: outputs, EMA step (otherwise), insertion */
     CASCADE_K_FAMILIES = 7
 };
 typedef struct cascade_profile {

@@ -5,6 +5,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -69,11 +70,13 @@ static int fail(cascade_ctx* ctx, int code, const std::string& msg)
 
 static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
-static int decode_splits(const Geom& g)
+static int decode_splits(const Geom& g, bool f32)
 {
-    // enough workgroups to fill 256 compute units several times over, at least 256 rows each
+    // the most a step may be split into: enough workgroups to fill 256 compute units several times over, at
+    // least 128 rows (a tile per wave of the MFMA kernel; fp32: 256) each; decode_split_count takes what suits the
+    // rows cached
     int s = (2048 + g.B * g.Hkv - 1) / (g.B * g.Hkv);
-    const int max_s = (g.slots + 255) / 256;
+    const int max_s = f32 ? (g.slots + 255) / 256 : (g.slots + 127) / 128;
     if (s > max_s) s = max_s;
     if (s < 1) s = 1;
     return s;
@@ -92,7 +95,7 @@ static WorkspaceBytes carve(const cascade_config* c, const Geom& g, char* state_
     const size_t BH = (size_t)g.B * g.Hkv, BHq = (size_t)g.B * g.Hq;
     const size_t mc = (size_t)c->max_chunk;
     const int n_qvar_max = 2 * g.N + 2;
-    const int splits = decode_splits(g);
+    const int splits = decode_splits(g, c->dtype == CASCADE_F32);
     const int rope_rows = 2 * g.slots + c->max_chunk + 1;
     size_t off = 0;
     char* base = state_base;
@@ -112,6 +115,9 @@ static WorkspaceBytes carve(const cascade_config* c, const Geom& g, char* state_
     base = shared_base;
     b.rope = (float2*)take((size_t)rope_rows * (g.d / 2) * 8);
     b.wrow = (float*)take(mc * 4);
+    // prefill scratch and decode scratch share their memory: a call needs the one or the other, and a decode
+    // step invalidates the packed tiles anyway
+    const size_t scratch0 = off;
     b.Qr = take((size_t)n_qvar_max * BHq * mc * g.d * elem);
     b.Krc = take(BH * mc * g.d * elem);
     b.Vch = take(BH * mc * g.d * elem);
@@ -120,6 +126,14 @@ static WorkspaceBytes carve(const cascade_config* c, const Geom& g, char* state_
     const int vt_tiles = mfma ? (g.slots + (int)mc) / 64 + kMaxSegments : 0;
     b.Kt = take(BH * (size_t)vt_tiles * 64 * g.d * elem);
     b.Vt = take(BH * (size_t)vt_tiles * 64 * g.d * elem);
+    const size_t prefill_end = off;
+    off = scratch0;
+    if (decode_supported(g)) {
+        b.logits = (float*)take(BH * (size_t)decode_max_tiles(g) * 32 * (size_t)decode_logit_heads(g) * 4);
+        b.part = (float*)take(BHq * (size_t)(splits + 1) * 2 * 4);
+        b.opart = (float*)take(BHq * (size_t)splits * g.d * 4);
+    }
+    off = std::max(off, prefill_end);
     b.knorm2 = (float*)take(BH * (size_t)vt_tiles * 4);
     b.lse = (float*)take(BHq * mc * 4);
     b.mu_chunk = (float*)take(BH * mc * 4);
@@ -134,9 +148,6 @@ static WorkspaceBytes carve(const cascade_config* c, const Geom& g, char* state_
     b.winners = (int32_t*)take(BH * g.N * (mc + 1) * 4);
     const int move_stage_rows = (g.N + 1) * ((int)mc + 1);    // every cascade and the sinks: at most max_chunk + 1 entries each
     b.move_stage = take(g.d % 16 == 0 ? BH * (size_t)move_stage_rows * (2 * g.d * elem + 8) : 0);
-    b.logits = (float*)take(BH * ((size_t)g.slots + 1) * (size_t)(g.G <= 8 ? decode_logit_heads(g) : g.G) * 4);
-    b.part = (float*)take(BHq * splits * 2 * 4);
-    b.opart = (float*)take(BHq * splits * g.d * 4);
     bytes.shared = off;
     b.rope_rows = rope_rows;
     b.dec_splits = splits;
@@ -224,8 +235,6 @@ static int init_context(const char* who, const cascade_config* cfg, const Geom& 
     if (const char* e = getenv("CASCADE_KV_ATTN_SPLITS")) ctx->buf.opt_attn_splits = atoi(e);
     ctx->buf.opt_score_narrow = -1;
     if (const char* e = getenv("CASCADE_KV_SCORE_NARROW")) ctx->buf.opt_score_narrow = e[0] == '1' ? 1 : 0;
-    ctx->buf.opt_decode_qk_direct = getenv("CASCADE_KV_DECODE_QK_DIRECT") != nullptr;
-    ctx->buf.opt_decode_pv_valu = getenv("CASCADE_KV_DECODE_PV_VALU") != nullptr;
     ctx->buf.opt_update_staged = getenv("CASCADE_KV_UPDATE_STAGED") != nullptr;
 
     // rows of a chunk whose EMA weight beta^k has not dropped below the cut
@@ -561,25 +570,31 @@ extern "C" int cascade_decode_step(cascade_ctx* ctx, const void* dev_q, const vo
     build_segments(g, ctx->st, false, 1, sl);
     ctx->packed_valid = false;   // the step writes cache rows the packed copies of the prefill path do not follow
     ctx->last_single_pass = false;
+    const int n_splits = decode_split_count(g, ctx->buf, decode_tiles(sl));
     {
         Timed t0(ctx, CASCADE_K_DECODE_QK, s);
-        launch_decode_qk(g, ctx->dtype, ctx->buf, sl, dev_q, dev_k, s);
+        launch_decode_attend(g, ctx->dtype, ctx->buf, sl, n_splits, dev_q, dev_k, s);
     }
-    {
-        Timed t1(ctx, CASCADE_K_DECODE_PV, s);
-        launch_decode_pv(g, ctx->dtype, ctx->buf, sl, s);
-        // homogeneous heads: the cached scores are shared here, the new token's inside decode_finish
-        if (g.head_policy == CASCADE_HEADS_HOMOGENEOUS && g.Hkv > 1) launch_share_scores(g, ctx->buf, 0, ctx->max_chunk, s);
-    }
-    // the snapshot holds the cached scores after this step's EMA update and before the insertion
-    int rc = snapshot_scores(ctx, 1, s);
-    if (rc) return rc;
     UpdatePlan pl;
+    DecodeInsert ins;
     HostState st_next = ctx->st;
     plan_update(g, st_next, 1, pl);
+    plan_insert(g, pl, ins);
+    // The scores take their EMA step in the launch that inserts the token, unless something comes in between:
+    // homogeneous heads share the cached scores (the new token's are shared inside decode_finish), and the
+    // diagnostic snapshot holds the cached scores after the step and before the insertion.
+    const bool share = g.head_policy == CASCADE_HEADS_HOMOGENEOUS && g.Hkv > 1;
+    const bool apart = share || ctx->cfg.keep_update_scores;
+    if (apart) {
+        Timed t1(ctx, CASCADE_K_DECODE_PV, s);
+        launch_decode_finish(g, ctx->dtype, ctx->buf, sl, ins, n_splits, true, false, ctx->max_chunk, dev_k, dev_v, dev_out, s);
+        if (share) launch_share_scores(g, ctx->buf, 0, ctx->max_chunk, s);
+    }
+    int rc = snapshot_scores(ctx, 1, s);
+    if (rc) return rc;
     {
         Timed t2(ctx, CASCADE_K_DECODE_FINISH, s);
-        launch_decode_finish(g, ctx->dtype, ctx->buf, sl, pl, ctx->max_chunk, dev_k, dev_v, dev_out, s);
+        launch_decode_finish(g, ctx->dtype, ctx->buf, sl, ins, n_splits, !apart, true, ctx->max_chunk, dev_k, dev_v, dev_out, s);
     }
     rc = hip_check(ctx, hipGetLastError(), "cascade_decode_step");
     if (rc != CASCADE_OK) { ctx->poisoned = true; return rc; }

@@ -850,7 +850,7 @@ void launch_attn_stream(const Geom& g, const DevBuffers& b, const SegList& sl, i
     }
 #ifdef CASCADE_KV_ATTN_PHASE_TIMING   // development builds only: per-phase cycle counts of one workgroup
     if (g.d == 128) {
-        long long* dbg = (long long*)b.logits;
+        long long* dbg = (long long*)b.move_stage;
         if (single_pass)
             hipLaunchKernelGGL((attn_stream_kernel<128, true, false, true>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q, (const float4*)b.rope_t, b.rope_rows, qscale,
                                (const bf16_t*)b.Kt, (const bf16_t*)b.Vt, (bf16_t*)out, b.lse, dbg, 1, (float*)nullptr, (float*)nullptr, b.knorm2, so, sp);

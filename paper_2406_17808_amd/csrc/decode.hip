@@ -1,92 +1,124 @@
 // Decode step (Eq. 2): one query per sequence against the whole cache plus its own key.
-// The cache is streamed once from HBM: K by decode_qk (logits), V by decode_pv (outputs and
-// EMA scores); the logits of a step (16 bytes per cached row at 4 query heads per KV head)
-// pass through a scratch array because the EMA update needs exact probabilities.
-#include <stdlib.h>
-
+//
+// Two launches.  decode_attend streams K and V once: every split of the cached rows leaves its
+// logits, its maximum, its sum of exponentials and its unnormalised output.  decode_finish
+// combines the splits, takes the EMA step of every cached row's score (Section 3.1; it needs the
+// final normaliser, hence the logits, 16 bytes per cached row at 4 query heads per KV head, that
+// pass through a scratch array) and inserts the token.  Logits are base-2 exponents: the queries
+// carry the softmax scale and log2(e).
 #include "async_copy.h"
 #include "launch.h"
-#include "small_update.h"
+#include "row_ops.h"
 
 namespace ckv {
 
 constexpr int kDecThreads = 256;
-constexpr int kLanesPerRow = 16;                            // lanes that share one row in the VALU kernels
-constexpr int kRowGroups = kDecThreads / kLanesPerRow;      // 16 row groups per workgroup
+constexpr int kDecWaves = kDecThreads / 64;
+constexpr int kDecRows = 32;         // cached rows per tile
 constexpr int kMaxG = 8;
+constexpr float kLog2e = 1.4426950408889634f;
 
-// Logits of a step: [B][Hkv][n_cached + 1][MAXG] floats, MAXG = group size rounded up to 1, 2, 4
-// or 8 (decode_logit_heads): the heads of a group are adjacent, so the kernel that computes them
-// stores, and the kernel that consumes them loads, whole 64-byte-aligned runs of a row block.
-__device__ inline size_t logit_index(const Geom& g, int maxg, size_t lrows, int b, int hk, int row, int hh)
+// The cached rows are cut into tiles of 32 rows, segment by segment (the last tile of a segment
+// may be short).  Logits of a step: [B*Hkv][tile][32 * MAXG] floats, MAXG = group size rounded up
+// to 1, 2, 4 or 8 (decode_logit_heads).  Row 16 gi + 4 c + j of a tile and head n sit at
+// ((gi * MAXG + n) * 4 + c) * 4 + j, the order in which the accumulators of the QK product hold them:
+// four rows of one head are 16 adjacent bytes for the kernel that writes them and the one that reads them.
+template <int MAXG> __device__ inline int logit_index(int row, int n)
 {
-    return ((((size_t)b * g.Hkv + hk) * lrows + row) * maxg) + hh;
+    return (((row >> 4) * MAXG + n) * 4 + ((row >> 2) & 3)) * 4 + (row & 3);
 }
 
-template <typename T, int EPL> struct VecLoad;
-template <> struct VecLoad<bf16_t, 8> {
-    __device__ static void load(const bf16_t* p, float* o)
+__device__ inline int tiles_of(int len) { return (len + kDecRows - 1) / kDecRows; }
+
+// Walks over the tiles of the segment list.
+struct TileWalk {
+    int tile, si, tile0;               // tile; its segment and that segment's first tile
+    int start, nvalid;                 // first slot and rows of the tile
+    __device__ void seek(const SegList& sl)      // segments are only ever left forwards
     {
-        const uint4 u = *reinterpret_cast<const uint4*>(p);
-        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { o[2 * i] = __uint_as_float(w[i] << 16); o[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u); }
+        while (si < sl.n && tile >= tile0 + tiles_of(sl.s[si].len)) { tile0 += tiles_of(sl.s[si].len); ++si; }
+        if (si < sl.n) {
+            const int r0 = (tile - tile0) * kDecRows;
+            start = sl.s[si].start + r0;
+            nvalid = min(kDecRows, sl.s[si].len - r0);
+        }
     }
-};
-template <> struct VecLoad<bf16_t, 4> {
-    __device__ static void load(const bf16_t* p, float* o)
-    {
-        const uint2 u = *reinterpret_cast<const uint2*>(p);
-        const uint32_t w[2] = {u.x, u.y};
-#pragma unroll
-        for (int i = 0; i < 2; ++i) { o[2 * i] = __uint_as_float(w[i] << 16); o[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u); }
-    }
-};
-template <> struct VecLoad<float, 8> {
-    __device__ static void load(const float* p, float* o)
-    {
-        const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
-        o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w; o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
-    }
-};
-template <> struct VecLoad<float, 4> {
-    __device__ static void load(const float* p, float* o)
-    {
-        const float4 a = *reinterpret_cast<const float4*>(p);
-        o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
-    }
+    __device__ void begin(const SegList& sl, int first) { tile = first; si = 0; tile0 = 0; start = 0; nvalid = 0; seek(sl); }
+    __device__ void advance(const SegList& sl, int by) { tile += by; seek(sl); }
 };
 
-// (max, sum of exp) pairs combine associatively
+// (max, sum of exp2) pairs combine associatively
 __device__ inline void ml_merge(float& m, float& l, float m2, float l2)
 {
     if (l2 > 0.f) {
         const float mn = fmaxf(m, m2);
-        l = l * __expf(m - mn) + l2 * __expf(m2 - mn);
+        l = l * __builtin_amdgcn_exp2f(m - mn) + l2 * __builtin_amdgcn_exp2f(m2 - mn);
         m = mn;
     }
 }
 
-// One rotated, scaled element of the query: the stored keys are rotated to their slot index,
-// so the query turns by (own index) - (cache index - slot index), one angle per segment.
-template <typename T>
-__device__ inline float q_rot_elem(const T* __restrict__ qh, const float2* __restrict__ rope, int rot, int half_d,
-                                   int e, float scale)
+// What sums relative to maximum m are multiplied by when the maximum becomes mn; the maximum exponents are taken
+// against.  (Logits that overflowed to -infinity are keys of probability zero, also where nothing else was seen yet.)
+__device__ inline float rescale_of(float m, float mn) { return m == mn ? 1.f : __builtin_amdgcn_exp2f(m - mn); }
+__device__ inline float finite_max(float m) { return m == -INFINITY ? 0.f : m; }
+
+// The step's partial results: part[(b, query head)][split] = (maximum, sum), one more entry for the token's own
+// key (its logit, 1); opart[(b, query head)][split][d] unnormalised.
+__device__ inline float* part_of(float* part, size_t head, int n_splits, int split) { return part + (head * (n_splits + 1) + split) * 2; }
+
+// The own key: <R(n) q, R(n) k> = <q, k>.  One wave per head of the group.
+template <typename T, int D>
+__device__ inline void own_logits(const Geom& g, int b, int hk, const T* __restrict__ q, const T* __restrict__ k_new, float qscale,
+                                  float* __restrict__ part, int n_splits)
 {
-    const int pe = e < half_d ? e : e - half_d;
-    const float2 cs = rope[(size_t)rot * half_d + pe];
-    const float a = Elem<T>::load(qh + pe), c = Elem<T>::load(qh + pe + half_d);
-    return (e < half_d ? a * cs.x - c * cs.y : c * cs.x + a * cs.y) * scale;
+    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const T* kn = k_new + ((size_t)b * g.Hkv + hk) * D;
+    for (int hh = wave; hh < g.G; hh += kDecWaves) {
+        const size_t head = (size_t)b * g.Hq + hk * g.G + hh;
+        float acc = 0.f;
+#pragma unroll
+        for (int e = 0; e < D; e += 64) acc += Elem<T>::load(q + head * D + e + l) * Elem<T>::load(kn + e + l);
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) acc += __shfl_xor(acc, w, 64);
+        if (l == 0) {
+            float* p = part_of(part, head, n_splits, n_splits);
+            p[0] = acc * qscale;
+            p[1] = 1.f;
+        }
+    }
 }
 
-// ------------------------------------------------------------------ QK, bf16: MFMA 16x16x32
+// ------------------------------------------------------------------ attend, bf16: MFMA fed from LDS
 //
 // v_mfma_f32_16x16x32_bf16: for lane l, A holds row l%16, B column l%16, both with the 8
-// contraction indices 8*(l/16)..+7; D holds column l%16, rows 4*(l/16)..+3.  Rows are 16 keys,
-// columns the query heads of the group (padded with zeros to 16), the contraction runs over the
-// head dimension.  Which element of the head dimension a contraction index means is free as
-// long as A and B agree: lane group c = l/16 takes elements [c*D/4 + 8*ks, +8) in step ks, so a
-// lane reads D/2 contiguous bytes of a key row and four lanes cover the row.
+// contraction indices 8*(l/16)..+7; D holds column l%16, rows 4*(l/16)..+3.  S = K Q^T: rows are 16
+// keys, columns the query heads of the group (padded with zeros to 16).  A lane then holds, for head
+// n = l%16, the keys 4c + {0..3} and 16 + 4c + {0..3} of the tile (c = l/16), and that is taken as the
+// contraction order of O^T = V^T P^T: the exponentials of the accumulators ARE the B operand, no
+// probability crosses a lane, and the A operand (8 rows of one column of V) is two transposing reads
+// (ds_read_b64_tr_b16) of rows 4c .. 4c+3 and 16 + 4c .. +3.
+//
+// Every wave streams its own tiles through a private ring of four LDS stages (K and V of two tiles)
+// filled by asynchronous copies, so ~96 KB per CU stay in flight whatever the waves compute, and no
+// workgroup barrier is needed inside the loop.  A wave keeps its own running maximum per head, raised
+// only when a tile exceeds it by 2^8 (most tiles then leave the accumulators alone).
+//
+// Bound by memory where the cache is large, by the latency of one tile where it is small.  Measured with
+// separate passes over K and V (three launches a step, one workgroup merging 33 splits) against this
+// kernel and decode_finish, us a step: 8K slots 59.1 -> 20.1, 4K slots 40.6 -> 18.0 a layer, 8 sequences of 16K slots
+// 254.7 -> 111.2.
+//
+// The piece permutations (16-byte pieces of a staged row): the 16 rows of a K fragment read, and the
+// 8 rows one half of a wave reads in a transposing read, fall into different banks.
+template <int D> struct DecSwizzle;
+template <> struct DecSwizzle<128> {
+    __device__ static int k(int row) { return row & 15; }
+    __device__ static int v(int row) { return 2 * (row & 7); }
+};
+template <> struct DecSwizzle<64> {
+    __device__ static int k(int row) { return (row >> 1) & 7; }
+    __device__ static int v(int row) { return 2 * ((row >> 1) & 3); }
+};
 
 typedef __attribute__((ext_vector_type(8))) __bf16 dbf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float df32x4_t;
@@ -104,990 +136,682 @@ __device__ inline uint32_t dec_pack_bf16(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, b2));
 }
 
-constexpr int kQkRowsPerWave = 64;   // four 16-key MFMA groups in flight per wave iteration
-
-template <int D, int MAXG>
-__global__ __launch_bounds__(kDecThreads) void decode_qk_mfma_kernel(
-    Geom g, SegList sl, int per_split, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k_new,
-    const bf16_t* __restrict__ Kr, const float2* __restrict__ rope, float* __restrict__ logits,
-    float* __restrict__ part, int n_splits)
-{
-    constexpr int KS = D / 32;            // MFMA steps over the head dimension
-    constexpr int NG = kQkRowsPerWave / 16;
-    __shared__ float red_m[kDecThreads / 64][16], red_l[kDecThreads / 64][16];
-    __shared__ float stage[kDecThreads / 64][kQkRowsPerWave * MAXG];   // a wave's logits of one iteration, [row][head]
-    const int split = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
-    const int bh = b * g.Hkv + hk;
-    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, n = l & 15, c = l >> 4;
-    const int ncached = sl.n_cached;
-    const int j0 = split * per_split, j1 = min(ncached, j0 + per_split);
-    const size_t lrows = (size_t)ncached + 1;
-    const bool head_ok = n < g.G;
-    const bf16_t* qh = q + ((size_t)b * g.Hq + hk * g.G + (head_ok ? n : 0)) * D;
-    float* lbase = logits + logit_index(g, MAXG, lrows, b, hk, 0, 0);
-    float m = -INFINITY, lsum = 0.f;
-
-    int seg_first = 0;                    // index of the segment's first row in the concatenation
-    for (int si = 0; si < sl.n; ++si) {
-        const Seg sg = sl.s[si];
-        const int lo = max(j0, seg_first), hi = min(j1, seg_first + sg.len);
-        if (lo < hi) {
-            // B operand: this segment's rotation of the group's queries, scaled, as bf16
-            DFrag qf[KS];
-            const int rot = sl.qrot0[sg.qvar];
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    const int e = ks * 32 + c * 8 + 2 * x;
-                    const float a0 = head_ok ? q_rot_elem<bf16_t>(qh, rope, rot, D / 2, e, g.scale) : 0.f;
-                    const float a1 = head_ok ? q_rot_elem<bf16_t>(qh, rope, rot, D / 2, e + 1, g.scale) : 0.f;
-                    qf[ks].u[x] = dec_pack_bf16(a0, a1);
-                }
-            // row index = index in the concatenation of the segments
-            const bf16_t* kseg = Kr + ((ptrdiff_t)bh * g.slots + sg.start - seg_first) * D;
-            for (int r0 = lo + wave * kQkRowsPerWave; r0 < hi; r0 += (kDecThreads / 64) * kQkRowsPerWave) {
-                DFrag kf[NG][KS];
-#pragma unroll
-                for (int gi = 0; gi < NG; ++gi) {
-                    const int row = min(r0 + gi * 16 + n, hi - 1);      // rows past the end repeat the last one
-                    const bf16_t* kp = kseg + (size_t)row * D + c * 8;
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) kf[gi][ks].u = *reinterpret_cast<const du32x4_t*>(kp + ks * 32);
-                }
-#pragma unroll
-                for (int gi = 0; gi < NG; ++gi) {
-                    df32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks)
-                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[gi][ks].v, qf[ks].v, acc, 0, 0, 0);
-                    // this lane: head n, keys r0 + 16*gi + 4*c + {0..3}
-                    const int rbase = r0 + gi * 16 + 4 * c;
-                    if (n < MAXG) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) stage[wave][(gi * 16 + 4 * c + j) * MAXG + n] = acc[j];
-                    }
-                    if (head_ok) {
-                        // one rescaling per four logits: the running maximum rarely moves
-                        float mx = m;
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (rbase + j < hi) mx = fmaxf(mx, acc[j]);
-                        if (mx > m) {   // (also keeps -inf - -inf out of the arithmetic)
-                            lsum *= __expf(m - mx);
-                            m = mx;
-                        }
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (rbase + j < hi) lsum += __expf(acc[j] - m);
-                    }
-                }
-                // the wave's 64 x MAXG logits leave as contiguous 256-byte stores (LDS accesses of one
-                // wave are ordered; no other wave touches this stage)
-#pragma unroll
-                for (int i = 0; i < MAXG; ++i) {
-                    const int idx = l + 64 * i;
-                    if (r0 + idx / MAXG < hi) lbase[(size_t)r0 * MAXG + idx] = stage[wave][idx];
-                }
-            }
-        }
-        seg_first += sg.len;
-    }
-    if (split == 0 && wave == 0) {
-        // own key: <R(n) q, R(n) k> = <q, k>; lanes c = 0 of the valid heads take it
-        if (head_ok && c == 0) {
-            const bf16_t* kn = k_new + ((size_t)b * g.Hkv + hk) * D;
-            float acc = 0.f;
-            for (int e = 0; e < D; ++e) acc += bf16_to_f32(qh[e]) * bf16_to_f32(kn[e]);
-            acc *= g.scale;
-            lbase[(size_t)ncached * MAXG + n] = acc;
-            const float mn = fmaxf(m, acc);
-            lsum = lsum * __expf(m - mn) + __expf(acc - mn);
-            m = mn;
-        }
-    }
-    // combine the four lane groups of a head, then the waves
-#pragma unroll
-    for (int w = 16; w < 64; w <<= 1) {
-        const float m2 = __shfl_xor(m, w, 64), l2 = __shfl_xor(lsum, w, 64);
-        ml_merge(m, lsum, m2, l2);
-    }
-    if (c == 0) { red_m[wave][n] = m; red_l[wave][n] = lsum; }
-    __syncthreads();
-    if (threadIdx.x < g.G) {
-        float mm = -INFINITY, ll = 0.f;
-        for (int w = 0; w < kDecThreads / 64; ++w) ml_merge(mm, ll, red_m[w][threadIdx.x], red_l[w][threadIdx.x]);
-        float* p = part + (((size_t)b * g.Hq + hk * g.G + threadIdx.x) * n_splits + split) * 2;
-        p[0] = mm;
-        p[1] = ll;
-    }
-}
-
-// ------------------------------------------------------------------ QK, any type: VALU
-
-// Sixteen lanes share a row; every lane owns D/16 contiguous elements of it and all heads of
-// the group.  Four rows per lane group are in flight.
-template <typename T, int EPL, int MAXG>
-__global__ __launch_bounds__(kDecThreads) void decode_qk_valu_kernel(
-    Geom g, SegList sl, int per_split, const T* __restrict__ q, const T* __restrict__ k_new,
-    const T* __restrict__ Kr, const float2* __restrict__ rope, float* __restrict__ logits,
-    float* __restrict__ part, int n_splits)
-{
-    constexpr int U = 4;
-    __shared__ float red_m[kRowGroups][MAXG], red_l[kRowGroups][MAXG];
-    const int split = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
-    const int bh = b * g.Hkv + hk;
-    const int grp = threadIdx.x / kLanesPerRow, lane = threadIdx.x % kLanesPerRow;
-    const int ncached = sl.n_cached, d = g.d;
-    const int j0 = split * per_split, j1 = min(ncached, j0 + per_split);
-    const size_t lrows = (size_t)ncached + 1;
-    float m[MAXG], lsum[MAXG];
-#pragma unroll
-    for (int hh = 0; hh < MAXG; ++hh) { m[hh] = -INFINITY; lsum[hh] = 0.f; }
-
-    int seg_first = 0;
-    for (int si = 0; si < sl.n; ++si) {
-        const Seg sg = sl.s[si];
-        const int lo = max(j0, seg_first), hi = min(j1, seg_first + sg.len);
-        if (lo < hi) {
-            float qr[MAXG][EPL];
-            const int rot = sl.qrot0[sg.qvar];
-#pragma unroll
-            for (int hh = 0; hh < MAXG; ++hh)
-                if (hh < g.G) {
-                    const T* qh = q + ((size_t)b * g.Hq + hk * g.G + hh) * d;
-#pragma unroll
-                    for (int x = 0; x < EPL; ++x) qr[hh][x] = q_rot_elem<T>(qh, rope, rot, d / 2, lane * EPL + x, g.scale);
-                }
-            const T* kseg = Kr + ((ptrdiff_t)bh * g.slots + sg.start - seg_first) * d;
-            for (int r0 = lo + grp * U; r0 < hi; r0 += kRowGroups * U) {
-                float kv[U][EPL];
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    VecLoad<T, EPL>::load(kseg + (size_t)min(r0 + u, hi - 1) * d + lane * EPL, kv[u]);
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int hh = 0; hh < MAXG; ++hh)
-                        if (hh < g.G) {
-                            float acc = 0.f;
-#pragma unroll
-                            for (int x = 0; x < EPL; ++x) acc += qr[hh][x] * kv[u][x];
-#pragma unroll
-                            for (int w = kLanesPerRow / 2; w > 0; w >>= 1) acc += __shfl_xor(acc, w, kLanesPerRow);
-                            if (lane == 0 && r0 + u < hi) {
-                                logits[logit_index(g, MAXG, lrows, b, hk, r0 + u, hh)] = acc;
-                                const float mn = fmaxf(m[hh], acc);
-                                lsum[hh] = lsum[hh] * __expf(m[hh] - mn) + __expf(acc - mn);
-                                m[hh] = mn;
-                            }
-                        }
-            }
-        }
-        seg_first += sg.len;
-    }
-    if (split == 0 && grp == 0) {
-        // own key: <R(n) q, R(n) k> = <q, k>
-        float kv[EPL];
-        VecLoad<T, EPL>::load(k_new + ((size_t)b * g.Hkv + hk) * d + lane * EPL, kv);
-#pragma unroll
-        for (int hh = 0; hh < MAXG; ++hh)
-            if (hh < g.G) {
-                float qv[EPL];
-                VecLoad<T, EPL>::load(q + ((size_t)b * g.Hq + hk * g.G + hh) * d + lane * EPL, qv);
-                float acc = 0.f;
-#pragma unroll
-                for (int x = 0; x < EPL; ++x) acc += qv[x] * kv[x];
-#pragma unroll
-                for (int w = kLanesPerRow / 2; w > 0; w >>= 1) acc += __shfl_xor(acc, w, kLanesPerRow);
-                acc *= g.scale;
-                if (lane == 0) {
-                    logits[logit_index(g, MAXG, lrows, b, hk, ncached, hh)] = acc;
-                    const float mn = fmaxf(m[hh], acc);
-                    lsum[hh] = lsum[hh] * __expf(m[hh] - mn) + __expf(acc - mn);
-                    m[hh] = mn;
-                }
-            }
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int hh = 0; hh < MAXG; ++hh) { red_m[grp][hh] = m[hh]; red_l[grp][hh] = lsum[hh]; }
-    }
-    __syncthreads();
-    if (threadIdx.x < g.G) {
-        float mm = -INFINITY, ll = 0.f;
-        for (int r = 0; r < kRowGroups; ++r) ml_merge(mm, ll, red_m[r][threadIdx.x], red_l[r][threadIdx.x]);
-        float* p = part + (((size_t)b * g.Hq + hk * g.G + threadIdx.x) * n_splits + split) * 2;
-        p[0] = mm;
-        p[1] = ll;
-    }
-}
-
-// ------------------------------------------------------------------ PV and EMA scores
-
-// Lane N of every row of 16 lanes, to all lanes of that row (DPP row_newbcast).
-template <int N> __device__ inline float row_bcast(float x)
-{
-    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x150 + N, 0xf, 0xf, false));
-}
-
-template <int J, int NPL> __device__ inline float pair_value(const float (&pl)[NPL])
-{
-    return row_bcast<J % 16>(pl[J / 16]);
-}
-
-template <int HH, int U, int MAXG, int EPL, int NPL>
-__device__ inline void pv_accumulate_head(const float (&pl)[NPL], const float (&vv)[U][EPL], float (&o)[MAXG][EPL],
-                                          float (&red)[U], bool use_max, int G)
-{
-    if (HH < G) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float p;
-            // the pair index must be a compile-time constant of the broadcast: spelled out per row
-            switch (u) {
-                case 0: p = pair_value<0 * MAXG + HH>(pl); break;
-                case 1: p = pair_value<1 * MAXG + HH>(pl); break;
-                case 2: p = pair_value<2 * MAXG + HH>(pl); break;
-                case 3: p = pair_value<3 * MAXG + HH>(pl); break;
-                case 4: p = pair_value<4 * MAXG + HH>(pl); break;
-                case 5: p = pair_value<5 * MAXG + HH>(pl); break;
-                case 6: p = pair_value<6 * MAXG + HH>(pl); break;
-                default: p = pair_value<7 * MAXG + HH>(pl); break;
-            }
-#pragma unroll
-            for (int x = 0; x < EPL; ++x) o[HH][x] += p * vv[u][x];
-            red[u] = use_max ? fmaxf(red[u], p) : red[u] + p;
-        }
-    }
-}
-
-// With the exact log-sum-exp (all splits of decode_qk combined) p = exp(logit - lse) is final,
-// so the partial outputs of the splits simply add up, and mu <- beta*mu + (1-beta)*reduce_heads(p)
-// is applied in the same pass (Section 3.1).  Sixteen lanes share a row (each owns EPL elements
-// of it), eight rows per lane group are in flight.  The probabilities of those rows (8 x MAXG
-// values) are computed once, spread over the sixteen lanes, and handed round by lane broadcasts.
-template <typename T, int EPL, int MAXG>
-__global__ __launch_bounds__(kDecThreads) void decode_pv_kernel(
-    Geom g, SegList sl, int per_split, const T* __restrict__ Vc, const float* __restrict__ logits,
-    const float* __restrict__ part, int n_splits, float* __restrict__ opart, float* __restrict__ mu,
-    float* __restrict__ lse_out)
-{
-    constexpr int U = 8;
-    constexpr int NP = U * MAXG, NPL = (NP + kLanesPerRow - 1) / kLanesPerRow;
-    __shared__ float lse_s[MAXG];
-    __shared__ float osum[kDecThreads / 64][MAXG][kLanesPerRow * EPL];
-    const int split = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
-    const int bh = b * g.Hkv + hk;
-    const int grp = threadIdx.x / kLanesPerRow, lane = threadIdx.x % kLanesPerRow;
-    const int ncached = sl.n_cached, d = g.d;
-    const size_t lrows = (size_t)ncached + 1;
-    if (threadIdx.x < MAXG) {
-        float v = 0.f;
-        if (threadIdx.x < g.G) {
-            const float* p = part + ((size_t)b * g.Hq + hk * g.G + threadIdx.x) * n_splits * 2;
-            float mm = -INFINITY, ll = 0.f;
-            for (int s = 0; s < n_splits; ++s) ml_merge(mm, ll, p[2 * s], p[2 * s + 1]);
-            v = mm + __logf(ll);
-            if (split == 0) lse_out[(size_t)b * g.Hq + hk * g.G + threadIdx.x] = v;
-        }
-        lse_s[threadIdx.x] = v;
-    }
-    __syncthreads();
-    // this lane's pairs: pair j = lane + 16 t is (row j / MAXG of the eight, head j % MAXG)
-    // (the pairs of eight consecutive rows are 8 x MAXG consecutive floats of the logits)
-    int pu[NPL];
-    float plse[NPL];
-    bool pvalid[NPL];
-    const float* lbase = logits + logit_index(g, MAXG, lrows, b, hk, 0, 0);
-#pragma unroll
-    for (int t = 0; t < NPL; ++t) {
-        const int j = lane + kLanesPerRow * t, hh = j % MAXG;
-        pu[t] = j / MAXG;
-        pvalid[t] = j < NP && hh < g.G;
-        plse[t] = lse_s[hh];
-    }
-    float o[MAXG][EPL];
-#pragma unroll
-    for (int hh = 0; hh < MAXG; ++hh)
-#pragma unroll
-        for (int x = 0; x < EPL; ++x) o[hh][x] = 0.f;
-    const int j0 = split * per_split, j1 = min(ncached, j0 + per_split);
-    const float beta = g.beta, omb = 1.f - g.beta;
-    const bool use_max = g.head_reduce == CASCADE_REDUCE_MAX;
-
-    int seg_first = 0;
-    for (int si = 0; si < sl.n; ++si) {
-        const Seg sg = sl.s[si];
-        const int lo = max(j0, seg_first), hi = min(j1, seg_first + sg.len);
-        if (lo < hi) {
-            const T* vseg = Vc + ((ptrdiff_t)bh * g.slots + sg.start - seg_first) * d;
-            float* museg = mu + ((ptrdiff_t)bh * g.slots + sg.start - seg_first);
-            // (holding the next iteration's rows in a second register set costs more in occupancy than it gains)
-            auto fetch = [&](int r0, float (&vv)[U][EPL], float (&lg)[NPL]) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) VecLoad<T, EPL>::load(vseg + (size_t)min(r0 + u, hi - 1) * d + lane * EPL, vv[u]);
-#pragma unroll
-                for (int t = 0; t < NPL; ++t)
-                    lg[t] = (pvalid[t] && r0 + pu[t] < hi) ? lbase[(size_t)r0 * MAXG + lane + kLanesPerRow * t] : -INFINITY;
-            };
-            auto consume = [&](int r0, const float (&vv)[U][EPL], const float (&lg)[NPL]) {
-                float pl[NPL];
-#pragma unroll
-                for (int t = 0; t < NPL; ++t) pl[t] = __expf(lg[t] - plse[t]);   // exp(-inf) = 0 for pairs that do not exist
-                float red[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) red[u] = 0.f;
-                pv_accumulate_head<0, U, MAXG, EPL, NPL>(pl, vv, o, red, use_max, g.G);
-                if (MAXG > 1) pv_accumulate_head<1 % MAXG, U, MAXG, EPL, NPL>(pl, vv, o, red, use_max, g.G);
-                if (MAXG > 2) {
-                    pv_accumulate_head<2 % MAXG, U, MAXG, EPL, NPL>(pl, vv, o, red, use_max, g.G);
-                    pv_accumulate_head<3 % MAXG, U, MAXG, EPL, NPL>(pl, vv, o, red, use_max, g.G);
-                }
-                if (MAXG > 4) {
-                    pv_accumulate_head<4 % MAXG, U, MAXG, EPL, NPL>(pl, vv, o, red, use_max, g.G);
-                    pv_accumulate_head<5 % MAXG, U, MAXG, EPL, NPL>(pl, vv, o, red, use_max, g.G);
-                    pv_accumulate_head<6 % MAXG, U, MAXG, EPL, NPL>(pl, vv, o, red, use_max, g.G);
-                    pv_accumulate_head<7 % MAXG, U, MAXG, EPL, NPL>(pl, vv, o, red, use_max, g.G);
-                }
-                if (lane == 0) {
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        if (r0 + u < hi) {
-                            float* pm = museg + r0 + u;
-                            *pm = beta * *pm + omb * (use_max ? red[u] : red[u] / (float)g.G);
-                        }
-                }
-            };
-            constexpr int STEP = kRowGroups * U;
-            float vvA[U][EPL], lgA[NPL];
-            int r0 = lo + grp * U;
-            if (r0 < hi) fetch(r0, vvA, lgA);
-            while (r0 < hi) {
-                consume(r0, vvA, lgA);
-                r0 += STEP;
-                if (r0 < hi) fetch(r0, vvA, lgA);
-            }
-        }
-        seg_first += sg.len;
-    }
-    // the four row groups of a wave first add up through lane shuffles
-#pragma unroll
-    for (int hh = 0; hh < MAXG; ++hh)
-#pragma unroll
-        for (int x = 0; x < EPL; ++x) {
-            float t = o[hh][x];
-            t += __shfl_xor(t, 16, 64);
-            t += __shfl_xor(t, 32, 64);
-            if (grp % 4 == 0) osum[grp / 4][hh][lane * EPL + x] = t;
-        }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < g.G * d; idx += kDecThreads) {
-        const int hh = idx / d, e = idx % d;
-        float s = 0.f;
-        for (int r = 0; r < kDecThreads / 64; ++r) s += osum[r][hh][e];
-        opart[(((size_t)b * g.Hq + hk * g.G + hh) * n_splits + split) * d + e] = s;
-    }
-}
-
-// out = sum of the split outputs + own value weighted by its probability; the new token's
-// score starts at (1-beta) * reduce_heads(p_own).  The same workgroup then inserts the token
-// (Alg. 2 for one token: small_update.h).
-template <typename T>
-__global__ void decode_finish_kernel(Geom g, UpdatePlan pl, UpdateBuffers upd, int n_cached, int n_splits, int qstride, int maxg,
-                                     const float* __restrict__ opart, const float* __restrict__ logits,
-                                     const float* __restrict__ lse, const T* __restrict__ v_new,
-                                     T* __restrict__ out, float* __restrict__ mu_chunk)
-{
-    const int hk = blockIdx.x, b = blockIdx.y;
-    const size_t lrows = (size_t)n_cached + 1;
-    for (int idx = threadIdx.x; idx < g.G * g.d; idx += blockDim.x) {
-        const int hh = idx / g.d, e = idx % g.d, h = hk * g.G + hh;
-        const float p = __expf(logits[logit_index(g, maxg, lrows, b, hk, n_cached, hh)] - lse[(size_t)b * g.Hq + h]);
-        float s = p * Elem<T>::load(v_new + ((size_t)b * g.Hkv + hk) * g.d + e);
-        const float* op = opart + ((size_t)b * g.Hq + h) * n_splits * g.d + e;
-        for (int sp = 0; sp < n_splits; ++sp) s += op[(size_t)sp * g.d];
-        Elem<T>::store(out + ((size_t)b * g.Hq + h) * g.d + e, s);
-    }
-    if (threadIdx.x == 0) {
-        // independent heads: the query heads of this KV head; homogeneous heads: all query heads (every
-        // workgroup of the sequence computes the same value, group by group in the same order)
-        const bool all = g.head_policy == CASCADE_HEADS_HOMOGENEOUS;
-        float total = 0.f;
-        for (int k2 = all ? 0 : hk; k2 < (all ? g.Hkv : hk + 1); ++k2) {
-            float red = 0.f;
-            for (int hh = 0; hh < g.G; ++hh) {
-                const int h = k2 * g.G + hh;
-                const float p = __expf(logits[logit_index(g, maxg, lrows, b, k2, n_cached, hh)] - lse[(size_t)b * g.Hq + h]);
-                red = (g.head_reduce == CASCADE_REDUCE_MAX) ? fmaxf(red, p) : red + p;
-            }
-            if (g.head_reduce == CASCADE_REDUCE_MEAN) red /= (float)g.G;
-            total = (g.head_reduce == CASCADE_REDUCE_MAX) ? fmaxf(total, red) : total + red;
-        }
-        if (all && g.head_reduce == CASCADE_REDUCE_MEAN) total /= (float)g.Hkv;
-        mu_chunk[((size_t)b * g.Hkv + hk) * qstride] = (1.f - g.beta) * total;
-    }
-    __syncthreads();   // the token's score is written
-    small_update<T>(g, pl, qstride, upd, b, hk);
-}
-
-// ------------------------------------------------------------------ PV and EMA scores, bf16: MFMA fed from LDS
-//
-// O^T = V^T P^T with v_mfma_f32_16x16x32_bf16: rows are 16 elements of the head dimension, columns
-// the query heads of the group (padded to 16), the contraction runs over 32 cached rows.  Every
-// wave streams its own 32-row tiles of V (and the tiles' logits and scores) through a private
-// ring of LDS stages filled by asynchronous copies, so the bytes in flight do not depend on what
-// the wave is computing and no workgroup barrier is needed inside the loop.  The A operand wants
-// 8 rows of one column per lane: ds_read_b64_tr_b16 transposes on the way out of LDS.
-//
-// A staged V tile keeps rows of D elements; the 16-byte pieces of a row are permuted (piece ^
-// swizzle(row)) so that the 8 rows one half of a wave reads in a transposing read fall into
-// different banks.  The copy applies the permutation on the global side (a copy instruction
-// writes LDS contiguously).
-constexpr int kPvStages = 4;
-constexpr int kPvRows = 32;           // cached rows per tile = contraction length of the MFMA
-constexpr int kPvWaves = kDecThreads / 64;
-
-template <int D> struct PvSwizzle;
-template <> struct PvSwizzle<128> {
-    __device__ static int of(int row) { return 2 * ((((row >> 3) & 1) << 2) | (row & 3)); }
-};
-template <> struct PvSwizzle<64> {
-    __device__ static int of(int row) { return 2 * ((((row >> 3) & 1) << 1) | ((row >> 1) & 1)); }
-};
-
-typedef short pv_v4i16_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) pv_v4i16_t pv_lds_v4i16_t;
+typedef short dec_v4i16_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) dec_v4i16_t dec_lds_v4i16_t;
 
 // ds_read_b64_tr_b16: the 16 lanes of a group address a 4-row x 16-column block of 16-bit
 // elements (lane i: row i/4, columns 4*(i%4)..+3); lane i receives column i of the 4 rows.
-__device__ inline uint2 pv_read_tr16(const unsigned char* p)
+__device__ inline uint2 read_tr16(const unsigned char* p)
 {
-    const pv_v4i16_t r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((pv_lds_v4i16_t*)p);
+    const dec_v4i16_t r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dec_lds_v4i16_t*)p);
     return __builtin_bit_cast(uint2, r);
 }
 
-// The tiles of one wave in order: inside every segment's part of [j0, j1) the tiles of 32 rows
-// first, first + stride, ... counted from the start of that part.
-struct WaveTiles {
-    int si, seg_first, r0, hi, start, first, stride;
-    bool valid;
-    __device__ void seek(const SegList& sl, int j0, int j1)
-    {
-        while (si < sl.n) {
-            const int len = sl.s[si].len;
-            hi = min(j1, seg_first + len);
-            r0 = max(j0, seg_first) + first;
-            start = sl.s[si].start;
-            if (r0 < hi) { valid = true; return; }
-            seg_first += len;
-            ++si;
-        }
-        valid = false;
-    }
-    __device__ void begin(const SegList& sl, int j0, int j1, int first_row, int row_stride)
-    {
-        si = 0; seg_first = 0; r0 = 0; hi = 0; start = 0;
-        first = first_row; stride = row_stride;
-        seek(sl, j0, j1);
-    }
-    __device__ void next(const SegList& sl, int j0, int j1)
-    {
-        r0 += stride;
-        if (r0 >= hi) {
-            seg_first += sl.s[si].len;
-            ++si;
-            seek(sl, j0, j1);
-        }
-    }
-};
-
-template <int D, int MAXG>
-struct PvStage {
-    static constexpr int kVBytes = kPvRows * D * 2;
-    static constexpr int kLogitCopies = (kPvRows * MAXG * 4 + 255) / 256;
-    static constexpr int kLgOff = kVBytes;                        // logits of the tile, [row][head]
-    static constexpr int kMuOff = kLgOff + kLogitCopies * 256;    // scores of the tile's rows
-    static constexpr int kBytes = kMuOff + 256;
-    static constexpr int kVCopies = kVBytes / 1024;
-    static constexpr int kCopies = kVCopies + kLogitCopies + 1;   // vector memory operations per tile
-};
-
-// Waits until the copies of the oldest tile in flight have landed: `ahead` later tiles (NC copies
-// each) have been issued after it, and (in steady state) the stores of kPvStages - 1 tiles (NS
-// each).  Counting fewer operations than are really outstanding only waits longer.
-template <int NC, int NS> __device__ inline void ring_wait(int ahead, bool steady)
+// maximum over the four lanes that hold one head's keys (l, l^16, l^32, l^48)
+__device__ inline float max_groups(float x)
 {
-    static_assert(kPvStages == 4, "cases below");
-    constexpr int ST = (kPvStages - 1) * NS;
-    static_assert(3 * NC + ST < 64, "vmcnt range");
-    if (steady) {
-        if (ahead >= 3) wait_vm_fenced<3 * NC + ST>();
-        else if (ahead == 2) wait_vm_fenced<2 * NC + ST>();
-        else if (ahead == 1) wait_vm_fenced<NC + ST>();
-        else wait_vm_fenced<0>();
-    } else {
-        if (ahead >= 3) wait_vm_fenced<3 * NC>();
-        else if (ahead == 2) wait_vm_fenced<2 * NC>();
-        else if (ahead == 1) wait_vm_fenced<NC>();
-        else wait_vm_fenced<0>();
-    }
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+constexpr float kDecRescale = 8.f;
+
 template <int D, int MAXG>
-__global__ __launch_bounds__(kDecThreads, 1) void decode_pv_mfma_kernel(
-    Geom g, SegList sl, int per_split, const bf16_t* __restrict__ Vc, const float* __restrict__ logits,
-    const float* __restrict__ part, int n_splits, float* __restrict__ opart, float* __restrict__ mu,
-    float* __restrict__ lse_out)
+__global__ __launch_bounds__(kDecThreads, 1) void decode_attend_kernel(
+    Geom g, SegList sl, int n_tiles, int n_splits, float qscale, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k_new,
+    const bf16_t* __restrict__ Kr, const bf16_t* __restrict__ Vc, const float2* __restrict__ rope, float* __restrict__ logits,
+    float* __restrict__ part, float* __restrict__ opart)
 {
-    using St = PvStage<D, MAXG>;
-    constexpr int DB = D / 16;                 // MFMA row blocks over the head dimension
-    constexpr int PPR = D / 8;                 // 16-byte pieces per row
-    constexpr int RPI = 64 / PPR;              // rows per copy instruction
-    __shared__ __attribute__((aligned(1024))) unsigned char ring[kPvWaves][kPvStages][St::kBytes];
-    __shared__ __attribute__((aligned(16))) bf16_t Pt[kPvWaves][MAXG][kPvRows];
-    __shared__ float lse_s[MAXG];
-    static_assert(sizeof(float) * kPvWaves * MAXG * D <= sizeof(ring), "the partial outputs reuse the ring");
+    constexpr int KS = D / 32;                     // MFMA steps over the head dimension (QK)
+    constexpr int DB = D / 16;                     // MFMA row blocks over the head dimension (PV)
+    constexpr int PPR = D / 8;                     // 16-byte pieces per row
+    constexpr int RPI = 64 / PPR;                  // rows per copy instruction
+    constexpr int kStage = kDecRows * D * 2;       // bytes of a staged K or V tile
+    constexpr int NC = kStage / 1024;              // copies per stage
+    constexpr int NS = 2;                          // stores of logits per tile
+    __shared__ __attribute__((aligned(1024))) unsigned char ring[kDecWaves][4][kStage];   // stages K, V of even tiles, K, V of odd ones
+    __shared__ float red_m[kDecWaves][16], red_l[kDecWaves][16];
+    static_assert(sizeof(float) * kDecWaves * MAXG * D <= sizeof(ring), "the partial outputs reuse the ring");
     const int split = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
     const int bh = b * g.Hkv + hk;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, n = l & 15, c = l >> 4;
-    const int ncached = sl.n_cached;
-    const size_t lrows = (size_t)ncached + 1;
-    if (threadIdx.x < MAXG) {
-        float v = 0.f;
-        if (threadIdx.x < g.G) {
-            const float* p = part + ((size_t)b * g.Hq + hk * g.G + threadIdx.x) * n_splits * 2;
-            float mm = -INFINITY, ll = 0.f;
-            for (int s = 0; s < n_splits; ++s) ml_merge(mm, ll, p[2 * s], p[2 * s + 1]);
-            v = mm + __logf(ll);
-            if (split == 0) lse_out[(size_t)b * g.Hq + hk * g.G + threadIdx.x] = v;
-        }
-        lse_s[threadIdx.x] = v;
-    }
-    __syncthreads();   // (also: every ordinary load of this kernel has returned before the first copy)
-
-    const int j0 = split * per_split, j1 = min(ncached, j0 + per_split);
-    const float* lbase = logits + logit_index(g, MAXG, lrows, b, hk, 0, 0);
+    // this split's tiles; the waves take them in turn
+    const int t_first = (int)((long long)n_tiles * split / n_splits), t_end = (int)((long long)n_tiles * (split + 1) / n_splits);
+    const bf16_t* kbh = Kr + (size_t)bh * g.slots * D;
     const bf16_t* vbh = Vc + (size_t)bh * g.slots * D;
-    float* mubh = mu + (size_t)bh * g.slots;
     const uint32_t ring_lds = lds_address(&ring[wave][0][0]);
-    unsigned char* ring_w = &ring[wave][0][0];
+    const unsigned char* ring_w = &ring[wave][0][0];
 
-    // copy addressing of this lane: V copy x brings rows x*RPI + l/PPR, piece l%PPR of the LDS row
-    // holds piece (l%PPR) ^ swizzle(row) of the global row
-    auto issue = [&](const WaveTiles& t, int stage) {
-        const int nvalid = min(kPvRows, t.hi - t.r0);          // rows past the end repeat the last one
-        const uint32_t dst = ring_lds + (uint32_t)stage * St::kBytes;
-        const int phys = t.start + (t.r0 - t.seg_first);       // first slot of the tile
-        const bf16_t* vsrc = vbh + (size_t)phys * D;
+    int k_off[NC], v_off[NC], c_row[NC];           // what this lane copies of a stage: row and byte offset inside it
 #pragma unroll
-        for (int x = 0; x < St::kVCopies; ++x) {
-            const int row = x * RPI + l / PPR;
-            const int piece = (l % PPR) ^ PvSwizzle<D>::of(row);
-            async_copy_1k_stream(vsrc, (uint32_t)((min(row, nvalid - 1) * PPR + piece) * 16),
-                                 __builtin_amdgcn_readfirstlane(dst + x * 1024u));
-        }
-        const float* lsrc = lbase + (size_t)t.r0 * MAXG;
+    for (int x = 0; x < NC; ++x) {
+        c_row[x] = x * RPI + l / PPR;
+        k_off[x] = ((l % PPR) ^ DecSwizzle<D>::k(c_row[x])) * 16;
+        v_off[x] = ((l % PPR) ^ DecSwizzle<D>::v(c_row[x])) * 16;
+    }
+    auto issue = [&](const bf16_t* base, const int (&off)[NC], const TileWalk& t, int stage) {
+        const bf16_t* src = base + (size_t)t.start * D;
 #pragma unroll
-        for (int x = 0; x < St::kLogitCopies; ++x)
-            async_copy_256_stream(lsrc, (uint32_t)(min(x * 64 + l, nvalid * MAXG - 1) * 4),
-                                  __builtin_amdgcn_readfirstlane(dst + St::kLgOff + x * 256u));
-        async_copy_256(mubh + phys, (uint32_t)(min(l, nvalid - 1) * 4), __builtin_amdgcn_readfirstlane(dst + St::kMuOff));
+        for (int x = 0; x < NC; ++x)               // rows past the end repeat the last one
+            async_copy_1k_stream(src, (uint32_t)(min(c_row[x], t.nvalid - 1) * (D * 2) + off[x]),
+                                 __builtin_amdgcn_readfirstlane(ring_lds + (uint32_t)(stage * kStage + x * 1024)));
     };
 
-    // transposing reads of this lane: rows 8c + 4*hf + (n>>2), column block db, 8 bytes at element 4*(n&3)
-    int tr_row[2], tr_sw[2];
+    TileWalk prod, cons;
+    prod.begin(sl, t_first + wave);
+    cons = prod;
 #pragma unroll
-    for (int hf = 0; hf < 2; ++hf) {
-        tr_row[hf] = 8 * c + 4 * hf + (n >> 2);
-        tr_sw[hf] = PvSwizzle<D>::of(tr_row[hf]);
+    for (int i = 0; i < 2; ++i)
+        if (prod.tile < t_end) {
+            issue(kbh, k_off, prod, 2 * i);
+            issue(vbh, v_off, prod, 2 * i + 1);
+            prod.advance(sl, kDecWaves);
+        }
+    if (split == 0) own_logits<bf16_t, D>(g, b, hk, q, k_new, qscale, part, n_splits);
+
+    // fragment reads of this lane.  K: row 16 gi + n, piece 4 ks + c.  V: row 16 hf + 4 c + n / 4, 8 bytes
+    // at element 16 db + 4 (n % 4)
+    int a_off[2][KS], t_off[2], t_sw[2];
+#pragma unroll
+    for (int gi = 0; gi < 2; ++gi) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) a_off[gi][ks] = (16 * gi + n) * (D * 2) + (((4 * ks + c) ^ DecSwizzle<D>::k(16 * gi + n)) * 16);
+        const int row = 16 * gi + 4 * c + (n >> 2);
+        t_off[gi] = row * (D * 2) + (n & 1) * 8;
+        t_sw[gi] = DecSwizzle<D>::v(row);
     }
 
     df32x4_t acc[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db) acc[db] = df32x4_t{0.f, 0.f, 0.f, 0.f};
-    const float beta = g.beta, omb = 1.f - g.beta;
-    const bool use_max = g.head_reduce == CASCADE_REDUCE_MAX;
-    float lse_r[MAXG];
+    float m = -INFINITY, lsum = 0.f;               // maximum of head n; this lane's part of its sum
+    DFrag qf[KS];
+    int q_var = -1;
+    float* lbase = logits + (size_t)bh * n_tiles * (kDecRows * MAXG) + (n * 4 + c) * 4;
+    int done = 0;
+    while (cons.tile < t_end) {
+        const int stage = 2 * (done & 1);
+        const bool next1 = cons.tile + kDecWaves < t_end, next2 = cons.tile + 2 * kDecWaves < t_end;
+        if (sl.s[cons.si].qvar != q_var) {
+            // B operand: the group's queries turned by (own index) - (cache index - slot index) of the segment
+            // (the stored keys are rotated to their slot index), scaled, as bf16.  (The wait for these
+            // loads also waits for the copies in flight: once per segment.)
+            q_var = sl.s[cons.si].qvar;
+            const bf16_t* qh = q + ((size_t)b * g.Hq + hk * g.G + n) * D;
+            const float2* cs = rope + (size_t)sl.qrot0[q_var] * (D / 2);
 #pragma unroll
-    for (int hh = 0; hh < MAXG; ++hh) lse_r[hh] = lse_s[hh];
-
-    WaveTiles prod, cons;
-    prod.begin(sl, j0, j1, wave * kPvRows, kPvWaves * kPvRows);
-    cons = prod;
-    int issued = 0, done = 0;
-    for (; issued < kPvStages && prod.valid; ++issued) {
-        issue(prod, issued);
-        prod.next(sl, j0, j1);
-    }
-    while (cons.valid) {
-        const int stage = done % kPvStages;
-        ring_wait<St::kCopies, 1>(issued - done - 1, done >= kPvStages - 1);
-        const unsigned char* sp = ring_w + stage * St::kBytes;
-        const int nvalid = min(kPvRows, cons.hi - cons.r0);
-        // probabilities of the tile: lane x < 32 takes row x and all heads
-        if (l < kPvRows) {
-            const float* lg = reinterpret_cast<const float*>(sp + St::kLgOff) + l * MAXG;
-            float red = 0.f;
+            for (int ks = 0; ks < KS; ++ks) qf[ks].u = du32x4_t{0u, 0u, 0u, 0u};
+            if (n < g.G) {
 #pragma unroll
-            for (int hh = 0; hh < MAXG; ++hh) {
-                const float p = (hh < g.G && l < nvalid) ? __expf(lg[hh] - lse_r[hh]) : 0.f;
-                red = use_max ? fmaxf(red, p) : red + p;
-                Pt[wave][hh][l] = (bf16_t)(dec_pack_bf16(p, 0.f) & 0xFFFFu);
-            }
-            if (l < nvalid) {   // lane 0 always stores: the operation count of ring_wait relies on it
-                const float old = reinterpret_cast<const float*>(sp + St::kMuOff)[l];
-                const int phys = cons.start + (cons.r0 - cons.seg_first);
-                counted_store_f32(mubh + phys, (uint32_t)(l * 4), beta * old + omb * (use_max ? red : red / (float)g.G));
+                for (int ks = 0; ks < KS / 2; ++ks) {
+                    const int e = ks * 32 + c * 8;
+                    float x0[8], x1[8], y0[8], y1[8];
+                    Vec8<bf16_t>::load(qh + e, x0);
+                    Vec8<bf16_t>::load(qh + e + D / 2, x1);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const float2 w = cs[e + i];
+                        y0[i] = rot_lo(x0[i], x1[i], w.x, w.y) * qscale;
+                        y1[i] = rot_hi(x0[i], x1[i], w.x, w.y) * qscale;
+                    }
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        qf[ks].u[x] = dec_pack_bf16(y0[2 * x], y0[2 * x + 1]);
+                        qf[ks + KS / 2].u[x] = dec_pack_bf16(y1[2 * x], y1[2 * x + 1]);
+                    }
+                }
             }
         }
-        __builtin_amdgcn_wave_barrier();   // LDS accesses of one wave are executed in order
+        // K of this tile has landed.  Issued after it: V of this tile, K and V of the next, and (once two
+        // tiles are done) the stores of two tiles.  Counting fewer than are outstanding only waits longer.
+        if (done >= 2) { if (next1) wait_vm_fenced<3 * NC + 2 * NS>(); else wait_vm_fenced<NC + 2 * NS>(); }
+        else           { if (next1) wait_vm_fenced<3 * NC>(); else wait_vm_fenced<NC>(); }
+        const unsigned char* kp = ring_w + stage * kStage;
+        df32x4_t s[2];
+#pragma unroll
+        for (int gi = 0; gi < 2; ++gi) {
+            s[gi] = df32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                DFrag kf;
+                kf.u = *reinterpret_cast<const du32x4_t*>(kp + a_off[gi][ks]);
+                s[gi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf.v, qf[ks].v, s[gi], 0, 0, 0);
+            }
+        }
+        wait_lds_reads();                          // the stage may be overwritten now
+        if (next2) issue(kbh, k_off, prod, stage);
+        // the logits leave (lane 0 always stores: the counts above and below rely on NS stores per tile)
+        if (n < MAXG) {
+            float* lt = lbase + (size_t)cons.tile * (kDecRows * MAXG);
+#pragma unroll
+            for (int gi = 0; gi < 2; ++gi) *reinterpret_cast<df32x4_t*>(lt + gi * (16 * MAXG)) = s[gi];
+        }
+        if (cons.nvalid < kDecRows) {
+#pragma unroll
+            for (int gi = 0; gi < 2; ++gi)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (16 * gi + 4 * c + j >= cons.nvalid) s[gi][j] = -INFINITY;
+        }
+        float mx = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])), fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+        mx = max_groups(mx);
+        if (__any(mx > m + kDecRescale)) {         // (the first tile: m is -infinity)
+            const float mn = fmaxf(m, mx), alpha = rescale_of(m, mn);
+            m = mn;
+            lsum *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[db][j] *= alpha;
+        }
         DFrag pf;
-        pf.u = du32x4_t{0u, 0u, 0u, 0u};
-        if (n < MAXG) pf.u = *reinterpret_cast<const du32x4_t*>(&Pt[wave][n][8 * c]);
+        const float mr = finite_max(m);
+#pragma unroll
+        for (int gi = 0; gi < 2; ++gi)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const float p0 = __builtin_amdgcn_exp2f(s[gi][2 * x] - mr), p1 = __builtin_amdgcn_exp2f(s[gi][2 * x + 1] - mr);
+                lsum += p0 + p1;
+                pf.u[2 * gi + x] = dec_pack_bf16(p0, p1);
+            }
+        // V of this tile has landed.  Issued after it: K and V of the next tile, K of the one after, the stores
+        if (done >= 1) { if (next2) wait_vm_fenced<3 * NC + 2 * NS>(); else if (next1) wait_vm_fenced<2 * NC + 2 * NS>(); else wait_vm_fenced<2 * NS>(); }
+        else           { if (next2) wait_vm_fenced<3 * NC>(); else if (next1) wait_vm_fenced<2 * NC>(); else wait_vm_fenced<0>(); }
+        const unsigned char* vp = ring_w + (stage + 1) * kStage;
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             DFrag vf;
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf) {
-                const int piece = (2 * db + ((n & 3) >> 1)) ^ tr_sw[hf];
-                const uint2 r = pv_read_tr16(sp + tr_row[hf] * (D * 2) + piece * 16 + (n & 1) * 8);
+                const uint2 r = read_tr16(vp + t_off[hf] + (((2 * db + ((n & 3) >> 1)) ^ t_sw[hf]) * 16));
                 vf.u[2 * hf] = r.x;
                 vf.u[2 * hf + 1] = r.y;
             }
             acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf.v, pf.v, acc[db], 0, 0, 0);
         }
-        wait_lds_reads();                  // the stage may be overwritten now
-        ++done;
-        cons.next(sl, j0, j1);
-        if (prod.valid) {
-            issue(prod, stage);
-            ++issued;
-            prod.next(sl, j0, j1);
+        wait_lds_reads();
+        if (next2) {
+            issue(vbh, v_off, prod, stage + 1);
+            prod.advance(sl, kDecWaves);
         }
+        ++done;
+        cons.advance(sl, kDecWaves);
     }
     wait_vm_fenced<0>();
-    __syncthreads();                       // every wave is done with its ring
+    lsum += __shfl_xor(lsum, 16, 64);
+    lsum += __shfl_xor(lsum, 32, 64);
+    if (c == 0) { red_m[wave][n] = m; red_l[wave][n] = lsum; }
+    __syncthreads();                               // every wave is done with its ring
     // this lane holds, for head n, elements 16*db + 4*c + j of the wave's partial output
     float* osum = reinterpret_cast<float*>(&ring[0][0][0]);   // [wave][MAXG][D]
     if (n < MAXG) {
+        float mm = -INFINITY;
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-            *reinterpret_cast<df32x4_t*>(&osum[((size_t)wave * MAXG + n) * D + 16 * db + 4 * c]) = acc[db];
+        for (int w = 0; w < kDecWaves; ++w) mm = fmaxf(mm, red_m[w][n]);
+        const float f = lsum > 0.f ? __builtin_amdgcn_exp2f(m - mm) : m == -INFINITY ? 0.f : lsum;   // (a wave without tiles adds nothing; NaN stays NaN)
+#pragma unroll
+        for (int db = 0; db < DB; ++db) *reinterpret_cast<df32x4_t*>(&osum[((size_t)wave * MAXG + n) * D + 16 * db + 4 * c]) = acc[db] * f;
     }
     __syncthreads();
     for (int idx = threadIdx.x; idx < g.G * D; idx += kDecThreads) {
         const int hh = idx / D, e = idx % D;
         float s = 0.f;
-        for (int w = 0; w < kPvWaves; ++w) s += osum[((size_t)w * MAXG + hh) * D + e];
+#pragma unroll
+        for (int w = 0; w < kDecWaves; ++w) s += osum[((size_t)w * MAXG + hh) * D + e];
         opart[(((size_t)b * g.Hq + hk * g.G + hh) * n_splits + split) * D + e] = s;
     }
-}
-
-// ------------------------------------------------------------------ QK, bf16: MFMA fed from LDS
-//
-// The same streaming structure for K: 32-row tiles through a private ring per wave, the A
-// fragments (16 keys x 8 elements per lane) read with ds_read_b128.  The 16-byte pieces of a
-// staged row are permuted so that the 16 rows of a fragment read fall into different banks.
-// The rotated, scaled query fragments of every rotation the step uses are computed once per
-// workgroup and kept in LDS, so the loop issues no ordinary load and no wait of the compiler's
-// drains the ring.
-template <int D> struct QkSwizzle;
-template <> struct QkSwizzle<128> { __device__ static int of(int row) { return row & 15; } };
-template <> struct QkSwizzle<64> { __device__ static int of(int row) { return (row >> 1) & 7; } };
-
-template <int MAXG> struct QkLimits {
-    static constexpr int kRotations = 96 / MAXG < kMaxQueryRotations ? 96 / MAXG : kMaxQueryRotations;   // query copies held in LDS
-};
-
-template <int D, int MAXG>
-__global__ __launch_bounds__(kDecThreads, 1) void decode_qk_stream_kernel(
-    Geom g, SegList sl, int per_split, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k_new,
-    const bf16_t* __restrict__ Kr, const float2* __restrict__ rope, float* __restrict__ logits,
-    float* __restrict__ part, int n_splits)
-{
-    constexpr int KS = D / 32;                 // MFMA steps over the head dimension
-    constexpr int PPR = D / 8;                 // 16-byte pieces per row
-    constexpr int RPI = 64 / PPR;              // rows per copy instruction
-    constexpr int kTileBytes = kPvRows * D * 2;
-    constexpr int NC = kTileBytes / 1024;      // copies per tile
-    constexpr int NS = (kPvRows * MAXG * 4 + 255) / 256;   // logit stores per tile
-    constexpr int NR = QkLimits<MAXG>::kRotations;
-    __shared__ __attribute__((aligned(1024))) unsigned char ring[kPvWaves][kPvStages][kTileBytes];
-    __shared__ __attribute__((aligned(16))) du32x4_t qfr[NR][KS][4][MAXG];
-    __shared__ __attribute__((aligned(16))) float stage[kPvWaves][kPvRows * MAXG];   // a tile's logits, [row][head]
-    __shared__ float red_m[kPvWaves][16], red_l[kPvWaves][16];
-    const int split = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
-    const int bh = b * g.Hkv + hk;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, n = l & 15, c = l >> 4;
-    const int ncached = sl.n_cached;
-    const size_t lrows = (size_t)ncached + 1;
-    const bool head_ok = n < g.G;
-    float* lbase = logits + logit_index(g, MAXG, lrows, b, hk, 0, 0);
-
-    // B operands: every rotation of the group's queries, scaled, as bf16 (zero for padded heads)
-    for (int idx = threadIdx.x; idx < sl.n_qvar * KS * 4 * MAXG; idx += kDecThreads) {
-        const int hh = idx % MAXG, cc = (idx / MAXG) % 4, ks = (idx / (4 * MAXG)) % KS, v = idx / (4 * MAXG * KS);
-        du32x4_t f = {0u, 0u, 0u, 0u};
-        if (hh < g.G) {
-            const bf16_t* qh = q + ((size_t)b * g.Hq + hk * g.G + hh) * D;
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const int e = ks * 32 + cc * 8 + 2 * x;
-                f[x] = dec_pack_bf16(q_rot_elem<bf16_t>(qh, rope, sl.qrot0[v], D / 2, e, g.scale),
-                                     q_rot_elem<bf16_t>(qh, rope, sl.qrot0[v], D / 2, e + 1, g.scale));
-            }
-        }
-        qfr[v][ks][cc][hh] = f;
-    }
-    __syncthreads();   // (also: every ordinary load so far has returned before the first copy)
-
-    const int j0 = split * per_split, j1 = min(ncached, j0 + per_split);
-    const bf16_t* kbh = Kr + (size_t)bh * g.slots * D;
-    const uint32_t ring_lds = lds_address(&ring[wave][0][0]);
-    const unsigned char* ring_w = &ring[wave][0][0];
-
-    auto issue = [&](const WaveTiles& t, int stg) {
-        const int nvalid = min(kPvRows, t.hi - t.r0);          // rows past the end repeat the last one
-        const uint32_t dst = ring_lds + (uint32_t)stg * kTileBytes;
-        const bf16_t* ksrc = kbh + (size_t)(t.start + (t.r0 - t.seg_first)) * D;
-#pragma unroll
-        for (int x = 0; x < NC; ++x) {
-            const int row = x * RPI + l / PPR;
-            const int piece = (l % PPR) ^ QkSwizzle<D>::of(row);
-            async_copy_1k_stream(ksrc, (uint32_t)((min(row, nvalid - 1) * PPR + piece) * 16),
-                                 __builtin_amdgcn_readfirstlane(dst + x * 1024u));
-        }
-    };
-
-    // fragment reads of this lane: key group gi, step ks: row 16*gi + n, piece 4*ks + c
-    int a_off[2][KS];
-#pragma unroll
-    for (int gi = 0; gi < 2; ++gi)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int row = 16 * gi + n;
-            a_off[gi][ks] = row * (D * 2) + (((4 * ks + c) ^ QkSwizzle<D>::of(row)) * 16);
-        }
-
-    float m = -INFINITY, lsum = 0.f;
-    DFrag qf[KS];
-    int q_si = -1;
-    WaveTiles prod, cons;
-    prod.begin(sl, j0, j1, wave * kPvRows, kPvWaves * kPvRows);
-    cons = prod;
-    int issued = 0, done = 0;
-    for (; issued < kPvStages && prod.valid; ++issued) {
-        issue(prod, issued);
-        prod.next(sl, j0, j1);
-    }
-    while (cons.valid) {
-        const int stg = done % kPvStages;
-        if (cons.si != q_si) {             // uniform for the wave
-            q_si = cons.si;
-            const int v = sl.s[q_si].qvar;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                qf[ks].u = du32x4_t{0u, 0u, 0u, 0u};
-                if (n < MAXG) qf[ks].u = qfr[v][ks][c][n];
-            }
-        }
-        ring_wait<NC, NS>(issued - done - 1, done >= kPvStages - 1);
-        const unsigned char* sp = ring_w + stg * kTileBytes;
-        const int nvalid = min(kPvRows, cons.hi - cons.r0);
-#pragma unroll
-        for (int gi = 0; gi < 2; ++gi) {
-            DFrag kf[KS];
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) kf[ks].u = *reinterpret_cast<const du32x4_t*>(sp + a_off[gi][ks]);
-            df32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks].v, qf[ks].v, acc, 0, 0, 0);
-            // this lane: head n, tile rows 16*gi + 4*c + {0..3}
-            const int rb = gi * 16 + 4 * c;
-            if (n < MAXG) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) stage[wave][(rb + j) * MAXG + n] = acc[j];
-            }
-            if (head_ok) {
-                // one rescaling per four logits: the running maximum rarely moves
-                float mx = m;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (rb + j < nvalid) mx = fmaxf(mx, acc[j]);
-                if (mx > m) {   // (also keeps -inf - -inf out of the arithmetic)
-                    lsum *= __expf(m - mx);
-                    m = mx;
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (rb + j < nvalid) lsum += __expf(acc[j] - m);
-            }
-        }
-        __builtin_amdgcn_wave_barrier();   // LDS accesses of one wave are executed in order
-        // the tile's logits leave as contiguous runs; every store is issued by all lanes (lanes past
-        // the end repeat the last logit), the operation count of ring_wait relies on it
-        float* ltile = lbase + (size_t)cons.r0 * MAXG;
-#pragma unroll
-        for (int x = 0; x < NS; ++x) {
-            const int idx = min(x * 64 + l, nvalid * MAXG - 1);
-            counted_store_f32(ltile, (uint32_t)(idx * 4), stage[wave][idx]);
-        }
-        wait_lds_reads();                  // the stage may be overwritten now
-        ++done;
-        cons.next(sl, j0, j1);
-        if (prod.valid) {
-            issue(prod, stg);
-            ++issued;
-            prod.next(sl, j0, j1);
-        }
-    }
-    wait_vm_fenced<0>();
-    if (split == 0 && wave == 0) {
-        // own key: <R(n) q, R(n) k> = <q, k>; lanes c = 0 of the valid heads take it
-        if (head_ok && c == 0) {
-            const bf16_t* qh = q + ((size_t)b * g.Hq + hk * g.G + n) * D;
-            const bf16_t* kn = k_new + ((size_t)b * g.Hkv + hk) * D;
-            float acc = 0.f;
-            for (int e = 0; e < D; ++e) acc += bf16_to_f32(qh[e]) * bf16_to_f32(kn[e]);
-            acc *= g.scale;
-            lbase[(size_t)ncached * MAXG + n] = acc;
-            const float mn = fmaxf(m, acc);
-            lsum = lsum * __expf(m - mn) + __expf(acc - mn);
-            m = mn;
-        }
-    }
-    // combine the four lane groups of a head, then the waves
-#pragma unroll
-    for (int w = 16; w < 64; w <<= 1) {
-        const float m2 = __shfl_xor(m, w, 64), l2 = __shfl_xor(lsum, w, 64);
-        ml_merge(m, lsum, m2, l2);
-    }
-    if (c == 0) { red_m[wave][n] = m; red_l[wave][n] = lsum; }
-    __syncthreads();
     if (threadIdx.x < g.G) {
         float mm = -INFINITY, ll = 0.f;
-        for (int w = 0; w < kPvWaves; ++w) ml_merge(mm, ll, red_m[w][threadIdx.x], red_l[w][threadIdx.x]);
-        float* p = part + (((size_t)b * g.Hq + hk * g.G + threadIdx.x) * n_splits + split) * 2;
+        for (int w = 0; w < kDecWaves; ++w) ml_merge(mm, ll, red_m[w][threadIdx.x], red_l[w][threadIdx.x]);
+        float* p = part_of(part, (size_t)b * g.Hq + hk * g.G + threadIdx.x, n_splits, split);
         p[0] = mm;
         p[1] = ll;
     }
 }
 
+// ------------------------------------------------------------------ attend, fp32: VALU
+//
+// The same split results in fp32 arithmetic.  Sixteen lanes share a row, every lane owns D/16 contiguous
+// elements of it and all heads of the group; a workgroup takes four tiles (128 rows) at a time, eight
+// consecutive rows per lane group, all eight loads of K and of V in flight together.
+template <int D, int MAXG>
+__global__ __launch_bounds__(kDecThreads) void decode_attend_f32_kernel(
+    Geom g, SegList sl, int n_tiles, int n_splits, float qscale, const float* __restrict__ q, const float* __restrict__ k_new,
+    const float* __restrict__ Kr, const float* __restrict__ Vc, const float2* __restrict__ rope, float* __restrict__ logits,
+    float* __restrict__ part, float* __restrict__ opart)
+{
+    constexpr int EPL = D / 16, U = 8, kTiles = 4;
+    __shared__ float ps[kTiles * kDecRows][MAXG];          // logits, then probabilities of the 128 rows
+    __shared__ float alpha_s[MAXG];
+    __shared__ float osum[kDecWaves][MAXG][D];
+    const int split = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
+    const int bh = b * g.Hkv + hk;
+    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const int grp = threadIdx.x / 16, lane = threadIdx.x % 16, r0 = (grp % 4) * U;   // tile grp / 4 of the four, rows r0 .. r0 + 7 of it
+    const int t_first = (int)((long long)n_tiles * split / n_splits), t_end = (int)((long long)n_tiles * (split + 1) / n_splits);
+    if (split == 0) own_logits<float, D>(g, b, hk, q, k_new, qscale, part, n_splits);
+    float o[MAXG][EPL], qr[MAXG][EPL];
+#pragma unroll
+    for (int hh = 0; hh < MAXG; ++hh)
+#pragma unroll
+        for (int x = 0; x < EPL; ++x) { o[hh][x] = 0.f; qr[hh][x] = 0.f; }
+    float m_run[(MAXG + kDecWaves - 1) / kDecWaves], l_run[(MAXG + kDecWaves - 1) / kDecWaves];   // heads wave, wave + 4
+#pragma unroll
+    for (int i = 0; i < (MAXG + kDecWaves - 1) / kDecWaves; ++i) { m_run[i] = -INFINITY; l_run[i] = 0.f; }
+    TileWalk t;
+    t.begin(sl, t_first + grp / 4);
+    int q_var = -1;
+    for (int tb = t_first; tb < t_end; tb += kTiles, t.advance(sl, kTiles)) {
+        const bool have = t.tile < t_end;
+        float vv[U][EPL];
+        if (have) {
+            if (sl.s[t.si].qvar != q_var) {
+                q_var = sl.s[t.si].qvar;
+                const float2* cs = rope + (size_t)sl.qrot0[q_var] * (D / 2);
+#pragma unroll
+                for (int hh = 0; hh < MAXG; ++hh)
+                    if (hh < g.G) {
+                        const float* qh = q + ((size_t)b * g.Hq + hk * g.G + hh) * D;
+#pragma unroll
+                        for (int x = 0; x < EPL; ++x) {
+                            const int e = lane * EPL + x, pe = e < D / 2 ? e : e - D / 2;
+                            const float2 w = cs[pe];
+                            qr[hh][x] = (e < D / 2 ? rot_lo(qh[pe], qh[pe + D / 2], w.x, w.y) : rot_hi(qh[pe], qh[pe + D / 2], w.x, w.y)) * qscale;
+                        }
+                    }
+            }
+            const size_t row0 = (size_t)bh * g.slots + t.start;
+            float kv[U][EPL];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const size_t off = (row0 + min(r0 + u, t.nvalid - 1)) * D + lane * EPL;
+#pragma unroll
+                for (int x = 0; x < EPL; x += 4) {
+                    *reinterpret_cast<float4*>(&kv[u][x]) = *reinterpret_cast<const float4*>(Kr + off + x);
+                    *reinterpret_cast<float4*>(&vv[u][x]) = *reinterpret_cast<const float4*>(Vc + off + x);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int hh = 0; hh < MAXG; ++hh) {
+                    float a = 0.f;
+#pragma unroll
+                    for (int x = 0; x < EPL; ++x) a += qr[hh][x] * kv[u][x];
+#pragma unroll
+                    for (int w = 8; w > 0; w >>= 1) a += __shfl_xor(a, w, 16);
+                    if (lane == 0) {
+                        ps[(grp / 4) * kDecRows + r0 + u][hh] = r0 + u < t.nvalid ? a : -INFINITY;
+                        logits[((size_t)bh * n_tiles + t.tile) * (kDecRows * MAXG) + logit_index<MAXG>(r0 + u, hh)] = a;
+                    }
+                }
+        } else if (lane == 0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int hh = 0; hh < MAXG; ++hh) ps[(grp / 4) * kDecRows + r0 + u][hh] = -INFINITY;
+        }
+        __syncthreads();
+        // wave w: the 128 rows of heads w and w + 4
+#pragma unroll
+        for (int i = 0; i < (MAXG + kDecWaves - 1) / kDecWaves; ++i) {
+            const int hh = wave + i * kDecWaves;
+            if (hh < g.G) {
+                const float a0 = ps[l][hh], a1 = ps[l + 64][hh];
+                float mx = fmaxf(a0, a1);
+#pragma unroll
+                for (int w = 32; w > 0; w >>= 1) mx = fmaxf(mx, __shfl_xor(mx, w, 64));
+                const float mn = fmaxf(m_run[i], mx), mr = finite_max(mn), alpha = rescale_of(m_run[i], mn), p0 = exp2f(a0 - mr), p1 = exp2f(a1 - mr);
+                float sum = p0 + p1;
+#pragma unroll
+                for (int w = 32; w > 0; w >>= 1) sum += __shfl_xor(sum, w, 64);
+                m_run[i] = mn;
+                l_run[i] = l_run[i] * alpha + sum;
+                ps[l][hh] = p0;
+                ps[l + 64][hh] = p1;
+                if (l == 0) alpha_s[hh] = alpha;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int hh = 0; hh < MAXG; ++hh)
+            if (hh < g.G) {
+                const float alpha = alpha_s[hh];
+#pragma unroll
+                for (int x = 0; x < EPL; ++x) o[hh][x] *= alpha;
+                if (have) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const float p = ps[(grp / 4) * kDecRows + r0 + u][hh];
+#pragma unroll
+                        for (int x = 0; x < EPL; ++x) o[hh][x] += p * vv[u][x];
+                    }
+                }
+            }
+        __syncthreads();
+    }
+    // the four lane groups of a wave add up through lane shuffles, the waves through LDS
+#pragma unroll
+    for (int hh = 0; hh < MAXG; ++hh)
+#pragma unroll
+        for (int x = 0; x < EPL; ++x) {
+            float s = o[hh][x];
+            s += __shfl_xor(s, 16, 64);
+            s += __shfl_xor(s, 32, 64);
+            if (l < 16) osum[wave][hh][lane * EPL + x] = s;
+        }
+#pragma unroll
+    for (int i = 0; i < (MAXG + kDecWaves - 1) / kDecWaves; ++i) {
+        const int hh = wave + i * kDecWaves;
+        if (hh < g.G && l == 0) {
+            float* p = part_of(part, (size_t)b * g.Hq + hk * g.G + hh, n_splits, split);
+            p[0] = m_run[i];
+            p[1] = l_run[i];
+        }
+    }
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < g.G * D; idx += kDecThreads) {
+        const int hh = idx / D, e = idx % D;
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < kDecWaves; ++w) s += osum[w][hh][e];
+        opart[(((size_t)b * g.Hq + hk * g.G + hh) * n_splits + split) * D + e] = s;
+    }
+}
+
+// ------------------------------------------------------------------ finish
+//
+// Workgroups of one (sequence, KV head), told apart by blockIdx.x; none waits for another:
+//   0            the token's own score and its insertion (Alg. 2 for one token)
+//   1 .. G       the output of one query head: the splits' outputs and the own value, combined
+//   the rest     the EMA step of the cached rows' scores
+// The insertion reads and replaces at most one cached row per cascade (DecodeInsert names their slots,
+// which follow from the structure alone): workgroup 0 takes the EMA step of those rows itself and the
+// others leave them out, so the whole step needs no order between workgroups.
+// parts: what a launch does.  Homogeneous heads share their scores between the EMA step and the
+// insertion, and the diagnostic snapshot is taken there: those steps launch the two parts one after the other.
+constexpr int kFinishScores = 1, kFinishRest = 2;
+
+__device__ inline float reduce_heads(const Geom& g, float red, float p) { return g.head_reduce == CASCADE_REDUCE_MAX ? fmaxf(red, p) : red + p; }
+
+template <typename T, int D, int MAXG>
+__global__ __launch_bounds__(kDecThreads) void decode_finish_kernel(
+    Geom g, SegList sl, DecodeInsert ins, int parts, int n_tiles, int n_splits, int tiles_per_wg, int qstride, const float2* __restrict__ rope,
+    const float* __restrict__ logits, const float* __restrict__ part, const float* __restrict__ opart, const T* __restrict__ k_new,
+    const T* __restrict__ v_new, T* __restrict__ out, T* __restrict__ Kc, T* __restrict__ Kr, T* __restrict__ Vc, float* __restrict__ mu,
+    int32_t* __restrict__ ids, int32_t* __restrict__ swaps, float* __restrict__ mu_chunk)
+{
+    __shared__ float lse_s[MAXG], own_s[MAXG];
+    __shared__ float buf[kDecThreads * 4];
+    const int role = blockIdx.x + (parts & kFinishRest ? 0 : 1 + g.G), hk = blockIdx.y, b = blockIdx.z;
+    const int bh = b * g.Hkv + hk, tid = threadIdx.x, wave = tid >> 6, l = tid & 63;
+    const bool both = parts == (kFinishScores | kFinishRest);
+
+    // log2-sum-exp2 of the heads of a group, the own key included
+    auto combine = [&](int kv_head) {
+        for (int hh = wave; hh < g.G; hh += kDecWaves) {
+            const float* p = part + ((size_t)b * g.Hq + kv_head * g.G + hh) * (n_splits + 1) * 2;
+            float m = -INFINITY, s = 0.f;
+            for (int e = l; e <= n_splits; e += 64) ml_merge(m, s, p[2 * e], p[2 * e + 1]);
+            float mm = m;
+#pragma unroll
+            for (int w = 32; w > 0; w >>= 1) mm = fmaxf(mm, __shfl_xor(mm, w, 64));
+            s = m == -INFINITY ? 0.f : s * __builtin_amdgcn_exp2f(m - mm);
+#pragma unroll
+            for (int w = 32; w > 0; w >>= 1) s += __shfl_xor(s, w, 64);
+            if (l == 0) { lse_s[hh] = mm + __log2f(s); own_s[hh] = p[2 * n_splits]; }
+        }
+        __syncthreads();
+    };
+    const float beta = g.beta, omb = 1.f - g.beta;
+
+    if (role > g.G) {
+        // ---- scores: a thread takes four consecutive rows of a tile (16 gi + 4 c .. + 3)
+        const int t0 = (role - 1 - g.G) * tiles_per_wg, t1 = min(n_tiles, t0 + tiles_per_wg);
+        const int sub = tid & 7, gi = sub >> 2, c = sub & 3;
+        bool first = true;
+        for (int tb = t0; tb < t1; tb += kDecThreads / 8) {
+            const int tile = tb + tid / 8;
+            int start = 0, nvalid = 0, tile0 = 0;
+            for (int si = 0; si < sl.n; ++si) {
+                const int nt = tiles_of(sl.s[si].len);
+                if (tile >= tile0 && tile < tile0 + nt) {
+                    start = sl.s[si].start + (tile - tile0) * kDecRows;
+                    nvalid = min(kDecRows, sl.s[si].len - (tile - tile0) * kDecRows);
+                }
+                tile0 += nt;
+            }
+            const int r0 = 16 * gi + 4 * c;
+            const bool have = tile < t1 && r0 < nvalid;
+            float4 lg[MAXG];
+            float old[4];
+            float* pm = mu + (size_t)bh * g.slots + start + r0;
+            if (have) {
+                const float* lt = logits + ((size_t)bh * n_tiles + tile) * (kDecRows * MAXG);
+#pragma unroll
+                for (int hh = 0; hh < MAXG; ++hh) lg[hh] = *reinterpret_cast<const float4*>(lt + logit_index<MAXG>(r0, hh));
+#pragma unroll
+                for (int j = 0; j < 4; ++j) old[j] = r0 + j < nvalid ? pm[j] : 0.f;
+            }
+            if (first) { combine(hk); first = false; }     // (uniform; behind the first loads)
+            if (have) {
+                float red[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int hh = 0; hh < MAXG; ++hh)
+                    if (hh < g.G) {
+                        const float lse = lse_s[hh];
+                        red[0] = reduce_heads(g, red[0], __builtin_amdgcn_exp2f(lg[hh].x - lse));
+                        red[1] = reduce_heads(g, red[1], __builtin_amdgcn_exp2f(lg[hh].y - lse));
+                        red[2] = reduce_heads(g, red[2], __builtin_amdgcn_exp2f(lg[hh].z - lse));
+                        red[3] = reduce_heads(g, red[3], __builtin_amdgcn_exp2f(lg[hh].w - lse));
+                    }
+                int skip = -1;                             // the insertion's rows are workgroup 0's (rarely here at all)
+                if (both)
+                    for (int i = 0; i < ins.n; ++i) {
+                        const int r = ins.slot[i] - (start + r0);
+                        if (r >= 0 && r < 4) skip = skip < 0 ? 1 << r : skip | (1 << r);
+                    }
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (r0 + j < nvalid && (skip < 0 || !(skip >> j & 1)))
+                        pm[j] = beta * old[j] + omb * (g.head_reduce == CASCADE_REDUCE_MAX ? red[j] : red[j] / (float)g.G);
+            }
+        }
+        return;
+    }
+
+    if (role > 0) {
+        // ---- output of query head hk * G + role - 1: four elements per thread, the splits over the thread groups
+        constexpr int TPR = D / 4, NG = kDecThreads / TPR;
+        const int hh = role - 1, e4 = tid % TPR, sg = tid / TPR;
+        const size_t head = (size_t)b * g.Hq + hk * g.G + hh;
+        combine(hk);
+        const float lse = lse_s[hh];
+        const float* p = part + head * (n_splits + 1) * 2;
+        const float4* op = reinterpret_cast<const float4*>(opart + head * n_splits * D) + e4;
+        float4 a = {0.f, 0.f, 0.f, 0.f};
+        for (int s = sg; s < n_splits; s += NG) {
+            const float w = p[2 * s + 1] == 0.f ? 0.f : __builtin_amdgcn_exp2f(p[2 * s] - lse);   // an empty split has no maximum
+            const float4 x = op[(size_t)s * TPR];
+            a.x += w * x.x; a.y += w * x.y; a.z += w * x.z; a.w += w * x.w;
+        }
+        reinterpret_cast<float4*>(buf)[tid] = a;
+        __syncthreads();
+        if (tid < D) {
+            float s = __builtin_amdgcn_exp2f(own_s[hh] - lse) * Elem<T>::load(v_new + ((size_t)b * g.Hkv + hk) * D + tid);
+#pragma unroll
+            for (int x = 0; x < NG; ++x) s += buf[x * D + tid];
+            Elem<T>::store(out + head * D + tid, s);
+        }
+        return;
+    }
+
+    // ---- the token's score, and its insertion
+    // independent heads: the query heads of this KV head; homogeneous heads: all query heads (every
+    // workgroup of the sequence computes the same value, group by group in the same order)
+    const bool all = g.head_policy == CASCADE_HEADS_HOMOGENEOUS;
+    float own = 0.f;
+    for (int kv = all ? 0 : hk; kv < (all ? g.Hkv : hk + 1); ++kv) {
+        if (all) __syncthreads();                          // the previous group's values have been read
+        combine(kv);
+        float red = 0.f;
+        for (int hh = 0; hh < g.G; ++hh) red = reduce_heads(g, red, __builtin_amdgcn_exp2f(own_s[hh] - lse_s[hh]));
+        if (g.head_reduce == CASCADE_REDUCE_MEAN) red /= (float)g.G;
+        own = reduce_heads(g, own, red);
+    }
+    if (all && g.head_reduce == CASCADE_REDUCE_MEAN) own /= (float)g.Hkv;
+    own *= omb;
+    // the scores of the rows that compete or move on, after this step
+    if (tid < ins.n && ins.kind[tid] != kInsertAppend) {
+        const int slot = ins.slot[tid];
+        float v = mu[(size_t)bh * g.slots + slot];
+        if (both) {
+            int tile0 = 0;
+            for (int si = 0; si < sl.n; ++si) {
+                const int r = slot - sl.s[si].start;
+                if (r >= 0 && r < sl.s[si].len) {
+                    const float* lt = logits + ((size_t)bh * n_tiles + tile0 + r / kDecRows) * (kDecRows * MAXG);
+                    float red = 0.f;
+                    for (int hh = 0; hh < g.G; ++hh)
+                        red = reduce_heads(g, red, __builtin_amdgcn_exp2f(lt[logit_index<MAXG>(r % kDecRows, hh)] - lse_s[hh]));
+                    v = beta * v + omb * (g.head_reduce == CASCADE_REDUCE_MAX ? red : red / (float)g.G);
+                }
+                tile0 += tiles_of(sl.s[si].len);
+            }
+        }
+        buf[tid] = v;
+    }
+    __syncthreads();
+    // Who ends up where: the token (or what the cascade before evicted) is offered to one cascade after the
+    // other; it is appended, or takes the place of the oldest item, which moves on, or competes with the
+    // newest item, which stays unless the offer's score is strictly higher.  A thread group per cascade moves its row.
+    constexpr int LPR = D / 16;
+    const int mine = tid / LPR, lane = tid % LPR;
+    float offered = own, my_score = 0.f;
+    bool my_move = false;
+    for (int i = 0; i < ins.n; ++i) {
+        const float held = buf[i];
+        const bool takes = ins.kind[i] != kInsertCompete || (g.token_selection && offered > held);
+        if (i == mine) { my_move = takes; my_score = takes ? offered : held; }
+        if (takes && ins.kind[i] == kInsertCompete && tid == 0) swaps[bh * g.N + i] += 1;
+        offered = held;
+    }
+    float k0[8], k1[8], v0[8], v1[8];
+    int id = ins.id0;
+    if (my_move) {
+        const T *ks = k_new + ((size_t)b * g.Hkv + hk) * D, *vs = v_new + ((size_t)b * g.Hkv + hk) * D;
+        if (mine > 0) {
+            const size_t srow = (size_t)bh * g.slots + ins.slot[mine - 1];
+            ks = Kc + srow * D;
+            vs = Vc + srow * D;
+            id = ids[srow];
+        }
+        Vec8<T>::load(ks + lane * 8, k0);
+        Vec8<T>::load(ks + D / 2 + lane * 8, k1);
+        Vec8<T>::load(vs + lane * 8, v0);
+        Vec8<T>::load(vs + D / 2 + lane * 8, v1);
+    }
+    __syncthreads();                                       // every source has been read
+    if (tid == 0) mu_chunk[(size_t)bh * qstride] = own;
+    if (mine < ins.n) {
+        const int dst = ins.slot[mine];
+        const size_t drow = (size_t)bh * g.slots + dst;
+        if (lane == 0) mu[drow] = my_score;
+        if (my_move) {
+            Vec8<T>::store(Kc + drow * D + lane * 8, k0);
+            Vec8<T>::store(Kc + drow * D + D / 2 + lane * 8, k1);
+            rotate8<T>(k0, k1, rope + (size_t)dst * (D / 2) + lane * 8, Kr + drow * D + lane * 8, Kr + drow * D + D / 2 + lane * 8);
+            Vec8<T>::store(Vc + drow * D + lane * 8, v0);
+            Vec8<T>::store(Vc + drow * D + D / 2 + lane * 8, v1);
+            if (lane == 0) ids[drow] = id;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ launchers
 
-static int per_split_of(const DevBuffers& bf, int n)
-{
-    int per_split = (n + bf.dec_splits - 1) / bf.dec_splits;
-    per_split = ((per_split + 63) / 64) * 64;
-    return per_split == 0 ? 64 : per_split;
-}
-
-static int maxg_of(const Geom& g) { return g.G <= 1 ? 1 : (g.G <= 2 ? 2 : (g.G <= 4 ? 4 : 8)); }
-
-int decode_logit_heads(const Geom& g) { return maxg_of(g); }
-
-template <typename T, int EPL, int MAXG>
-static void qk_valu(const Geom& g, const DevBuffers& bf, const SegList& sl, const void* q, const void* k, hipStream_t s)
-{
-    const dim3 grid(bf.dec_splits, g.Hkv, g.B), block(kDecThreads);
-    hipLaunchKernelGGL((decode_qk_valu_kernel<T, EPL, MAXG>), grid, block, 0, s, g, sl, per_split_of(bf, sl.n_cached),
-                       (const T*)q, (const T*)k, (const T*)bf.Kr, bf.rope, bf.logits, bf.part, bf.dec_splits);
-}
-
-template <typename T, int EPL, int MAXG>
-static void pv_typed(const Geom& g, const DevBuffers& bf, const SegList& sl, hipStream_t s)
-{
-    const dim3 grid(bf.dec_splits, g.Hkv, g.B), block(kDecThreads);
-    // the log-sum-exp of the step lives in the first B*Hq entries of the chunk scratch
-    hipLaunchKernelGGL((decode_pv_kernel<T, EPL, MAXG>), grid, block, 0, s, g, sl, per_split_of(bf, sl.n_cached),
-                       (const T*)bf.Vc, bf.logits, bf.part, bf.dec_splits, bf.opart, bf.mu, bf.lse);
-}
-
-#define CKV_G_SWITCH(fn, T, EPL, ...)                          \
-    switch (maxg_of(g)) {                                      \
-        case 1: fn<T, EPL, 1>(__VA_ARGS__); break;             \
-        case 2: fn<T, EPL, 2>(__VA_ARGS__); break;             \
-        case 4: fn<T, EPL, 4>(__VA_ARGS__); break;             \
-        default: fn<T, EPL, 8>(__VA_ARGS__); break;            \
-    }
-
-#define CKV_DISPATCH(fn, ...)                                                                   \
-    do {                                                                                        \
-        const int epl = g.d / kLanesPerRow;                                                     \
-        if (dtype == CASCADE_F32) {                                                             \
-            if (epl == 8) { CKV_G_SWITCH(fn, float, 8, __VA_ARGS__) } else { CKV_G_SWITCH(fn, float, 4, __VA_ARGS__) } \
-        } else {                                                                                \
-            if (epl == 8) { CKV_G_SWITCH(fn, bf16_t, 8, __VA_ARGS__) } else { CKV_G_SWITCH(fn, bf16_t, 4, __VA_ARGS__) } \
-        }                                                                                       \
-    } while (0)
-
-void launch_decode_qk(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, const void* q, const void* k,
-                      hipStream_t s)
-{
-    if (dtype == CASCADE_BF16) {
-        const dim3 grid(b.dec_splits, g.Hkv, g.B), block(kDecThreads);
-        const int ps = per_split_of(b, sl.n_cached);
-        const bool direct_only = b.opt_decode_qk_direct != 0;
-        const int mg = maxg_of(g);
-        const int rotations = 96 / mg < kMaxQueryRotations ? 96 / mg : kMaxQueryRotations;
-        // the streaming kernel keeps every rotation of the queries in LDS
-        const bool stream = !direct_only && sl.n_qvar <= rotations;
-#define CKV_QK_MFMA(D, MG)                                                                                        \
-    do {                                                                                                          \
-        if (stream)                                                                                               \
-            hipLaunchKernelGGL((decode_qk_stream_kernel<D, MG>), grid, block, 0, s, g, sl, ps, (const bf16_t*)q,    \
-                               (const bf16_t*)k, (const bf16_t*)b.Kr, b.rope, b.logits, b.part, b.dec_splits);    \
-        else                                                                                                      \
-            hipLaunchKernelGGL((decode_qk_mfma_kernel<D, MG>), grid, block, 0, s, g, sl, ps, (const bf16_t*)q,      \
-                               (const bf16_t*)k, (const bf16_t*)b.Kr, b.rope, b.logits, b.part, b.dec_splits);    \
-    } while (0)
-        if (g.d == 128) {
-            if (mg == 1) CKV_QK_MFMA(128, 1); else if (mg == 2) CKV_QK_MFMA(128, 2); else if (mg == 4) CKV_QK_MFMA(128, 4); else CKV_QK_MFMA(128, 8);
-        } else {
-            if (mg == 1) CKV_QK_MFMA(64, 1); else if (mg == 2) CKV_QK_MFMA(64, 2); else if (mg == 4) CKV_QK_MFMA(64, 4); else CKV_QK_MFMA(64, 8);
-        }
-#undef CKV_QK_MFMA
-        return;
-    }
-    CKV_DISPATCH(qk_valu, g, b, sl, q, k, s);
-}
-
-void launch_decode_pv(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, hipStream_t s)
-{
-    const bool valu_only = b.opt_decode_pv_valu != 0;
-    if (dtype == CASCADE_BF16 && !valu_only) {
-        const dim3 grid(b.dec_splits, g.Hkv, g.B), block(kDecThreads);
-        const int ps = per_split_of(b, sl.n_cached);
-#define CKV_PV_MFMA(D, MG)                                                                                 \
-    hipLaunchKernelGGL((decode_pv_mfma_kernel<D, MG>), grid, block, 0, s, g, sl, ps, (const bf16_t*)b.Vc, b.logits, \
-                       b.part, b.dec_splits, b.opart, b.mu, b.lse)
-        const int mg = maxg_of(g);
-        if (g.d == 128) {
-            if (mg == 1) CKV_PV_MFMA(128, 1); else if (mg == 2) CKV_PV_MFMA(128, 2); else if (mg == 4) CKV_PV_MFMA(128, 4); else CKV_PV_MFMA(128, 8);
-        } else {
-            if (mg == 1) CKV_PV_MFMA(64, 1); else if (mg == 2) CKV_PV_MFMA(64, 2); else if (mg == 4) CKV_PV_MFMA(64, 4); else CKV_PV_MFMA(64, 8);
-        }
-#undef CKV_PV_MFMA
-        return;
-    }
-    CKV_DISPATCH(pv_typed, g, b, sl, s);
-}
-
-void launch_decode_finish(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, const UpdatePlan& pl, int qstride,
-                          const void* k, const void* v, void* out, hipStream_t s)
-{
-    const dim3 grid(g.Hkv, g.B), block(256);
-    const UpdateBuffers upd = {b.rope, b.offers, b.winners, b.swaps, b.Kc, b.Kr, b.Vc, b.mu, b.ids, b.mu_chunk,
-                               k, v, (long)g.Hkv * g.d, (long)g.Hkv * g.d};
-    if (dtype == CASCADE_F32)
-        hipLaunchKernelGGL(decode_finish_kernel<float>, grid, block, 0, s, g, pl, upd, sl.n_cached, b.dec_splits, qstride, maxg_of(g), b.opart,
-                           b.logits, b.lse, (const float*)v, (float*)out, b.mu_chunk);
-    else
-        hipLaunchKernelGGL(decode_finish_kernel<bf16_t>, grid, block, 0, s, g, pl, upd, sl.n_cached, b.dec_splits, qstride, maxg_of(g), b.opart,
-                           b.logits, b.lse, (const bf16_t*)v, (bf16_t*)out, b.mu_chunk);
-}
-
 bool decode_supported(const Geom& g) { return (g.d == 64 || g.d == 128) && g.G <= kMaxG; }
+
+int decode_logit_heads(const Geom& g) { return g.G <= 1 ? 1 : (g.G <= 2 ? 2 : (g.G <= 4 ? 4 : 8)); }
+
+int decode_max_tiles(const Geom& g) { return g.slots / kDecRows + 2 * g.N + 1; }
+
+int decode_tiles(const SegList& sl)
+{
+    int n = 0;
+    for (int i = 0; i < sl.n; ++i) n += (sl.s[i].len + kDecRows - 1) / kDecRows;
+    return n;
+}
+
+// Splits of a step: as many as make the busiest compute unit finish first.  A CU holds one workgroup of
+// the MFMA kernel (its ring fills the LDS at d = 128), whose four waves share the split's tiles; a
+// workgroup costs about as much as kWgTiles rounds of its waves besides (first copies, queries, epilogue).
+int decode_split_count(const Geom& g, const DevBuffers& b, int n_tiles)
+{
+    constexpr int kWgTiles = 2;
+    const int bh = g.B * g.Hkv;
+    int best = 1;
+    long best_cost = -1;
+    for (int s = 1; s <= b.dec_splits; ++s) {
+        const long rounds = (bh * (long)s + 255) / 256, tiles = (n_tiles + s - 1) / s;
+        const long cost = rounds * ((tiles + kDecWaves - 1) / kDecWaves + kWgTiles);
+        if (best_cost < 0 || cost < best_cost) { best = s; best_cost = cost; }
+    }
+    return best;
+}
+
+#define CKV_DECODE_G(fn, T, D)                                 \
+    switch (decode_logit_heads(g)) {                           \
+        case 1: fn(T, D, 1); break;                            \
+        case 2: fn(T, D, 2); break;                            \
+        case 4: fn(T, D, 4); break;                            \
+        default: fn(T, D, 8); break;                           \
+    }
+
+void launch_decode_attend(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, int n_splits, const void* q, const void* k,
+                          hipStream_t s)
+{
+    const dim3 grid(n_splits, g.Hkv, g.B), block(kDecThreads);
+    const int n_tiles = decode_tiles(sl);
+    const float qscale = g.scale * kLog2e;
+#define CKV_ATTEND_F32(T, D, MG)                                                                                          \
+    hipLaunchKernelGGL((decode_attend_f32_kernel<D, MG>), grid, block, 0, s, g, sl, n_tiles, n_splits, qscale, (const T*)q, \
+                       (const T*)k, (const T*)b.Kr, (const T*)b.Vc, b.rope, b.logits, b.part, b.opart)
+#define CKV_ATTEND_MFMA(T, D, MG)                                                                                         \
+    hipLaunchKernelGGL((decode_attend_kernel<D, MG>), grid, block, 0, s, g, sl, n_tiles, n_splits, qscale, (const T*)q,     \
+                       (const T*)k, (const T*)b.Kr, (const T*)b.Vc, b.rope, b.logits, b.part, b.opart)
+    if (dtype == CASCADE_F32) {
+        if (g.d == 128) { CKV_DECODE_G(CKV_ATTEND_F32, float, 128) } else { CKV_DECODE_G(CKV_ATTEND_F32, float, 64) }
+    } else {
+        if (g.d == 128) { CKV_DECODE_G(CKV_ATTEND_MFMA, bf16_t, 128) } else { CKV_DECODE_G(CKV_ATTEND_MFMA, bf16_t, 64) }
+    }
+#undef CKV_ATTEND_F32
+#undef CKV_ATTEND_MFMA
+}
+
+void launch_decode_finish(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, const DecodeInsert& ins, int n_splits, bool scores,
+                          bool rest, int qstride, const void* k, const void* v, void* out, hipStream_t s)
+{
+    const int n_tiles = decode_tiles(sl);
+    // score workgroups: 32 tiles each (one round of their threads), up to four rounds where there are many
+    int per_wg = 32;
+    while (per_wg < 128 && (long)g.B * g.Hkv * ((n_tiles + per_wg - 1) / per_wg) > 2048) per_wg *= 2;
+    const int wgs = (rest ? 1 + g.G : 0) + (scores ? (n_tiles + per_wg - 1) / per_wg : 0);
+    if (wgs == 0) return;
+    const dim3 grid(wgs, g.Hkv, g.B), block(kDecThreads);
+    const int parts = (scores ? kFinishScores : 0) | (rest ? kFinishRest : 0);
+#define CKV_FINISH(T, D, MG)                                                                                                       \
+    hipLaunchKernelGGL((decode_finish_kernel<T, D, MG>), grid, block, 0, s, g, sl, ins, parts, n_tiles, n_splits, per_wg, qstride, b.rope, \
+                       b.logits, b.part, b.opart, (const T*)k, (const T*)v, (T*)out, (T*)b.Kc, (T*)b.Kr, (T*)b.Vc, b.mu, b.ids,     \
+                       b.swaps, b.mu_chunk)
+    if (dtype == CASCADE_F32) {
+        if (g.d == 128) { CKV_DECODE_G(CKV_FINISH, float, 128) } else { CKV_DECODE_G(CKV_FINISH, float, 64) }
+    } else {
+        if (g.d == 128) { CKV_DECODE_G(CKV_FINISH, bf16_t, 128) } else { CKV_DECODE_G(CKV_FINISH, bf16_t, 64) }
+    }
+#undef CKV_FINISH
+}
 
 }  // namespace ckv

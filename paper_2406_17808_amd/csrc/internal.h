@@ -104,6 +104,18 @@ struct UpdatePlan {
     CascStep c[kMaxCascades];
 };
 
+// The insertion of one token: what every cascade it or an evicted item reaches does with its offer, and the
+// slot concerned.  Entry 0 is the first cascade (or a free sink slot), entry i is offered what entry i - 1 held.
+constexpr int kInsertAppend = 0;    // the slot is free; nothing goes further
+constexpr int kInsertPush = 1;      // the slot's item (the oldest) moves on to the next entry
+constexpr int kInsertCompete = 2;   // the offer competes with the slot's item (the newest); nothing goes further
+struct DecodeInsert {
+    int n;
+    int id0;                        // original index of the token
+    int slot[kMaxCascades];
+    int kind[kMaxCascades];
+};
+
 // A few runs of 64-row tiles (of the packed K / V copies the bf16 attention kernel reads).
 constexpr int kMaxTileRuns = 2 * CASCADE_MAX_CASCADES + 2;   // sinks, two per ring, the chunk
 struct TileRuns {

@@ -39,9 +39,9 @@ struct DevBuffers {
     int32_t* winners;// [B,Hkv,N,max_chunk+1]
     void* move_stage;// [B,Hkv,move_stage_rows] x (K row, V row, score, id): sources of the update's moves, gathered before any is overwritten
     int move_stage_rows;
-    // decode scratch
-    float* logits;   // [B,Hkv,slots+1,decode_logit_heads]
-    float* part;     // [B,Hq,dec_splits,2] (max, sum) of every split
+    // decode scratch (in the memory of the per-call scratch of the prefill path)
+    float* logits;   // [B,Hkv,decode_max_tiles,32,decode_logit_heads] (the stride is the number of tiles of the step)
+    float* part;     // [B,Hq,dec_splits+1,2] (max, sum) of every split, and the own logit
     float* opart;    // [B,Hq,dec_splits,d]
     int rope_rows;
     int dec_splits;
@@ -50,8 +50,6 @@ struct DevBuffers {
     // created; no launch looks at the environment
     int opt_attn_splits;       // CASCADE_KV_ATTN_SPLITS: workgroups per row block of a small attention launch; 0 = automatic
     int opt_score_narrow;      // CASCADE_KV_SCORE_NARROW: 0 / 1 force the 64- / 32-key form of the score kernel; -1 = automatic
-    int opt_decode_qk_direct;  // CASCADE_KV_DECODE_QK_DIRECT: bf16 decode logits by the register-load kernel
-    int opt_decode_pv_valu;    // CASCADE_KV_DECODE_PV_VALU: bf16 decode outputs by the VALU kernel
     int opt_update_staged;     // CASCADE_KV_UPDATE_STAGED: always plan the update cascade by cascade (plan_kernel)
 };
 
@@ -98,12 +96,15 @@ void launch_score_mfma(const Geom& g, const DevBuffers& b, const SegList& sl, in
                        int tail_rows, float decay, hipStream_t s);
 
 // decode
-void launch_decode_qk(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl,
-                      const void* q, const void* k, hipStream_t s);
-void launch_decode_pv(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, hipStream_t s);
-// merges the split outputs into `out`, gives the new token its score and inserts it (plan and moves of `pl`, one token)
-void launch_decode_finish(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, const UpdatePlan& pl, int qstride,
-                          const void* k, const void* v, void* out, hipStream_t s);
+int decode_max_tiles(const Geom& g);     // logits are kept for at most this many tiles of 32 rows per (batch, KV head)
+int decode_split_count(const Geom& g, const DevBuffers& b, int n_tiles);
+int decode_tiles(const SegList& sl);
+void launch_decode_attend(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, int n_splits, const void* q, const void* k,
+                          hipStream_t s);
+// scores: the EMA step of the cached rows' scores; rest: merges the split outputs into `out`, gives the new token its
+// score and inserts it.  One launch may do both.
+void launch_decode_finish(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, const DecodeInsert& ins, int n_splits, bool scores,
+                          bool rest, int qstride, const void* k, const void* v, void* out, hipStream_t s);
 bool decode_supported(const Geom& g);
 int decode_logit_heads(const Geom& g);   // heads per row of the logits buffer (group size rounded up to 1, 2, 4, 8)
 

@@ -167,14 +167,31 @@ void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, 
         if (cnt < cap) {
             add(base, cnt, rank - base, 0);
         } else {
-            const int o = xi % 64, wrapped = rank + (cap - xi) - base;
-            add(base, o, wrapped, 0);                                 // wrapped part: ring [0, xi), in two pieces
+            const int o = with_chunk ? xi % 64 : 0, wrapped = rank + (cap - xi) - base;
+            add(base, o, wrapped, 0);                                 // wrapped part: ring [0, xi), in two pieces (packed tiles only)
             add(base + o, xi - o, wrapped, 0);
             add(base + xi, cap - xi, rank - (base + xi), 0);          // oldest part: ring [xi, cap)
         }
         rank += cnt;
     }
     if (with_chunk) add(0, Q, n, 1);                 // chunk key i is rotated to i and sits at n + i
+}
+
+void plan_insert(const Geom& g, const UpdatePlan& plan, DecodeInsert& out)
+{
+    out.n = 0;
+    out.id0 = plan.id0;
+    auto add = [&](int kind, int slot) { out.kind[out.n] = kind; out.slot[out.n] = slot; ++out.n; };
+    if (plan.n_to_sink > 0) {
+        add(kInsertAppend, plan.sink_fill0);
+        return;
+    }
+    for (int c = 0; c < g.N && plan.c[c].M > 0; ++c) {
+        const CascStep& cs = plan.c[c];
+        if (cs.A > 0) add(kInsertAppend, cs.base + cs.wpos0);
+        else if (cs.P > 0) add(kInsertPush, cs.base + cs.wpos0);
+        else add(kInsertCompete, cs.base + cs.newest0);
+    }
 }
 
 void packed_layout(const Geom& g, const HostState& st, PackedLayout& out)

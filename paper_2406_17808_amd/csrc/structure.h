@@ -44,6 +44,9 @@ struct HostState {
 // Structure of inserting Q tokens in order (Alg. 2 applied Q times); advances `st`.
 void plan_update(const Geom& g, HostState& st, int Q, UpdatePlan& plan);
 
+// The plan of one token (plan_update with Q = 1) as a chain of slots.
+void plan_insert(const Geom& g, const UpdatePlan& plan, DecodeInsert& out);
+
 // Runs of physical rows that share one query rotation, for the state BEFORE a chunk of Q tokens.
 // with_chunk: append the segment of the chunk's own keys.
 void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, SegList& out);

@@ -545,3 +545,36 @@ def test_error_paths_on_device(oracle_mod):
     st = c.read_state()
     assert st.count == 0 and st.n_seen == 0
     c.close()
+
+
+@pytest.mark.parametrize("dtype,d,G,sizes", [
+    (B.CASCADE_BF16, 128, 4, [37, 64, 23]), (B.CASCADE_BF16, 64, 8, [1, 2, 33]), (B.CASCADE_BF16, 128, 1, [300, 31]),
+    (B.CASCADE_BF16, 64, 3, [128] * 4), (B.CASCADE_F32, 64, 2, [40, 9]), (B.CASCADE_F32, 128, 5, [150, 64]),
+])
+def test_decode_in_one_finish_launch(dtype, d, G, sizes):
+    """The scores' EMA step and the insertion in one launch (the rows the insertion looks at are left to
+    it) leave bit for bit what they leave as two launches (keep_update_scores: a snapshot comes in between)."""
+    import torch
+    from paper_2406_17808_amd.cache import CascadeKVCache
+    caches = []
+    for keep in (0, 1):
+        cfg = B.make_config(batch=2, n_q_heads=2 * G, n_kv_heads=2, head_dim=d, dtype=dtype, n_sink=3, cascade_sizes=sizes,
+                            ema_beta=0.9, rope_base=10000.0, max_chunk=64, keep_update_scores=keep)
+        caches.append(CascadeKVCache(cfg))
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(d + G)
+    for step in range(220):
+        n = 50 if step == 10 else 1
+        q, k, v = (torch.randn((2, n, h, d), generator=gen, device="cuda:0").to(caches[0].torch_dtype) for h in (2 * G, 2, 2))
+        if n == 1:
+            a, b = (c.decode_step(q[:, 0], k[:, 0], v[:, 0]) for c in caches)
+        else:
+            a, b = (c.prefill_chunk(q, k, v) for c in caches)
+        assert torch.equal(a, b), step
+        if step % 20 == 19 or step < 12:
+            x, y = (c.read_state(with_kv=True) for c in caches)
+            for name in ("ids", "mu", "slot", "k", "v"):
+                assert np.array_equal(getattr(x, name), getattr(y, name)), (step, name)
+            assert np.array_equal(x.swaps, y.swaps), step
+    for c in caches:
+        c.close()
