@@ -66,27 +66,45 @@ __device__ inline float finite_max(float m) { return m == -INFINITY ? 0.f : m; }
 // key (its logit, 1); opart[(b, query head)][split][d] unnormalised.
 __device__ inline float* part_of(float* part, size_t head, int n_splits, int split) { return part + (head * (n_splits + 1) + split) * 2; }
 
-// The own key: <R(n) q, R(n) k> = <q, k>.  One wave per head of the group.
+// The own key: <R(n) q, R(n) k> = <q, k>.  One wave per head of the group (heads wave and wave + 4); load() early,
+// finish() when there is nothing better to do.
 template <typename T, int D>
-__device__ inline void own_logits(const Geom& g, int b, int hk, const T* __restrict__ q, const T* __restrict__ k_new, float qscale,
-                                  float* __restrict__ part, int n_splits)
-{
-    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const T* kn = k_new + ((size_t)b * g.Hkv + hk) * D;
-    for (int hh = wave; hh < g.G; hh += kDecWaves) {
-        const size_t head = (size_t)b * g.Hq + hk * g.G + hh;
-        float acc = 0.f;
+struct OwnLogits {
+    static constexpr int NH = kMaxG / kDecWaves, NE = D / 64;
+    float qe[NH][NE], ke[NE];
+    __device__ void load(const Geom& g, int b, int hk, const T* __restrict__ q, const T* __restrict__ k_new)
+    {
+        const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
 #pragma unroll
-        for (int e = 0; e < D; e += 64) acc += Elem<T>::load(q + head * D + e + l) * Elem<T>::load(kn + e + l);
+        for (int x = 0; x < NE; ++x) {
+            ke[x] = Elem<T>::load(k_new + ((size_t)b * g.Hkv + hk) * D + x * 64 + l);
 #pragma unroll
-        for (int w = 32; w > 0; w >>= 1) acc += __shfl_xor(acc, w, 64);
-        if (l == 0) {
-            float* p = part_of(part, head, n_splits, n_splits);
-            p[0] = acc * qscale;
-            p[1] = 1.f;
+            for (int i = 0; i < NH; ++i) {
+                const int hh = min(wave + i * kDecWaves, g.G - 1);
+                qe[i][x] = Elem<T>::load(q + ((size_t)b * g.Hq + hk * g.G + hh) * D + x * 64 + l);
+            }
         }
     }
-}
+    __device__ void finish(const Geom& g, int b, int hk, float qscale, float* __restrict__ part, int n_splits) const
+    {
+        const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+#pragma unroll
+        for (int i = 0; i < NH; ++i) {
+            const int hh = wave + i * kDecWaves;
+            if (hh >= g.G) break;
+            float acc = 0.f;
+#pragma unroll
+            for (int x = 0; x < NE; ++x) acc += qe[i][x] * ke[x];
+#pragma unroll
+            for (int w = 32; w > 0; w >>= 1) acc += __shfl_xor(acc, w, 64);
+            if (l == 0) {
+                float* p = part_of(part, (size_t)b * g.Hq + hk * g.G + hh, n_splits, n_splits);
+                p[0] = acc * qscale;
+                p[1] = 1.f;
+            }
+        }
+    }
+};
 
 // ------------------------------------------------------------------ attend, bf16: MFMA fed from LDS
 //
@@ -105,8 +123,8 @@ __device__ inline void own_logits(const Geom& g, int b, int hk, const T* __restr
 //
 // Bound by memory where the cache is large, by the latency of one tile where it is small.  Measured with
 // separate passes over K and V (three launches a step, one workgroup merging 33 splits) against this
-// kernel and decode_finish, us a step: 8K slots 59.1 -> 20.1, 4K slots 40.6 -> 18.0 a layer, 8 sequences of 16K slots
-// 254.7 -> 111.2.
+// kernel and decode_finish, us a step: 8K slots 59.1 -> 18.9, 4K slots 40.6 -> 16.1 a layer, 8 sequences of 16K slots
+// 254.7 -> 109.5.
 //
 // The piece permutations (16-byte pieces of a staged row): the 16 rows of a K fragment read, and the
 // 8 rows one half of a wave reads in a transposing read, fall into different banks.
@@ -209,7 +227,8 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_attend_kernel(
             issue(vbh, v_off, prod, 2 * i + 1);
             prod.advance(sl, kDecWaves);
         }
-    if (split == 0) own_logits<bf16_t, D>(g, b, hk, q, k_new, qscale, part, n_splits);
+    OwnLogits<bf16_t, D> own;
+    if (split == 0) own.load(g, b, hk, q, k_new);
 
     // fragment reads of this lane.  K: row 16 gi + n, piece 4 ks + c.  V: row 16 hf + 4 c + n / 4, 8 bytes
     // at element 16 db + 4 (n % 4)
@@ -340,6 +359,7 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_attend_kernel(
         cons.advance(sl, kDecWaves);
     }
     wait_vm_fenced<0>();
+    if (split == 0) own.finish(g, b, hk, qscale, part, n_splits);
     lsum += __shfl_xor(lsum, 16, 64);
     lsum += __shfl_xor(lsum, 32, 64);
     if (c == 0) { red_m[wave][n] = m; red_l[wave][n] = lsum; }
@@ -391,7 +411,11 @@ __global__ __launch_bounds__(kDecThreads) void decode_attend_f32_kernel(
     const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
     const int grp = threadIdx.x / 16, lane = threadIdx.x % 16, r0 = (grp % 4) * U;   // tile grp / 4 of the four, rows r0 .. r0 + 7 of it
     const int t_first = (int)((long long)n_tiles * split / n_splits), t_end = (int)((long long)n_tiles * (split + 1) / n_splits);
-    if (split == 0) own_logits<float, D>(g, b, hk, q, k_new, qscale, part, n_splits);
+    if (split == 0) {
+        OwnLogits<float, D> own;
+        own.load(g, b, hk, q, k_new);
+        own.finish(g, b, hk, qscale, part, n_splits);
+    }
     float o[MAXG][EPL], qr[MAXG][EPL];
 #pragma unroll
     for (int hh = 0; hh < MAXG; ++hh)
@@ -530,6 +554,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_attend_f32_kernel(
 // The insertion reads and replaces at most one cached row per cascade (DecodeInsert names their slots,
 // which follow from the structure alone): workgroup 0 takes the EMA step of those rows itself and the
 // others leave them out, so the whole step needs no order between workgroups.
+// Bound by latency: every workgroup loads what it may need before it waits for the combined maxima (8 sequences
+// and below: 8.1 -> 6.7 us against loads that follow the decisions they depend on).
 // parts: what a launch does.  Homogeneous heads share their scores between the EMA step and the
 // insertion, and the diagnostic snapshot is taken there: those steps launch the two parts one after the other.
 constexpr int kFinishScores = 1, kFinishRest = 2;
@@ -627,20 +653,32 @@ __global__ __launch_bounds__(kDecThreads) void decode_finish_kernel(
         constexpr int TPR = D / 4, NG = kDecThreads / TPR;
         const int hh = role - 1, e4 = tid % TPR, sg = tid / TPR;
         const size_t head = (size_t)b * g.Hq + hk * g.G + hh;
-        combine(hk);
-        const float lse = lse_s[hh];
         const float* p = part + head * (n_splits + 1) * 2;
         const float4* op = reinterpret_cast<const float4*>(opart + head * n_splits * D) + e4;
-        float4 a = {0.f, 0.f, 0.f, 0.f};
-        for (int s = sg; s < n_splits; s += NG) {
-            const float w = p[2 * s + 1] == 0.f ? 0.f : __builtin_amdgcn_exp2f(p[2 * s] - lse);   // an empty split has no maximum
-            const float4 x = op[(size_t)s * TPR];
-            a.x += w * x.x; a.y += w * x.y; a.z += w * x.z; a.w += w * x.w;
+        // the first splits' outputs are on their way while the maxima are combined
+        constexpr int kEarly = 4;
+        float4 x[kEarly];
+        float2 ml[kEarly];
+#pragma unroll
+        for (int i = 0; i < kEarly; ++i) {
+            const int s = min(sg + i * NG, n_splits - 1);
+            x[i] = op[(size_t)s * TPR];
+            ml[i] = *reinterpret_cast<const float2*>(p + 2 * s);
         }
+        const float vn = tid < D ? Elem<T>::load(v_new + ((size_t)b * g.Hkv + hk) * D + tid) : 0.f;
+        combine(hk);
+        const float lse = lse_s[hh];
+        auto weight = [&](float m, float l) { return l == 0.f ? 0.f : __builtin_amdgcn_exp2f(m - lse); };   // an empty split has no maximum
+        float4 a = {0.f, 0.f, 0.f, 0.f};
+        auto add = [&](float w, const float4& y) { a.x += w * y.x; a.y += w * y.y; a.z += w * y.z; a.w += w * y.w; };
+#pragma unroll
+        for (int i = 0; i < kEarly; ++i)
+            if (sg + i * NG < n_splits) add(weight(ml[i].x, ml[i].y), x[i]);
+        for (int s = sg + kEarly * NG; s < n_splits; s += NG) add(weight(p[2 * s], p[2 * s + 1]), op[(size_t)s * TPR]);
         reinterpret_cast<float4*>(buf)[tid] = a;
         __syncthreads();
         if (tid < D) {
-            float s = __builtin_amdgcn_exp2f(own_s[hh] - lse) * Elem<T>::load(v_new + ((size_t)b * g.Hkv + hk) * D + tid);
+            float s = __builtin_amdgcn_exp2f(own_s[hh] - lse) * vn;
 #pragma unroll
             for (int x = 0; x < NG; ++x) s += buf[x * D + tid];
             Elem<T>::store(out + head * D + tid, s);
@@ -649,6 +687,43 @@ __global__ __launch_bounds__(kDecThreads) void decode_finish_kernel(
     }
 
     // ---- the token's score, and its insertion
+    // Everything the decisions and the moves may need is loaded first, whatever the decisions will be: the row
+    // every cascade may be offered (a thread group per cascade), the scores and logits of the rows that
+    // compete or move on (a thread per cascade).
+    constexpr int LPR = D / 16;
+    const int mine = tid / LPR, lane = tid % LPR;
+    int dst = 0, src = -1, rank_slot = -1;                 // slot of this group's cascade, slot of its offer; slot of this thread's cascade
+    for (int i = 0; i < ins.n; ++i) {
+        if (i == mine) dst = ins.slot[i];
+        if (i + 1 == mine) src = ins.slot[i];
+        if (i == tid && ins.kind[i] != kInsertAppend) rank_slot = ins.slot[i];
+    }
+    float k0[8], k1[8], v0[8], v1[8];
+    int id = ins.id0;
+    if (mine < ins.n) {
+        const size_t srow = mine == 0 ? (size_t)b * g.Hkv + hk : (size_t)bh * g.slots + src;
+        const T *ks = (mine == 0 ? k_new : (const T*)Kc) + srow * D, *vs = (mine == 0 ? v_new : (const T*)Vc) + srow * D;
+        if (mine > 0) id = ids[srow];
+        Vec8<T>::load(ks + lane * 8, k0);
+        Vec8<T>::load(ks + D / 2 + lane * 8, k1);
+        Vec8<T>::load(vs + lane * 8, v0);
+        Vec8<T>::load(vs + D / 2 + lane * 8, v1);
+    }
+    float held = 0.f, lg[MAXG];
+    if (rank_slot >= 0) {
+        held = mu[(size_t)bh * g.slots + rank_slot];
+        if (both) {
+            int tile0 = 0, at = 0;
+            for (int si = 0; si < sl.n; ++si) {
+                const int r = rank_slot - sl.s[si].start;
+                if (r >= 0 && r < sl.s[si].len) at = (tile0 + r / kDecRows) * (kDecRows * MAXG) + logit_index<MAXG>(r % kDecRows, 0);
+                tile0 += tiles_of(sl.s[si].len);
+            }
+            const float* lt = logits + (size_t)bh * n_tiles * (kDecRows * MAXG) + at;
+#pragma unroll
+            for (int hh = 0; hh < MAXG; ++hh) lg[hh] = lt[logit_index<MAXG>(0, hh)];
+        }
+    }
     // independent heads: the query heads of this KV head; homogeneous heads: all query heads (every
     // workgroup of the sequence computes the same value, group by group in the same order)
     const bool all = g.head_policy == CASCADE_HEADS_HOMOGENEOUS;
@@ -663,60 +738,31 @@ __global__ __launch_bounds__(kDecThreads) void decode_finish_kernel(
     }
     if (all && g.head_reduce == CASCADE_REDUCE_MEAN) own /= (float)g.Hkv;
     own *= omb;
-    // the scores of the rows that compete or move on, after this step
-    if (tid < ins.n && ins.kind[tid] != kInsertAppend) {
-        const int slot = ins.slot[tid];
-        float v = mu[(size_t)bh * g.slots + slot];
-        if (both) {
-            int tile0 = 0;
-            for (int si = 0; si < sl.n; ++si) {
-                const int r = slot - sl.s[si].start;
-                if (r >= 0 && r < sl.s[si].len) {
-                    const float* lt = logits + ((size_t)bh * n_tiles + tile0 + r / kDecRows) * (kDecRows * MAXG);
-                    float red = 0.f;
-                    for (int hh = 0; hh < g.G; ++hh)
-                        red = reduce_heads(g, red, __builtin_amdgcn_exp2f(lt[logit_index<MAXG>(r % kDecRows, hh)] - lse_s[hh]));
-                    v = beta * v + omb * (g.head_reduce == CASCADE_REDUCE_MAX ? red : red / (float)g.G);
-                }
-                tile0 += tiles_of(sl.s[si].len);
-            }
+    if (rank_slot >= 0) {
+        if (both) {                                        // (never with homogeneous heads of several KV heads: lse_s is this group's)
+            float red = 0.f;
+#pragma unroll
+            for (int hh = 0; hh < MAXG; ++hh)
+                if (hh < g.G) red = reduce_heads(g, red, __builtin_amdgcn_exp2f(lg[hh] - lse_s[hh]));
+            held = beta * held + omb * (g.head_reduce == CASCADE_REDUCE_MAX ? red : red / (float)g.G);
         }
-        buf[tid] = v;
+        buf[tid] = held;
     }
-    __syncthreads();
+    __syncthreads();                                       // (every source row has been read, too)
     // Who ends up where: the token (or what the cascade before evicted) is offered to one cascade after the
     // other; it is appended, or takes the place of the oldest item, which moves on, or competes with the
-    // newest item, which stays unless the offer's score is strictly higher.  A thread group per cascade moves its row.
-    constexpr int LPR = D / 16;
-    const int mine = tid / LPR, lane = tid % LPR;
+    // newest item, which stays unless the offer's score is strictly higher.
     float offered = own, my_score = 0.f;
     bool my_move = false;
     for (int i = 0; i < ins.n; ++i) {
-        const float held = buf[i];
-        const bool takes = ins.kind[i] != kInsertCompete || (g.token_selection && offered > held);
-        if (i == mine) { my_move = takes; my_score = takes ? offered : held; }
-        if (takes && ins.kind[i] == kInsertCompete && tid == 0) swaps[bh * g.N + i] += 1;
-        offered = held;
+        const float there = buf[i];
+        const bool takes = ins.kind[i] != kInsertCompete || (g.token_selection && offered > there);
+        if (i == mine) { my_move = takes; my_score = takes ? offered : there; }
+        if (takes && ins.kind[i] == kInsertCompete && tid == 0) atomicAdd(&swaps[bh * g.N + i], 1);
+        offered = there;
     }
-    float k0[8], k1[8], v0[8], v1[8];
-    int id = ins.id0;
-    if (my_move) {
-        const T *ks = k_new + ((size_t)b * g.Hkv + hk) * D, *vs = v_new + ((size_t)b * g.Hkv + hk) * D;
-        if (mine > 0) {
-            const size_t srow = (size_t)bh * g.slots + ins.slot[mine - 1];
-            ks = Kc + srow * D;
-            vs = Vc + srow * D;
-            id = ids[srow];
-        }
-        Vec8<T>::load(ks + lane * 8, k0);
-        Vec8<T>::load(ks + D / 2 + lane * 8, k1);
-        Vec8<T>::load(vs + lane * 8, v0);
-        Vec8<T>::load(vs + D / 2 + lane * 8, v1);
-    }
-    __syncthreads();                                       // every source has been read
     if (tid == 0) mu_chunk[(size_t)bh * qstride] = own;
     if (mine < ins.n) {
-        const int dst = ins.slot[mine];
         const size_t drow = (size_t)bh * g.slots + dst;
         if (lane == 0) mu[drow] = my_score;
         if (my_move) {
@@ -747,18 +793,22 @@ int decode_tiles(const SegList& sl)
 
 // Splits of a step: as many as make the busiest compute unit finish first.  A CU holds one workgroup of
 // the MFMA kernel (its ring fills the LDS at d = 128), whose four waves share the split's tiles; a
-// workgroup costs about as much as kWgTiles rounds of its waves besides (first copies, queries, epilogue).
+// workgroup costs about as much as two rounds of its waves besides (first copies, queries, epilogue).  Where the
+// waves' shares differ by a tile, half a tile is charged (4K slots, 8 KV heads: 32 splits 17.3 us, 17 splits 18.0;
+// 8K slots: 32 or 22 splits 20.2, 16 21.7, 64 23.8; 64 x 16K slots: 4 splits 111, 8 113, 32 127).
+// Where even then a wave has hundreds of tiles, more rounds even out the CUs (256 x 65K slots: 8 splits 1656, 1 split 1676).
 int decode_split_count(const Geom& g, const DevBuffers& b, int n_tiles)
 {
-    constexpr int kWgTiles = 2;
     const int bh = g.B * g.Hkv;
     int best = 1;
-    long best_cost = -1;
+    float best_cost = -1.f;
     for (int s = 1; s <= b.dec_splits; ++s) {
         const long rounds = (bh * (long)s + 255) / 256, tiles = (n_tiles + s - 1) / s;
-        const long cost = rounds * ((tiles + kDecWaves - 1) / kDecWaves + kWgTiles);
-        if (best_cost < 0 || cost < best_cost) { best = s; best_cost = cost; }
+        const float share = (float)n_tiles / (float)(s * kDecWaves);
+        const float cost = (float)rounds * (0.5f * ((float)((tiles + kDecWaves - 1) / kDecWaves) + share) + 2.f);
+        if (best_cost < 0.f || cost < best_cost) { best = s; best_cost = cost; }
     }
+    while (2 * best <= b.dec_splits && n_tiles / (2 * best * kDecWaves) >= 64) best *= 2;
     return best;
 }
 
