@@ -26,7 +26,8 @@ struct cascade_ctx {
     size_t elem;
     int max_chunk;
     int tail_k;          // rows of a chunk (counted from its end) that enter the score sums
-    bool mfma;
+    bool mfma;           // bf16 MFMA kernels; f32_mfma: the fp32 ones; neither: scalar kernels
+    bool f32_mfma;
     // bf16 path: Kt / Vt / Knorm2 belong to this context alone (not shared between layers), and, if
     // packed_valid, hold every cache tile where `packed` puts it, except those named by `stale`.
     // packed_reuse: tiles that are still valid are not packed again.
@@ -229,7 +230,8 @@ static int init_context(const char* who, const cascade_config* cfg, const Geom& 
     carve(cfg, g, state_base, shared_base, &ctx->buf);
     ctx->mfma = cfg->dtype == CASCADE_BF16;
     // development switches: the environment is read here and nowhere else
-    if (const char* e = getenv("CASCADE_KV_SCALAR_ATTENTION")) if (e[0] == '1') ctx->mfma = false;
+    ctx->f32_mfma = attn_f32_ok(g, cfg->dtype);
+    if (const char* e = getenv("CASCADE_KV_SCALAR_ATTENTION")) if (e[0] == '1') ctx->mfma = ctx->f32_mfma = false;
     if (const char* e = getenv("CASCADE_KV_PACK_REUSE")) ctx->packed_reuse = e[0] != '0';   // 0: pack every tile for every chunk
     ctx->buf.opt_attn_splits = 0;
     if (const char* e = getenv("CASCADE_KV_ATTN_SPLITS")) ctx->buf.opt_attn_splits = atoi(e);
@@ -518,6 +520,7 @@ extern "C" int cascade_prefill_chunk(cascade_ctx* ctx, const void* dev_q, const 
     {
         Timed t(ctx, CASCADE_K_ATTENTION, s);
         if (ctx->mfma) launch_attn_stream(g, ctx->buf, sl, Q, dev_q, qscale, tail, ctx->max_chunk, dev_out, single_pass, s);
+        else if (ctx->f32_mfma) launch_attn_f32(g, ctx->buf, sl, Q, dev_out, s);
         else launch_attn_simple(g, ctx->dtype, ctx->buf, sl, Q, ctx->max_chunk, dev_out, s);
     }
     const float decay = (float)pow((double)g.beta, (double)Q);
@@ -525,6 +528,7 @@ extern "C" int cascade_prefill_chunk(cascade_ctx* ctx, const void* dev_q, const 
         Timed t(ctx, CASCADE_K_SCORES, s);
         if (single_pass) launch_single_pass_merge(g, ctx->buf, sl, Q, ctx->max_chunk, decay, s);
         else if (ctx->mfma) launch_score_mfma(g, ctx->buf, sl, Q, ctx->max_chunk, tail, decay, s);
+        else if (ctx->f32_mfma) launch_score_f32(g, ctx->buf, sl, Q, ctx->max_chunk, tail, decay, s);
         else launch_score_simple(g, ctx->dtype, ctx->buf, sl, Q, ctx->max_chunk, tail, decay, s);
         if (g.head_policy == CASCADE_HEADS_HOMOGENEOUS && g.Hkv > 1) launch_share_scores(g, ctx->buf, Q, ctx->max_chunk, s);
     }

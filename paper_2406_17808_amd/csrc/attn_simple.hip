@@ -1,6 +1,6 @@
 // Chunk attention and score sums with scalar fp32 arithmetic, for any element type and head
-// dimension.  This is the path of the fp32 configuration; the bf16 configurations use the
-// MFMA kernels instead.
+// dimension: the path of head dimensions other than 64 and 128, for which there are MFMA kernels
+// (attn_stream.hip, attn_f32.hip).
 #include "launch.h"
 
 namespace ckv {

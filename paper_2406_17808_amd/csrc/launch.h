@@ -79,6 +79,11 @@ void launch_attn_simple(const Geom& g, int dtype, const DevBuffers& b, const Seg
 void launch_score_simple(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, int Q,
                          int max_chunk, int tail_rows, float decay, hipStream_t s);
 
+// attention, fp32 MFMA (attn_f32_ok): b.lse then holds base-2 logarithms, from the one launch to the other
+bool attn_f32_ok(const Geom& g, int dtype);
+void launch_attn_f32(const Geom& g, const DevBuffers& b, const SegList& sl, int Q, void* out, hipStream_t s);
+void launch_score_f32(const Geom& g, const DevBuffers& b, const SegList& sl, int Q, int max_chunk, int tail_rows, float decay, hipStream_t s);
+
 // attention, bf16 MFMA (head_dim 64 or 128).  launch_kv_pack copies the keys and values of the
 // segment list into Kt / Vt, tile by tile (tile n = rows 64n .. 64n+63 of the concatenated
 // segments), for the tiles named by `runs` only (false if Kt / Vt do not hold that many tiles);

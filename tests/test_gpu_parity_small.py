@@ -567,7 +567,10 @@ def test_decode_in_one_finish_launch(dtype, d, G, sizes):
         n = 50 if step == 10 else 1
         q, k, v = (torch.randn((2, n, h, d), generator=gen, device="cuda:0").to(caches[0].torch_dtype) for h in (2 * G, 2, 2))
         if n == 1:
-            a, b = (c.decode_step(q[:, 0], k[:, 0], v[:, 0]) for c in caches)
+            a = caches[0].decode_step(q[:, 0], k[:, 0], v[:, 0])
+            # the other cache's inputs start at an odd element: the step takes inputs of any alignment
+            q, k, v = (torch.cat([x.new_zeros(1), x.flatten()])[1:].view(2, h, d) for x, h in ((q, 2 * G), (k, 2), (v, 2)))
+            b = caches[1].decode_step(q, k, v)
         else:
             a, b = (c.prefill_chunk(q, k, v) for c in caches)
         assert torch.equal(a, b), step
@@ -578,3 +581,24 @@ def test_decode_in_one_finish_launch(dtype, d, G, sizes):
             assert np.array_equal(x.swaps, y.swaps), step
     for c in caches:
         c.close()
+
+
+@pytest.mark.parametrize("d,G,Hkv,sizes,reduce_mean,chunks", [
+    (64, 1, 1, [64] * 4, False, [32] * 12), (64, 3, 2, [7, 33], False, [1, 15, 16, 17, 48, 5, 31]),
+    (128, 5, 1, [150], True, [64, 2, 63, 33]), (128, 8, 2, [20, 1, 3], False, [16, 40, 1, 64]),
+])
+def test_f32_matrix_kernels(oracle_mod, d, G, Hkv, sizes, reduce_mean, chunks):
+    """The fp32 MFMA kernels at the edges of their 16-key and 16-row tiles (row blocks that cross heads, fewer
+    tiles than waves, chunks longer than the cache) against the oracle."""
+    from gpu_harness import ParityRun
+    cfg = B.make_config(batch=2, n_q_heads=Hkv * G, n_kv_heads=Hkv, head_dim=d, dtype=B.CASCADE_F32, n_sink=3, cascade_sizes=sizes,
+                        ema_beta=0.95, rope_base=10000.0, max_chunk=64, keep_update_scores=1,
+                        head_reduce=B.CASCADE_REDUCE_MEAN if reduce_mean else B.CASCADE_REDUCE_MAX)
+    rng = np.random.default_rng(d + G)
+    run = ParityRun(cfg, one_step_ahead=True)
+    out_tol, score_tol = _tolerances(cfg)
+    for step, n in enumerate(chunks):
+        rep = run.step(*_inputs(rng, cfg, n))
+        assert rep.replay_exact, step
+        assert rep.out_err <= out_tol and rep.score_err <= score_tol, (step, rep)
+    run.close()
