@@ -160,10 +160,12 @@ __device__ inline void write_score_offset(const ScoreOffsets& so, size_t head, i
 // to part_o / part_ml, and attn_merge_kernel combines them.
 // SP: single-pass scores (needs Q % 256 == 0 and no SPLIT: a row block is one head's 256 tokens; and
 // every row of the chunk carrying EMA weight, so that every row block takes part).
-template <int D, bool DBG, bool SPLIT, bool SP = false>
+// QC: the rotated copies of the queries that the exact score pass reads exist for every row of the
+// chunk (all of them carry EMA weight): the kernel reads its queries there.
+template <int D, bool DBG, bool SPLIT, bool SP, bool QC>
 __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
-    Geom g, SegList sl, int Q, int tiles_per_bh, const bf16_t* __restrict__ q, const float4* __restrict__ rope_t, int rope_rows, float qscale,
-    const bf16_t* __restrict__ Kt, const bf16_t* __restrict__ Vt, bf16_t* __restrict__ out, float* __restrict__ lse,
+    Geom g, SegList sl, int Q, int tiles_per_bh, const bf16_t* __restrict__ q, const bf16_t* __restrict__ Qr, const float4* __restrict__ rope_t,
+    int rope_rows, float qscale, const bf16_t* __restrict__ Kt, const bf16_t* __restrict__ Vt, bf16_t* __restrict__ out, float* __restrict__ lse,
     long long* dbg, int n_split, float* __restrict__ part_o, float* __restrict__ part_ml, const float* __restrict__ Knorm2,
     ScoreOffsets so, SinglePass sp)
 {
@@ -256,6 +258,22 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     float qn2 = 0.f;      // this lane's half of the squared norm of its (scaled) query, summed by the first load_q
     auto load_q = [&](const Seg& sg) {
         qn2 = 0.f;
+        if constexpr (QC) {
+            // 8 loads a reload instead of 24 and no arithmetic: the 16 loads of (cos, sin) are most of what a
+            // reload costs, with all eight waves of the workgroup stopped.  4096 tokens against 16K slots: 1034 ->
+            // 1016 us; 512 against 8K, whose workgroups have 34 tiles each: 78.5 -> 74.1.
+            const bf16_t* qsrc = Qr + ((((size_t)sg.qvar * g.B + b) * g.Hq + qh) * Q + qi) * D + half * 8;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) qf[ks].u = *reinterpret_cast<const u32x4_t*>(qsrc + ks * 16);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const float lo = __uint_as_float(qf[ks].u[x] << 16), hi = __uint_as_float(qf[ks].u[x] & 0xFFFF0000u);
+                    qn2 += lo * lo + hi * hi;
+                }
+            return;
+        }
         const bf16_t* qsrc = q + (((size_t)b * Q + qi) * g.Hq + qh) * D + half * 8;
         // (cos, sin) of this lane's 8 rotary pairs per step from the index-minor table: group ks * 8 + half * 4 + x
         const float4* cs = rope_t + ((size_t)half * 4 * rope_rows + (size_t)(sl.qrot0[sg.qvar] + qi));
@@ -832,31 +850,36 @@ void launch_attn_stream(const Geom& g, const DevBuffers& b, const SegList& sl, i
     const int tiles = (g.G * Q + BM - 1) / BM;
     const int n_split = attn_splits(g, Q, b.opt_attn_splits);
     const dim3 grid(tiles * g.B * g.Hkv * n_split), block(kSWaves * 64);
+    float* part_o = b.attn_part;
+    float* part_ml = b.attn_part + (size_t)kAttnPartRows * g.d;
+    // prep_kernel wrote rotated copies of the last tail_rows rows, for the exact score pass
+    const bool copies = !single_pass && tail_rows >= Q;
+#define CKV_ATTN(D, DBG, SPLIT, SP, QC, dbg)                                                                                                  \
+    hipLaunchKernelGGL((attn_stream_kernel<D, DBG, SPLIT, SP, QC>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q,               \
+                       (const bf16_t*)b.Qr, (const float4*)b.rope_t, b.rope_rows, qscale, (const bf16_t*)b.Kt, (const bf16_t*)b.Vt, (bf16_t*)out, \
+                       b.lse, dbg, n_split, part_o, part_ml, b.knorm2, so, sp)
+#define CKV_ATTN_D(DBG, SPLIT, SP, QC, dbg)                                                            \
+    do {                                                                                               \
+        if (g.d == 128) CKV_ATTN(128, DBG, SPLIT, SP, QC, dbg); else CKV_ATTN(64, DBG, SPLIT, SP, QC, dbg); \
+    } while (0)
+    long long* const no_dbg = nullptr;
     if (n_split > 1) {
-        float* part_o = b.attn_part;
-        float* part_ml = b.attn_part + (size_t)kAttnPartRows * g.d;
-        if (g.d == 128) {
-            hipLaunchKernelGGL((attn_stream_kernel<128, false, true>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q, (const float4*)b.rope_t, b.rope_rows, qscale,
-                               (const bf16_t*)b.Kt, (const bf16_t*)b.Vt, (bf16_t*)out, b.lse, (long long*)nullptr, n_split, part_o, part_ml, b.knorm2, so, sp);
+        if (copies) CKV_ATTN_D(false, true, false, true, no_dbg);
+        else CKV_ATTN_D(false, true, false, false, no_dbg);
+        if (g.d == 128)
             hipLaunchKernelGGL(attn_merge_kernel<128>, dim3(g.G * Q, g.B * g.Hkv), dim3(128), 0, s, g, Q, tiles, n_split, BM,
                                part_o, part_ml, (bf16_t*)out, b.lse, so);
-        } else {
-            hipLaunchKernelGGL((attn_stream_kernel<64, false, true>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q, (const float4*)b.rope_t, b.rope_rows, qscale,
-                               (const bf16_t*)b.Kt, (const bf16_t*)b.Vt, (bf16_t*)out, b.lse, (long long*)nullptr, n_split, part_o, part_ml, b.knorm2, so, sp);
+        else
             hipLaunchKernelGGL(attn_merge_kernel<64>, dim3(g.G * Q, g.B * g.Hkv), dim3(64), 0, s, g, Q, tiles, n_split, BM,
                                part_o, part_ml, (bf16_t*)out, b.lse, so);
-        }
         return;
     }
 #ifdef CASCADE_KV_ATTN_PHASE_TIMING   // development builds only: per-phase cycle counts of one workgroup
     if (g.d == 128) {
         long long* dbg = (long long*)b.move_stage;
-        if (single_pass)
-            hipLaunchKernelGGL((attn_stream_kernel<128, true, false, true>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q, (const float4*)b.rope_t, b.rope_rows, qscale,
-                               (const bf16_t*)b.Kt, (const bf16_t*)b.Vt, (bf16_t*)out, b.lse, dbg, 1, (float*)nullptr, (float*)nullptr, b.knorm2, so, sp);
-        else
-            hipLaunchKernelGGL((attn_stream_kernel<128, true, false>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q, (const float4*)b.rope_t, b.rope_rows, qscale,
-                               (const bf16_t*)b.Kt, (const bf16_t*)b.Vt, (bf16_t*)out, b.lse, dbg, 1, (float*)nullptr, (float*)nullptr, b.knorm2, so, sp);
+        if (single_pass) CKV_ATTN(128, true, false, true, false, dbg);
+        else if (copies) CKV_ATTN(128, true, false, false, true, dbg);
+        else CKV_ATTN(128, true, false, false, false, dbg);
         long long h[16];
         (void)hipStreamSynchronize(s);
         (void)hipMemcpy(h, dbg, sizeof(h), hipMemcpyDeviceToHost);
@@ -867,21 +890,11 @@ void launch_attn_stream(const Geom& g, const DevBuffers& b, const SegList& sl, i
         return;
     }
 #endif
-    if (single_pass) {      // (the caller has checked attn_single_pass_ok)
-        if (g.d == 128)
-            hipLaunchKernelGGL((attn_stream_kernel<128, false, false, true>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q, (const float4*)b.rope_t, b.rope_rows, qscale,
-                               (const bf16_t*)b.Kt, (const bf16_t*)b.Vt, (bf16_t*)out, b.lse, (long long*)nullptr, 1, (float*)nullptr, (float*)nullptr, b.knorm2, so, sp);
-        else
-            hipLaunchKernelGGL((attn_stream_kernel<64, false, false, true>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q, (const float4*)b.rope_t, b.rope_rows, qscale,
-                               (const bf16_t*)b.Kt, (const bf16_t*)b.Vt, (bf16_t*)out, b.lse, (long long*)nullptr, 1, (float*)nullptr, (float*)nullptr, b.knorm2, so, sp);
-        return;
-    }
-    if (g.d == 128)
-        hipLaunchKernelGGL((attn_stream_kernel<128, false, false>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q, (const float4*)b.rope_t, b.rope_rows, qscale,
-                           (const bf16_t*)b.Kt, (const bf16_t*)b.Vt, (bf16_t*)out, b.lse, (long long*)nullptr, 1, (float*)nullptr, (float*)nullptr, b.knorm2, so, sp);
-    else
-        hipLaunchKernelGGL((attn_stream_kernel<64, false, false>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q, (const float4*)b.rope_t, b.rope_rows, qscale,
-                           (const bf16_t*)b.Kt, (const bf16_t*)b.Vt, (bf16_t*)out, b.lse, (long long*)nullptr, 1, (float*)nullptr, (float*)nullptr, b.knorm2, so, sp);
+    if (single_pass) CKV_ATTN_D(false, false, true, false, no_dbg);      // (the caller has checked attn_single_pass_ok)
+    else if (copies) CKV_ATTN_D(false, false, false, true, no_dbg);
+    else CKV_ATTN_D(false, false, false, false, no_dbg);
+#undef CKV_ATTN_D
+#undef CKV_ATTN
 }
 
 }  // namespace ckv
