@@ -128,28 +128,29 @@ void launch_load_state(const Geom& g, int dtype, const DevBuffers& b, const void
 // For every rotated query copy v: Qr[v][b][h][i] = qscale * R(qrot0[v] + i) q[b][i][h] (the bf16
 // MFMA kernels want the softmax scale and log2(e) folded into the queries; everybody else passes
 // 1); chunk keys are rotated to their chunk index, chunk values are copied head-major.  A thread takes 8 rotary
-// pairs of one row (two 16-byte pieces for bf16) and, for a query row, produces all copies.
+// pairs of one row (two 16-byte pieces for bf16); of the queries it takes kPrepHeads heads, which share
+// the (cos, sin) of their index, and vars of the copies.
+constexpr int kPrepHeads = 4;
 template <typename T>
-__global__ void prep_kernel(Geom g, SegList sl, int Q, float qscale, int q_first_row, const float2* __restrict__ rope,
+__global__ void prep_kernel(Geom g, SegList sl, int Q, float qscale, int q_first_row, int vars, const float2* __restrict__ rope,
                             const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                             T* __restrict__ Qr, T* __restrict__ Krc, T* __restrict__ Vch)
 {
     const int half = g.d / 2, groups = half / 8;
-    // threads [0, n_kv): one per (sequence, token, K or V head, group); then one per (sequence, query row
-    // that needs rotated copies, query head, group)
-    const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long n_kv = (long)g.B * Q * 2 * g.Hkv * groups;
-    const int q_rows = Q - q_first_row;
-    float x0[8], x1[8];
+    // threads [0, n_kv): one per (sequence, token, K or V head, group); then one per (range of copies, sequence,
+    // query row that needs rotated copies, group of query heads, group).  32-bit numbers: 2^32 threads would move
+    // more than 128 GB of K and V three times over.
+    const uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x, n_kv = (uint32_t)g.B * Q * 2 * g.Hkv * groups;
     if (idx < n_kv) {
         const int e = (int)(idx % groups) * 8;
-        long r = idx / groups;
+        uint32_t r = idx / groups;
         const int rr = (int)(r % (2 * g.Hkv));
         r /= 2 * g.Hkv;
         const int i = (int)(r % Q), b = (int)(r / Q);
         const int h = rr % g.Hkv;
         const size_t src = (((size_t)b * Q + i) * g.Hkv + h) * g.d;
         const size_t dst = (((size_t)b * g.Hkv + h) * Q + i) * g.d;
+        float x0[8], x1[8];
         if (rr < g.Hkv) {
             Vec8<T>::load(k + src + e, x0);
             Vec8<T>::load(k + src + e + half, x1);
@@ -162,21 +163,40 @@ __global__ void prep_kernel(Geom g, SegList sl, int Q, float qscale, int q_first
         }
         return;
     }
-    const long qidx = idx - n_kv;
-    if (qidx >= (long)g.B * q_rows * g.Hq * groups) return;
+    const uint32_t q_rows = Q - q_first_row, head_groups = (g.Hq + kPrepHeads - 1) / kPrepHeads;
+    if (q_rows == 0) return;
+    const uint32_t qidx = idx - n_kv;
     const int e = (int)(qidx % groups) * 8;
-    long r = qidx / groups;
-    const int h = (int)(r % g.Hq);
-    r /= g.Hq;
-    const int i = q_first_row + (int)(r % q_rows), b = (int)(r / q_rows);
-    const size_t src = (((size_t)b * Q + i) * g.Hq + h) * g.d;
-    Vec8<T>::load(q + src + e, x0);
-    Vec8<T>::load(q + src + e + half, x1);
+    uint32_t r = qidx / groups;
+    const int h0 = (int)(r % head_groups) * kPrepHeads;
+    r /= head_groups;
+    const int i = q_first_row + (int)(r % q_rows);
+    r /= q_rows;
+    const int b = (int)(r % g.B), v0 = (int)(r / g.B) * vars;
+    if (v0 >= sl.n_qvar) return;
+    float y0[kPrepHeads][8], y1[kPrepHeads][8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) { x0[j] *= qscale; x1[j] *= qscale; }
-    for (int vq = 0; vq < sl.n_qvar; ++vq) {
-        const size_t dst = ((((size_t)vq * g.B + b) * g.Hq + h) * Q + i) * g.d;
-        rotate8<T>(x0, x1, rope + (size_t)(sl.qrot0[vq] + i) * half + e, Qr + dst + e, Qr + dst + e + half);
+    for (int x = 0; x < kPrepHeads; ++x) {
+        const size_t src = (((size_t)b * Q + i) * g.Hq + min(h0 + x, g.Hq - 1)) * g.d;
+        Vec8<T>::load(q + src + e, y0[x]);
+        Vec8<T>::load(q + src + e + half, y1[x]);
+    }
+#pragma unroll
+    for (int x = 0; x < kPrepHeads; ++x)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { y0[x][j] *= qscale; y1[x][j] *= qscale; }
+    for (int vq = v0; vq < min(v0 + vars, sl.n_qvar); ++vq) {
+        const size_t dst = ((((size_t)vq * g.B + b) * g.Hq + h0) * Q + i) * g.d;
+        float2 cs[8];
+        const float2* rp = rope + (size_t)(sl.qrot0[vq] + i) * half + e;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) cs[j] = rp[j];
+#pragma unroll
+        for (int x = 0; x < kPrepHeads; ++x)
+            if (h0 + x < g.Hq) {
+                T* to = Qr + dst + (size_t)x * Q * g.d + e;
+                rotate8<T>(y0[x], y1[x], cs, to, to + half);
+            }
     }
 }
 
@@ -227,13 +247,18 @@ void launch_prep(const Geom& g, int dtype, const DevBuffers& b, const SegList& s
 {
     const dim3 block(256);
     if (g.d % 16 == 0) {
-        const long n = (long)g.B * (Q * 2 * g.Hkv + (Q - q_first_row) * g.Hq) * (g.d / 16);
+        // as few copies per thread as it takes to give the chip two rounds of threads (the queries are read once
+        // per thread, so no fewer than that)
+        const long one = (long)g.B * (Q - q_first_row) * ((g.Hq + kPrepHeads - 1) / kPrepHeads) * (g.d / 16);
+        int vars = sl.n_qvar;
+        while (vars > 1 && one * ((sl.n_qvar + vars - 1) / vars) < 2 * 256 * 1024) --vars;
+        const long n = (long)g.B * Q * 2 * g.Hkv * (g.d / 16) + one * ((sl.n_qvar + vars - 1) / vars);
         const dim3 grid((unsigned)((n + 255) / 256));
         if (dtype == CASCADE_F32)
-            hipLaunchKernelGGL(prep_kernel<float>, grid, block, 0, s, g, sl, Q, qscale, q_first_row, b.rope, (const float*)q, (const float*)k,
+            hipLaunchKernelGGL(prep_kernel<float>, grid, block, 0, s, g, sl, Q, qscale, q_first_row, vars, b.rope, (const float*)q, (const float*)k,
                                (const float*)v, (float*)b.Qr, (float*)b.Krc, (float*)b.Vch);
         else
-            hipLaunchKernelGGL(prep_kernel<bf16_t>, grid, block, 0, s, g, sl, Q, qscale, q_first_row, b.rope, (const bf16_t*)q, (const bf16_t*)k,
+            hipLaunchKernelGGL(prep_kernel<bf16_t>, grid, block, 0, s, g, sl, Q, qscale, q_first_row, vars, b.rope, (const bf16_t*)q, (const bf16_t*)k,
                                (const bf16_t*)v, (bf16_t*)b.Qr, (bf16_t*)b.Krc, (bf16_t*)b.Vch);
         return;
     }
