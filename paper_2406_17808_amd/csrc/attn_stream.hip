@@ -24,6 +24,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "async_copy.h"
@@ -835,15 +836,17 @@ __global__ __launch_bounds__(kBN) void single_pass_merge_kernel(Geom g, SegList 
     }
 }
 
-// Workgroups per (row block, KV head) so that a small launch still fills the chip: none for 256
-// workgroups or more.
-int attn_splits(const Geom& g, int Q, int forced)
+// Workgroups per (row block, KV head) so that a small launch still fills the chip: none for 129
+// workgroups or more.  Beyond kMaxAttnSplits only where each has kMinSplitTiles tiles left (a workgroup costs about
+// as much as that many tiles besides: its queries, the first copies, the partial result).  us a call
+// with 8 splits and with up to 32: 64 tokens against 16K slots 122 -> 104, 16 against 64K 332 -> 250, 128 against 4K 74.5 -> 73.
+int attn_splits(const Geom& g, int Q, int forced, int tiles)
 {
     constexpr int BM = kSWaves * 32;
     const int wgs = ((g.G * Q + BM - 1) / BM) * g.B * g.Hkv;
-    int n = forced > 0 ? forced : 256 / wgs;
-    if (n > 256 / wgs) n = 256 / wgs;       // the partial results are sized for 256 workgroups
-    if (n > kMaxAttnSplits) n = kMaxAttnSplits;
+    const int most = 256 / wgs;             // the partial results are sized for 256 workgroups
+    int n = forced > 0 ? forced : std::max(kMaxAttnSplits, tiles / kMinSplitTiles);
+    if (n > most) n = most;
     return n < 1 ? 1 : n;
 }
 
@@ -853,7 +856,7 @@ int attn_splits(const Geom& g, int Q, int forced)
 // whole heads' pieces (Q a multiple of 256); other chunks of such a context take the exact pass.
 bool attn_single_pass_ok(const Geom& g, const DevBuffers& b, int Q, int tail_rows)
 {
-    return b.sp_part != nullptr && tail_rows >= Q && Q % (kSWaves * 32) == 0 && attn_splits(g, Q, b.opt_attn_splits) == 1;
+    return b.sp_part != nullptr && tail_rows >= Q && Q % (kSWaves * 32) == 0 && attn_splits(g, Q, b.opt_attn_splits, 0) == 1;
 }
 
 void launch_single_pass_merge(const Geom& g, const DevBuffers& b, const SegList& sl, int Q, int max_chunk, float decay, hipStream_t s)
@@ -871,7 +874,7 @@ void launch_attn_stream(const Geom& g, const DevBuffers& b, const SegList& sl, i
     const int tiles_per_bh = b.vt_tiles;   // stride between the packed streams of two (batch, KV head)
     constexpr int BM = kSWaves * 32;
     const int tiles = (g.G * Q + BM - 1) / BM;
-    const int n_split = attn_splits(g, Q, b.opt_attn_splits);
+    const int n_split = attn_splits(g, Q, b.opt_attn_splits, packed_tiles(sl));
     const dim3 grid(tiles * g.B * g.Hkv * n_split), block(kSWaves * 64);
     float* part_o = b.attn_part;
     float* part_ml = b.attn_part + (size_t)kAttnPartRows * g.d;

@@ -8,6 +8,7 @@ namespace ckv {
 // A split attention launch has at most 256 workgroups of 256 rows.
 constexpr int kAttnPartRows = 256 * 256;
 constexpr int kMaxAttnSplits = 8;
+constexpr int kMinSplitTiles = 8;
 
 // Device memory of one context, carved out of the caller's workspace.
 struct DevBuffers {

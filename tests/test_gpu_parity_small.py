@@ -115,6 +115,11 @@ def test_tiny_f32_free_running(oracle_mod):
          sizes=[256, 128], chunks=[256] * 4 + [64] * 3 + [192] + [256] * 3, max_chunk=256, attn_splits=1, pack_reuse=1),
     dict(name="bf16_logit_step_chunk_tail_d64", dtype=B.CASCADE_BF16, d=64, Hq=4, Hkv=2, batch=1, n_sink=4,
          sizes=[96, 96, 96], chunks=[256] * 5, max_chunk=256, logit_step="chunk_tail", rope_base=1e6, compare_membership=False),
+    # more splits of a row block than it has tiles: some are empty
+    dict(name="bf16_d64_sixteen_splits", dtype=B.CASCADE_BF16, d=64, Hq=4, Hkv=2, batch=1, n_sink=4,
+         sizes=[96, 96, 96], chunks=[64, 100, 256, 33, 256, 1, 64], max_chunk=256, attn_splits=16),
+    dict(name="bf16_big_tiles_sixteen_splits", dtype=B.CASCADE_BF16, d=128, Hq=2, Hkv=1, batch=1, n_sink=64,
+         sizes=[256, 256, 256, 256], chunks=[256] * 5 + [60], max_chunk=256, beta=0.99, attn_splits=16),
 ], ids=lambda c: c["name"])
 def test_prefill_one_step_ahead(oracle_mod, case, monkeypatch):
     from gpu_harness import ParityRun
