@@ -491,8 +491,8 @@ extern "C" int cascade_prefill_chunk(cascade_ctx* ctx, const void* dev_q, const 
         Timed t(ctx, CASCADE_K_PREP, s);
         // bf16: the attention kernel rotates its queries itself; only the score kernel reads rotated copies
         // (single-pass scores: nobody reads rotated query copies)
-        launch_prep(g, ctx->dtype, ctx->buf, sl, Q, qscale, ctx->mfma ? (single_pass ? Q : Q - tail) : 0, dev_q, dev_k, dev_v, s);
-        if (ctx->mfma) {
+        if (!ctx->mfma) launch_prep(g, ctx->dtype, ctx->buf, sl, Q, qscale, 0, dev_q, dev_k, dev_v, s);
+        else {
             // The tiles of a full cache keep their place while the ring heads keep their offsets
             // inside a tile: then only the tiles the last update wrote, and the chunk's own, are
             // packed again.
@@ -512,7 +512,7 @@ extern "C" int cascade_prefill_chunk(cascade_ctx* ctx, const void* dev_q, const 
                 add_tile_run(runs, 0, packed_tiles_of(sl));
             }
             ctx->packed_valid = false;   // until this call has gone through
-            if (!launch_kv_pack(g, ctx->buf, sl, runs, Q, s))
+            if (!launch_kv_pack(g, ctx->buf, sl, runs, Q, qscale, single_pass ? Q : Q - tail, dev_q, dev_k, dev_v, s))
                 return fail(ctx, CASCADE_E_WORKSPACE_TOO_SMALL, "cascade_prefill_chunk: packed K/V buffers too small for this segment list");
             packed_stable = ctx->packed_own && lay.full;
         }

@@ -1,6 +1,7 @@
 // bf16 chunk attention of the strided prefill (Alg. 1, Fig. 4; online softmax of Eq. 2).
 //
-// kv_pack_kernel, once per chunk: the keys and values the chunk attends to (cache segments, then
+// kv_pack_kernel, once per chunk, which also rotates the chunk's keys and writes the rotated copies of
+// the queries that the exact score pass reads: the keys and values the chunk attends to (cache segments, then
 // the chunk itself) are copied tile after tile (64 keys) in the order the attention kernel
 // visits them; when the caller knows that a tile still holds what it held for the previous
 // chunk, it leaves that tile out of the launch.  A packed tile is the exact LDS image the attention kernel wants: K with the
@@ -29,6 +30,7 @@
 
 #include "async_copy.h"
 #include "mfma_util.h"
+#include "row_ops.h"
 
 namespace ckv {
 
@@ -51,11 +53,17 @@ template <int D> struct Swz {
 constexpr int kPackThreads = 256;
 
 // Tile n of the packed K and V copies of one (batch, KV head): 64 rows of a segment (rows past
-// its end become zeros); K with its chunks swizzled, V transposed through LDS.
+// its end become zeros); K with its chunks swizzled, V transposed through LDS.  Chunk rows come from the
+// caller's tensors; their keys are rotated here, and left in Krc for the score pass.  The workgroups
+// behind the tiles' take the rotated copies of the queries (rotate_queries).  One launch instead of two, and no
+// separate copy of the chunk's K and V, us for both: 4096 tokens with 9 copies against 16K slots 129 -> 95,
+// 2048 with 17 copies of 264 rows (eight rings) 50 -> 41, 1024 against 4K 22.3 -> 13.3, 512 against 8K 20.8 -> 16.7.
 template <int D>
 __global__ __launch_bounds__(kPackThreads) void kv_pack_kernel(Geom g, SegList sl, TileRuns runs, int Q, int tiles_per_bh,
-                                                               const bf16_t* __restrict__ Kr, const bf16_t* __restrict__ Krc,
-                                                               const bf16_t* __restrict__ Vc, const bf16_t* __restrict__ Vch,
+                                                               float qscale, int q_first_row, int vars, const float2* __restrict__ rope,
+                                                               const bf16_t* __restrict__ q, const bf16_t* __restrict__ k_in, const bf16_t* __restrict__ v_in,
+                                                               const bf16_t* __restrict__ Kr, const bf16_t* __restrict__ Vc,
+                                                               bf16_t* __restrict__ Qr, bf16_t* __restrict__ Krc,
                                                                bf16_t* __restrict__ Kt, bf16_t* __restrict__ Vt,
                                                                float* __restrict__ Knorm2)
 {
@@ -63,6 +71,10 @@ __global__ __launch_bounds__(kPackThreads) void kv_pack_kernel(Geom g, SegList s
     __shared__ __attribute__((aligned(16))) bf16_t T[kBN * STR];
     __shared__ float wave_max[kPackThreads / 64];
     const int BH = g.B * g.Hkv;
+    if (blockIdx.x >= (uint32_t)(runs.total * BH)) {
+        rotate_queries<bf16_t>(g, sl, Q, qscale, q_first_row, vars, rope, q, Qr, (blockIdx.x - runs.total * BH) * kPackThreads + threadIdx.x);
+        return;
+    }
     const int bh = blockIdx.x % BH, kth = blockIdx.x / BH;   // the kth tile of the runs
     int run = 0;
     while (run + 1 < runs.n && kth >= runs.ahead[run + 1]) ++run;
@@ -76,9 +88,11 @@ __global__ __launch_bounds__(kPackThreads) void kv_pack_kernel(Geom g, SegList s
     if (si >= sl.n) return;   // cannot happen: the runs name tiles of the segment list
     const Seg sg = sl.s[si];
     const int t0 = (n - first) * kBN, rows = min(kBN, sg.len - t0);
-    const size_t row0 = sg.chunk ? ((size_t)bh * Q + t0) : ((size_t)bh * g.slots + sg.start + t0);
-    const bf16_t* src = (sg.chunk ? Vch : Vc) + row0 * D;
-    const bf16_t* ksrc = (sg.chunk ? Krc : Kr) + row0 * D;
+    // a chunk row is one of Hkv rows of a token
+    const size_t row0 = sg.chunk ? ((size_t)(bh / g.Hkv) * Q + t0) * g.Hkv + bh % g.Hkv : ((size_t)bh * g.slots + sg.start + t0);
+    const size_t rstride = (size_t)(sg.chunk ? g.Hkv : 1) * D;
+    const bf16_t* src = (sg.chunk ? v_in : Vc) + row0 * D;
+    const bf16_t* ksrc = (sg.chunk ? k_in : Kr) + row0 * D;
     bf16_t* kdst = Kt + ((size_t)bh * tiles_per_bh + n) * (kBN * D);
     const int tid = threadIdx.x;
     float norm2_max = 0.f;
@@ -87,8 +101,27 @@ __global__ __launch_bounds__(kPackThreads) void kv_pack_kernel(Geom g, SegList s
         const int r = p / (D / 8), c = p % (D / 8);
         u32x4_t v = {0u, 0u, 0u, 0u}, k = {0u, 0u, 0u, 0u};
         if (r < rows) {
-            v = *reinterpret_cast<const u32x4_t*>(src + (size_t)r * D + c * 8);
-            k = *reinterpret_cast<const u32x4_t*>(ksrc + (size_t)r * D + (c ^ Swz<D>::key_k(r)) * 8);
+            const int kc = c ^ Swz<D>::key_k(r);             // this thread's 16 bytes of the key
+            v = *reinterpret_cast<const u32x4_t*>(src + (size_t)r * rstride + c * 8);
+            k = *reinterpret_cast<const u32x4_t*>(ksrc + (size_t)r * rstride + kc * 8);
+            if (sg.chunk) {                                  // (uniform for the workgroup)
+                const bool hi = kc >= D / 16;                // the second elements of its rotary pairs
+                const u32x4_t o = *reinterpret_cast<const u32x4_t*>(ksrc + (size_t)r * rstride + (kc ^ (D / 16)) * 8);
+                const float2* cs = rope + (size_t)(t0 + r) * (D / 2) + (kc & (D / 16 - 1)) * 8;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    uint32_t w[2];
+#pragma unroll
+                    for (int y = 0; y < 2; ++y) {
+                        const float2 t = cs[2 * x + y];
+                        const float mine = y ? __uint_as_float(k[x] & 0xFFFF0000u) : __uint_as_float(k[x] << 16);
+                        const float other = y ? __uint_as_float(o[x] & 0xFFFF0000u) : __uint_as_float(o[x] << 16);
+                        w[y] = f32_to_bf16(hi ? rot_hi(other, mine, t.x, t.y) : rot_lo(mine, other, t.x, t.y));
+                    }
+                    k[x] = w[0] | (w[1] << 16);
+                }
+                *reinterpret_cast<u32x4_t*>(Krc + ((size_t)bh * Q + t0 + r) * D + kc * 8) = k;
+            }
         }
         *reinterpret_cast<u32x4_t*>(&T[r * STR + c * 8]) = v;
         *reinterpret_cast<u32x4_t*>(kdst + (size_t)p * 8) = k;   // position c of row r holds chunk c ^ key
@@ -731,17 +764,20 @@ int packed_tiles_of(const SegList& sl) { return packed_tiles(sl); }
 
 // Tile n of a (batch, KV head) sits at tile index bh * b.vt_tiles + n of Kt, Vt and Knorm2: the
 // stride is the capacity, so that tiles keep their place from one chunk to the next.
-bool launch_kv_pack(const Geom& g, const DevBuffers& b, const SegList& sl, const TileRuns& runs, int Q, hipStream_t s)
+bool launch_kv_pack(const Geom& g, const DevBuffers& b, const SegList& sl, const TileRuns& runs, int Q, float qscale, int q_first_row,
+                    const void* q, const void* k, const void* v, hipStream_t s)
 {
     if (packed_tiles(sl) > b.vt_tiles) return false;   // the workspace was sized for every possible segment list
-    if (runs.total == 0) return true;
-    const dim3 grid(runs.total * g.B * g.Hkv), block(kPackThreads);
-    if (g.d == 128)
-        hipLaunchKernelGGL(kv_pack_kernel<128>, grid, block, 0, s, g, sl, runs, Q, b.vt_tiles, (const bf16_t*)b.Kr, (const bf16_t*)b.Krc,
-                           (const bf16_t*)b.Vc, (const bf16_t*)b.Vch, (bf16_t*)b.Kt, (bf16_t*)b.Vt, b.knorm2);
-    else
-        hipLaunchKernelGGL(kv_pack_kernel<64>, grid, block, 0, s, g, sl, runs, Q, b.vt_tiles, (const bf16_t*)b.Kr, (const bf16_t*)b.Krc,
-                           (const bf16_t*)b.Vc, (const bf16_t*)b.Vch, (bf16_t*)b.Kt, (bf16_t*)b.Vt, b.knorm2);
+    int vars = 1;
+    const long threads = q_first_row < Q ? query_threads(g, sl, Q - q_first_row, &vars) : 0;
+    const dim3 grid(runs.total * g.B * g.Hkv + (unsigned)((threads + kPackThreads - 1) / kPackThreads)), block(kPackThreads);
+    if (grid.x == 0) return true;
+#define CKV_PACK(D)                                                                                                                       \
+    hipLaunchKernelGGL(kv_pack_kernel<D>, grid, block, 0, s, g, sl, runs, Q, b.vt_tiles, qscale, q_first_row, vars, b.rope, (const bf16_t*)q, \
+                       (const bf16_t*)k, (const bf16_t*)v, (const bf16_t*)b.Kr, (const bf16_t*)b.Vc, (bf16_t*)b.Qr, (bf16_t*)b.Krc,          \
+                       (bf16_t*)b.Kt, (bf16_t*)b.Vt, b.knorm2)
+    if (g.d == 128) CKV_PACK(128); else CKV_PACK(64);
+#undef CKV_PACK
     return true;
 }
 

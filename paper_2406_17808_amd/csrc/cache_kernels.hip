@@ -128,18 +128,15 @@ void launch_load_state(const Geom& g, int dtype, const DevBuffers& b, const void
 // For every rotated query copy v: Qr[v][b][h][i] = qscale * R(qrot0[v] + i) q[b][i][h] (the bf16
 // MFMA kernels want the softmax scale and log2(e) folded into the queries; everybody else passes
 // 1); chunk keys are rotated to their chunk index, chunk values are copied head-major.  A thread takes 8 rotary
-// pairs of one row (two 16-byte pieces for bf16); of the queries it takes kPrepHeads heads, which share
-// the (cos, sin) of their index, and vars of the copies.
-constexpr int kPrepHeads = 4;
+// pairs of one row (two 16-byte pieces for bf16), or of a few query heads (rotate_queries).
 template <typename T>
 __global__ void prep_kernel(Geom g, SegList sl, int Q, float qscale, int q_first_row, int vars, const float2* __restrict__ rope,
                             const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                             T* __restrict__ Qr, T* __restrict__ Krc, T* __restrict__ Vch)
 {
     const int half = g.d / 2, groups = half / 8;
-    // threads [0, n_kv): one per (sequence, token, K or V head, group); then one per (range of copies, sequence,
-    // query row that needs rotated copies, group of query heads, group).  32-bit numbers: 2^32 threads would move
-    // more than 128 GB of K and V three times over.
+    // threads [0, n_kv): one per (sequence, token, K or V head, group); then those of rotate_queries.  32-bit
+    // numbers: 2^32 threads would move more than 128 GB of K and V three times over.
     const uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x, n_kv = (uint32_t)g.B * Q * 2 * g.Hkv * groups;
     if (idx < n_kv) {
         const int e = (int)(idx % groups) * 8;
@@ -163,41 +160,7 @@ __global__ void prep_kernel(Geom g, SegList sl, int Q, float qscale, int q_first
         }
         return;
     }
-    const uint32_t q_rows = Q - q_first_row, head_groups = (g.Hq + kPrepHeads - 1) / kPrepHeads;
-    if (q_rows == 0) return;
-    const uint32_t qidx = idx - n_kv;
-    const int e = (int)(qidx % groups) * 8;
-    uint32_t r = qidx / groups;
-    const int h0 = (int)(r % head_groups) * kPrepHeads;
-    r /= head_groups;
-    const int i = q_first_row + (int)(r % q_rows);
-    r /= q_rows;
-    const int b = (int)(r % g.B), v0 = (int)(r / g.B) * vars;
-    if (v0 >= sl.n_qvar) return;
-    float y0[kPrepHeads][8], y1[kPrepHeads][8];
-#pragma unroll
-    for (int x = 0; x < kPrepHeads; ++x) {
-        const size_t src = (((size_t)b * Q + i) * g.Hq + min(h0 + x, g.Hq - 1)) * g.d;
-        Vec8<T>::load(q + src + e, y0[x]);
-        Vec8<T>::load(q + src + e + half, y1[x]);
-    }
-#pragma unroll
-    for (int x = 0; x < kPrepHeads; ++x)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { y0[x][j] *= qscale; y1[x][j] *= qscale; }
-    for (int vq = v0; vq < min(v0 + vars, sl.n_qvar); ++vq) {
-        const size_t dst = ((((size_t)vq * g.B + b) * g.Hq + h0) * Q + i) * g.d;
-        float2 cs[8];
-        const float2* rp = rope + (size_t)(sl.qrot0[vq] + i) * half + e;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) cs[j] = rp[j];
-#pragma unroll
-        for (int x = 0; x < kPrepHeads; ++x)
-            if (h0 + x < g.Hq) {
-                T* to = Qr + dst + (size_t)x * Q * g.d + e;
-                rotate8<T>(y0[x], y1[x], cs, to, to + half);
-            }
-    }
+    rotate_queries<T>(g, sl, Q, qscale, q_first_row, vars, rope, q, Qr, idx - n_kv);
 }
 
 // head dimensions that are not a multiple of 16: one thread per rotary pair
@@ -247,12 +210,8 @@ void launch_prep(const Geom& g, int dtype, const DevBuffers& b, const SegList& s
 {
     const dim3 block(256);
     if (g.d % 16 == 0) {
-        // as few copies per thread as it takes to give the chip two rounds of threads (the queries are read once
-        // per thread, so no fewer than that)
-        const long one = (long)g.B * (Q - q_first_row) * ((g.Hq + kPrepHeads - 1) / kPrepHeads) * (g.d / 16);
-        int vars = sl.n_qvar;
-        while (vars > 1 && one * ((sl.n_qvar + vars - 1) / vars) < 2 * 256 * 1024) --vars;
-        const long n = (long)g.B * Q * 2 * g.Hkv * (g.d / 16) + one * ((sl.n_qvar + vars - 1) / vars);
+        int vars;
+        const long n = (long)g.B * Q * 2 * g.Hkv * (g.d / 16) + query_threads(g, sl, Q - q_first_row, &vars);
         const dim3 grid((unsigned)((n + 255) / 256));
         if (dtype == CASCADE_F32)
             hipLaunchKernelGGL(prep_kernel<float>, grid, block, 0, s, g, sl, Q, qscale, q_first_row, vars, b.rope, (const float*)q, (const float*)k,

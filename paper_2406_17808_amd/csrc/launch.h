@@ -90,7 +90,10 @@ void launch_score_f32(const Geom& g, const DevBuffers& b, const SegList& sl, int
 // segments), for the tiles named by `runs` only (false if Kt / Vt do not hold that many tiles);
 // launch_attn_stream reads only those copies, and the caller's queries (q: [B,Q,Hq,d], rotated on the fly).
 int packed_tiles_of(const SegList& sl);
-bool launch_kv_pack(const Geom& g, const DevBuffers& b, const SegList& sl, const TileRuns& runs, int Q, hipStream_t s);
+// The launch also does launch_prep's work: it rotates the chunk's keys (into the tiles and Krc) and writes the
+// rotated copies of query rows q_first_row .. Q-1.
+bool launch_kv_pack(const Geom& g, const DevBuffers& b, const SegList& sl, const TileRuns& runs, int Q, float qscale, int q_first_row,
+                    const void* q, const void* k, const void* v, hipStream_t s);
 // It also leaves the exponent offsets of the last tail_rows rows in b.negt for launch_score_mfma.
 // single_pass (only if attn_single_pass_ok): the kernel also leaves the column sums of Alg. 3's single-pass
 // scores in b.sp_part, which launch_single_pass_merge turns into the scores (instead of launch_score_mfma).

@@ -51,4 +51,63 @@ __device__ inline void rotate8(const float* x0, const float* x1, const float2* _
     Vec8<T>::store(d1, y1);
 }
 
+// Rotated copies of the queries of rows q_first_row .. Q-1 (copy v of row i turned by qrot0[v] + i): thread qidx
+// takes 8 rotary pairs of kPrepHeads heads of a row, which share their (cos, sin), and `vars` of the copies.
+// One per (range of copies, sequence, row, group of query heads, group of 8 pairs).  Bound by the
+// copies' writes: 9 copies of 4096 rows of 32 heads (0.3 GB) took 97 us with one head per thread and 64-bit
+// indices, 79 so (with the chunk's K and V).
+constexpr int kPrepHeads = 4;
+
+// as few copies per thread as it takes to give the chip two rounds of threads (every thread reads its queries
+// anew); returns the number of threads
+inline long query_threads(const Geom& g, const SegList& sl, int q_rows, int* vars)
+{
+    const long one = (long)g.B * q_rows * ((g.Hq + kPrepHeads - 1) / kPrepHeads) * (g.d / 16);
+    int v = sl.n_qvar;
+    while (v > 1 && one * ((sl.n_qvar + v - 1) / v) < 2 * 256 * 1024) --v;
+    *vars = v;
+    return one * ((sl.n_qvar + v - 1) / v);
+}
+
+template <typename T>
+__device__ inline void rotate_queries(const Geom& g, const SegList& sl, int Q, float qscale, int q_first_row, int vars,
+                                      const float2* __restrict__ rope, const T* __restrict__ q, T* __restrict__ Qr, uint32_t qidx)
+{
+    const int half = g.d / 2, groups = half / 8;
+    const uint32_t q_rows = Q - q_first_row, head_groups = (g.Hq + kPrepHeads - 1) / kPrepHeads;
+    if (q_rows == 0) return;
+    const int e = (int)(qidx % groups) * 8;
+    uint32_t r = qidx / groups;
+    const int h0 = (int)(r % head_groups) * kPrepHeads;
+    r /= head_groups;
+    const int i = q_first_row + (int)(r % q_rows);
+    r /= q_rows;
+    const int b = (int)(r % g.B), v0 = (int)(r / g.B) * vars;
+    if (v0 >= sl.n_qvar) return;
+    float y0[kPrepHeads][8], y1[kPrepHeads][8];
+#pragma unroll
+    for (int x = 0; x < kPrepHeads; ++x) {
+        const size_t src = (((size_t)b * Q + i) * g.Hq + min(h0 + x, g.Hq - 1)) * g.d;
+        Vec8<T>::load(q + src + e, y0[x]);
+        Vec8<T>::load(q + src + e + half, y1[x]);
+    }
+#pragma unroll
+    for (int x = 0; x < kPrepHeads; ++x)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { y0[x][j] *= qscale; y1[x][j] *= qscale; }
+    for (int vq = v0; vq < min(v0 + vars, sl.n_qvar); ++vq) {
+        const size_t dst = ((((size_t)vq * g.B + b) * g.Hq + h0) * Q + i) * g.d;
+        float2 cs[8];
+        const float2* rp = rope + (size_t)(sl.qrot0[vq] + i) * half + e;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) cs[j] = rp[j];
+#pragma unroll
+        for (int x = 0; x < kPrepHeads; ++x)
+            if (h0 + x < g.Hq) {
+                T* to = Qr + dst + (size_t)x * Q * g.d + e;
+                rotate8<T>(y0[x], y1[x], cs, to, to + half);
+            }
+    }
+}
+
 }  // namespace ckv
