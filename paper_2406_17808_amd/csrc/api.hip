@@ -237,6 +237,8 @@ static int init_context(const char* who, const cascade_config* cfg, const Geom& 
     if (const char* e = getenv("CASCADE_KV_ATTN_SPLITS")) ctx->buf.opt_attn_splits = atoi(e);
     ctx->buf.opt_score_narrow = -1;
     if (const char* e = getenv("CASCADE_KV_SCORE_NARROW")) ctx->buf.opt_score_narrow = e[0] == '1' ? 1 : 0;
+    ctx->buf.opt_score_parts = -1;
+    if (const char* e = getenv("CASCADE_KV_SCORE_PARTS")) ctx->buf.opt_score_parts = atoi(e);
     ctx->buf.opt_update_staged = getenv("CASCADE_KV_UPDATE_STAGED") != nullptr;
 
     // rows of a chunk whose EMA weight beta^k has not dropped below the cut

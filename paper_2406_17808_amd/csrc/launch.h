@@ -51,6 +51,7 @@ struct DevBuffers {
     // created; no launch looks at the environment
     int opt_attn_splits;       // CASCADE_KV_ATTN_SPLITS: workgroups per row block of a small attention launch; 0 = automatic
     int opt_score_narrow;      // CASCADE_KV_SCORE_NARROW: 0 / 1 force the 64- / 32-key form of the score kernel; -1 = automatic
+    int opt_score_parts;       // CASCADE_KV_SCORE_PARTS: row parts of the score sums per head (0: one workgroup takes all heads and rows); -1 = automatic
     int opt_update_staged;     // CASCADE_KV_UPDATE_STAGED: always plan the update cascade by cascade (plan_kernel)
 };
 

@@ -6,6 +6,8 @@
 #include <stdio.h>
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "async_copy.h"
 #include "mfma_util.h"
 
@@ -36,13 +38,27 @@ template <int D> struct ScoreSwz {   // permutation of the 16-byte pieces of a s
     __device__ static int of(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
 };
 
+// The segment a block of `keys` keys of the segment list belongs to, and its number inside it.
+__device__ inline int score_tile_segment(const SegList& sl, int keys, int tile, int* within)
+{
+    int si = 0;
+    while (si < sl.n) {
+        const int nt = (sl.s[si].len + keys - 1) / keys;
+        if (tile < nt) break;
+        tile -= nt;
+        ++si;
+    }
+    *within = tile;
+    return si;
+}
+
 // NKB: 32-key blocks per wave.  Two halve the LDS reads per MFMA; one gives twice as many
 // workgroups, for launches that would otherwise leave compute units without work.
 template <int D, int NKB>
 __global__ __launch_bounds__(kScoreThreads, 3) void score_stream_kernel(
-    Geom g, SegList sl, int Q, int qstride, int tail, int qpad, float decay, const bf16_t* __restrict__ Qr,
+    Geom g, SegList sl, int Q, int qstride, int tail, int qpad, int n_tiles, int row_parts, float decay, const bf16_t* __restrict__ Qr,
     const bf16_t* __restrict__ Kr, const bf16_t* __restrict__ Krc, const float* __restrict__ negt,
-    float* __restrict__ mu, float* __restrict__ mu_chunk)
+    float* __restrict__ mu, float* __restrict__ mu_chunk, float* __restrict__ sums)
 {
     constexpr int KS = D / 16;
     constexpr int kScoreKeys = kScoreKeysPerBlock * NKB, kWaveKeys = 32 * NKB;
@@ -55,15 +71,10 @@ __global__ __launch_bounds__(kScoreThreads, 3) void score_stream_kernel(
     __shared__ __attribute__((aligned(256))) float tneg[kStStages][4][kStRows];   // every wave keeps its own copy
     const int BH = g.B * g.Hkv;
     const int bh = blockIdx.x % BH;
-    int tile = blockIdx.x / BH;
+    const int list_tile = (blockIdx.x / BH) % n_tiles, part = blockIdx.x / BH / n_tiles;
+    int tile;
     const int b = bh / g.Hkv, hk = bh % g.Hkv;
-    int si = 0;
-    while (si < sl.n) {
-        const int nt = (sl.s[si].len + kScoreKeys - 1) / kScoreKeys;
-        if (tile < nt) break;
-        tile -= nt;
-        ++si;
-    }
+    const int si = score_tile_segment(sl, kScoreKeys, list_tile, &tile);
     if (si >= sl.n) return;       // uniform for the workgroup
     const Seg sg = sl.s[si];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l32 = l & 31, half = l >> 5;
@@ -80,19 +91,24 @@ __global__ __launch_bounds__(kScoreThreads, 3) void score_stream_kernel(
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) kf[kb][ks].u = *reinterpret_cast<const u32x4_t*>(krow + ks * 16 + half * 8);
     }
-    // fragment reads of this lane: row block rb, step ks: row 32*rb + l32, piece 2*ks + half
-    int a_off[2][KS];
+    // fragment reads of this lane: row block rb, step ks: row 32*rb + l32, piece 2*ks + half (rows 32 apart are
+    // permuted alike)
+    int a_off[KS];
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int row = 32 * rb + l32;
-            a_off[rb][ks] = row * (D * 2) + (((2 * ks + half) ^ ScoreSwz<D>::of(row)) * 16);
-        }
+    for (int ks = 0; ks < KS; ++ks) a_off[ks] = l32 * (D * 2) + (((2 * ks + half) ^ ScoreSwz<D>::of(l32)) * 16);
 
-    const int i_first = Q - tail;                              // first row that contributes
-    const int spp = (tail + kStRows - 1) / kStRows;            // stages per head
-    const int T = g.G * spp;
+    // This workgroup's heads, and its stages of 64 rows of each: all of both, or one part of one head
+    const int head0 = row_parts ? part / row_parts : 0, n_heads = row_parts ? 1 : g.G;
+    const int all_stages = (tail + kStRows - 1) / kStRows;
+    int st0 = 0, st1 = all_stages;
+    if (row_parts) {
+        st0 = all_stages * (part % row_parts) / row_parts;
+        st1 = all_stages * (part % row_parts + 1) / row_parts;
+    }
+    if (sg.chunk) st0 = max(st0, (tile * kScoreKeys - (Q - tail)) / kStRows);   // earlier rows see none of these keys
+    const int i_first = Q - tail + st0 * kStRows;              // first row that contributes
+    const int spp = max(st1 - st0, 0);                         // stages per head
+    const int T = n_heads * spp;
     const uint32_t ring_lds = lds_address(&ring[0][0]), tneg_lds = lds_address(&tneg[0][0][0]);
     // the keys are in registers before the first copy is issued (a wait for them inside the loop
     // would also wait for every copy in flight)
@@ -110,7 +126,7 @@ __global__ __launch_bounds__(kScoreThreads, 3) void score_stream_kernel(
     int iss_hh = 0, iss_sp = 0;                                 // stage s, the next to issue, is stage iss_sp of head iss_hh
     auto issue = [&](int s) {
         const int i_base = i_first + iss_sp * kStRows;
-        const int h = hk * g.G + iss_hh, slot = s % kStStages;
+        const int h = hk * g.G + head0 + iss_hh, slot = s % kStStages;
         if (++iss_sp == spp) { iss_sp = 0; ++iss_hh; }
         const bf16_t* qbase = Qr + (((size_t)sg.qvar * g.B + b) * g.Hq + h) * (size_t)Q * D;
         if (i_base + kStRows <= Q) {          // all rows of the stage exist: the lane offsets are constants
@@ -132,9 +148,51 @@ __global__ __launch_bounds__(kScoreThreads, 3) void score_stream_kernel(
                        __builtin_amdgcn_readfirstlane(tneg_lds + (uint32_t)((slot * 4 + wave) * kStRows * 4)));
     };
 
+    float red[NKB] = {}, colsum[NKB] = {};
+    // A stage whose 64 rows all see all keys of the wave.  Fragments are read kAhead steps before their use and
+    // the first MFMAs start from the offsets where they were read: 82 vector and 20 scalar instructions per
+    // 32 rows instead of 109 and 65, in a kernel whose exponentials alone are 512 of the vector ALU's cycles
+    // per 512 of MFMA: 4096 rows against 16K slots 626 -> 592 us.  (A separate register
+    // copy of the offsets or eight steps ahead spill at D = 128; raising the priority of the wave that is ahead
+    // in its block changes nothing.)
+    auto whole_stage = [&](const unsigned char* qs, const float* tn) {
+        constexpr int kAhead = 4;
+        static_assert(kAhead <= KS, "the first fragments belong to the first row block");
+        Frag fr[kAhead];
+        f32x16_t acc[NKB];   // acc[NKB - 1] takes the exponent offsets; the first MFMAs start from there
+        auto read_t = [&](int rb) {
+#pragma unroll
+            for (int jq = 0; jq < 4; ++jq) {
+                const float4 t4 = *reinterpret_cast<const float4*>(tn + rb * 32 + jq * 8 + half * 4);
+                acc[NKB - 1][jq * 4 + 0] = t4.x; acc[NKB - 1][jq * 4 + 1] = t4.y; acc[NKB - 1][jq * 4 + 2] = t4.z; acc[NKB - 1][jq * 4 + 3] = t4.w;
+            }
+        };
+        auto read_q = [&](int i) { fr[i % kAhead].u = *reinterpret_cast<const u32x4_t*>(qs + a_off[i % KS] + (i / KS) * (64 * D)); };
+        read_t(0);
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) read_q(i);
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb)
+                    acc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[ks % kAhead].v, kf[kb][ks].v, ks == 0 ? acc[NKB - 1] : acc[kb], 0, 0, 0);
+                if (rb * KS + ks + kAhead < 2 * KS) read_q(rb * KS + ks + kAhead);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb) colsum[kb] += __builtin_amdgcn_exp2f(acc[kb][j]);
+            }
+            if (rb == 0) read_t(1);
+        }
+    };
+
     int issued = 0;
     for (; issued < kStStages - 1 && issued < T; ++issued) issue(issued);
-    float red[NKB] = {}, colsum[NKB] = {};
     int hh = 0, sp = 0;                                         // stage s = stage sp of head hh
     for (int s = 0; s < T; ++s) {
         const int ahead = issued - s - 1;                       // stages issued after stage s
@@ -148,8 +206,10 @@ __global__ __launch_bounds__(kScoreThreads, 3) void score_stream_kernel(
         const int i_base = i_first + sp * kStRows;
         const int rows = min(kStRows, Q - i_base);
         const unsigned char* qs = &ring[slot][0];
+        if (rows == kStRows && !(sg.chunk && i_base < wave_k0 + kWaveKeys - 1)) whole_stage(qs, &tneg[slot][wave][0]);
+        else
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
+        for (int rb = 0; rb < 2; ++rb) {       // the end of the chunk, the diagonal, rows that see none of the keys
             const int i0 = i_base + rb * 32;
             if (rb * 32 >= rows) continue;
             if (sg.chunk && i0 + 31 < wave_k0) continue;        // chunk keys are seen by later rows only
@@ -163,7 +223,7 @@ __global__ __launch_bounds__(kScoreThreads, 3) void score_stream_kernel(
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 Frag qf;
-                qf.u = *reinterpret_cast<const u32x4_t*>(qs + a_off[rb][ks]);
+                qf.u = *reinterpret_cast<const u32x4_t*>(qs + a_off[ks] + rb * (64 * D));
 #pragma unroll
                 for (int kb = 0; kb < NKB; ++kb)
                     acc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf.v, kf[kb][ks].v, acc[kb], 0, 0, 0);
@@ -197,6 +257,16 @@ __global__ __launch_bounds__(kScoreThreads, 3) void score_stream_kernel(
             ++hh;
         }
     }
+    if (row_parts) {
+        // column sums of this part (T == 0: chunk keys that none of its rows sees); score_merge_kernel does the rest
+        if (half == 0) {
+            float* p = sums + ((size_t)(bh * g.G + head0) * row_parts + part % row_parts) * ((size_t)n_tiles * kScoreKeys) +
+                       (size_t)list_tile * kScoreKeys + wave * kWaveKeys + l32;
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb) p[kb * 32] = red[kb];
+        }
+        return;
+    }
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
         float r = red[kb];
@@ -211,25 +281,74 @@ __global__ __launch_bounds__(kScoreThreads, 3) void score_stream_kernel(
     }
 }
 
+// The parts' column sums of every key added up in a fixed order, the query heads of the group reduced, and the
+// EMA step taken (one thread per key).
+__global__ __launch_bounds__(2 * kScoreKeysPerBlock) void score_merge_kernel(Geom g, SegList sl, int qstride, int n_tiles, int row_parts, float decay,
+                                                                             const float* __restrict__ sums, float* __restrict__ mu,
+                                                                             float* __restrict__ mu_chunk)
+{
+    const int keys = blockDim.x, bh = blockIdx.y;
+    int tile;
+    const int si = score_tile_segment(sl, keys, blockIdx.x, &tile);
+    if (si >= sl.n) return;
+    const Seg sg = sl.s[si];
+    const int k = tile * keys + threadIdx.x;
+    if (k >= sg.len) return;
+    const size_t stride = (size_t)n_tiles * keys;
+    const float* p = sums + (size_t)bh * g.G * row_parts * stride + (size_t)blockIdx.x * keys + threadIdx.x;
+    float* m = sg.chunk ? mu_chunk + (size_t)bh * qstride + k : mu + (size_t)bh * g.slots + sg.start + k;
+    const float old = sg.chunk ? 0.f : *m;
+    float red = 0.f;
+    for (int hh = 0; hh < g.G; ++hh) {
+        float v = 0.f;
+        for (int r = 0; r < row_parts; ++r, p += stride) v += *p;
+        red = g.head_reduce == CASCADE_REDUCE_MAX ? (hh == 0 ? v : fmaxf(red, v)) : red + v;
+    }
+    if (g.head_reduce == CASCADE_REDUCE_MEAN) red /= (float)g.G;
+    *m = sg.chunk ? red : decay * old + red;
+}
+
 void launch_score_mfma(const Geom& g, const DevBuffers& b, const SegList& sl, int Q, int max_chunk,
                        int tail_rows, float decay, hipStream_t s)
 {
-    auto workgroups = [&](int keys) {
+    auto tiles_of = [&](int keys) {
         int tiles = 0;
         for (int i = 0; i < sl.n; ++i) tiles += (sl.s[i].len + keys - 1) / keys;
-        return tiles * g.B * g.Hkv;
+        return tiles;
     };
+    const int BH = g.B * g.Hkv, stages = (tail_rows + kStRows - 1) / kStRows;
+    const int wide = tiles_of(2 * kScoreKeysPerBlock) * BH;
+    // Every head by itself, in up to 4 or 8 parts of its rows: the launch is then spread evenly over the compute
+    // units (640 workgroups on 768 slots leave a third of them with two instead of three), for a second launch of
+    // 5 to 6 us.  us a call, whole against in parts: 4096 rows against 16K slots 1796 -> 1727, against 2K slots
+    // 756 -> 644 in one part a head and 622 in four; 512 rows against 8K slots
+    // 158.7 -> 157.0 (against half as many keys a wave); 300 rows, 64 workgroups 36 -> 23
+    // for the kernels.  With fewer stages than that the second launch costs more than the balance gives: 264 rows against
+    // 16K slots 589 whole, 593 in parts.
+    int row_parts = 0;
+    if (stages >= 8 || (wide < 256 && stages >= 4)) {
+        row_parts = 1;
+        while (wide * g.G * row_parts < 1536 && stages / (2 * row_parts) >= 8) row_parts *= 2;
+        if (g.G * row_parts == 1) row_parts = 0;
+    }
+    if (b.opt_score_parts >= 0) row_parts = std::min(b.opt_score_parts, stages);
     // 256 keys per workgroup unless that leaves a good part of the 256 x 3 workgroup slots empty
-    bool narrow = workgroups(2 * kScoreKeysPerBlock) < 600;
+    bool narrow = row_parts == 0 && wide < 600;
     if (b.opt_score_narrow >= 0) narrow = b.opt_score_narrow == 1;
-    const dim3 grid(workgroups(narrow ? kScoreKeysPerBlock : 2 * kScoreKeysPerBlock)), block(kScoreThreads);
+    const int keys = narrow ? kScoreKeysPerBlock : 2 * kScoreKeysPerBlock, n_tiles = tiles_of(keys);
+    // the parts' sums lie where a split attention launch keeps its partial results
+    while (row_parts > 0 && (size_t)BH * g.G * row_parts * n_tiles * keys > (size_t)kAttnPartRows * (g.d + 2)) --row_parts;
+    const dim3 grid(n_tiles * BH * (row_parts ? g.G * row_parts : 1)), block(kScoreThreads);
     const int qpad = max_chunk + kStRows;   // the attention launch left the offsets of this chunk's rows in b.negt
 #define CKV_SCORE(D, NKB)                                                                                              \
-    hipLaunchKernelGGL((score_stream_kernel<D, NKB>), grid, block, 0, s, g, sl, Q, max_chunk, tail_rows, qpad, decay,     \
-                       (const bf16_t*)b.Qr, (const bf16_t*)b.Kr, (const bf16_t*)b.Krc, b.negt, b.mu, b.mu_chunk)
+    hipLaunchKernelGGL((score_stream_kernel<D, NKB>), grid, block, 0, s, g, sl, Q, max_chunk, tail_rows, qpad, n_tiles, row_parts, decay, \
+                       (const bf16_t*)b.Qr, (const bf16_t*)b.Kr, (const bf16_t*)b.Krc, b.negt, b.mu, b.mu_chunk, b.attn_part)
     if (g.d == 128) { if (narrow) CKV_SCORE(128, 1); else CKV_SCORE(128, 2); }
     else { if (narrow) CKV_SCORE(64, 1); else CKV_SCORE(64, 2); }
 #undef CKV_SCORE
+    if (row_parts)
+        hipLaunchKernelGGL(score_merge_kernel, dim3(n_tiles, BH), dim3(keys), 0, s, g, sl, max_chunk, n_tiles, row_parts, decay, b.attn_part, b.mu,
+                           b.mu_chunk);
 }
 
 }  // namespace ckv

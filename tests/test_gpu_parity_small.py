@@ -115,6 +115,14 @@ def test_tiny_f32_free_running(oracle_mod):
          sizes=[256, 128], chunks=[256] * 4 + [64] * 3 + [192] + [256] * 3, max_chunk=256, attn_splits=1, pack_reuse=1),
     dict(name="bf16_logit_step_chunk_tail_d64", dtype=B.CASCADE_BF16, d=64, Hq=4, Hkv=2, batch=1, n_sink=4,
          sizes=[96, 96, 96], chunks=[256] * 5, max_chunk=256, logit_step="chunk_tail", rope_base=1e6, compare_membership=False),
+    # score sums in parts: one head each; fewer stages than parts, a ragged last one; and by the rule (many rows)
+    dict(name="bf16_score_parts_per_head", dtype=B.CASCADE_BF16, d=128, Hq=8, Hkv=2, batch=1, n_sink=5,
+         sizes=[48, 40, 36], chunks=[1, 7, 64, 100, 33, 128, 128, 2, 90, 128, 128, 77, 128], max_chunk=128, score_parts=1),
+    dict(name="bf16_score_parts_mean_d64", dtype=B.CASCADE_BF16, d=64, Hq=6, Hkv=2, batch=2, n_sink=4,
+         sizes=[64, 64], chunks=[300, 300, 129, 65, 300], max_chunk=300, beta=0.99, score_tail_eps=-1.0, score_parts=3,
+         head_reduce=B.CASCADE_REDUCE_MEAN),
+    dict(name="bf16_score_parts_one_head", dtype=B.CASCADE_BF16, d=128, Hq=1, Hkv=1, batch=1, n_sink=0,
+         sizes=[200], chunks=[200, 1030, 1100], max_chunk=1100, beta=0.999),
     # more splits of a row block than it has tiles: some are empty
     dict(name="bf16_d64_sixteen_splits", dtype=B.CASCADE_BF16, d=64, Hq=4, Hkv=2, batch=1, n_sink=4,
          sizes=[96, 96, 96], chunks=[64, 100, 256, 33, 256, 1, 64], max_chunk=256, attn_splits=16),
@@ -127,6 +135,8 @@ def test_prefill_one_step_ahead(oracle_mod, case, monkeypatch):
         monkeypatch.setenv("CASCADE_KV_ATTN_SPLITS", str(case["attn_splits"]))
     if "score_narrow" in case:   # 0: the score kernel keeps 64 keys per wave however small the launch
         monkeypatch.setenv("CASCADE_KV_SCORE_NARROW", str(case["score_narrow"]))
+    if "score_parts" in case:   # rows of a head in this many parts, every head by itself
+        monkeypatch.setenv("CASCADE_KV_SCORE_PARTS", str(case["score_parts"]))
     if "pack_reuse" in case:   # 0: every tile is packed for every chunk
         monkeypatch.setenv("CASCADE_KV_PACK_REUSE", str(case["pack_reuse"]))
     cfg = B.make_config(batch=case["batch"], n_q_heads=case["Hq"], n_kv_heads=case["Hkv"], head_dim=case["d"],
