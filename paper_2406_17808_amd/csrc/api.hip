@@ -28,14 +28,7 @@ struct cascade_ctx {
     int tail_k;          // rows of a chunk (counted from its end) that enter the score sums
     bool mfma;           // bf16 MFMA kernels; f32_mfma: the fp32 ones; neither: scalar kernels
     bool f32_mfma;
-    // bf16 path: Kt / Vt / Knorm2 belong to this context alone (not shared between layers), and, if
-    // packed_valid, hold every cache tile where `packed` puts it, except those named by `stale`.
-    // packed_reuse: tiles that are still valid are not packed again.
-    bool packed_own = true;
-    bool packed_reuse = true;
-    bool packed_valid = false;
-    PackedLayout packed;
-    TileRuns stale;
+    PackedCopies packed;   // bf16 path: what Kt / Vt / Knorm2 hold
     bool profiling = false;
     uint32_t prof_mask = ~0u;   // kernel families that get events while profiling
     bool is_static = false;   // one of the per-device contexts of cascade_init_static: never deleted
@@ -232,7 +225,8 @@ static int init_context(const char* who, const cascade_config* cfg, const Geom& 
     // development switches: the environment is read here and nowhere else
     ctx->f32_mfma = attn_f32_ok(g, cfg->dtype);
     if (const char* e = getenv("CASCADE_KV_SCALAR_ATTENTION")) if (e[0] == '1') ctx->mfma = ctx->f32_mfma = false;
-    if (const char* e = getenv("CASCADE_KV_PACK_REUSE")) ctx->packed_reuse = e[0] != '0';   // 0: pack every tile for every chunk
+    if (const char* e = getenv("CASCADE_KV_PACK_REUSE")) ctx->packed.reuse = e[0] != '0';   // 0: pack every tile for every chunk
+    ctx->packed.may_fix = cfg->score_mode == CASCADE_SCORES_EXACT;
     ctx->buf.opt_attn_splits = 0;
     if (const char* e = getenv("CASCADE_KV_ATTN_SPLITS")) ctx->buf.opt_attn_splits = atoi(e);
     ctx->buf.opt_score_narrow = -1;
@@ -338,7 +332,7 @@ extern "C" int cascade_init_layers(const cascade_config* cfg, int32_t n_layers, 
             for (int j = 0; j < i; ++j) { cascade_destroy(out_ctxs[j]); out_ctxs[j] = nullptr; }
             return rc;
         }
-        out_ctxs[i]->packed_own = n_layers == 1;   // layers pack into one shared copy, which the next layer overwrites
+        out_ctxs[i]->packed.own = n_layers == 1;   // layers pack into one shared copy, which the next layer overwrites
     }
     return CASCADE_OK;
 }
@@ -481,9 +475,10 @@ extern "C" int cascade_prefill_chunk(cascade_ctx* ctx, const void* dev_q, const 
     const int Q = n_tokens;
 
     SegList sl;
-    build_segments(g, ctx->st, true, Q, sl);
-    bool packed_stable = false;   // the packed tiles of this call stay where they are for the next one
     PackedLayout lay;
+    TileRuns runs;
+    if (ctx->mfma) plan_packing(g, ctx->st, Q, ctx->packed, sl, lay, runs);
+    else build_segments(g, ctx->st, true, Q, sl);
     // the MFMA kernels take logits directly as base-2 exponents
     const float qscale = ctx->mfma ? g.scale * 1.4426950408889634f : 1.f;
     const int tail = Q < ctx->tail_k ? Q : ctx->tail_k;    // rows that carry weight in the score sums
@@ -495,28 +490,11 @@ extern "C" int cascade_prefill_chunk(cascade_ctx* ctx, const void* dev_q, const 
         // (single-pass scores: nobody reads rotated query copies)
         if (!ctx->mfma) launch_prep(g, ctx->dtype, ctx->buf, sl, Q, qscale, 0, dev_q, dev_k, dev_v, s);
         else {
-            // The tiles of a full cache keep their place while the ring heads keep their offsets
-            // inside a tile: then only the tiles the last update wrote, and the chunk's own, are
-            // packed again.
-            packed_layout(g, ctx->st, lay);
-            const int chunk_tiles = (Q + 63) / 64;
-            if (lay.full && packed_tiles_of(sl) != lay.cache_tiles + chunk_tiles)
+            if (lay.full && packed_tiles_of(sl) != lay.cache_tiles + (Q + 63) / 64)
                 return fail(ctx, CASCADE_E_INTERNAL, "cascade_prefill_chunk: the segment list does not have the tiles of the packed layout");
-            TileRuns runs;
-            runs.n = 0; runs.total = 0;
-            bool partial = ctx->packed_reuse && ctx->packed_own && lay.full && ctx->packed_valid && same_offsets(g, lay, ctx->packed);
-            if (partial) {
-                runs = ctx->stale;
-                partial = add_tile_run(runs, lay.cache_tiles, chunk_tiles);
-            }
-            if (!partial) {
-                runs.n = 0; runs.total = 0;
-                add_tile_run(runs, 0, packed_tiles_of(sl));
-            }
-            ctx->packed_valid = false;   // until this call has gone through
+            ctx->packed.valid = false;   // until this call has gone through
             if (!launch_kv_pack(g, ctx->buf, sl, runs, Q, qscale, single_pass ? Q : Q - tail, dev_q, dev_k, dev_v, s))
                 return fail(ctx, CASCADE_E_WORKSPACE_TOO_SMALL, "cascade_prefill_chunk: packed K/V buffers too small for this segment list");
-            packed_stable = ctx->packed_own && lay.full;
         }
     }
     {
@@ -550,12 +528,8 @@ extern "C" int cascade_prefill_chunk(cascade_ctx* ctx, const void* dev_q, const 
         ctx->poisoned = true;
         return rc_launch;
     }
+    if (ctx->mfma) packed_after_update(g, lay, ctx->st, st_next, pl, ctx->packed);
     ctx->st = st_next;
-    if (packed_stable) {
-        ctx->packed = lay;
-        ctx->stale.n = 0; ctx->stale.total = 0;
-        ctx->packed_valid = add_touched_tiles(g, lay, pl, ctx->stale);
-    }
     return CASCADE_OK;
 }
 
@@ -574,7 +548,7 @@ extern "C" int cascade_decode_step(cascade_ctx* ctx, const void* dev_q, const vo
 
     SegList sl;
     build_segments(g, ctx->st, false, 1, sl);
-    ctx->packed_valid = false;   // the step writes cache rows the packed copies of the prefill path do not follow
+    ctx->packed.valid = false;   // the step writes cache rows the packed copies of the prefill path do not follow
     ctx->last_single_pass = false;
     const int n_splits = decode_split_count(g, ctx->buf, decode_tiles(sl));
     {

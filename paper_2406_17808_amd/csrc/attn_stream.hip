@@ -52,6 +52,8 @@ template <int D> struct Swz {
 
 constexpr int kPackThreads = 256;
 
+__host__ __device__ inline int seg_tiles(const Seg& s) { return (s.len + s.pad + kBN - 1) / kBN; }
+
 // Tile n of the packed K and V copies of one (batch, KV head): 64 rows of a segment (rows past
 // its end become zeros); K with its chunks swizzled, V transposed through LDS.  Chunk rows come from the
 // caller's tensors; their keys are rotated here, and left in Krc for the score pass.  The workgroups
@@ -81,15 +83,16 @@ __global__ __launch_bounds__(kPackThreads) void kv_pack_kernel(Geom g, SegList s
     const int n = runs.first[run] + (kth - runs.ahead[run]);
     int si = 0, first = 0;
     for (; si < sl.n; ++si) {
-        const int nt = (sl.s[si].len + kBN - 1) / kBN;
+        const int nt = seg_tiles(sl.s[si]);
         if (n < first + nt) break;
         first += nt;
     }
     if (si >= sl.n) return;   // cannot happen: the runs name tiles of the segment list
     const Seg sg = sl.s[si];
-    const int t0 = (n - first) * kBN, rows = min(kBN, sg.len - t0);
+    const int t0 = (n - first) * kBN - sg.pad, rows = min(kBN, sg.len - t0);   // (t0 < 0: rows before the segment become zeros, too)
     // a chunk row is one of Hkv rows of a token
-    const size_t row0 = sg.chunk ? ((size_t)(bh / g.Hkv) * Q + t0) * g.Hkv + bh % g.Hkv : ((size_t)bh * g.slots + sg.start + t0);
+    const size_t row0 = sg.chunk ? ((size_t)(bh / g.Hkv) * Q + t0) * g.Hkv + bh % g.Hkv
+                                 : ((size_t)bh * g.slots + (sg.start + t0));   // (a padded segment starts at least pad rows into its ring)
     const size_t rstride = (size_t)(sg.chunk ? g.Hkv : 1) * D;
     const bf16_t* src = (sg.chunk ? v_in : Vc) + row0 * D;
     const bf16_t* ksrc = (sg.chunk ? k_in : Kr) + row0 * D;
@@ -100,7 +103,7 @@ __global__ __launch_bounds__(kPackThreads) void kv_pack_kernel(Geom g, SegList s
     for (int p = tid; p < kBN * D / 8; p += kPackThreads) {
         const int r = p / (D / 8), c = p % (D / 8);
         u32x4_t v = {0u, 0u, 0u, 0u}, k = {0u, 0u, 0u, 0u};
-        if (r < rows) {
+        if (r < rows && t0 + r >= 0) {
             const int kc = c ^ Swz<D>::key_k(r);             // this thread's 16 bytes of the key
             v = *reinterpret_cast<const u32x4_t*>(src + (size_t)r * rstride + c * 8);
             k = *reinterpret_cast<const u32x4_t*>(ksrc + (size_t)r * rstride + kc * 8);
@@ -419,6 +422,16 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     // tiles skip the rescaling of O), and turn S^T into probabilities.  FIRST: S^T is absolute
     // and m_run not set yet (the first tile of a workgroup).
     auto softmax_tile = [&](const TileIter& it, bool first, auto interior, int step) {
+        if (!SP && !decltype(interior)::value && it.t0 < 0) {   // the tile starts before its segment
+            const int lo = -it.t0 - half * 4;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    if (kb * 32 + (j >> 2) * 8 + (j & 3) < lo) s[kb][j] = -INFINITY;
+                    if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+                }
+        }
         if (!decltype(interior)::value && ((it.t0 + kBN > it.sg.len) || (it.sg.chunk && it.t0 + kBN - 1 > wave_imin))) {
             const int lim = it.sg.chunk ? min(it.sg.len - 1, qi) : it.sg.len - 1;   // last visible key
             const int rel = lim - it.t0 - half * 4;   // accumulator j of block kb is key t0 + 4*half + (32 kb + 8 (j/4) + j%4)
@@ -479,7 +492,7 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     // In iteration t, tile t is multiplied with V, tile t+1 with Q; the copies of V of tile t+2
     // and of K of tile t+3 are issued.  Only the softmax needs to know which segment a tile is from.
     int NT = 0;   // tiles this workgroup visits: chunk keys after its last row are never visible
-    for (int i = 0; i < sl.n; ++i) NT += ((sl.s[i].chunk ? min(sl.s[i].len, wg_imax + 1) : sl.s[i].len) + kBN - 1) / kBN;
+    for (int i = 0; i < sl.n; ++i) NT += ((sl.s[i].chunk ? min(sl.s[i].len, wg_imax + 1) : sl.s[i].len) + sl.s[i].pad + kBN - 1) / kBN;
     if (SP) inv_steps = 1.f / (float)NT;
     int tile_first = 0;                  // SPLIT: first tile of this workgroup's range
     TileIter it1;
@@ -570,7 +583,7 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     // rounding of the rotated operands).  If that is within kBoundLog2 of the maximum of the first
     // tile for every row of the wave, probabilities stay below 2^kBoundLog2 whatever the later
     // tiles hold, m_run can stay where it is, and the per-tile maximum is skipped.
-    if (!SPLIT) bounded = !__any(sqrtf(qnorm2 * kn2) * 1.01f > m_run + kBoundLog2);
+    if (!SPLIT) bounded = !__any(sqrtf(qnorm2 * kn2) * 1.01f > m_run + kBoundLog2);   // (measured in split launches, too: -0.2 %)
     it1.next(sl, wg_imax);
     __syncthreads();      // barrier 0: every wave has read K of tile 0, its buffer may be refilled
 #pragma unroll
@@ -645,6 +658,7 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
         // same copies.
         if (q_var == it1.sg.qvar) {
             int k = min((it1.len - it1.t0 - 1) / kBN, NT - 4 - n0);
+            if (it1.t0 < 0) k = 0;
             if (it1.sg.chunk) k = min(k, (wave_imin + 1 - it1.t0) / kBN);   // chunk tiles every row of the wave sees whole
             for (; k > 0; --k) {
                 lap(0);
@@ -756,7 +770,7 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
 static int packed_tiles(const SegList& sl)
 {
     int n = 0;
-    for (int i = 0; i < sl.n; ++i) n += (sl.s[i].len + kBN - 1) / kBN;
+    for (int i = 0; i < sl.n; ++i) n += seg_tiles(sl.s[i]);
     return n;
 }
 
@@ -851,13 +865,13 @@ __global__ __launch_bounds__(kSpmHeads * kBN) void single_pass_merge_kernel(Geom
     const int n = blockIdx.x, bh = blockIdx.y, x = threadIdx.x % kBN, grp = threadIdx.x / kBN;
     int si = 0, first = 0;
     for (; si < sl.n; ++si) {
-        const int nt = (sl.s[si].len + kBN - 1) / kBN;
+        const int nt = seg_tiles(sl.s[si]);
         if (n < first + nt) break;
         first += nt;
     }
     if (si >= sl.n) return;                 // uniform for the workgroup
     const Seg sg = sl.s[si];
-    const int t0 = (n - first) * kBN, key = t0 + x;
+    const int t0 = (n - first) * kBN, key = t0 + x;      // (single-pass chunks have no padded segments)
     // row block r of a head covers tokens 256 r .. 256 r + 255 and visits the chunk's tiles up to its last token
     const int rbs = Q / 256, r_lo = sg.chunk ? t0 / 256 : 0;
     const size_t stride = (size_t)tiles_per_bh * kBN;

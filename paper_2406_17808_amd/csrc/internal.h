@@ -69,6 +69,7 @@ struct Seg {
     int len;
     int qvar;     // which rotated copy of the queries to use
     int chunk;    // 1: the chunk's own keys (causal), 0: cached rows
+    int pad;      // packed tiles: the first tile starts this many rows (0 .. 63) before the segment
 };
 
 struct SegList {

@@ -50,12 +50,13 @@ constexpr float kBoundLog2 = 90.f;    // exponents proven to stay this close to 
 
 // Iterates over the 64-key tiles of all segments.  All fields are workgroup-uniform.
 struct TileIter {
-    int si, t0, len;
+    int si, t0, len;   // t0: first key of the tile inside the segment, negative where the tile starts before it
     Seg sg;
     __device__ void load(const SegList& sl, int wg_imax)
     {
         sg = sl.s[si];
         len = sg.chunk ? min(sg.len, wg_imax + 1) : sg.len;   // chunk keys after the last row are never visible
+        t0 = -sg.pad;
     }
     __device__ bool valid(const SegList& sl) const { return si < sl.n; }
     __device__ void first(const SegList& sl, int wg_imax)
@@ -67,7 +68,7 @@ struct TileIter {
     {
         t0 += kBN;
         if (t0 >= len) {
-            ++si; t0 = 0;
+            ++si;
             if (valid(sl)) load(sl, wg_imax);
         }
     }

@@ -144,21 +144,24 @@ void plan_update(const Geom& g, HostState& st, int Q, UpdatePlan& plan)
 // physical order (the wrapped part of a ring before its oldest part): attention does not care
 // in which order it meets the keys, and a full cache then always reads front to back.  The
 // wrapped part of a full ring is listed as [0, o) and [o, xi), o = xi mod 64, which fixes the
-// place of every 64-row tile of the ring (see PackedLayout).
-void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, SegList& out)
+// place of every 64-row tile of the ring (see PackedLayout, also for the other cut).
+// Fixed tiles, xi the first row of one: rows of the oldest part in front of the extra cut (0: nothing to cut).
+static int cut_of(int cap, int xi) { return std::min(32, (cap - xi) / 2); }
+
+void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, SegList& out, bool fixed)
 {
     out.n = 0;
     out.n_qvar = 0;
     const int n = st.n_cached(g);
     out.n_cached = n;
-    auto add = [&](int start, int len, int delta, int chunk) {
+    auto add = [&](int start, int len, int delta, int chunk, int pad = 0) {
         if (len <= 0) return;
         const int rot0 = n - delta;
         int v = -1;
         for (int i = 0; i < out.n_qvar; ++i) if (out.qrot0[i] == rot0) v = i;
         if (v < 0) { v = out.n_qvar++; out.qrot0[v] = rot0; }
         Seg& s = out.s[out.n++];
-        s.start = start; s.len = len; s.qvar = v; s.chunk = chunk;
+        s.start = start; s.len = len; s.qvar = v; s.chunk = chunk; s.pad = pad;
     };
     add(0, st.sink_fill, 0, 0);
     int rank = st.sink_fill;                         // cache index of the oldest item of the cascade
@@ -167,6 +170,14 @@ void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, 
         if (cnt < cap) {
             add(base, cnt, rank - base, 0);
         } else {
+            if (fixed) {
+                const int o = xi % 64, cut = o ? 0 : cut_of(cap, xi), oldest = rank - (base + xi);
+                add(base, xi, rank + (cap - xi) - base, 0);
+                add(base + xi, cut, oldest, 0);
+                add(base + xi + cut, cap - xi - cut, oldest, 0, o + cut);
+                rank += cnt;
+                continue;
+            }
             const int o = with_chunk ? xi % 64 : 0, wrapped = rank + (cap - xi) - base;
             add(base, o, wrapped, 0);                                 // wrapped part: ring [0, xi), in two pieces (packed tiles only)
             add(base + o, xi - o, wrapped, 0);
@@ -194,8 +205,9 @@ void plan_insert(const Geom& g, const UpdatePlan& plan, DecodeInsert& out)
     }
 }
 
-void packed_layout(const Geom& g, const HostState& st, PackedLayout& out)
+void packed_layout(const Geom& g, const HostState& st, PackedLayout& out, bool fixed)
 {
+    out.fixed = fixed;
     out.full = st.sink_fill == g.n_sink;
     int tiles = (g.n_sink + 63) / 64;
     for (int c = g.N - 1; c >= 0; --c) {             // physical order: the last cascade first
@@ -203,7 +215,7 @@ void packed_layout(const Geom& g, const HostState& st, PackedLayout& out)
         const int o = st.xi[c] % 64;
         out.off[c] = o;
         out.tile0[c] = tiles;
-        tiles += (o > 0 ? 1 : 0) + (g.cap[c] - o + 63) / 64;
+        tiles += fixed ? 1 + (g.cap[c] + 63) / 64 : (o > 0 ? 1 : 0) + (g.cap[c] - o + 63) / 64;
     }
     out.cache_tiles = tiles;
 }
@@ -212,6 +224,73 @@ bool same_offsets(const Geom& g, const PackedLayout& a, const PackedLayout& b)
 {
     for (int c = 0; c < g.N; ++c) if (a.off[c] != b.off[c]) return false;
     return true;
+}
+
+// Packing everything costs a read and a write of all cached rows (16K slots 31 us, 64K 100).  The cut by offset
+// has no tile more than it needs and keeps its tiles when a chunk moves every ring by whole tiles; any other
+// chunk changes the offsets and starts with fixed tiles, which stay in use until something else
+// (a decode step, an update that was not followed) makes the copies invalid.  The cut does not depend on whether the
+// copies can be kept at all: contexts that share them follow the same rule, and get the same sums.
+void plan_packing(const Geom& g, const HostState& st, int Q, const PackedCopies& pc, SegList& sl, PackedLayout& lay, TileRuns& runs)
+{
+    packed_layout(g, st, lay, false);
+    bool partial = false;
+    if (lay.full) {
+        bool possible = pc.may_fix;      // (a last row that begins a tile cannot be cut)
+        for (int c = 0; c < g.N; ++c) possible = possible && (st.xi[c] % 64 != 0 || cut_of(g.cap[c], st.xi[c]) > 0);
+        if (pc.valid && !pc.lay.fixed && same_offsets(g, lay, pc.lay)) partial = true;
+        else if (possible) {
+            bool fixed = pc.valid && pc.lay.fixed;
+            partial = fixed;
+            if (!fixed) {
+                HostState next = st;
+                UpdatePlan pl;
+                PackedLayout after;
+                plan_update(g, next, Q, pl);
+                packed_layout(g, next, after, false);
+                fixed = !same_offsets(g, lay, after);
+            }
+            if (fixed) packed_layout(g, st, lay, true);
+        }
+    }
+    build_segments(g, st, true, Q, sl, lay.fixed);
+    const int chunk_tiles = (Q + 63) / 64;
+    if (partial && pc.own && pc.reuse) {
+        runs = pc.stale;
+        if (add_tile_run(runs, lay.cache_tiles, chunk_tiles)) return;
+    }
+    int tiles = 0;
+    for (int i = 0; i < sl.n; ++i) tiles += (sl.s[i].len + sl.s[i].pad + 63) / 64;
+    runs.n = 0;
+    runs.total = 0;
+    add_tile_run(runs, 0, tiles);
+}
+
+void packed_after_update(const Geom& g, const PackedLayout& lay, const HostState& before, const HostState& after, const UpdatePlan& pl, PackedCopies& pc)
+{
+    pc.valid = false;
+    if (!lay.full) return;
+    pc.lay = lay;
+    pc.stale.n = 0;
+    pc.stale.total = 0;
+    pc.valid = true;
+    if (!lay.fixed) {
+        pc.valid = add_touched_tiles(g, lay, pl, pc.stale);
+        return;
+    }
+    for (int c = 0; c < pl.N && pl.c[c].M > 0; ++c) {
+        const CascStep& cs = pl.c[c];
+        const int xi = before.xi[c], tiles = 1 + (cs.cap + 63) / 64;
+        if (cs.J + cs.pre == 0) continue;
+        // from the first row written to the tile the ring head now stands in, second listing included; a ring
+        // that starts over, or whose newest item is its last row, is packed anew
+        int first = 0, last = tiles - 1;
+        if (!(xi + cs.J >= cs.cap || (cs.pre && xi == 0))) {
+            first = (xi - cs.pre) / 64;
+            last = std::min(last, after.xi[c] / 64 + 1);
+        }
+        pc.valid = pc.valid && add_tile_run(pc.stale, lay.tile0[c] + first, last - first + 1);
+    }
 }
 
 static int tile_of_slot(const Geom& g, const PackedLayout& lay, int slot)

@@ -48,21 +48,41 @@ void plan_update(const Geom& g, HostState& st, int Q, UpdatePlan& plan);
 void plan_insert(const Geom& g, const UpdatePlan& plan, DecodeInsert& out);
 
 // Runs of physical rows that share one query rotation, for the state BEFORE a chunk of Q tokens.
-// with_chunk: append the segment of the chunk's own keys.
-void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, SegList& out);
+// with_chunk: append the segment of the chunk's own keys.  fixed: cut for the fixed tiles of PackedLayout.
+void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, SegList& out, bool fixed = false);
 
-// Where the 64-row tiles of the packed K / V copies sit when every ring is full.  build_segments
-// lists a full ring as [0, o), [o, xi), [xi, cap) with o = xi mod 64, so ring rows o + 64k ..
-// o + 64k + 63 always form tile (o > 0) + k of the ring whatever xi is: as long as no o changes,
-// a tile keeps its place and its content from chunk to chunk until one of its rows is written.
+// Where the 64-row tiles of the packed K / V copies sit when every ring is full.  Two ways to cut a ring:
+//   by offset  build_segments lists it as [0, o), [o, xi), [xi, cap) with o = xi mod 64, so ring rows o + 64k ..
+//              o + 64k + 63 always form tile (o > 0) + k of the ring whatever xi is: as long as no o changes, a
+//              tile keeps its place and its content from chunk to chunk until one of its rows is written;
+//   fixed      tiles start at ring rows 64k whatever xi is, and the one xi stands in is listed twice, for the
+//              wrapped part and for the oldest part: rows before xi are in tile k, later ones in tile k + 1.  (Where
+//              xi is the first row of a tile, the oldest part is cut once more inside that tile, so that
+//              the ring has the same number of tiles.)  As xi moves on, tiles change place only where
+//              rows were written, and all of a ring's once it starts over.
 struct PackedLayout {
     bool full;                    // sinks and every ring are full
+    bool fixed;
     int off[kMaxCascades];        // o of every ring
     int tile0[kMaxCascades];      // first tile of every ring
     int cache_tiles;              // tiles of all cached rows; the chunk's tiles follow
 };
-void packed_layout(const Geom& g, const HostState& st, PackedLayout& out);
+void packed_layout(const Geom& g, const HostState& st, PackedLayout& out, bool fixed);
 bool same_offsets(const Geom& g, const PackedLayout& a, const PackedLayout& b);
+
+// What the packed copies hold from call to call, and what a chunk has to pack.
+struct PackedCopies {
+    bool own = true;              // the copies belong to one context (if not, another layer overwrites them: everything is packed)
+    bool reuse = true;            // tiles that are still valid are not packed again
+    bool may_fix = true;          // fixed tiles may be used (single-pass scores depend on the order of visits: not there)
+    bool valid = false;           // they hold every cache tile where `lay` puts it, except those named by `stale`
+    PackedLayout lay;
+    TileRuns stale;
+};
+// The segments of a chunk of Q tokens, the layout of its tiles, and the tiles to pack.
+void plan_packing(const Geom& g, const HostState& st, int Q, const PackedCopies& pc, SegList& sl, PackedLayout& lay, TileRuns& runs);
+// After the chunk's update (plan pl, from `before` to `after`): the copies hold `lay` except what it wrote.
+void packed_after_update(const Geom& g, const PackedLayout& lay, const HostState& before, const HostState& after, const UpdatePlan& pl, PackedCopies& pc);
 
 // The physical slots an update may write (ring positions opened, and the resident item the
 // first offers compete with), as runs [lo, hi) of slots inside one ring or the sinks; returns the

@@ -128,6 +128,13 @@ def test_tiny_f32_free_running(oracle_mod):
          sizes=[96, 96, 96], chunks=[64, 100, 256, 33, 256, 1, 64], max_chunk=256, attn_splits=16),
     dict(name="bf16_big_tiles_sixteen_splits", dtype=B.CASCADE_BF16, d=128, Hq=2, Hkv=1, batch=1, n_sink=64,
          sizes=[256, 256, 256, 256], chunks=[256] * 5 + [60], max_chunk=256, beta=0.99, attn_splits=16),
+    # full rings whose heads leave the tile grid: tiles of fixed rows, the one under a ring head listed twice, rings that
+    # start over, heads on the first row of a tile; then chunks of whole tiles, and one row block per workgroup
+    dict(name="bf16_fixed_tiles", dtype=B.CASCADE_BF16, d=128, Hq=4, Hkv=2, batch=1, n_sink=4,
+         sizes=[128, 100, 96], chunks=[256] * 4 + [60] * 5 + [16] * 6 + [33, 1, 100, 256, 16, 16], max_chunk=256, pack_reuse=1,
+         model=(2.0 ** -7, 2.0 ** -12)),
+    dict(name="bf16_fixed_tiles_d64_no_sinks_unsplit", dtype=B.CASCADE_BF16, d=64, Hq=4, Hkv=1, batch=2, n_sink=0,
+         sizes=[320, 65], chunks=[512] * 2 + [96] * 9 + [32] * 6 + [500], max_chunk=512, attn_splits=1, pack_reuse=1, beta=0.99),
 ], ids=lambda c: c["name"])
 def test_prefill_one_step_ahead(oracle_mod, case, monkeypatch):
     from gpu_harness import ParityRun

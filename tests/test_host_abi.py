@@ -223,3 +223,22 @@ def test_update_writes_stay_in_predicted_runs(lib, seed):
     cfg = _cfg(n_sink=n_sink, cascade_sizes=sizes, accept_period=periods, max_chunk=256, token_selection=1 - seed % 4 // 3)
     sim = B.cascade_simulate_structure(cfg, chunks, scores)   # raises on any error code
     assert sim.count == min(sum(chunks), n_sink + sum(sizes)) or sim.count <= n_sink + sum(sizes)
+
+
+@pytest.mark.parametrize("seed", range(24))
+def test_packed_tiles_hold_the_rows_of_their_segments(seed):
+    """Which tiles of the packed K / V copies a chunk packs again is decided from the structure alone.  The replay
+    packs token numbers in their place and fails if a cached row is not where the attention kernel reads
+    it: ring sizes on and off the tile grid, with and without sinks, rings that start over, chunks of any length."""
+    rng = np.random.default_rng(seed)
+    n = int(rng.integers(1, 5))
+    sizes = [int(rng.choice([1, 2, 33, 64, 65, 97, 128, 192, 250, 320])) for _ in range(n)]
+    max_chunk = int(rng.choice([1, 7, 16, 64, 100, 256]))
+    cfg = B.make_config(batch=1, n_q_heads=1, n_kv_heads=1, head_dim=64, dtype=B.CASCADE_BF16, n_sink=int(rng.choice([0, 3, 64])),
+                        cascade_sizes=sizes, ema_beta=0.9, rope_base=10000.0, max_chunk=max_chunk)
+    left, chunks = min(max(sizes) * 2 ** n + 700, 5000), []
+    while left > 0:
+        chunks.append(int(max_chunk if rng.random() < 0.7 else rng.integers(1, max_chunk + 1)))
+        left -= chunks[-1]
+    sim = B.cascade_simulate_structure(cfg, chunks, rng.random(sum(chunks)).astype(np.float32))   # raises on any error code
+    assert int(sim.n_seen) == sum(chunks)
