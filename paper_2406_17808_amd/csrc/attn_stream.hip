@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     // when that exceeds kRescaleLog2 (the probabilities then stay below 2^kRescaleLog2, and most
     // tiles skip the rescaling of O), and turn S^T into probabilities.  FIRST: S^T is absolute
     // and m_run not set yet (the first tile of a workgroup).
-    auto softmax_tile = [&](const TileIter& it, bool first, auto interior, int step) {
+    auto softmax_tile = [&](const TileIter<!SP>& it, bool first, auto interior, int step) {
         if (!SP && !decltype(interior)::value && it.t0 < 0) {   // the tile starts before its segment
             const int lo = -it.t0 - half * 4;
 #pragma unroll
@@ -487,15 +487,15 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
         }
         if (SP) column_weights(step);
     };
-    auto wave_active = [&](const TileIter& it) { return !(it.sg.chunk && it.t0 > wave_imax); };
+    auto wave_active = [&](const TileIter<!SP>& it) { return !(it.sg.chunk && it.t0 > wave_imax); };
 
     // In iteration t, tile t is multiplied with V, tile t+1 with Q; the copies of V of tile t+2
     // and of K of tile t+3 are issued.  Only the softmax needs to know which segment a tile is from.
     int NT = 0;   // tiles this workgroup visits: chunk keys after its last row are never visible
-    for (int i = 0; i < sl.n; ++i) NT += ((sl.s[i].chunk ? min(sl.s[i].len, wg_imax + 1) : sl.s[i].len) + sl.s[i].pad + kBN - 1) / kBN;
+    for (int i = 0; i < sl.n; ++i) NT += ((sl.s[i].chunk ? min(sl.s[i].len, wg_imax + 1) : sl.s[i].len) + (SP ? 0 : sl.s[i].pad) + kBN - 1) / kBN;
     if (SP) inv_steps = 1.f / (float)NT;
     int tile_first = 0;                  // SPLIT: first tile of this workgroup's range
-    TileIter it1;
+    TileIter<!SP> it1;
     it1.first(sl, wg_imax);
     if (!it1.valid(sl)) return;          // cannot happen: the chunk itself is always a segment
     // this lane's row of the partial results
@@ -658,7 +658,7 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
         // same copies.
         if (q_var == it1.sg.qvar) {
             int k = min((it1.len - it1.t0 - 1) / kBN, NT - 4 - n0);
-            if (it1.t0 < 0) k = 0;
+            if (!SP && it1.t0 < 0) k = 0;
             if (it1.sg.chunk) k = min(k, (wave_imin + 1 - it1.t0) / kBN);   // chunk tiles every row of the wave sees whole
             for (; k > 0; --k) {
                 lap(0);

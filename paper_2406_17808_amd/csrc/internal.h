@@ -68,8 +68,8 @@ struct Seg {
     int start;    // first physical slot (cache) or first chunk index (chunk segment)
     int len;
     int qvar;     // which rotated copy of the queries to use
-    int chunk;    // 1: the chunk's own keys (causal), 0: cached rows
-    int pad;      // packed tiles: the first tile starts this many rows (0 .. 63) before the segment
+    int16_t chunk;   // 1: the chunk's own keys (causal), 0: cached rows
+    int16_t pad;     // packed tiles: the first tile starts this many rows (0 .. 63) before the segment
 };
 
 struct SegList {

@@ -49,14 +49,15 @@ constexpr float kRescaleLog2 = 8.f;   // the running maximum is only raised when
 constexpr float kBoundLog2 = 90.f;    // exponents proven to stay this close to the running maximum need no tracking (2^90 x 2^17 keys < 2^127)
 
 // Iterates over the 64-key tiles of all segments.  All fields are workgroup-uniform.
-struct TileIter {
+// PADDED: segments may start inside their first tile (never those of single-pass chunks).
+template <bool PADDED> struct TileIter {
     int si, t0, len;   // t0: first key of the tile inside the segment, negative where the tile starts before it
     Seg sg;
     __device__ void load(const SegList& sl, int wg_imax)
     {
         sg = sl.s[si];
         len = sg.chunk ? min(sg.len, wg_imax + 1) : sg.len;   // chunk keys after the last row are never visible
-        t0 = -sg.pad;
+        t0 = PADDED ? -sg.pad : 0;
     }
     __device__ bool valid(const SegList& sl) const { return si < sl.n; }
     __device__ void first(const SegList& sl, int wg_imax)

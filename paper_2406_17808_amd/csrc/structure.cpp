@@ -161,7 +161,7 @@ void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, 
         for (int i = 0; i < out.n_qvar; ++i) if (out.qrot0[i] == rot0) v = i;
         if (v < 0) { v = out.n_qvar++; out.qrot0[v] = rot0; }
         Seg& s = out.s[out.n++];
-        s.start = start; s.len = len; s.qvar = v; s.chunk = chunk; s.pad = pad;
+        s.start = start; s.len = len; s.qvar = v; s.chunk = (int16_t)chunk; s.pad = (int16_t)pad;
     };
     add(0, st.sink_fill, 0, 0);
     int rank = st.sink_fill;                         // cache index of the oldest item of the cascade
