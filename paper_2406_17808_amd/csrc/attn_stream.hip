@@ -52,7 +52,7 @@ template <int D> struct Swz {
 
 constexpr int kPackThreads = 256;
 
-__host__ __device__ inline int seg_tiles(const Seg& s) { return (s.len + s.pad + kBN - 1) / kBN; }
+__host__ __device__ inline int seg_tiles(const SegList& sl, int i) { return (sl.s[i].len + sl.pad[i] + kBN - 1) / kBN; }
 
 // Tile n of the packed K and V copies of one (batch, KV head): 64 rows of a segment (rows past
 // its end become zeros); K with its chunks swizzled, V transposed through LDS.  Chunk rows come from the
@@ -83,13 +83,13 @@ __global__ __launch_bounds__(kPackThreads) void kv_pack_kernel(Geom g, SegList s
     const int n = runs.first[run] + (kth - runs.ahead[run]);
     int si = 0, first = 0;
     for (; si < sl.n; ++si) {
-        const int nt = seg_tiles(sl.s[si]);
+        const int nt = seg_tiles(sl, si);
         if (n < first + nt) break;
         first += nt;
     }
     if (si >= sl.n) return;   // cannot happen: the runs name tiles of the segment list
     const Seg sg = sl.s[si];
-    const int t0 = (n - first) * kBN - sg.pad, rows = min(kBN, sg.len - t0);   // (t0 < 0: rows before the segment become zeros, too)
+    const int t0 = (n - first) * kBN - sl.pad[si], rows = min(kBN, sg.len - t0);   // (t0 < 0: rows before the segment become zeros, too)
     // a chunk row is one of Hkv rows of a token
     const size_t row0 = sg.chunk ? ((size_t)(bh / g.Hkv) * Q + t0) * g.Hkv + bh % g.Hkv
                                  : ((size_t)bh * g.slots + (sg.start + t0));   // (a padded segment starts at least pad rows into its ring)
@@ -492,7 +492,7 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     // In iteration t, tile t is multiplied with V, tile t+1 with Q; the copies of V of tile t+2
     // and of K of tile t+3 are issued.  Only the softmax needs to know which segment a tile is from.
     int NT = 0;   // tiles this workgroup visits: chunk keys after its last row are never visible
-    for (int i = 0; i < sl.n; ++i) NT += ((sl.s[i].chunk ? min(sl.s[i].len, wg_imax + 1) : sl.s[i].len) + (SP ? 0 : sl.s[i].pad) + kBN - 1) / kBN;
+    for (int i = 0; i < sl.n; ++i) NT += ((sl.s[i].chunk ? min(sl.s[i].len, wg_imax + 1) : sl.s[i].len) + (SP ? 0 : sl.pad[i]) + kBN - 1) / kBN;
     if (SP) inv_steps = 1.f / (float)NT;
     int tile_first = 0;                  // SPLIT: first tile of this workgroup's range
     TileIter<!SP> it1;
@@ -770,7 +770,7 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
 static int packed_tiles(const SegList& sl)
 {
     int n = 0;
-    for (int i = 0; i < sl.n; ++i) n += seg_tiles(sl.s[i]);
+    for (int i = 0; i < sl.n; ++i) n += seg_tiles(sl, i);
     return n;
 }
 
@@ -865,7 +865,7 @@ __global__ __launch_bounds__(kSpmHeads * kBN) void single_pass_merge_kernel(Geom
     const int n = blockIdx.x, bh = blockIdx.y, x = threadIdx.x % kBN, grp = threadIdx.x / kBN;
     int si = 0, first = 0;
     for (; si < sl.n; ++si) {
-        const int nt = seg_tiles(sl.s[si]);
+        const int nt = (sl.s[si].len + kBN - 1) / kBN;
         if (n < first + nt) break;
         first += nt;
     }

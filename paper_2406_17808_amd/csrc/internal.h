@@ -68,8 +68,7 @@ struct Seg {
     int start;    // first physical slot (cache) or first chunk index (chunk segment)
     int len;
     int qvar;     // which rotated copy of the queries to use
-    int16_t chunk;   // 1: the chunk's own keys (causal), 0: cached rows
-    int16_t pad;     // packed tiles: the first tile starts this many rows (0 .. 63) before the segment
+    int chunk;    // 1: the chunk's own keys (causal), 0: cached rows
 };
 
 struct SegList {
@@ -78,6 +77,7 @@ struct SegList {
     int n_cached;          // cached rows before the chunk = positional index of chunk token 0
     int qrot0[kMaxQueryRotations];   // rotation index of chunk row 0 for query copy v (row i uses qrot0 + i)
     Seg s[kMaxSegments];
+    int pad[kMaxSegments];           // packed tiles: the first tile of a segment starts this many rows (0 .. 63) before it
 };
 
 // ------------------------------------------------------------------ structure of one cache update

@@ -57,7 +57,7 @@ template <bool PADDED> struct TileIter {
     {
         sg = sl.s[si];
         len = sg.chunk ? min(sg.len, wg_imax + 1) : sg.len;   // chunk keys after the last row are never visible
-        t0 = PADDED ? -sg.pad : 0;
+        t0 = PADDED ? -sl.pad[si] : 0;
     }
     __device__ bool valid(const SegList& sl) const { return si < sl.n; }
     __device__ void first(const SegList& sl, int wg_imax)

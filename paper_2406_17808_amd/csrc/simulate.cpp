@@ -31,7 +31,7 @@ static bool check_packing(const Geom& g, const HostState& st, int Q, const Packe
     for (int i = 0; i < sl.n; ++i) {
         const Seg& sg = sl.s[i];
         if (!sg.chunk) rows += sg.len;
-        for (int t0 = -sg.pad; t0 < sg.len; t0 += 64, ++n) {
+        for (int t0 = -sl.pad[i]; t0 < sg.len; t0 += 64, ++n) {
             if ((int)packed.size() <= n) packed.resize(n + 1, std::vector<int32_t>(64, -2));
             bool pack = false;
             for (int r = 0; r < runs.n; ++r) pack = pack || (n >= runs.first[r] && n < runs.first[r] + (r + 1 < runs.n ? runs.ahead[r + 1] : runs.total) - runs.ahead[r]);

@@ -160,8 +160,9 @@ void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, 
         int v = -1;
         for (int i = 0; i < out.n_qvar; ++i) if (out.qrot0[i] == rot0) v = i;
         if (v < 0) { v = out.n_qvar++; out.qrot0[v] = rot0; }
+        out.pad[out.n] = pad;
         Seg& s = out.s[out.n++];
-        s.start = start; s.len = len; s.qvar = v; s.chunk = (int16_t)chunk; s.pad = (int16_t)pad;
+        s.start = start; s.len = len; s.qvar = v; s.chunk = chunk;
     };
     add(0, st.sink_fill, 0, 0);
     int rank = st.sink_fill;                         // cache index of the oldest item of the cascade
@@ -260,7 +261,7 @@ void plan_packing(const Geom& g, const HostState& st, int Q, const PackedCopies&
         if (add_tile_run(runs, lay.cache_tiles, chunk_tiles)) return;
     }
     int tiles = 0;
-    for (int i = 0; i < sl.n; ++i) tiles += (sl.s[i].len + sl.s[i].pad + 63) / 64;
+    for (int i = 0; i < sl.n; ++i) tiles += (sl.s[i].len + sl.pad[i] + 63) / 64;
     runs.n = 0;
     runs.total = 0;
     add_tile_run(runs, 0, tiles);
