@@ -19,8 +19,8 @@
 // SIMD run these blocks in opposite phase, held there by two barriers per tile, so the matrix
 // pipe and the vector ALU of the SIMD work at the same time.
 //
-// A chunk too short to give every compute unit a workgroup is split over the keys as well: up to
-// eight workgroups share the tiles of one row block and write unnormalised partial results,
+// A chunk too short to give every compute unit a workgroup is split over the keys as well: several
+// workgroups (attn_splits) share the tiles of one row block and write unnormalised partial results,
 // which attn_merge_kernel combines (online-softmax merge of Eq. 2's sums).
 #include <stdio.h>
 #include <stdlib.h>
