@@ -5,6 +5,8 @@
 // B[l/16][l%16]; D: column l%16, rows 4*(l/16) .. +3.  Which element of the head dimension a
 // contraction index means is free as long as A and B agree: lane group c = l/16 takes elements
 // c*D/4 + step, so a lane reads D/4 contiguous floats of its row.
+#include <type_traits>
+
 #include "launch.h"
 
 namespace ckv {
@@ -38,6 +40,20 @@ __device__ inline float max_of_groups(float x)   // over lanes l, l^16, l^32, l^
     return fmaxf(x, __shfl_xor(x, 32, 64));
 }
 
+// O^T += V^T P^T for the keys of one tile that a row sees (those before `end`), product by product.
+template <int D>
+__device__ inline void add_visible(const float* __restrict__ vbase, int k0, int end, int n, int c, const float (&p)[4], f32x4_t (&o)[D / 16])
+{
+    for (int x = 0; x < kF32Keys; ++x) {
+        const int j = x & 3;
+        const float px = __shfl(j == 0 ? p[0] : j == 1 ? p[1] : j == 2 ? p[2] : p[3], (x >> 2) * 16 + n, 64);   // key x of this lane's row
+        if (k0 + x >= end) continue;
+        const f32x4_t* v = reinterpret_cast<const f32x4_t*>(vbase + (size_t)(k0 + x) * D + 4 * c);
+#pragma unroll
+        for (int db = 0; db < D / 16; ++db) o[db] += v[4 * db] * px;
+    }
+}
+
 // ------------------------------------------------------------------ attention
 //
 // A workgroup owns 16 (head, token) rows of one KV head; its eight waves take the 16-key tiles in turn,
@@ -45,8 +61,10 @@ __device__ inline float max_of_groups(float x)   // over lanes l, l^16, l^32, l^
 // configuration is for, are bound by the latency of one wave's tiles, so the keys are spread over waves.
 // S^T = K Q^T leaves query l%16 and keys 4*(l/16) + j in a lane, which is the B operand of step j of
 // O^T = V^T P^T (contraction index c = key 4c + j).  Operands come straight from memory (the caches hold
-// them: 33 KB per tile row at most).  One head, d = 64, 260 slots, chunks of 32: 114 us with one workgroup per
-// row and scalar arithmetic, 11 with this.
+// them: 16 KB of K and V a tile at most).  One head, d = 64, 260 slots, chunks of 32: 114 us with one workgroup per
+// row and scalar arithmetic, 11 with this.  Tiles at an edge look for values that are not finite, in a loop of their
+// own: the same call 29.9 -> 30.4 us, 128 rows of 32 heads against 1K slots 129.3 either way; the test in the one loop cost the
+// large launches 6 %.
 constexpr int kF32Waves = 8;
 
 template <int D>
@@ -63,7 +81,8 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(Geom g, SegLis
     const int r0 = blockIdx.x * 16, GQ = g.G * Q;
     const int r = min(r0 + n, GQ - 1), h = hk * g.G + r / Q, i = r % Q;      // this lane's query
     const int r_last = min(r0 + 15, GQ - 1);
-    const int imax = r0 / Q == r_last / Q ? r_last % Q : Q - 1;              // chunk keys after it are seen by no row here
+    const bool one_head = r0 / Q == r_last / Q;
+    const int imax = one_head ? r_last % Q : Q - 1, imin = one_head ? r0 % Q : 0;   // chunk keys after imax are seen by no row here, those up to imin by all
     const float sc = g.scale * kF32Log2e;
 
     f32x4_t o[DB];
@@ -77,7 +96,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(Geom g, SegLis
         const int len = sg.chunk ? min(sg.len, imax + 1) : sg.len, nt = (len + kF32Keys - 1) / kF32Keys;
         const size_t row0 = sg.chunk ? (size_t)bh * Q : (size_t)bh * g.slots + sg.start;
         const float *kbase = (sg.chunk ? Krc : Kr) + row0 * D, *vbase = (sg.chunk ? Vch : Vc) + row0 * D;
-        for (int t = (wave + kF32Waves - first % kF32Waves) % kF32Waves; t < nt; t += kF32Waves) {
+        auto tile = [&](int t, auto edge) {                                  // edge: the end of the segment, or keys of the chunk that some row does not see
             if (sg.qvar != q_var) {
                 q_var = sg.qvar;
                 load_quarter<D>(Qr + ((((size_t)q_var * g.B + b) * g.Hq + h) * Q + i) * D, c, q);
@@ -105,6 +124,27 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(Geom g, SegLis
                 for (int db = 0; db < DB; ++db) o[db] *= alpha;
             }
             const float mr = m == -INFINITY ? 0.f : m;                       // a row that has seen no key yet
+            if (decltype(edge)::value) {
+                // a key that a row does not see has probability zero, but zero times an infinite or undefined value (a
+                // later token's, or the last row's standing in for rows that do not exist) is not zero
+                float not_finite = 0.f;
+#pragma unroll
+                for (int db = 0; db < DB; ++db) not_finite += v[3][db] * 0.f;                // (lanes that hold the last row's)
+                if (sg.chunk) {
+#pragma unroll
+                    for (int db = 0; db < DB; ++db) not_finite += (v[0][db] * 0.f + v[1][db] * 0.f) + v[2][db] * 0.f;
+                }
+                if (__any(not_finite != 0.f)) {
+                    float p[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        p[j] = exp2f(s[j] - mr);
+                        lsum += p[j];
+                    }
+                    add_visible<D>(vbase, k0, sg.chunk ? min(len, i + 1) : len, n, c, p, o);
+                    return;
+                }
+            }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const float p = exp2f(s[j] - mr);
@@ -112,7 +152,11 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(Geom g, SegLis
 #pragma unroll
                 for (int db = 0; db < DB; ++db) o[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[j][db], p, o[db], 0, 0, 0);
             }
-        }
+        };
+        const int whole = (sg.chunk ? imin + 1 : len) / kF32Keys;            // tiles every row here sees whole
+        int t = (wave + kF32Waves - first % kF32Waves) % kF32Waves;
+        for (; t < whole; t += kF32Waves) tile(t, std::false_type());
+        for (; t < nt; t += kF32Waves) tile(t, std::true_type());
         first += nt;
     }
     lsum += __shfl_xor(lsum, 16, 64);

@@ -624,3 +624,56 @@ def test_f32_matrix_kernels(oracle_mod, d, G, Hkv, sizes, reduce_mean, chunks):
         assert rep.replay_exact, step
         assert rep.out_err <= out_tol and rep.score_err <= score_tol, (step, rep)
     run.close()
+
+
+@pytest.mark.parametrize("d,G,at,value", [(64, 1, 5, float("inf")), (64, 3, 16, float("nan")), (128, 2, 30, float("-inf")), (128, 1, 39, float("nan"))])
+def test_f32_chunk_rows_do_not_see_later_values(d, G, at, value):
+    """An infinite or undefined value in a token of the chunk reaches the rows that see the token and no other: the rows
+    before it come out as if it were finite (products in another order: 16 keys a tile, 2^-24 each), the scores bit for bit."""
+    import torch
+    from paper_2406_17808_amd.cache import CascadeKVCache
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(d + at)
+    n = 40                                                 # two whole tiles of 16 keys and a part of one
+    q, k, v = (torch.randn((1, n, h, d), generator=gen, device="cuda:0") for h in (2 * G, 2, 2))
+    odd = v.clone()
+    odd[:, at, 1, 3] = value
+    outs, states = [], []
+    for x in (v, odd):
+        cfg = B.make_config(batch=1, n_q_heads=2 * G, n_kv_heads=2, head_dim=d, dtype=B.CASCADE_F32, n_sink=3, cascade_sizes=[50, 30],
+                            ema_beta=0.9, rope_base=10000.0, max_chunk=64)
+        c = CascadeKVCache(cfg)
+        c.prefill_chunk(q.flip(1).contiguous(), k.flip(1).contiguous(), v.flip(1).contiguous())
+        outs.append(c.prefill_chunk(q, k, x))
+        states.append(c.read_state())
+        c.close()
+    clean, got = outs
+    assert torch.isfinite(clean).all()
+    sees = torch.zeros_like(clean, dtype=torch.bool)
+    sees[:, at:, G:, 3] = True                             # the rows, heads and the element that the value belongs to
+    assert not torch.isfinite(got[sees]).any()
+    assert torch.isfinite(got[~sees]).all()
+    assert (got[~sees] - clean[~sees]).abs().max() <= 40 * 2.0 ** -24 * v.abs().max()
+    assert np.array_equal(states[0].mu, states[1].mu) and np.array_equal(states[0].ids, states[1].ids)
+
+
+@pytest.mark.parametrize("d,G,value", [(64, 2, float("inf")), (128, 1, float("-inf"))])
+def test_f32_chunk_keeps_an_infinite_value(d, G, value):
+    """An infinite value in a cached row that every row sees with a probability above zero gives that infinity, also where the
+    row is the last of a run that ends inside a tile of keys (the sinks: three rows of 16)."""
+    import torch
+    from paper_2406_17808_amd.cache import CascadeKVCache
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(d)
+    q, k, v = (torch.randn((1, 20, h, d), generator=gen, device="cuda:0") for h in (2 * G, 2, 2))
+    cfg = B.make_config(batch=1, n_q_heads=2 * G, n_kv_heads=2, head_dim=d, dtype=B.CASCADE_F32, n_sink=3, cascade_sizes=[50, 30],
+                        ema_beta=0.9, rope_base=10000.0, max_chunk=64)
+    c = CascadeKVCache(cfg)
+    odd = v.clone()
+    odd[:, 2, 1, 3] = value                                # the last sink
+    c.prefill_chunk(q, k, odd)
+    out = c.prefill_chunk(q, k, v)
+    c.close()
+    assert (out[:, :, G:, 3] == value).all()
+    out[:, :, G:, 3] = 0.0
+    assert torch.isfinite(out).all()
