@@ -505,7 +505,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_attend_f32_kernel(
                 const float alpha = alpha_s[hh];
 #pragma unroll
                 for (int x = 0; x < EPL; ++x) o[hh][x] *= alpha;
-                if (have) {
+                if (have && r0 < t.nvalid) {       // (a lane group without rows would add zero times the last row)
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const float p = ps[(grp / 4) * kDecRows + r0 + u][hh];

@@ -677,3 +677,25 @@ def test_f32_chunk_keeps_an_infinite_value(d, G, value):
     assert (out[:, :, G:, 3] == value).all()
     out[:, :, G:, 3] = 0.0
     assert torch.isfinite(out).all()
+
+
+@pytest.mark.parametrize("d,G,rows", [(64, 2, 8), (128, 1, 8), (128, 5, 40)])
+def test_f32_decode_keeps_an_infinite_value(d, G, rows):
+    """A decode step, too: the last sink, in runs of whole lane groups (eight rows) that are not whole tiles (32)."""
+    import torch
+    from paper_2406_17808_amd.cache import CascadeKVCache
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(d + rows)
+    cfg = B.make_config(batch=1, n_q_heads=2 * G, n_kv_heads=2, head_dim=d, dtype=B.CASCADE_F32, n_sink=rows, cascade_sizes=[64],
+                        ema_beta=0.9, rope_base=10000.0, max_chunk=64)
+    c = CascadeKVCache(cfg)
+    q, k, v = (torch.randn((1, rows, h, d), generator=gen, device="cuda:0") for h in (2 * G, 2, 2))
+    v[:, rows - 1, 1, 3] = float("inf")
+    c.prefill_chunk(q, k, v)
+    for _ in range(3):
+        q, k, v = (torch.randn((1, h, d), generator=gen, device="cuda:0") for h in (2 * G, 2, 2))
+        out = c.decode_step(q, k, v)
+        assert (out[:, G:, 3] == float("inf")).all()
+        out[:, G:, 3] = 0.0
+        assert torch.isfinite(out).all()
+    c.close()
