@@ -18,34 +18,6 @@ static int fail(int code, const std::string& msg)
     return code;
 }
 
-// Packs what plan_packing names (the token ids of the rows in place of the rows) and looks whether every cached row
-// is then where the attention kernel reads it.
-static bool check_packing(const Geom& g, const HostState& st, int Q, const PackedCopies& pc, const std::vector<int32_t>& ids,
-                          std::vector<std::vector<int32_t>>& packed, PackedLayout& lay)
-{
-    SegList sl;
-    TileRuns runs;
-    plan_packing(g, st, Q, pc, sl, lay, runs);
-    int n = 0, rows = 0;
-    bool ok = true;
-    for (int i = 0; i < sl.n; ++i) {
-        const Seg& sg = sl.s[i];
-        if (!sg.chunk) rows += sg.len;
-        for (int t0 = -sl.pad[i]; t0 < sg.len; t0 += 64, ++n) {
-            if ((int)packed.size() <= n) packed.resize(n + 1, std::vector<int32_t>(64, -2));
-            bool pack = false;
-            for (int r = 0; r < runs.n; ++r) pack = pack || (n >= runs.first[r] && n < runs.first[r] + (r + 1 < runs.n ? runs.ahead[r + 1] : runs.total) - runs.ahead[r]);
-            ok = ok && (pack || !sg.chunk);
-            for (int x = 0; x < 64 && !sg.chunk; ++x) {
-                const bool in = t0 + x >= 0 && t0 + x < sg.len;
-                if (pack) packed[n][x] = in ? ids[sg.start + t0 + x] : -2;
-                ok = ok && (!in || packed[n][x] == ids[sg.start + t0 + x]);
-            }
-        }
-    }
-    return ok && rows == st.n_cached(g) && (!lay.full || n == lay.cache_tiles + (Q + 63) / 64);
-}
-
 // Fill, ring heads and counters after feeding chunks of the given sizes to an empty cache; with
 // scores also the membership.  Pure host arithmetic (no device is touched).  The membership is
 // computed by the same segment / eviction routines the device kernels run (plan_core.h), one
@@ -65,19 +37,12 @@ extern "C" int cascade_simulate_structure(const cascade_config* cfg, const int32
     std::vector<int64_t> swaps(g.N, 0);
     if (host_scores) { mu.assign(g.slots, 0.f); ids.assign(g.slots, -1); }
     size_t consumed = 0;
-    PackedCopies pc;                               // the packed copies of a context of its own, and the token in every row
-    std::vector<std::vector<int32_t>> packed;
     for (int ci = 0; ci < n_chunks; ++ci) {
         const int Q = chunk_sizes[ci];
         if (Q < 1) return fail(CASCADE_E_BAD_ARG, "cascade_simulate_structure: chunk sizes must be >= 1");
-        const HostState before = st;
         UpdatePlan pl;
         plan_update(g, st, Q, pl);
         if (!host_scores) continue;
-        PackedLayout lay;
-        if (!check_packing(g, before, Q, pc, ids, packed, lay))
-            return fail(CASCADE_E_INTERNAL, "cascade_simulate_structure: a packed tile does not hold the rows of its segment");
-        packed_after_update(g, lay, before, st, pl, pc);
         const float* muc = host_scores + consumed;
         consumed += Q;
         int run_lo[kMaxTileRuns], run_hi[kMaxTileRuns];

@@ -1,0 +1,160 @@
+// Test infrastructure: rules of the library's host side (structure.cpp) driven directly, without a device.
+//   packing SEED   which tiles of the packed K / V copies a chunk packs again: a replay of a random geometry that
+//                  packs token numbers in the place of rows.  Exit code 0 = every row is where it is read.
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <vector>
+
+#include "../../paper_2406_17808_amd/csrc/structure.h"
+
+using namespace ckv;
+
+static uint64_t rng_state;
+static uint32_t rnd(uint32_t n)   // splitmix64, value in [0, n)
+{
+    uint64_t z = (rng_state += 0x9E3779B97F4A7C15ull);
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    z ^= z >> 31;
+    return (uint32_t)(z % n);
+}
+
+// ------------------------------------------------------------------ packed tiles
+
+// Alg. 2 token by token on physical slots; whether an offer beats the newest item is drawn.
+struct Rows {
+    std::vector<int> id;
+    std::vector<int> count, head;
+    int sinks = 0;
+    long t = 0, seen = 0;
+    void insert(const Geom& g, const cascade_config& cfg)
+    {
+        int x = (int)seen++;
+        if (sinks < g.n_sink) { id[sinks++] = x; return; }
+        const long now = t++;
+        for (int c = 0; c < g.N; ++c) {
+            const int base = g.base[c], cap = g.cap[c];
+            if (count[c] < cap) { id[base + count[c]++] = x; return; }
+            const int period = cfg.accept_period[0] ? cfg.accept_period[c] : 1 << c;
+            if (now % period) {
+                if (rnd(2)) id[base + (head[c] + cap - 1) % cap] = x;
+                return;
+            }
+            std::swap(x, id[base + head[c]]);
+            head[c] = (head[c] + 1) % cap;
+        }
+    }
+};
+
+// Packs what plan_packing names and looks whether every cached row is then where the attention kernel reads it.
+static const char* pack(const Geom& g, const HostState& st, int Q, const PackedCopies& pc, const std::vector<int>& id,
+                        std::vector<std::vector<int>>& packed, PackedLayout& lay, int max_tiles, long* tiles_packed)
+{
+    SegList sl;
+    TileRuns runs;
+    plan_packing(g, st, Q, pc, sl, lay, runs);
+    int n = 0, rows = 0, total = 0;
+    const char* wrong = nullptr;
+    for (int i = 0; i < sl.n; ++i) {
+        const Seg& sg = sl.s[i];
+        if (!sg.chunk) rows += sg.len;
+        if (sl.pad[i] < 0 || sl.pad[i] > 63 || sl.pad[i] > sg.start) wrong = "padding reaches outside the ring";
+        for (int t0 = -sl.pad[i]; t0 < sg.len; t0 += 64, ++n) {
+            if ((int)packed.size() <= n) packed.resize(n + 1, std::vector<int>(64, -2));
+            bool now = false;
+            for (int r = 0; r < runs.n; ++r) {
+                const int end = (r + 1 < runs.n ? runs.ahead[r + 1] : runs.total) - runs.ahead[r];
+                now = now || (n >= runs.first[r] && n < runs.first[r] + end);
+            }
+            total += now;
+            if (sg.chunk && !now) wrong = "a tile of the chunk is not packed";
+            for (int x = 0; x < 64 && !sg.chunk; ++x) {
+                const bool in = t0 + x >= 0 && t0 + x < sg.len;
+                if (now) packed[n][x] = in ? id[sg.start + t0 + x] : -2;
+                if (in && packed[n][x] != id[sg.start + t0 + x]) wrong = "a packed tile does not hold the rows of its segment";
+            }
+        }
+    }
+    for (int r = 0; r < runs.n; ++r)
+        if (runs.first[r] < 0 || runs.first[r] + (r + 1 < runs.n ? runs.ahead[r + 1] : runs.total) - runs.ahead[r] > n) wrong = "a run names tiles that do not exist";
+    if (total > runs.total) wrong = "the runs hold fewer tiles than they name";
+    if (rows != st.n_cached(g)) wrong = "the segments do not hold all cached rows";
+    if (lay.full && n != lay.cache_tiles + (Q + 63) / 64) wrong = "the segments do not have the tiles of the layout";
+    if (n > max_tiles) wrong = "more tiles than the workspace holds";
+    *tiles_packed += runs.total;
+    return wrong;
+}
+
+// kind 0: a context of its own; 1: copies shared between layers; 2: single-pass scores; 3: decode steps in between
+static int packing_case(int seed, int kind, long* tiles_packed)
+{
+    rng_state = 0x1234567ull * (uint64_t)(seed + 1);
+    static const int ring[] = {1, 2, 33, 64, 65, 97, 128, 192, 250, 320}, chunk[] = {1, 7, 16, 64, 100, 256}, sinks[] = {0, 3, 64};
+    cascade_config cfg;
+    memset(&cfg, 0, sizeof(cfg));
+    cfg.batch = 1; cfg.n_q_heads = 1; cfg.n_kv_heads = 1; cfg.head_dim = 64; cfg.dtype = CASCADE_BF16;
+    cfg.n_sink = sinks[rnd(3)];
+    cfg.n_cascades = 1 + (int)rnd(4);
+    cfg.max_chunk = chunk[rnd(6)];
+    cfg.ema_beta = 0.9f; cfg.rope_base = 10000.f;
+    const bool periods = rnd(4) == 0;
+    int largest = 0;
+    for (int c = 0; c < cfg.n_cascades; ++c) {
+        cfg.cascade_sizes[c] = ring[rnd(10)];
+        cfg.accept_period[c] = periods ? (c == 0 ? 1 : 1 + (int)rnd(5)) : 0;
+        largest = cfg.cascade_sizes[c] > largest ? cfg.cascade_sizes[c] : largest;
+    }
+    std::string why;
+    if (check_config(&cfg, why) != CASCADE_OK) { fprintf(stderr, "seed %d: %s\n", seed, why.c_str()); return 1; }
+    Geom g;
+    make_geom(&cfg, g);
+    Rows rows;
+    rows.id.assign(g.slots, -1);
+    rows.count.assign(g.N, 0);
+    rows.head.assign(g.N, 0);
+    HostState st;
+    PackedCopies pc;
+    pc.own = kind != 1;
+    pc.may_fix = kind != 2;
+    std::vector<std::vector<int>> packed;
+    const int max_tiles = (g.slots + cfg.max_chunk) / 64 + kMaxSegments;
+    int left = (largest << g.N) + 700;
+    if (left > 6000) left = 6000;
+    for (int step = 0; left > 0; ++step) {
+        const int Q = rnd(10) < 7 ? cfg.max_chunk : 1 + (int)rnd(cfg.max_chunk);
+        left -= Q;
+        UpdatePlan pl;
+        if (kind == 3 && rnd(3) == 0)
+            for (int i = 1 + (int)rnd(3); i > 0; --i) {      // what a decode step does to the copies and the cache
+                pc.valid = false;
+                rows.insert(g, cfg);
+                plan_update(g, st, 1, pl);
+            }
+        if (!pc.own) for (auto& tile : packed) tile.assign(64, -3);   // another layer has packed its own
+        PackedLayout lay;
+        const HostState before = st;
+        const char* wrong = pack(g, st, Q, pc, rows.id, packed, lay, max_tiles, tiles_packed);
+        if (wrong) { fprintf(stderr, "seed %d kind %d step %d: %s\n", seed, kind, step, wrong); return 1; }
+        for (int i = 0; i < Q; ++i) rows.insert(g, cfg);
+        plan_update(g, st, Q, pl);
+        packed_after_update(g, lay, before, st, pl, pc);
+        for (int c = 0; c < g.N; ++c)
+            if (st.count[c] != rows.count[c] || (st.count[c] == g.cap[c] && st.xi[c] != rows.head[c])) { fprintf(stderr, "seed %d step %d: ring %d differs\n", seed, step, c); return 1; }
+    }
+    return 0;
+}
+
+int main(int argc, char** argv)
+{
+    if (argc == 3 && !strcmp(argv[1], "packing")) {
+        int bad = 0;
+        long tiles[4] = {0, 0, 0, 0};
+        for (int kind = 0; kind < 4; ++kind) bad += packing_case(atoi(argv[2]), kind, &tiles[kind]);
+        printf("tiles packed: own %ld shared %ld single-pass %ld with decode steps %ld\n", tiles[0], tiles[1], tiles[2], tiles[3]);
+        return bad ? 1 : 0;
+    }
+    fprintf(stderr, "usage: host_rules packing SEED\n");
+    return 2;
+}
