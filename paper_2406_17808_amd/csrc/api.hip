@@ -550,7 +550,7 @@ extern "C" int cascade_decode_step(cascade_ctx* ctx, const void* dev_q, const vo
     build_segments(g, ctx->st, false, 1, sl);
     ctx->packed.valid = false;   // the step writes cache rows the packed copies of the prefill path do not follow
     ctx->last_single_pass = false;
-    const int n_splits = decode_split_count(g, ctx->buf, decode_tiles(sl));
+    const int n_splits = decode_split_count(g.B * g.Hkv, ctx->buf.dec_splits, decode_tiles(sl));
     {
         Timed t0(ctx, CASCADE_K_DECODE_QK, s);
         launch_decode_attend(g, ctx->dtype, ctx->buf, sl, n_splits, dev_q, dev_k, s);

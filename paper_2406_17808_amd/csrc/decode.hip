@@ -791,27 +791,6 @@ int decode_tiles(const SegList& sl)
     return n;
 }
 
-// Splits of a step: as many as make the busiest compute unit finish first.  A CU holds one workgroup of
-// the MFMA kernel (its ring fills the LDS at d = 128), whose four waves share the split's tiles; a
-// workgroup costs about as much as two rounds of its waves besides (first copies, queries, epilogue).  Where the
-// waves' shares differ by a tile, half a tile is charged (4K slots, 8 KV heads: 32 splits 17.3 us, 17 splits 18.0;
-// 8K slots: 32 or 22 splits 20.2, 16 21.7, 64 23.8; 64 x 16K slots: 4 splits 111, 8 113, 32 127).
-// Where even then a wave has hundreds of tiles, more rounds even out the CUs (256 x 65K slots: 8 splits 1656, 1 split 1676).
-int decode_split_count(const Geom& g, const DevBuffers& b, int n_tiles)
-{
-    const int bh = g.B * g.Hkv;
-    int best = 1;
-    float best_cost = -1.f;
-    for (int s = 1; s <= b.dec_splits; ++s) {
-        const long rounds = (bh * (long)s + 255) / 256, tiles = (n_tiles + s - 1) / s;
-        const float share = (float)n_tiles / (float)(s * kDecWaves);
-        const float cost = (float)rounds * (0.5f * ((float)((tiles + kDecWaves - 1) / kDecWaves) + share) + 2.f);
-        if (best_cost < 0.f || cost < best_cost) { best = s; best_cost = cost; }
-    }
-    while (2 * best <= b.dec_splits && n_tiles / (2 * best * kDecWaves) >= 64) best *= 2;
-    return best;
-}
-
 #define CKV_DECODE_G(fn, T, D)                                 \
     switch (decode_logit_heads(g)) {                           \
         case 1: fn(T, D, 1); break;                            \

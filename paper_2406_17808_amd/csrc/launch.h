@@ -107,7 +107,6 @@ void launch_score_mfma(const Geom& g, const DevBuffers& b, const SegList& sl, in
 
 // decode
 int decode_max_tiles(const Geom& g);     // logits are kept for at most this many tiles of 32 rows per (batch, KV head)
-int decode_split_count(const Geom& g, const DevBuffers& b, int n_tiles);
 int decode_tiles(const SegList& sl);
 void launch_decode_attend(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, int n_splits, const void* q, const void* k,
                           hipStream_t s);

@@ -206,6 +206,34 @@ void plan_insert(const Geom& g, const UpdatePlan& plan, DecodeInsert& out)
     }
 }
 
+// Splits of a decode step: as many as make the busiest compute unit finish first.  A CU holds one workgroup of
+// the bf16 kernel at d = 128 (its ring fills the LDS), whose four waves share the split's tiles; a
+// workgroup costs about as much as two rounds of its waves besides (first copies, queries, epilogue).  Where the
+// waves' shares differ by a tile, half a tile is charged (4K slots, 8 KV heads: 32 splits 17.3 us, 17 splits 18.0;
+// 8K slots: 32 or 22 splits 20.2, 16 21.7, 64 23.8; 64 x 16K slots: 4 splits 111, 8 113, 32 127).
+// Where even then a wave has hundreds of tiles, more rounds even out the CUs (256 x 65K slots: 8 splits 1656, 1 split 1676).
+// For a given number of rounds the cost falls with every split, so only the most splits of each number of
+// rounds are looked at: nine at most, 0.05 us of host time a step (all of up to 2048 split counts: 9.7).
+int decode_split_count(int pairs, int most, int n_tiles)
+{
+    constexpr int kWaves = 4, kCus = 256;
+    if (n_tiles == 0) return 1;
+    int best = 1;
+    float best_cost = -1.f;
+    int s = 0;
+    for (long rounds = (pairs + kCus - 1) / kCus; s < most; ++rounds) {
+        const int fit = (int)std::min((long)most, kCus * rounds / pairs);
+        if (fit <= s) continue;
+        s = fit;
+        const long used = (pairs * (long)s + kCus - 1) / kCus, tiles = (n_tiles + s - 1) / s;
+        const float share = (float)n_tiles / (float)(s * kWaves);
+        const float cost = (float)used * (0.5f * ((float)((tiles + kWaves - 1) / kWaves) + share) + 2.f);
+        if (best_cost < 0.f || cost < best_cost) { best = s; best_cost = cost; }
+    }
+    while (2 * best <= most && n_tiles / (2 * best * kWaves) >= 64) best *= 2;
+    return best;
+}
+
 void packed_layout(const Geom& g, const HostState& st, PackedLayout& out, bool fixed)
 {
     out.fixed = fixed;

@@ -47,6 +47,9 @@ void plan_update(const Geom& g, HostState& st, int Q, UpdatePlan& plan);
 // The plan of one token (plan_update with Q = 1) as a chain of slots.
 void plan_insert(const Geom& g, const UpdatePlan& plan, DecodeInsert& out);
 
+// Workgroups that share the cached rows (n_tiles tiles of 32) of one sequence and KV head in a decode step, at most `most`.
+int decode_split_count(int pairs, int most, int n_tiles);
+
 // Runs of physical rows that share one query rotation, for the state BEFORE a chunk of Q tokens.
 // with_chunk: append the segment of the chunk's own keys.  fixed: cut for the fixed tiles of PackedLayout.
 void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, SegList& out, bool fixed = false);

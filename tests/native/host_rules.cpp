@@ -1,10 +1,12 @@
 // Test infrastructure: rules of the library's host side (structure.cpp) driven directly, without a device.
 //   packing SEED   which tiles of the packed K / V copies a chunk packs again: a replay of a random geometry that
 //                  packs token numbers in the place of rows.  Exit code 0 = every row is where it is read.
+//   splits         the split count of a decode step against the same costs looked at for every count, and its time.
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
 
+#include <chrono>
 #include <vector>
 
 #include "../../paper_2406_17808_amd/csrc/structure.h"
@@ -146,8 +148,49 @@ static int packing_case(int seed, int kind, long* tiles_packed)
     return 0;
 }
 
+// ------------------------------------------------------------------ splits of a decode step
+
+static int best_of_all_splits(int pairs, int most, int n_tiles)
+{
+    int best = 1;
+    float best_cost = -1.f;
+    for (int s = 1; s <= most; ++s) {
+        const long rounds = (pairs * (long)s + 255) / 256, tiles = (n_tiles + s - 1) / s;
+        const float cost = (float)rounds * (0.5f * ((float)((tiles + 3) / 4) + (float)n_tiles / (float)(s * 4)) + 2.f);
+        if (best_cost < 0.f || cost < best_cost) { best = s; best_cost = cost; }
+    }
+    while (2 * best <= most && n_tiles / (8 * best) >= 64) best *= 2;
+    return best;
+}
+
+static int splits_case()
+{
+    long n = 0, wrong = 0;
+    for (int pairs = 1; pairs <= 2600; pairs = pairs < 300 ? pairs + 1 : pairs + 37)
+        for (int slots = 1; slots < 1 << 21; slots = slots < 2000 ? slots + 331 : slots * 5 / 3 + 7) {
+            int most = (2048 + pairs - 1) / pairs;         // the counts a workspace is laid out for
+            if (most > (slots + 127) / 128) most = (slots + 127) / 128;
+            for (int i = 0; i < 12; ++i, ++n) {
+                const int tiles = i < 3 ? i : (int)((long)(slots / 32 + 9) * i / 11), got = decode_split_count(pairs, most, tiles);
+                if (got != best_of_all_splits(pairs, most, tiles) && ++wrong <= 5)
+                    fprintf(stderr, "%d pairs, %d splits at most, %d tiles: %d\n", pairs, most, tiles, got);
+            }
+        }
+    double best = 1e9;
+    for (int r = 0; r < 9; ++r) {
+        long sum = 0;
+        const auto t = std::chrono::steady_clock::now();
+        for (int i = 0; i < 200; ++i) sum += decode_split_count(1, 2048, 8192 + i);
+        const double us = std::chrono::duration<double>(std::chrono::steady_clock::now() - t).count() * 1e6 / 200;
+        if (sum && us < best) best = us;
+    }
+    printf("%ld of %ld counts wrong, %.3f us a call\n", wrong, n, best);
+    return wrong || best > 2.0 ? 1 : 0;       // a call of the whole step takes about ten
+}
+
 int main(int argc, char** argv)
 {
+    if (argc == 2 && !strcmp(argv[1], "splits")) return splits_case();
     if (argc == 3 && !strcmp(argv[1], "packing")) {
         int bad = 0;
         long tiles[4] = {0, 0, 0, 0};
@@ -155,6 +198,6 @@ int main(int argc, char** argv)
         printf("tiles packed: own %ld shared %ld single-pass %ld with decode steps %ld\n", tiles[0], tiles[1], tiles[2], tiles[3]);
         return bad ? 1 : 0;
     }
-    fprintf(stderr, "usage: host_rules packing SEED\n");
+    fprintf(stderr, "usage: host_rules packing SEED | splits\n");
     return 2;
 }

@@ -251,6 +251,12 @@ def test_packed_tiles_hold_the_rows_of_their_segments(host_rules, seed):
     assert res.returncode == 0, res.stderr
 
 
+def test_decode_split_count(host_rules):
+    """Few split counts of a decode step are looked at; they give what looking at all of them gives, in little host time."""
+    res = subprocess.run([host_rules, "splits"], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
 def test_simulated_chunks_cost_their_tokens_not_the_cache(lib):
     """cascade_simulate_structure replays every token once: a chunk costs what its tokens cost, however many rows are cached."""
     def seconds(size):
