@@ -605,6 +605,47 @@ def test_decode_in_one_finish_launch(dtype, d, G, sizes):
         c.close()
 
 
+def _decode_after_fill(cfg, fill, steps, seqs=None, steps_before=0):
+    """Decode steps compared with the oracle after `steps_before` compared steps from the empty cache and `fill` tokens
+    that are not compared."""
+    import torch
+    from gpu_harness import ParityRun
+    run = ParityRun(cfg, one_step_ahead=True, seqs=seqs)
+    rng = np.random.default_rng(cfg.head_dim + cfg.n_q_heads)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(cfg.head_dim)
+    tol_out, tol_score = _tolerances(cfg)
+    for step in range(steps_before + steps):
+        if step == steps_before:
+            for n in fill:
+                run.advance_gpu_only(*(torch.randn((cfg.batch, n, h, cfg.head_dim), generator=gen, device="cuda:0").to(run.gpu.torch_dtype)
+                                       for h in (cfg.n_q_heads, cfg.n_kv_heads, cfg.n_kv_heads)))
+            run.sync_oracle_from_gpu()
+        rep = run.step(*_inputs(rng, cfg, 1), decode=True)
+        assert rep.replay_exact, step
+        assert rep.out_err <= tol_out and rep.score_err <= tol_score, (step, rep)
+    run.close()
+
+
+@pytest.mark.parametrize("d,G", [(64, 2), (64, 8), (128, 1), (128, 8)])
+def test_decode_waves_refill_their_ring(oracle_mod, d, G):
+    """256 (sequence, KV head) pairs leave one split each: every wave takes six or seven of the 24 to 27 tiles, so the stages of
+    its LDS ring are filled again while copies and stores are in flight; the ring heads stand inside tiles, so the
+    rotation of the queries changes on the way."""
+    cfg = B.make_config(batch=64, n_q_heads=4 * G, n_kv_heads=4, head_dim=d, dtype=B.CASCADE_BF16, n_sink=5, cascade_sizes=[301, 250, 129],
+                        ema_beta=0.9, rope_base=10000.0, max_chunk=512, keep_update_scores=1)
+    _decode_after_fill(cfg, [512, 512, 512], 5, seqs=[0, 41])
+
+
+@pytest.mark.parametrize("dtype,d,G", [(B.CASCADE_BF16, 128, 4), (B.CASCADE_BF16, 64, 8), (B.CASCADE_F32, 64, 2)])
+def test_decode_of_one_head_takes_many_splits(oracle_mod, dtype, d, G):
+    """One KV head with 16K slots: 129 splits (fp32: 65), more than are loaded ahead of the combined maxima and than one wave
+    combines in one round; from the empty cache, where most splits have no rows."""
+    cfg = B.make_config(batch=1, n_q_heads=G, n_kv_heads=1, head_dim=d, dtype=dtype, n_sink=5, cascade_sizes=[16400],
+                        ema_beta=0.9, rope_base=10000.0, max_chunk=4096, keep_update_scores=1)
+    _decode_after_fill(cfg, [4096] * 5, 4, steps_before=3)
+
+
 @pytest.mark.parametrize("d,G,Hkv,sizes,reduce_mean,chunks", [
     (64, 1, 1, [64] * 4, False, [32] * 12), (64, 3, 2, [7, 33], False, [1, 15, 16, 17, 48, 5, 31]),
     (128, 5, 1, [150], True, [64, 2, 63, 33]), (128, 8, 2, [20, 1, 3], False, [16, 40, 1, 64]),
