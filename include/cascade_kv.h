@@ -287,8 +287,8 @@ int cascade_profile_end(cascade_ctx* ctx, cascade_profile* out);
  * GPU; the published peaks of another say little about it): number of compute units and clocks
  * from the device properties, a streaming read of dev_buffer (GB/s; all workgroups sweeping one
  * front), the same with a contiguous region per workgroup (the pattern of the decode kernels),
- * that again while one byte is written for every sixteen read (the logits of the decode step's
- * first pass against the keys it reads; GB/s of the bytes READ), that launch and a plain read
+ * that again while one byte is written for every sixteen read (a decode step writes one byte of
+ * logits for every 32 of keys and values; GB/s of the bytes READ), that launch and a plain read
  * alternating (two_pass_read_gb_s), a copy of its first half onto
  * its second (GB/s of bytes read plus bytes written), and a loop of nothing but
  * v_mfma_f32_32x32x16_bf16 on register operands, two waves per SIMD (TFLOP/s).  dev_buffer: at least
@@ -307,7 +307,7 @@ typedef struct cascade_ceilings {
     double read_regions_gb_s;
     double read_with_stores_gb_s;
     double two_pass_read_gb_s;  /* a read with stores on one half of the buffer followed by a plain read of the other half
-                                   (the two passes of a decode step as traffic alone), pairs back to back: bytes read by both
+                                   (what separate passes over keys and values would cost as traffic alone), pairs back to back: bytes read by both
                                    per second (what the first launch wrote may still be on its way to memory while the
                                    second reads). */
 } cascade_ceilings;

@@ -488,7 +488,7 @@ extern "C" int cascade_prefill_chunk(cascade_ctx* ctx, const void* dev_q, const 
         Timed t(ctx, CASCADE_K_PREP, s);
         // bf16: rotated query copies are written for the rows the exact score pass reads (none with single-pass
         // scores); the attention kernel reads them where they cover the chunk, and otherwise rotates its queries itself
-        if (!ctx->mfma) launch_prep(g, ctx->dtype, ctx->buf, sl, Q, qscale, 0, dev_q, dev_k, dev_v, s);
+        if (!ctx->mfma) launch_prep(g, ctx->dtype, ctx->buf, sl, Q, qscale, dev_q, dev_k, dev_v, s);
         else {
             if (lay.full && packed_tiles_of(sl) != lay.cache_tiles + (Q + 63) / 64)
                 return fail(ctx, CASCADE_E_INTERNAL, "cascade_prefill_chunk: the segment list does not have the tiles of the packed layout");

@@ -289,7 +289,7 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     // index, so the query turns by (own cache index) - (cache index - slot index) of the segment,
     // sl.qrot0[variant] + qi.  The fragment of step ks holds elements 16 ks + 8 half .. + 7, whose
     // rotary partners (element + D/2) are the fragment of step ks + KS/2 of the same lane.  The
-    // arithmetic is that of prep_kernel (scale first, then the rotation, then one rounding), which
+    // arithmetic is that of rotate_queries (scale first, then the rotation, then one rounding), which
     // writes the same values for the rows the score kernel reads.
     Frag qf[KS];
     float qn2 = 0.f;      // this lane's half of the squared norm of its (scaled) query, summed by the first load_q
@@ -910,7 +910,7 @@ __global__ __launch_bounds__(kSpmHeads * kBN) void single_pass_merge_kernel(Geom
 }
 
 // Workgroups per (row block, KV head) so that a small launch still fills the chip: none for 129
-// workgroups or more.  Beyond kMaxAttnSplits only where each has kMinSplitTiles tiles left (a workgroup costs about
+// workgroups or more.  Beyond kFewAttnSplits only where each has kMinSplitTiles tiles left (a workgroup costs about
 // as much as that many tiles besides: its queries, the first copies, the partial result).  us a call
 // with 8 splits and with up to 32: 64 tokens against 16K slots 122 -> 104, 16 against 64K 332 -> 250, 128 against 4K 74.5 -> 73.
 int attn_splits(const Geom& g, int Q, int forced, int tiles)
@@ -918,7 +918,7 @@ int attn_splits(const Geom& g, int Q, int forced, int tiles)
     constexpr int BM = kSWaves * 32;
     const int wgs = ((g.G * Q + BM - 1) / BM) * g.B * g.Hkv;
     const int most = 256 / wgs;             // the partial results are sized for 256 workgroups
-    int n = forced > 0 ? forced : std::max(kMaxAttnSplits, tiles / kMinSplitTiles);
+    int n = forced > 0 ? forced : std::max(kFewAttnSplits, tiles / kMinSplitTiles);
     if (n > most) n = most;
     return n < 1 ? 1 : n;
 }
@@ -951,7 +951,7 @@ void launch_attn_stream(const Geom& g, const DevBuffers& b, const SegList& sl, i
     const dim3 grid(tiles * g.B * g.Hkv * n_split), block(kSWaves * 64);
     float* part_o = b.attn_part;
     float* part_ml = b.attn_part + (size_t)kAttnPartRows * g.d;
-    // prep_kernel wrote rotated copies of the last tail_rows rows, for the exact score pass
+    // kv_pack_kernel wrote rotated copies of the last tail_rows rows, for the exact score pass
     const bool copies = !single_pass && tail_rows >= Q;
 #define CKV_ATTN(D, DBG, SPLIT, SP, QC, dbg)                                                                                                  \
     hipLaunchKernelGGL((attn_stream_kernel<D, DBG, SPLIT, SP, QC>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q,               \

@@ -130,7 +130,7 @@ void launch_load_state(const Geom& g, int dtype, const DevBuffers& b, const void
 // 1); chunk keys are rotated to their chunk index, chunk values are copied head-major.  A thread takes 8 rotary
 // pairs of one row (two 16-byte pieces for bf16), or of a few query heads (rotate_queries).
 template <typename T>
-__global__ void prep_kernel(Geom g, SegList sl, int Q, float qscale, int q_first_row, int vars, const float2* __restrict__ rope,
+__global__ void prep_kernel(Geom g, SegList sl, int Q, float qscale, int vars, const float2* __restrict__ rope,
                             const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                             T* __restrict__ Qr, T* __restrict__ Krc, T* __restrict__ Vch)
 {
@@ -160,12 +160,12 @@ __global__ void prep_kernel(Geom g, SegList sl, int Q, float qscale, int q_first
         }
         return;
     }
-    rotate_queries<T>(g, sl, Q, qscale, q_first_row, vars, rope, q, Qr, idx - n_kv);
+    rotate_queries<T>(g, sl, Q, qscale, 0, vars, rope, q, Qr, idx - n_kv);
 }
 
 // head dimensions that are not a multiple of 16: one thread per rotary pair
 template <typename T>
-__global__ void prep_pair_kernel(Geom g, SegList sl, int Q, float qscale, int q_first_row, const float2* __restrict__ rope,
+__global__ void prep_pair_kernel(Geom g, SegList sl, int Q, float qscale, const float2* __restrict__ rope,
                                  const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                                  T* __restrict__ Qr, T* __restrict__ Krc, T* __restrict__ Vch)
 {
@@ -180,7 +180,6 @@ __global__ void prep_pair_kernel(Geom g, SegList sl, int Q, float qscale, int q_
     r /= rows_per_tok;
     const int i = (int)(r % Q), b = (int)(r / Q);
     if (row < sl.n_qvar * g.Hq) {
-        if (i < q_first_row) return;
         const int vq = row / g.Hq, h = row % g.Hq;
         const size_t src = (((size_t)b * Q + i) * g.Hq + h) * g.d;
         const size_t dst = ((((size_t)vq * g.B + b) * g.Hq + h) * Q + i) * g.d;
@@ -205,29 +204,29 @@ __global__ void prep_pair_kernel(Geom g, SegList sl, int Q, float qscale, int q_
     }
 }
 
-void launch_prep(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, int Q, float qscale, int q_first_row,
+void launch_prep(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, int Q, float qscale,
                  const void* q, const void* k, const void* v, hipStream_t s)
 {
     const dim3 block(256);
     if (g.d % 16 == 0) {
         int vars;
-        const long n = (long)g.B * Q * 2 * g.Hkv * (g.d / 16) + query_threads(g, sl, Q - q_first_row, &vars);
+        const long n = (long)g.B * Q * 2 * g.Hkv * (g.d / 16) + query_threads(g, sl, Q, &vars);
         const dim3 grid((unsigned)((n + 255) / 256));
         if (dtype == CASCADE_F32)
-            hipLaunchKernelGGL(prep_kernel<float>, grid, block, 0, s, g, sl, Q, qscale, q_first_row, vars, b.rope, (const float*)q, (const float*)k,
+            hipLaunchKernelGGL(prep_kernel<float>, grid, block, 0, s, g, sl, Q, qscale, vars, b.rope, (const float*)q, (const float*)k,
                                (const float*)v, (float*)b.Qr, (float*)b.Krc, (float*)b.Vch);
         else
-            hipLaunchKernelGGL(prep_kernel<bf16_t>, grid, block, 0, s, g, sl, Q, qscale, q_first_row, vars, b.rope, (const bf16_t*)q, (const bf16_t*)k,
+            hipLaunchKernelGGL(prep_kernel<bf16_t>, grid, block, 0, s, g, sl, Q, qscale, vars, b.rope, (const bf16_t*)q, (const bf16_t*)k,
                                (const bf16_t*)v, (bf16_t*)b.Qr, (bf16_t*)b.Krc, (bf16_t*)b.Vch);
         return;
     }
     const long n = (long)g.B * Q * (sl.n_qvar * g.Hq + 2 * g.Hkv) * (g.d / 2);
     const dim3 grid((unsigned)((n + 255) / 256));
     if (dtype == CASCADE_F32)
-        hipLaunchKernelGGL(prep_pair_kernel<float>, grid, block, 0, s, g, sl, Q, qscale, q_first_row, b.rope, (const float*)q, (const float*)k,
+        hipLaunchKernelGGL(prep_pair_kernel<float>, grid, block, 0, s, g, sl, Q, qscale, b.rope, (const float*)q, (const float*)k,
                            (const float*)v, (float*)b.Qr, (float*)b.Krc, (float*)b.Vch);
     else
-        hipLaunchKernelGGL(prep_pair_kernel<bf16_t>, grid, block, 0, s, g, sl, Q, qscale, q_first_row, b.rope, (const bf16_t*)q,
+        hipLaunchKernelGGL(prep_pair_kernel<bf16_t>, grid, block, 0, s, g, sl, Q, qscale, b.rope, (const bf16_t*)q,
                            (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)b.Qr, (bf16_t*)b.Krc, (bf16_t*)b.Vch);
 }
 

@@ -164,9 +164,8 @@ extern "C" int cascade_measure_ceilings(void* dev_buffer, size_t bytes, void* st
         }, &ms);
         if (rc) return ceil_fail(rc, "cascade_measure_ceilings: streaming read with stores");
         out->read_with_stores_gb_s = (double)per_wg16 * wgs_r * 16 / (ms * 1e-3) / 1e9;   // bytes read only
-        // The two passes of a decode step one after the other, as traffic alone: a read with stores (the keys,
-        // the logits written) on one half of the buffer, then a plain read (the values) on the other half,
-        // eight such pairs back to back (what the first launch wrote may still be on its way to memory while the
+        // A launch that reads and stores followed by one that only reads, as traffic alone: the first on one half of
+        // the buffer, the second on the other half, eight such pairs back to back (what the first launch wrote may still be on its way to memory while the
         // second reads).
         const size_t half16 = ((full / 2) / 16) & ~(size_t)255;
         const size_t per_a16 = ((half16 * 15 / 16) / wgs_r) & ~(size_t)4095;

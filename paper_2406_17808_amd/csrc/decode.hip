@@ -395,7 +395,11 @@ __global__ __launch_bounds__(kDecThreads, 1) void decode_attend_kernel(
 //
 // The same split results in fp32 arithmetic.  Sixteen lanes share a row, every lane owns D/16 contiguous
 // elements of it and all heads of the group; a workgroup takes four tiles (128 rows) at a time, eight
-// consecutive rows per lane group, all eight loads of K and of V in flight together.
+// consecutive rows per lane group, all eight loads of K and of V in flight together.  Bound by the latency of one
+// round where the cache is small, by the products in the lanes where it is large; from 3 heads a group at d = 128 on a
+// SIMD holds one wave (256 registers).  8 heads of 4K slots, us a step with separate passes over K and V and
+// with this: d = 64, groups of 4 heads 59.2 -> 31.8; d = 128, groups of 1, 4 and 8 42.0 -> 21.9, 78.3 -> 46.8,
+// 131.7 -> 83.5.
 template <int D, int MAXG>
 __global__ __launch_bounds__(kDecThreads) void decode_attend_f32_kernel(
     Geom g, SegList sl, int n_tiles, int n_splits, float qscale, const float* __restrict__ q, const float* __restrict__ k_new,

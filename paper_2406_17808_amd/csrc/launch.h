@@ -7,7 +7,7 @@ namespace ckv {
 
 // A split attention launch has at most 256 workgroups of 256 rows.
 constexpr int kAttnPartRows = 256 * 256;
-constexpr int kMaxAttnSplits = 8;
+constexpr int kFewAttnSplits = 8;    // allowed however few tiles a split is left with
 constexpr int kMinSplitTiles = 8;
 
 // Device memory of one context, carved out of the caller's workspace.
@@ -27,7 +27,7 @@ struct DevBuffers {
     // per-call scratch
     void* Qr;        // [n_qvar_max, B, Hq, max_chunk, d] rotated query copies (bf16 MFMA path: times scale * log2 e)
     void* Krc;       // [B,Hkv,max_chunk,d] chunk keys rotated to their chunk index
-    void* Vch;       // [B,Hkv,max_chunk,d] chunk values, head-major
+    void* Vch;       // [B,Hkv,max_chunk,d] chunk values, head-major (fp32, and the scalar kernels that CASCADE_KV_SCALAR_ATTENTION selects)
     void* Kt;        // [B,Hkv,vt_tiles,64,d] bf16 MFMA path: rotated keys of cache and chunk, tile by tile
     void* Vt;        // [B,Hkv,vt_tiles,d,64] the same for V, every tile transposed
     float* knorm2;   // [B,Hkv,vt_tiles] largest squared key norm of every packed tile
@@ -63,8 +63,7 @@ void launch_wrow_table(float beta, float* wrow, int n, hipStream_t s);
 void launch_fill_i32(int32_t* p, size_t n, int32_t value, hipStream_t s);
 void launch_load_state(const Geom& g, int dtype, const DevBuffers& b, const void* k, const void* v,
                        const float* mu, const int32_t* ids, const int* counts, int total, hipStream_t s);
-// q_first_row: the rotated query copies are written for chunk rows q_first_row .. Q-1 only
-void launch_prep(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, int Q, float qscale, int q_first_row,
+void launch_prep(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, int Q, float qscale,
                  const void* q, const void* k, const void* v, hipStream_t s);
 // homogeneous heads: the scores of the cached rows (and of n_new new tokens) reduced over the KV heads and shared
 void launch_share_scores(const Geom& g, const DevBuffers& b, int n_new, int max_chunk, hipStream_t s);

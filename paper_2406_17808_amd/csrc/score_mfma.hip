@@ -318,7 +318,7 @@ void launch_score_mfma(const Geom& g, const DevBuffers& b, const SegList& sl, in
     };
     const int BH = g.B * g.Hkv, stages = (tail_rows + kStRows - 1) / kStRows;
     const int wide = tiles_of(2 * kScoreKeysPerBlock) * BH;
-    // Every head by itself, in up to 4 or 8 parts of its rows: the launch is then spread evenly over the compute
+    // Every head by itself, and in small launches its rows in parts of at least 8 stages: the launch is then spread evenly over the compute
     // units (640 workgroups on 768 slots leave a third of them with two instead of three), for a second launch of
     // 5 to 6 us.  us a call, whole against in parts: 4096 rows against 16K slots 1796 -> 1727, against 2K slots
     // 756 -> 644 in one part a head and 622 in four; 512 rows against 8K slots

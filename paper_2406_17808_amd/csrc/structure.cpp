@@ -137,6 +137,9 @@ void plan_update(const Geom& g, HostState& st, int Q, UpdatePlan& plan)
     st.sink_fill += plan.n_to_sink;
 }
 
+// Fixed tiles, xi the first row of one: rows of the oldest part in front of the extra cut (0: nothing to cut).
+static int cut_of(int cap, int xi) { return std::min(32, (cap - xi) / 2); }
+
 // Cache order is sinks, last cascade oldest..newest, ..., first cascade (Section 3.1
 // "Positional Encoding": the index inside the cache).  Stored keys are rotated to their
 // physical slot index, so within a run where (cache index - slot index) is constant the
@@ -145,9 +148,6 @@ void plan_update(const Geom& g, HostState& st, int Q, UpdatePlan& plan)
 // in which order it meets the keys, and a full cache then always reads front to back.  The
 // wrapped part of a full ring is listed as [0, o) and [o, xi), o = xi mod 64, which fixes the
 // place of every 64-row tile of the ring (see PackedLayout, also for the other cut).
-// Fixed tiles, xi the first row of one: rows of the oldest part in front of the extra cut (0: nothing to cut).
-static int cut_of(int cap, int xi) { return std::min(32, (cap - xi) / 2); }
-
 void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, SegList& out, bool fixed)
 {
     out.n = 0;
@@ -211,6 +211,10 @@ void plan_insert(const Geom& g, const UpdatePlan& plan, DecodeInsert& out)
 // workgroup costs about as much as two rounds of its waves besides (first copies, queries, epilogue).  Where the
 // waves' shares differ by a tile, half a tile is charged (4K slots, 8 KV heads: 32 splits 17.3 us, 17 splits 18.0;
 // 8K slots: 32 or 22 splits 20.2, 16 21.7, 64 23.8; 64 x 16K slots: 4 splits 111, 8 113, 32 127).
+// The same rule serves the other kernels, of which a CU holds more.  bf16 at d = 64, the rule's count / the best of 13
+// others: 8 heads of 16K slots 17.3 / 17.1 us, 32 of 8K 28.6 / 26.9, 128 of 4K 38.3 / 37.8.  fp32 (four tiles at a time):
+// d = 128, 8 heads of 4K 46.7 / 46.4, 64 of 4K 117 / 126, 256 of 2K 267 / 280; d = 64, 8 of 4K 31.9 / 31.7, but 64 of 4K
+// 84.6 / 58.3 (11 splits).
 // Where even then a wave has hundreds of tiles, more rounds even out the CUs (256 x 65K slots: 8 splits 1656, 1 split 1676).
 // For a given number of rounds the cost falls with every split, so only the most splits of each number of
 // rounds are looked at: nine at most, 0.05 us of host time a step (all of up to 2048 split counts: 9.7).
@@ -256,11 +260,12 @@ bool same_offsets(const Geom& g, const PackedLayout& a, const PackedLayout& b)
 }
 
 // Packing everything costs a read and a write of all cached rows (16K slots 31 us, 64K 100; us a call with and without
-// fixed tiles: 16 tokens against 64K slots 254 -> 169, 64 against 16K 103 -> 86).  The cut by offset
+// fixed tiles, one context: 16 tokens against 64K slots 254 -> 169, 64 against 16K 103 -> 86).  The cut by offset
 // has no tile more than it needs and keeps its tiles when a chunk moves every ring by whole tiles; any other
 // chunk changes the offsets and starts with fixed tiles, which stay in use until something else
 // (a decode step, an update that was not followed) makes the copies invalid.  The cut does not depend on whether the
-// copies can be kept at all: contexts that share them follow the same rule, and get the same sums.
+// copies can be kept at all: contexts that share them (the layers of one workspace) follow the same rule and get the
+// same sums, but pack everything for every chunk either way.
 void plan_packing(const Geom& g, const HostState& st, int Q, const PackedCopies& pc, SegList& sl, PackedLayout& lay, TileRuns& runs)
 {
     packed_layout(g, st, lay, false);
