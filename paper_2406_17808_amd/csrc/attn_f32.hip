@@ -63,7 +63,7 @@ __device__ inline void add_visible(const float* __restrict__ vbase, int k0, int 
 // O^T = V^T P^T (contraction index c = key 4c + j).  Operands come straight from memory (the caches hold
 // them: 16 KB of K and V a tile at most).  One head, d = 64, 260 slots, chunks of 32: 114 us with one workgroup per
 // row and scalar arithmetic, 11 with this.  Tiles at an edge look for values that are not finite, in a loop of their
-// own: the same call 29.9 -> 30.4 us, 128 rows of 32 heads against 1K slots 129.3 either way; the test in the one loop cost the
+// own: the same call 29.4 -> 30.1 us, 128 rows of 32 heads against 1K slots 129.3 either way; the test in the one loop cost the
 // large launches 6 %.
 constexpr int kF32Waves = 8;
 
