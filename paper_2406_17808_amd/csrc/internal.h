@@ -114,7 +114,21 @@ struct DecodeInsert {
     int n;
     int id0;                        // original index of the token
     int slot[kMaxCascades];
-    int kind[kMaxCascades];
+    int row[kMaxCascades];          // rows in the tiles before the slot's (filled in by the launcher)
+    uint32_t kinds;                 // two bits per entry
+};
+__host__ __device__ inline int insert_kind(const DecodeInsert& ins, int i) { return (int)(ins.kinds >> (2 * i) & 3u); }
+
+// The cached rows of a decode step: runs of physical rows that share one query rotation, cut into tiles of
+// kDecodeTileRows rows run by run (the last tile of a run may be short).
+constexpr int kDecodeTileRows = 32;
+constexpr int kMaxDecodeRuns = 2 * CASCADE_MAX_CASCADES + 1;   // sinks, two per ring
+struct DecodeRuns {
+    int n, n_tiles;
+    int tile0[kMaxDecodeRuns];   // first tile of run i; ascending, INT32_MAX from entry n on
+    int start[kMaxDecodeRuns];   // first slot
+    int len[kMaxDecodeRuns];
+    int rot[kMaxDecodeRuns];     // rotation index of the queries
 };
 
 // A few runs of 64-row tiles (of the packed K / V copies the bf16 attention kernel reads).

@@ -37,6 +37,28 @@ template <> struct Vec8<float> {
     }
 };
 
+// Eight elements as they are in memory: nothing waits for them before they are used.
+typedef __attribute__((ext_vector_type(4))) uint32_t raw_u32x4_t;
+template <typename T> struct Raw8 {
+    raw_u32x4_t lo, hi;                // (hi: fp32 only)
+    __device__ void load(const T* p)
+    {
+        lo = reinterpret_cast<const raw_u32x4_t*>(p)[0];
+        if (sizeof(T) == 4) hi = reinterpret_cast<const raw_u32x4_t*>(p)[1];
+    }
+    __device__ void store(T* p) const
+    {
+        reinterpret_cast<raw_u32x4_t*>(p)[0] = lo;
+        if (sizeof(T) == 4) reinterpret_cast<raw_u32x4_t*>(p)[1] = hi;
+    }
+    __device__ void values(float* o) const
+    {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            o[i] = __uint_as_float(sizeof(T) == 4 ? (i < 4 ? lo[i & 3] : hi[i & 3]) : i & 1 ? lo[i / 2] & 0xFFFF0000u : lo[i / 2] << 16);
+    }
+};
+
 template <typename T>
 __device__ inline void rotate8(const float* x0, const float* x1, const float2* __restrict__ cs, T* d0, T* d1)
 {

@@ -191,9 +191,9 @@ void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, 
 
 void plan_insert(const Geom& g, const UpdatePlan& plan, DecodeInsert& out)
 {
-    out.n = 0;
+    out = DecodeInsert();
     out.id0 = plan.id0;
-    auto add = [&](int kind, int slot) { out.kind[out.n] = kind; out.slot[out.n] = slot; ++out.n; };
+    auto add = [&](int kind, int slot) { out.kinds |= (uint32_t)kind << (2 * out.n); out.slot[out.n] = slot; ++out.n; };
     if (plan.n_to_sink > 0) {
         add(kInsertAppend, plan.sink_fill0);
         return;
@@ -207,20 +207,18 @@ void plan_insert(const Geom& g, const UpdatePlan& plan, DecodeInsert& out)
 }
 
 // Splits of a decode step: as many as make the busiest compute unit finish first.  A CU holds one workgroup of
-// the bf16 kernel at d = 128 (its ring fills the LDS), whose four waves share the split's tiles; a
-// workgroup costs about as much as two rounds of its waves besides (first copies, queries, epilogue).  Where the
-// waves' shares differ by a tile, half a tile is charged (4K slots, 8 KV heads: 32 splits 17.3 us, 17 splits 18.0;
-// 8K slots: 32 or 22 splits 20.2, 16 21.7, 64 23.8; 64 x 16K slots: 4 splits 111, 8 113, 32 127).
-// The same rule serves the other kernels, of which a CU holds more.  bf16 at d = 64, the rule's count / the best of 13
-// others: 8 heads of 16K slots 17.3 / 17.1 us, 32 of 8K 28.6 / 26.9, 128 of 4K 38.3 / 37.8.  fp32 (four tiles at a time):
-// d = 128, 8 heads of 4K 46.7 / 46.4, 64 of 4K 117 / 126, 256 of 2K 267 / 280; d = 64, 8 of 4K 31.9 / 31.7, but 64 of 4K
-// 84.6 / 58.3 (11 splits).
-// Where even then a wave has hundreds of tiles, more rounds even out the CUs (256 x 65K slots: 8 splits 1656, 1 split 1676).
+// the bf16 kernels (their rings fill the LDS); a workgroup costs about as much as two rounds of four tiles besides (first
+// copies, queries, epilogue).  Where the shares differ by a tile, half a tile is charged.  The rule's count / the best of up to 29,
+// us a step: bf16, d = 128, 8 KV heads: 8K slots 13.4 / 12.8 (24 splits), 16K 16.9 / 17.0, 64K 53.1 / 51.9 (24); 16 heads of 8K
+// 17.8 / 18.0; 64 of 16K 104.8 / 104.2; 256 of 8K 221 / 211 (5); d = 64, 8 heads of 16K 13.1 / 12.5, 64 of 16K 61.2 / 59.1.
+// fp32 (four tiles at a time): d = 128, 8 heads of 4K 46.7 / 46.4, 64 of 4K 117 / 126, 256 of 2K 267 / 280; d = 64, 8 of 4K
+// 31.9 / 31.7, but 64 of 4K 84.6 / 58.3 (11 splits).
+// Where even then there are hundreds of tiles for each of four waves, more rounds even out the CUs (256 x 65K slots: 8 splits 1656, 1 split 1676).
 // For a given number of rounds the cost falls with every split, so only the most splits of each number of
 // rounds are looked at: nine at most, 0.05 us of host time a step (all of up to 2048 split counts: 9.7).
 int decode_split_count(int pairs, int most, int n_tiles)
 {
-    constexpr int kWaves = 4, kCus = 256;
+    constexpr int kWaves = 4, kCus = 256;     // (a tile of four waves at a time: fp32; the bf16 kernels have eight)
     if (n_tiles == 0) return 1;
     int best = 1;
     float best_cost = -1.f;

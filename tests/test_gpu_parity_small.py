@@ -629,12 +629,49 @@ def _decode_after_fill(cfg, fill, steps, seqs=None, steps_before=0):
 
 @pytest.mark.parametrize("d,G", [(64, 2), (64, 8), (128, 1), (128, 8)])
 def test_decode_waves_refill_their_ring(oracle_mod, d, G):
-    """256 (sequence, KV head) pairs leave one split each: every wave takes six or seven of the 24 to 27 tiles, so the stages of
+    """256 (sequence, KV head) pairs leave one split each: every wave takes three or four of the 24 to 27 tiles, so the stages of
     its LDS ring are filled again while copies and stores are in flight; the ring heads stand inside tiles, so the
     rotation of the queries changes on the way."""
     cfg = B.make_config(batch=64, n_q_heads=4 * G, n_kv_heads=4, head_dim=d, dtype=B.CASCADE_BF16, n_sink=5, cascade_sizes=[301, 250, 129],
                         ema_beta=0.9, rope_base=10000.0, max_chunk=512, keep_update_scores=1)
     _decode_after_fill(cfg, [512, 512, 512], 5, seqs=[0, 41])
+
+
+@pytest.mark.parametrize("d,G,sizes", [(128, 1, [130, 60]), (128, 4, [130, 60]), (128, 8, [130, 60]), (64, 4, [300, 150])])
+def test_decode_splits_of_one_tile_more_than_stages(oracle_mod, d, G, sizes):
+    """One split for each of 256 pairs, of 8, 9 or 10 tiles at head size 128 and of 16, 17 or 18 at 64 as the ring heads move: as
+    many as the workgroup has LDS stages, one more (which has a stage of its own, except with 8 heads of 128), two more."""
+    cfg = B.make_config(batch=64, n_q_heads=4 * G, n_kv_heads=4, head_dim=d, dtype=B.CASCADE_BF16, n_sink=5, cascade_sizes=sizes,
+                        ema_beta=0.9, rope_base=10000.0, max_chunk=512, keep_update_scores=1)
+    _decode_after_fill(cfg, [512, 512, 8], 25, seqs=[0, 41])
+
+
+@pytest.mark.parametrize("d,G", [(64, 1), (128, 4), (128, 5), (128, 8)])
+def test_decode_of_queries_at_any_address(d, G):
+    """Queries and keys that do not start at a multiple of 16 bytes: the same bits as those that do."""
+    import torch
+    from paper_2406_17808_amd.cache import CascadeKVCache
+    cfg = B.make_config(batch=2, n_q_heads=2 * G, n_kv_heads=2, head_dim=d, dtype=B.CASCADE_BF16, n_sink=4, cascade_sizes=[70, 40],
+                        ema_beta=0.9, rope_base=10000.0, max_chunk=64)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(3)
+    caches = [CascadeKVCache(cfg), CascadeKVCache(cfg)]
+    chunk = [torch.randn((2, 64, h, d), generator=gen, device="cuda:0").to(torch.bfloat16) for h in (2 * G, 2, 2)]
+    for c in caches:
+        for _ in range(3):
+            c.prefill_chunk(*chunk)
+    for _ in range(6):
+        token = [torch.randn((2, h, d), generator=gen, device="cuda:0").to(torch.bfloat16) for h in (2 * G, 2, 2)]
+        moved = []
+        for x in token:
+            buf = torch.empty(x.numel() + 4, dtype=x.dtype, device=x.device)
+            moved.append(buf[4:].view(x.shape).copy_(x))
+            assert moved[-1].data_ptr() % 16 == 8
+        assert torch.equal(caches[0].decode_step(*token), caches[1].decode_step(*moved))
+    a, b = (c.read_state(with_kv=True) for c in caches)
+    assert all(np.array_equal(getattr(a, n), getattr(b, n)) for n in ("ids", "mu", "k", "v"))
+    for c in caches:
+        c.close()
 
 
 @pytest.mark.parametrize("dtype,d,G", [(B.CASCADE_BF16, 128, 4), (B.CASCADE_BF16, 64, 8), (B.CASCADE_F32, 64, 2)])
