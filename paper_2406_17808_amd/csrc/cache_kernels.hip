@@ -621,7 +621,7 @@ static void moves_two_phase(const Geom& g, const DevBuffers& b, const UpdatePlan
 // backwards), so writing the last cascade first keeps every source intact until it has been read.
 bool update_is_direct(const Geom& g, const DevBuffers& b, const UpdatePlan& pl)
 {
-    if (!(g.d % 16 == 0 && b.move_stage) || b.opt_update_staged || !plan_is_direct(pl)) return false;
+    if (!(g.d % 16 == 0 && b.move_stage) || 64 % (g.d / 16) != 0 || b.opt_update_staged || !plan_is_direct(pl)) return false;   // (thread groups inside a wave)
     int total = pl.n_to_sink;
     for (int c = 0; c < pl.N; ++c) {
         if (pl.c[c].M == 0) continue;
