@@ -627,6 +627,20 @@ def _decode_after_fill(cfg, fill, steps, seqs=None, steps_before=0):
     run.close()
 
 
+@pytest.mark.parametrize("d", [48, 80, 96])
+def test_update_with_head_sizes_that_do_not_divide_a_wave(oracle_mod, d):
+    """d / 16 threads move a row: three, five or six of them do not divide a wave, so the offers are not compared inside one."""
+    from gpu_harness import ParityRun
+    cfg = B.make_config(batch=1, n_q_heads=2, n_kv_heads=2, head_dim=d, dtype=B.CASCADE_F32, n_sink=3, cascade_sizes=[96, 96, 96],
+                        ema_beta=0.9, rope_base=10000.0, max_chunk=64, keep_update_scores=1)
+    rng = np.random.default_rng(d)
+    run = ParityRun(cfg, one_step_ahead=True)
+    for step in range(16):
+        rep = run.step(*_inputs(rng, cfg, 64))
+        assert rep.replay_exact, step
+    run.close()
+
+
 @pytest.mark.parametrize("d,G", [(64, 2), (64, 8), (128, 1), (128, 8)])
 def test_decode_waves_refill_their_ring(oracle_mod, d, G):
     """256 (sequence, KV head) pairs leave one split each: every wave takes three or four of the 24 to 27 tiles, so the stages of
