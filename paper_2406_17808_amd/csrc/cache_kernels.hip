@@ -1,5 +1,6 @@
 // Cache maintenance kernels: tables, query/key rotation, the score-dependent part of the
 // cascade update (Alg. 2) and the row moves that carry it out.
+#include "async_copy.h"
 #include "launch.h"
 #include "plan_core.h"
 #include "row_ops.h"
@@ -478,6 +479,163 @@ __global__ void scatter_kernel(Geom g, UpdatePlan pl, MoveList ml, int qstride, 
     }
 }
 
+// The winner of segment j of cascade c (j = -1: the newest item's), under plan_is_direct, decided by the `lanes` threads of a
+// group together: the same first-maximum rule as segment_winner (a later offer replaces the holder only on a strictly higher
+// score), with the scores of `lanes` offers loaded at a time instead of one after the other.  Groups lie inside a wave; all
+// lanes of the wave call it (c < 0: nothing to decide).  Returns the ref, *dst the slot, *swaps the replacements.
+__device__ inline int direct_winner(const Geom& g, const UpdatePlan& pl, int c, int j, int lanes, int lane, const float* __restrict__ mub,
+                                    const float* __restrict__ muc, int* dst, int* swaps)
+{
+    const int lead = (threadIdx.x & 63) - lane;              // first lane of this group inside the wave
+    int ref = 0, kb = 0, ke = 0, sw = 0;
+    float bs = 0.f;
+    if (c >= 0) {
+        const CascStep& cs = pl.c[c];
+        if (j < 0) {
+            *dst = ref = cs.base + cs.newest0;
+        } else {
+            *dst = cs.base + ring_position(cs, j);
+            kb = segment_first_offer(cs, j);
+            ref = offer_ref_direct(pl, c, kb, g.slots);
+            ++kb;
+        }
+        ke = g.token_selection ? segment_first_offer(cs, j + 1) : kb;
+        if (ke > kb) bs = ref_score(ref, g.slots, mub, muc);
+    }
+    // rounds of `lanes` offers; groups of one wave may need different numbers of rounds
+    const int rounds = ke > kb ? (ke - kb + lanes - 1) / lanes : 0;
+    int max_rounds = rounds;
+    for (int w = lanes; w < 64; w <<= 1) max_rounds = max(max_rounds, __shfl_xor(max_rounds, w, 64));
+    for (int r = 0; r < max_rounds; ++r) {
+        const int k = kb + r * lanes + lane;
+        const bool valid = r < rounds && k < ke;
+        int rk = 0;
+        float s = -INFINITY;
+        if (valid) {
+            rk = offer_ref_direct(pl, c, k, g.slots);
+            s = ref_score(rk, g.slots, mub, muc);
+        }
+        // highest score among the holder and the offers before this lane's
+        float before = bs;
+        for (int x = 0; x < lanes; ++x) {
+            const float sx = __shfl(s, lead + x, 64);
+            if (x < lane) before = fmaxf(before, sx);
+        }
+        const bool record = valid && s > before;             // this offer would replace the holder when its turn comes
+        const unsigned long long rec = __ballot(record) >> lead & ((1ull << lanes) - 1ull);
+        if (rec) {
+            const int last = 63 - __builtin_clzll(rec);      // the last replacement of the round holds the slot after it
+            ref = __shfl(rk, lead + last, 64);
+            bs = __shfl(s, lead + last, 64);
+            sw += __builtin_popcountll(rec);
+        }
+    }
+    *swaps = sw;
+    return ref;
+}
+
+// A direct update in one launch: a workgroup takes whole trees (MoveTrees), a thread group ND slots of them.  It decides who
+// ends up in its slots, reads those rows and, when every group of the workgroup has read its own, writes
+// them: nobody else reads or writes the slots of these trees, so no row has to be staged in memory.
+// Bound by latency (offers, scores, rows, stores, one after the other) where it is small, by memory from 4096 tokens on.  Against
+// a launch that decides and stages and one that writes, us with 8 KV heads: 512 tokens 12.7 -> 7.5, 1024 14.9 -> 10.8, 2048 with
+// eight cascades 24.9 -> 14.8, 4096 36.3 -> 30.3; fp32, 32 tokens, one head 9.3 -> 6.0.
+template <typename T, int ND>
+__global__ __launch_bounds__(1024) void move_trees_kernel(Geom g, UpdatePlan pl_arg, MoveTrees mt_arg, int qstride, const float2* __restrict__ rope,
+                                                          const float* __restrict__ mu_chunk, const T* __restrict__ k_in, const T* __restrict__ v_in,
+                                                          long tok_stride, long batch_stride, T* Kc, T* __restrict__ Kr, T* Vc, float* mu,
+                                                          int32_t* ids, int32_t* __restrict__ swaps)
+{
+    // The plan lies in LDS: one load for all of it, where every look at an argument is a load of its own, most of them one
+    // after the other, with cold caches.
+    __shared__ UpdatePlan pl;
+    __shared__ MoveTrees mt;
+    __shared__ int wg_swaps[kMaxCascades];   // replacements counted by this workgroup, per cascade
+    const int lanes = g.d / 16, half = g.d / 2, groups = blockDim.x / lanes;
+    const int bh = blockIdx.y, b = bh / g.Hkv, h = bh % g.Hkv;
+    const int grp = threadIdx.x / lanes, lane = threadIdx.x % lanes;
+    for (int i = threadIdx.x; i < (int)(sizeof(UpdatePlan) / 4); i += blockDim.x)
+        reinterpret_cast<int*>(&pl)[i] = reinterpret_cast<const int*>(&pl_arg)[i];
+    for (int i = threadIdx.x; i < (int)(sizeof(MoveTrees) / 4); i += blockDim.x)
+        reinterpret_cast<int*>(&mt)[i] = reinterpret_cast<const int*>(&mt_arg)[i];
+    if (threadIdx.x < kMaxCascades) wg_swaps[threadIdx.x] = 0;
+    __syncthreads();
+    int cls = 0;
+    while (cls + 1 < mt.n && (int)blockIdx.x >= mt.first_wg[cls + 1]) ++cls;
+    const int root = mt.c[cls], r0 = ((int)blockIdx.x - mt.first_wg[cls]) * mt.per[cls], r1 = min(mt.count[cls], r0 + mt.per[cls]);
+    int ref[ND], dst[ND], id[ND];
+    float score[ND];
+    bool move[ND];
+    Raw8<T> k0[ND], k1[ND], v0[ND], v1[ND];
+    float2 cs[ND][8];                        // of the destination
+#pragma unroll
+    for (int n = 0; n < ND; ++n) {
+        // this group's slot: the trees' segments cascade by cascade, the roots first
+        const int x = n * groups + grp;
+        int c = -2, j = 0;
+        if (root < 0) {
+            if (x < r1 - r0) { c = -1; j = r0 + x; }
+        } else {
+            int j0 = mt.lo[cls] + r0, j1 = mt.lo[cls] + r1, ahead = 0;
+            for (int lc = root;; --lc) {
+                if (x >= ahead && x < ahead + j1 - j0) { c = lc; j = j0 + x - ahead; }
+                ahead += j1 - j0;
+                if (lc == 0) break;
+                child_segments(pl, lc, &j0, &j1);
+            }
+        }
+        int sw = 0;
+        ref[n] = direct_winner(g, pl, c, j, lanes, lane, mu + (size_t)bh * g.slots, mu_chunk + (size_t)bh * qstride, &dst[n], &sw);
+        if (c == -1) { dst[n] = pl.sink_fill0 + j; ref[n] = g.slots + j; }
+        if (lane == 0 && sw) atomicAdd(&wg_swaps[c], sw);
+        move[n] = c >= -1 && ref[n] != dst[n];
+        if (move[n]) {
+            const T *ks, *vs;
+            if (ref[n] < g.slots) {
+                const size_t srow = (size_t)bh * g.slots + ref[n];
+                ks = Kc + srow * g.d;
+                vs = Vc + srow * g.d;
+                score[n] = mu[srow];
+                id[n] = ids[srow];
+            } else {
+                const int i = ref[n] - g.slots;
+                const size_t srow = (size_t)b * batch_stride + (size_t)i * tok_stride + (size_t)h * g.d;
+                ks = k_in + srow;
+                vs = v_in + srow;
+                score[n] = mu_chunk[(size_t)bh * qstride + i];
+                id[n] = pl.id0 + i;
+            }
+            k0[n].load(ks + lane * 8);
+            k1[n].load(ks + half + lane * 8);
+            v0[n].load(vs + lane * 8);
+            v1[n].load(vs + half + lane * 8);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) cs[n][i] = rope[(size_t)dst[n] * half + lane * 8 + i];
+        }
+    }
+    wait_vm_fenced<0>();                     // (a barrier alone need not wait for loads)
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < ND; ++n)
+        if (move[n]) {
+            const size_t drow = ((size_t)bh * g.slots + dst[n]) * g.d;
+            const int e = lane * 8;
+            k0[n].store(Kc + drow + e);
+            k1[n].store(Kc + drow + half + e);
+            v0[n].store(Vc + drow + e);
+            v1[n].store(Vc + drow + half + e);
+            float x0[8], x1[8];
+            k0[n].values(x0);
+            k1[n].values(x1);
+            rotate8<T>(x0, x1, cs[n], Kr + drow + e, Kr + drow + half + e);
+            if (lane == 0) {
+                mu[(size_t)bh * g.slots + dst[n]] = score[n];
+                ids[(size_t)bh * g.slots + dst[n]] = id[n];
+            }
+        }
+    if (threadIdx.x < pl.N && wg_swaps[threadIdx.x]) atomicAdd(&swaps[bh * pl.N + threadIdx.x], wg_swaps[threadIdx.x]);
+}
+
 // gather_kernel for updates whose plan is direct (plan_is_direct): the thread group of an entry
 // decides its segment itself (the offers are named from the structure alone), leaves the winner
 // in `winners` for scatter_kernel, counts the replacements, and stages the winner if it is a cache
@@ -498,81 +656,25 @@ __global__ void gather_direct_kernel(Geom g, UpdatePlan pl, MoveList ml, int n_e
     const int lane = threadIdx.x % lanes;
     if (threadIdx.x < kMaxCascades) wg_swaps[threadIdx.x] = 0;
     __syncthreads();
-    int c = -1, j = 0, ref = 0, dst = 0;
-    bool move = false;
+    int c = -1, j = 0, dst = 0;
     if (eg < n_entries) {                // the entries of the cascades beyond the first come first in the list
         int i = 0;
         while (i + 1 < ml.n && eg >= ml.first[i + 1]) ++i;
         c = ml.c[i];
         {
-            const CascStep& cs = pl.c[c];
             // entry e < E is slot j = e of the J <= cap slots opened (final_entry); entry E is the segment of
             // the item that was newest before the update
             const int e = eg - ml.first[i];
             j = e < ml.E[i] ? e : -1;
-            dst = j < 0 ? cs.base + cs.newest0 : cs.base + (cs.wpos0 + j) % cs.cap;
         }
     }
-    // The segment of every entry, decided by the `lanes` threads of its group together: the same
-    // first-maximum rule as segment_winner (a later offer replaces the holder only on a strictly
-    // higher score), with the scores of `lanes` offers loaded at a time instead of one after the other.
-    {
-        const int lead = (threadIdx.x & 63) - lane;          // first lane of this group inside the wave
-        int kb = 0, ke = 0, sw = 0;
-        float bs = 0.f;
-        const float* mub = mu + (size_t)bh * g.slots;
-        const float* muc = mu_chunk + (size_t)bh * qstride;
-        if (c >= 0) {
-            const CascStep& cs = pl.c[c];
-            if (j < 0) {
-                ref = cs.base + cs.newest0;
-                kb = 0;
-                ke = cs.kp0 < cs.M ? cs.kp0 : cs.M;
-            } else {
-                const int kh = j < cs.A ? j : cs.kp0 + (j - cs.A) * cs.pstride;
-                ref = offer_ref_direct(pl, c, kh, g.slots);
-                kb = kh + 1;
-                if (j + 1 < cs.A) ke = kb;
-                else if (j + 1 == cs.A) ke = cs.kp0 < cs.M ? cs.kp0 : cs.M;
-                else ke = kh + cs.pstride < cs.M ? kh + cs.pstride : cs.M;
-            }
-            if (!g.token_selection) ke = kb;
-            if (ke > kb) bs = ref_score(ref, g.slots, mub, muc);
-        }
-        // rounds of `lanes` offers; groups of one wave may need different numbers of rounds
-        int rounds = c >= 0 && ke > kb ? (ke - kb + lanes - 1) / lanes : 0;
-        int max_rounds = rounds;
-        for (int w = lanes; w < 64; w <<= 1) max_rounds = max(max_rounds, __shfl_xor(max_rounds, w, 64));
-        for (int r = 0; r < max_rounds; ++r) {
-            const int k = kb + r * lanes + lane;
-            const bool valid = r < rounds && k < ke;
-            int rk = 0;
-            float s = -INFINITY;
-            if (valid) {
-                rk = offer_ref_direct(pl, c, k, g.slots);
-                s = ref_score(rk, g.slots, mub, muc);
-            }
-            // highest score among the holder and the offers before this lane's
-            float before = bs;
-            for (int x = 0; x < lanes; ++x) {
-                const float sx = __shfl(s, lead + x, 64);
-                if (x < lane) before = fmaxf(before, sx);
-            }
-            const bool record = valid && s > before;         // this offer would replace the holder when its turn comes
-            const unsigned long long rec = __ballot(record) >> lead & ((1ull << lanes) - 1ull);
-            if (rec) {
-                const int last = 63 - __builtin_clzll(rec);  // the last replacement of the round holds the slot after it
-                ref = __shfl(rk, lead + last, 64);
-                bs = __shfl(s, lead + last, 64);
-                sw += __builtin_popcountll(rec);
-            }
-        }
-        if (c >= 0 && lane == 0) {
-            winners[((size_t)bh * pl.N + c) * (qstride + 1) + 1 + j] = ref;
-            if (sw) atomicAdd(&wg_swaps[c], sw);
-        }
+    int sw;
+    const int ref = direct_winner(g, pl, c, j, lanes, lane, mu + (size_t)bh * g.slots, mu_chunk + (size_t)bh * qstride, &dst, &sw);
+    if (c >= 0 && lane == 0) {
+        winners[((size_t)bh * pl.N + c) * (qstride + 1) + 1 + j] = ref;
+        if (sw) atomicAdd(&wg_swaps[c], sw);
     }
-    move = c >= 0 && ref < g.slots && ref != dst;   // a cache row that goes somewhere else (chunk tokens are read by scatter_kernel)
+    const bool move = c >= 0 && ref < g.slots && ref != dst;   // a cache row that goes somewhere else (chunk tokens are read by scatter_kernel)
     if (move) {
         const size_t srow = ((size_t)bh * g.slots + ref) * g.d, trow = ((size_t)bh * stage_rows + eg) * g.d;
         float x[8];
@@ -633,9 +735,37 @@ bool update_is_direct(const Geom& g, const DevBuffers& b, const UpdatePlan& pl)
 }
 
 // `direct`: no plan_kernel has run; the gather launch decides the segments itself (update_is_direct)
+// A direct update whose trees fit workgroups: as few threads as hold the largest tree (four cascades with the default
+// periods: 15 slots).  Larger ones (more than eight cascades at d = 128) go through the staging array.
+template <typename T>
+static bool moves_of_trees(const Geom& g, const DevBuffers& b, const UpdatePlan& pl, int max_chunk, const void* k, const void* v, int k_token_stride,
+                           int k_batch_stride, hipStream_t s)
+{
+    const int lanes = g.d / 16;
+    MoveTrees mt;
+    for (int x = 0; x < 4; ++x) {
+        const int threads = x < 2 ? 256 << x : 1024, nodes = x < 3 ? 1 : 2;
+        plan_trees(pl, threads / lanes * nodes, mt);
+        if (mt.wgs == 0) continue;
+        const dim3 grid(mt.wgs, g.B * g.Hkv), block(threads);
+        if (nodes == 1)
+            hipLaunchKernelGGL((move_trees_kernel<T, 1>), grid, block, 0, s, g, pl, mt, max_chunk, b.rope, b.mu_chunk, (const T*)k, (const T*)v,
+                               (long)k_token_stride, (long)k_batch_stride, (T*)b.Kc, (T*)b.Kr, (T*)b.Vc, b.mu, b.ids, b.swaps);
+        else
+            hipLaunchKernelGGL((move_trees_kernel<T, 2>), grid, block, 0, s, g, pl, mt, max_chunk, b.rope, b.mu_chunk, (const T*)k, (const T*)v,
+                               (long)k_token_stride, (long)k_batch_stride, (T*)b.Kc, (T*)b.Kr, (T*)b.Vc, b.mu, b.ids, b.swaps);
+        return true;
+    }
+    return false;
+}
+
 void launch_moves(const Geom& g, int dtype, const DevBuffers& b, const UpdatePlan& pl, int max_chunk,
                   const void* k, const void* v, int k_token_stride, int k_batch_stride, bool direct, hipStream_t s)
 {
+    if (direct &&
+        (dtype == CASCADE_F32 ? moves_of_trees<float>(g, b, pl, max_chunk, k, v, k_token_stride, k_batch_stride, s)
+                              : moves_of_trees<bf16_t>(g, b, pl, max_chunk, k, v, k_token_stride, k_batch_stride, s)))
+        return;
     if (g.d % 16 == 0 && b.move_stage) {
         MoveList ml;
         ml.n = 0;

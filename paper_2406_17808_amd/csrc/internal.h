@@ -105,6 +105,20 @@ struct UpdatePlan {
     CascStep c[kMaxCascades];
 };
 
+// A direct update (plan_is_direct) falls into trees that have nothing to do with each other: a slot that is opened in
+// cascade c >= 1 (or the slot of its newest item, which offers compete for) is the parent of the slots of cascade c - 1 whose
+// items are offered to it, because those items are read by the parent and overwritten by the child.  Roots are the slots of
+// the last cascade that is offered anything, and, in the others, the slots that evict nothing: appends and the newest item.
+// A workgroup takes consecutive roots of one cascade with all that hangs on them.
+struct MoveTrees {
+    int n, wgs;                           // classes of roots; workgroups per (sequence, KV head); 0: a tree has too many slots for a workgroup
+    int c[kMaxCascades + 1];              // cascade of the roots; -1: the sinks
+    int lo[kMaxCascades + 1];             // segment of the first root (sinks: 0)
+    int count[kMaxCascades + 1];          // roots
+    int per[kMaxCascades + 1];            // roots a workgroup takes
+    int first_wg[kMaxCascades + 1];
+};
+
 // The insertion of one token: what every cascade it or an evicted item reaches does with its offer, and the
 // slot concerned.  Entry 0 is the first cascade (or a free sink slot), entry i is offered what entry i - 1 held.
 constexpr int kInsertAppend = 0;    // the slot is free; nothing goes further

@@ -37,12 +37,19 @@ __host__ __device__ inline bool plan_is_direct(const UpdatePlan& pl)
     return true;
 }
 
+// Ring position of the j-th slot opened, under plan_is_direct (j < J <= cap)
+__host__ __device__ inline int ring_position(const CascStep& cs, int j)
+{
+    const int p = cs.wpos0 + j;
+    return p < cs.cap ? p : p - cs.cap;
+}
+
 // ref of offer k of cascade c under plan_is_direct: push k of cascade c - 1 evicts ring position wpos0 + A + k
 __host__ __device__ inline int offer_ref_direct(const UpdatePlan& pl, int c, int k, int slots)
 {
     if (c == 0) return slots + pl.n_to_sink + k;
     const CascStep& prev = pl.c[c - 1];
-    return prev.base + (prev.wpos0 + prev.A + k) % prev.cap;
+    return prev.base + ring_position(prev, prev.A + k);
 }
 
 // Winner of segment j of cascade c (j = -1: the item that was newest before the update and the
@@ -77,6 +84,22 @@ __host__ __device__ inline int segment_winner(const CascStep& cs, int c, int j, 
     }
     *swaps = n_swaps;
     return best;
+}
+
+// First offer of segment j; j = J: one past the last offer.
+__host__ __device__ inline int segment_first_offer(const CascStep& cs, int j)
+{
+    if (j < 0) return 0;
+    if (j >= cs.J) return cs.M;
+    return j < cs.A ? j : cs.kp0 + (j - cs.A) * cs.pstride;
+}
+
+// Under plan_is_direct: the segments [j0, j1) of cascade c >= 1 are offered what segments [j0', j1') of cascade c - 1 evict.
+__host__ __device__ inline void child_segments(const UpdatePlan& pl, int c, int* j0, int* j1)
+{
+    const int a = pl.c[c - 1].A;
+    *j0 = a + segment_first_offer(pl.c[c], *j0);
+    *j1 = a + segment_first_offer(pl.c[c], *j1);
 }
 
 // The item evicted by push i of the cascade: what its ring position held before the write.

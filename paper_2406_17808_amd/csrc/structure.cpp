@@ -206,6 +206,32 @@ void plan_insert(const Geom& g, const UpdatePlan& plan, DecodeInsert& out)
     }
 }
 
+void plan_trees(const UpdatePlan& plan, int capacity, MoveTrees& out)
+{
+    out = MoveTrees();
+    auto add = [&](int c, int lo, int count, int per) {
+        if (count <= 0) return;
+        out.c[out.n] = c; out.lo[out.n] = lo; out.count[out.n] = count; out.per[out.n] = per; out.first_wg[out.n] = out.wgs;
+        out.wgs += (count + per - 1) / per;
+        ++out.n;
+    };
+    long size = 0;                                   // at most this many slots hang on a slot of the cascade, itself included
+    for (int c = 0; c < plan.N && plan.c[c].M > 0; ++c) {
+        const CascStep& cs = plan.c[c];
+        // offers to one slot: until the first push for the newest item and the last append, a stride for a push
+        int offers = 1;
+        if (cs.pre) offers = std::max(offers, cs.kp0);
+        if (cs.A > 0) offers = std::max(offers, cs.kp0 - (cs.A - 1));
+        if (cs.P > 0) offers = std::max(offers, cs.pstride);
+        size = c == 0 ? 1 : 1 + std::min(offers, cs.M) * size;
+        const bool last = c + 1 == plan.N || plan.c[c + 1].M == 0;
+        const int roots = cs.pre + (last ? cs.J : cs.A);
+        if (roots > 0 && size > capacity) { out = MoveTrees(); return; }
+        add(c, -cs.pre, roots, (int)(capacity / size));
+    }
+    add(-1, 0, plan.n_to_sink, capacity);
+}
+
 // Splits of a decode step: as many as make the busiest compute unit finish first.  A CU holds one workgroup of
 // the bf16 kernels (their rings fill the LDS); a workgroup costs about as much as two rounds of four tiles besides (first
 // copies, queries, epilogue).  Where the shares differ by a tile, half a tile is charged.  The rule's count / the best of up to 29,

@@ -47,6 +47,9 @@ void plan_update(const Geom& g, HostState& st, int Q, UpdatePlan& plan);
 // The plan of one token (plan_update with Q = 1) as a chain of slots.
 void plan_insert(const Geom& g, const UpdatePlan& plan, DecodeInsert& out);
 
+// The trees of a direct update for workgroups of `capacity` slots.
+void plan_trees(const UpdatePlan& plan, int capacity, MoveTrees& out);
+
 // Workgroups that share the cached rows (n_tiles tiles of 32) of one sequence and KV head in a decode step, at most `most`.
 int decode_split_count(int pairs, int most, int n_tiles);
 

@@ -1,14 +1,19 @@
 // Test infrastructure: rules of the library's host side (structure.cpp) driven directly, without a device.
 //   packing SEED   which tiles of the packed K / V copies a chunk packs again: a replay of a random geometry that
 //                  packs token numbers in the place of rows.  Exit code 0 = every row is where it is read.
+//   trees SEED     the update of a chunk in trees: workgroup after workgroup in a drawn order, each reading its slots' new
+//                  rows from the cache as it then is and writing them, against Alg. 2 token by token.
 //   splits         the split count of a decode step against the same costs looked at for every count, and its time.
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <chrono>
+#include <string>
 #include <vector>
 
+#include "../../paper_2406_17808_amd/csrc/plan_core.h"
 #include "../../paper_2406_17808_amd/csrc/structure.h"
 
 using namespace ckv;
@@ -148,6 +153,98 @@ static int packing_case(int seed, int kind, long* tiles_packed)
     return 0;
 }
 
+// ------------------------------------------------------------------ updates in trees
+
+struct Item { int id; float mu; };
+
+static int trees_case(int seed, long* updates, long* refused)
+{
+    rng_state = 0x7654321ull * (uint64_t)(seed + 1);
+    static const int ring[] = {1, 2, 7, 16, 33, 64, 100}, chunk[] = {1, 3, 16, 33, 64, 100}, sinks[] = {0, 3, 64}, room[] = {8, 16, 32, 64, 128, 256};
+    cascade_config cfg;
+    memset(&cfg, 0, sizeof(cfg));
+    cfg.batch = 1; cfg.n_q_heads = 1; cfg.n_kv_heads = 1; cfg.head_dim = 64; cfg.dtype = CASCADE_BF16;
+    cfg.n_sink = sinks[rnd(3)];
+    cfg.n_cascades = 1 + (int)rnd(8);
+    cfg.max_chunk = chunk[rnd(6)];
+    cfg.ema_beta = 0.9f; cfg.rope_base = 10000.f;
+    cfg.token_selection = rnd(8) != 0;
+    const bool periods = rnd(3) == 0, equal = rnd(2) == 0;
+    for (int c = 0; c < cfg.n_cascades; ++c) {
+        cfg.cascade_sizes[c] = equal ? 100 : ring[rnd(7)];
+        cfg.accept_period[c] = periods ? (c == 0 ? 1 : 1 + (int)rnd(5)) : 0;
+    }
+    std::string why;
+    if (check_config(&cfg, why) != CASCADE_OK) { fprintf(stderr, "seed %d: %s\n", seed, why.c_str()); return 1; }
+    Geom g;
+    make_geom(&cfg, g);
+    std::vector<Item> cache(g.slots, Item{-1, 0.f});
+    HostState st;
+    for (int step = 0; step < 60; ++step) {
+        const int Q = rnd(10) < 7 ? cfg.max_chunk : 1 + (int)rnd(cfg.max_chunk);
+        std::vector<Item> fresh(Q);
+        for (int i = 0; i < Q; ++i) fresh[i] = Item{(int)st.n_seen + i, (float)rnd(6)};     // ties
+        // the chunk's scores replace those of the cached rows in a real call; here they stay
+        std::vector<Item> want = cache;
+        HostState one = st;
+        for (int i = 0; i < Q; ++i) {
+            Item x = fresh[i];
+            UpdatePlan pl;
+            DecodeInsert ins;
+            plan_update(g, one, 1, pl);
+            plan_insert(g, pl, ins);
+            for (int e = 0; e < ins.n; ++e) {
+                Item& there = want[ins.slot[e]];
+                if (insert_kind(ins, e) != kInsertCompete) std::swap(x, there);
+                else if (g.token_selection && x.mu > there.mu) there = x;
+            }
+        }
+        UpdatePlan pl;
+        plan_update(g, st, Q, pl);
+        MoveTrees mt;
+        const int capacity = room[rnd(6)];
+        mt.wgs = 0;
+        if (plan_is_direct(pl)) plan_trees(pl, capacity, mt);
+        if (mt.wgs == 0) { cache = want; ++*refused; continue; }
+        ++*updates;
+        std::vector<float> mu(g.slots), muc(Q);
+        for (int i = 0; i < g.slots; ++i) mu[i] = cache[i].mu;
+        for (int i = 0; i < Q; ++i) muc[i] = fresh[i].mu;
+        std::vector<int> order(mt.wgs);
+        for (int i = 0; i < mt.wgs; ++i) order[i] = i;
+        for (int i = mt.wgs - 1; i > 0; --i) std::swap(order[i], order[rnd(i + 1)]);
+        for (int wg : order) {
+            int cls = 0;
+            while (cls + 1 < mt.n && wg >= mt.first_wg[cls + 1]) ++cls;
+            const int r0 = (wg - mt.first_wg[cls]) * mt.per[cls], r1 = std::min(mt.count[cls], r0 + mt.per[cls]);
+            std::vector<int> dst, ref;
+            if (mt.c[cls] < 0)
+                for (int x = r0; x < r1; ++x) { dst.push_back(pl.sink_fill0 + x); ref.push_back(g.slots + x); }
+            else {
+                int j0 = mt.lo[cls] + r0, j1 = mt.lo[cls] + r1;
+                for (int c = mt.c[cls];; --c) {
+                    for (int j = j0; j < j1; ++j) {
+                        int sw;
+                        // the scores as they are in the cache by now
+                        for (int i = 0; i < g.slots; ++i) mu[i] = cache[i].mu;
+                        ref.push_back(segment_winner(pl.c[c], c, j, g.slots, pl.n_to_sink, g.token_selection, nullptr, mu.data(), muc.data(), &sw, &pl));
+                        dst.push_back(j < 0 ? pl.c[c].base + pl.c[c].newest0 : pl.c[c].base + (pl.c[c].wpos0 + j) % pl.c[c].cap);
+                    }
+                    if (c == 0) break;
+                    child_segments(pl, c, &j0, &j1);
+                }
+            }
+            if ((int)dst.size() > capacity) { fprintf(stderr, "seed %d step %d: %d slots for a workgroup of %d\n", seed, step, (int)dst.size(), capacity); return 1; }
+            std::vector<Item> rows;
+            for (int x : ref) rows.push_back(x < g.slots ? cache[x] : fresh[x - g.slots]);
+            for (size_t i = 0; i < dst.size(); ++i) cache[dst[i]] = rows[i];
+        }
+        for (int i = 0; i < g.slots; ++i)
+            if (cache[i].id != want[i].id || cache[i].mu != want[i].mu) { fprintf(stderr, "seed %d step %d: slot %d holds %d, not %d\n", seed, step, i, cache[i].id, want[i].id); return 1; }
+    }
+    return 0;
+}
+
 // ------------------------------------------------------------------ splits of a decode step
 
 static int best_of_all_splits(int pairs, int most, int n_tiles)
@@ -198,6 +295,13 @@ int main(int argc, char** argv)
         printf("tiles packed: own %ld shared %ld single-pass %ld with decode steps %ld\n", tiles[0], tiles[1], tiles[2], tiles[3]);
         return bad ? 1 : 0;
     }
-    fprintf(stderr, "usage: host_rules packing SEED | splits\n");
+    if (argc == 3 && !strcmp(argv[1], "trees")) {
+        long updates = 0, refused = 0;
+        int bad = 0;
+        for (int i = 0; i < 40; ++i) bad += trees_case(40 * atoi(argv[2]) + i, &updates, &refused);
+        printf("%ld updates in trees, %ld not\n", updates, refused);
+        return bad || updates < refused / 4 ? 1 : 0;
+    }
+    fprintf(stderr, "usage: host_rules packing SEED | trees SEED | splits\n");
     return 2;
 }

@@ -627,6 +627,28 @@ def _decode_after_fill(cfg, fill, steps, seqs=None, steps_before=0):
     run.close()
 
 
+@pytest.mark.parametrize("dtype,d,n_cascades", [(B.CASCADE_BF16, 128, 5), (B.CASCADE_BF16, 128, 6), (B.CASCADE_BF16, 128, 7),
+                                                (B.CASCADE_BF16, 128, 8), (B.CASCADE_BF16, 64, 8), (B.CASCADE_F32, 32, 8), (B.CASCADE_F32, 256, 7)])
+def test_update_trees_of_many_cascades(oracle_mod, dtype, d, n_cascades):
+    """Full caches of five to eight cascades: trees of 31 to 255 slots in workgroups of 256 to 1024 threads, one or two slots a
+    thread group; chunks that begin and end anywhere in the acceptance phases."""
+    import torch
+    from gpu_harness import ParityRun
+    cfg = B.make_config(batch=1, n_q_heads=2, n_kv_heads=2, head_dim=d, dtype=dtype, n_sink=3, cascade_sizes=[130] * n_cascades,
+                        ema_beta=0.99, rope_base=10000.0, max_chunk=128, keep_update_scores=1)
+    run = ParityRun(cfg, one_step_ahead=True)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(n_cascades)
+    for n in [41] + [128] * ((130 << n_cascades) // 128):
+        run.advance_gpu_only(*(torch.randn((1, n, 2, d), generator=gen, device="cuda:0").to(run.gpu.torch_dtype) for _ in range(3)))
+    run.sync_oracle_from_gpu()
+    rng = np.random.default_rng(d)
+    for step, n in enumerate([128, 77, 128]):
+        rep = run.step(*_inputs(rng, cfg, n))
+        assert rep.replay_exact, step
+    run.close()
+
+
 @pytest.mark.parametrize("d", [48, 80, 96])
 def test_update_with_head_sizes_that_do_not_divide_a_wave(oracle_mod, d):
     """d / 16 threads move a row: three, five or six of them do not divide a wave, so the offers are not compared inside one."""

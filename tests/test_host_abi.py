@@ -251,6 +251,15 @@ def test_packed_tiles_hold_the_rows_of_their_segments(host_rules, seed):
     assert res.returncode == 0, res.stderr
 
 
+@pytest.mark.parametrize("seed", range(12))
+def test_update_trees_are_independent(host_rules, seed):
+    """The slots a direct update writes, divided over workgroups in whole trees: carried out one workgroup after the other, in
+    any order and in place, they give what Alg. 2 gives token by token.  Forty streams a seed: up to eight cascades, any
+    periods, caches that fill, chunks of 1 to 100 tokens, equal scores, workgroups of 8 to 256 slots."""
+    res = subprocess.run([host_rules, "trees", str(seed)], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
 def test_decode_split_count(host_rules):
     """Few split counts of a decode step are looked at; they give what looking at all of them gives, in little host time."""
     res = subprocess.run([host_rules, "splits"], capture_output=True, text=True, timeout=300)
