@@ -78,18 +78,10 @@ __global__ __launch_bounds__(kPackThreads) void kv_pack_kernel(Geom g, SegList s
         return;
     }
     const int bh = blockIdx.x % BH, kth = blockIdx.x / BH;   // the kth tile of the runs
-    int run = 0;
-    while (run + 1 < runs.n && kth >= runs.ahead[run + 1]) ++run;
-    const int n = runs.first[run] + (kth - runs.ahead[run]);
-    int si = 0, first = 0;
-    for (; si < sl.n; ++si) {
-        const int nt = seg_tiles(sl, si);
-        if (n < first + nt) break;
-        first += nt;
-    }
-    if (si >= sl.n) return;   // cannot happen: the runs name tiles of the segment list
+    const int run = table_entry(runs.ahead, kth), n = runs.first[run] + (kth - runs.ahead[run]);
+    const int si = table_entry(sl.tile0, n);
     const Seg sg = sl.s[si];
-    const int t0 = (n - first) * kBN - sl.pad[si], rows = min(kBN, sg.len - t0);   // (t0 < 0: rows before the segment become zeros, too)
+    const int t0 = (n - sl.tile0[si]) * kBN - sl.pad[si], rows = min(kBN, sg.len - t0);   // (t0 < 0: rows before the segment become zeros, too)
     // a chunk row is one of Hkv rows of a token
     const size_t row0 = sg.chunk ? ((size_t)(bh / g.Hkv) * Q + t0) * g.Hkv + bh % g.Hkv
                                  : ((size_t)bh * g.slots + (sg.start + t0));   // (a padded segment starts at least pad rows into its ring)
@@ -491,13 +483,11 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
 
     // In iteration t, tile t is multiplied with V, tile t+1 with Q; the copies of V of tile t+2
     // and of K of tile t+3 are issued.  Only the softmax needs to know which segment a tile is from.
-    int NT = 0;   // tiles this workgroup visits: chunk keys after its last row are never visible
-    for (int i = 0; i < sl.n; ++i) NT += ((sl.s[i].chunk ? min(sl.s[i].len, wg_imax + 1) : sl.s[i].len) + (SP ? 0 : sl.pad[i]) + kBN - 1) / kBN;
+    // The chunk is the last segment; tiles this workgroup visits: chunk keys after its last row are never visible
+    int NT = sl.tile0[sl.n - 1] + (min(sl.s[sl.n - 1].len, wg_imax + 1) + kBN - 1) / kBN;
     if (SP) inv_steps = 1.f / (float)NT;
     int tile_first = 0;                  // SPLIT: first tile of this workgroup's range
     TileIter<!SP> it1;
-    it1.first(sl, wg_imax);
-    if (!it1.valid(sl)) return;          // cannot happen: the chunk itself is always a segment
     // this lane's row of the partial results
     const size_t prow = ((((size_t)split * BH + bh) * n_tiles + tile) * BM) + wave * 32 + l32;
     if (SPLIT) {
@@ -506,12 +496,12 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
             if (half == 0) { part_ml[prow * 2] = 0.f; part_ml[prow * 2 + 1] = 0.f; }
             return;
         }
-        for (int i = 0; i < tb; ++i) it1.next(sl, wg_imax);
         tile_first = tb;
         kt_bh += (size_t)tb * TILE;
         vt_bh += (size_t)tb * TILE;
         NT = te - tb;
     }
+    it1.seek(sl, wg_imax, tile_first);
 
     // Copies.  Batch t is K of tile t+4 and V of tile t+3, each into the stage of the tile four
     // before it.  A wave issues its share of batch t at the start of its vector block t (those
@@ -545,27 +535,31 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     };
     Frag fr[kAhead];
 
-    // prologue: K of tiles 0..3, V of tiles 0..2; S^T and probabilities of tile 0
-#pragma unroll
-    for (int n = 0; n < 4; ++n)
-        if (n < NT) copy_tile(kt_bh, lds_k, n, n);
-#pragma unroll
-    for (int n = 0; n < 3; ++n)
-        if (n < NT) copy_tile(vt_bh, lds_v, n, n);
-    load_q(it1.sg);
-    int q_var = it1.sg.qvar;   // the rotation the query fragments hold (two segments may share one)
+    // prologue: K of tiles 0..3, V of tiles 0..2; S^T and probabilities of tile 0.  K of tile 0 and the queries come
+    // first: with everything in front of them, a workgroup began its first product 8 to 11 us after its start.
+    copy_tile(kt_bh, lds_k, 0, 0);
     // the largest squared key norm among the tiles of this workgroup
     float kn2 = 0.f;
     {
         const float* kn = Knorm2 + (size_t)bh * tiles_per_bh + (SPLIT ? tile_first : 0);
         for (int i = tid; i < NT; i += kSWaves * 64) kn2 = fmaxf(kn2, kn[i]);
-#pragma unroll
-        for (int w = 32; w > 0; w >>= 1) kn2 = fmaxf(kn2, __shfl_xor(kn2, w, 64));
-        if (l == 0) kn_wave[wave] = kn2;
     }
-    const float qnorm2 = qn2 + __shfl_xor(qn2, 32, 64);
+    load_q(it1.sg);
+    int q_var = it1.sg.qvar;   // the rotation the query fragments hold (two segments may share one)
     wait_vm<0>();
-    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    if (1 < NT) copy_tile(kt_bh, lds_k, 1, 1);
+    copy_tile(vt_bh, lds_v, 0, 0);
+    if (1 < NT) copy_tile(vt_bh, lds_v, 1, 1);
+    if (2 < NT) copy_tile(kt_bh, lds_k, 2, 2);
+    if (3 < NT) copy_tile(kt_bh, lds_k, 3, 3);      // this and the next: batch -1 below
+    if (2 < NT) copy_tile(vt_bh, lds_v, 2, 2);
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) kn2 = fmaxf(kn2, __shfl_xor(kn2, w, 64));
+    if (l == 0) kn_wave[wave] = kn2;
+    const float qnorm2 = qn2 + __shfl_xor(qn2, 32, 64);
+    wait_lds_reads();
+    wg_barrier();              // K of tile 0 is complete
 #pragma unroll
     for (int w = 0; w < kSWaves; ++w) kn2 = fmaxf(kn2, kn_wave[w]);
     qk_tile(Ks);
@@ -585,7 +579,9 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     // tiles hold, m_run can stay where it is, and the per-tile maximum is skipped.
     if (!SPLIT) bounded = !__any(sqrtf(qnorm2 * kn2) * 1.01f > m_run + kBoundLog2);   // (measured in split launches, too: -0.2 %)
     it1.next(sl, wg_imax);
-    __syncthreads();      // barrier 0: every wave has read K of tile 0, its buffer may be refilled
+    publish((3 < NT ? PW : 0) + (2 < NT ? PW : 0));
+    wait_lds_reads();
+    wg_barrier();         // barrier 0: every wave has read K of tile 0, its buffer may be refilled; all but batch -1 has landed
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) fr[i] = read_frag(Vs, Ks, i);
     if (late) wg_barrier();     // barrier 1
@@ -782,12 +778,14 @@ bool launch_kv_pack(const Geom& g, const DevBuffers& b, const SegList& sl, const
                     const void* q, const void* k, const void* v, hipStream_t s)
 {
     if (packed_tiles(sl) > b.vt_tiles) return false;   // the workspace was sized for every possible segment list
+    TileRuns list = runs;
+    for (int i = list.n; i < kMaxTileRuns; ++i) list.ahead[i] = INT32_MAX;
     int vars = 1;
     const long threads = q_first_row < Q ? query_threads(g, sl, Q - q_first_row, &vars) : 0;
     const dim3 grid(runs.total * g.B * g.Hkv + (unsigned)((threads + kPackThreads - 1) / kPackThreads)), block(kPackThreads);
     if (grid.x == 0) return true;
 #define CKV_PACK(D)                                                                                                                       \
-    hipLaunchKernelGGL(kv_pack_kernel<D>, grid, block, 0, s, g, sl, runs, Q, b.vt_tiles, qscale, q_first_row, vars, b.rope, (const bf16_t*)q, \
+    hipLaunchKernelGGL(kv_pack_kernel<D>, grid, block, 0, s, g, sl, list, Q, b.vt_tiles, qscale, q_first_row, vars, b.rope, (const bf16_t*)q, \
                        (const bf16_t*)k, (const bf16_t*)v, (const bf16_t*)b.Kr, (const bf16_t*)b.Vc, (bf16_t*)b.Qr, (bf16_t*)b.Krc,          \
                        (bf16_t*)b.Kt, (bf16_t*)b.Vt, b.knorm2)
     if (g.d == 128) CKV_PACK(128); else CKV_PACK(64);
@@ -800,12 +798,12 @@ bool launch_kv_pack(const Geom& g, const DevBuffers& b, const SegList& sl, const
 // Bound by the one pass over the partial results: with a workgroup per row that read one split after the other,
 // 16384 rows of four splits 20.0 -> 8.2 us (4.3 TB/s), 32768 of two 28.8 -> 13.0, 9600 of six at d = 64 12.7 -> 5.2.
 constexpr int kMergeThreads = 256;
-template <int D>
+template <int D, int AT_ONCE>
 __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(Geom g, int Q, int n_tiles, int n_split, int BM,
                                                                    const float* __restrict__ part_o, const float* __restrict__ part_ml,
                                                                    bf16_t* __restrict__ out, float* __restrict__ lse, ScoreOffsets so)
 {
-    constexpr int TPR = D / 4, AT_ONCE = 8;
+    constexpr int TPR = D / 4;
     const int BH = g.B * g.Hkv;
     const int bh = blockIdx.y, r = blockIdx.x * (kMergeThreads / TPR) + threadIdx.x / TPR;            // r = head-in-group * Q + token
     if (r >= g.G * Q) return;
@@ -863,15 +861,9 @@ __global__ __launch_bounds__(kSpmHeads * kBN) void single_pass_merge_kernel(Geom
 {
     __shared__ float head_sum[kSpmHeads][kBN];
     const int n = blockIdx.x, bh = blockIdx.y, x = threadIdx.x % kBN, grp = threadIdx.x / kBN;
-    int si = 0, first = 0;
-    for (; si < sl.n; ++si) {
-        const int nt = (sl.s[si].len + kBN - 1) / kBN;
-        if (n < first + nt) break;
-        first += nt;
-    }
-    if (si >= sl.n) return;                 // uniform for the workgroup
+    const int si = table_entry(sl.tile0, n);
     const Seg sg = sl.s[si];
-    const int t0 = (n - first) * kBN, key = t0 + x;      // (single-pass chunks have no padded segments)
+    const int t0 = (n - sl.tile0[si]) * kBN, key = t0 + x;      // (single-pass chunks have no padded segments)
     // row block r of a head covers tokens 256 r .. 256 r + 255 and visits the chunk's tiles up to its last token
     const int rbs = Q / 256, r_lo = sg.chunk ? t0 / 256 : 0;
     const size_t stride = (size_t)tiles_per_bh * kBN;
@@ -965,12 +957,12 @@ void launch_attn_stream(const Geom& g, const DevBuffers& b, const SegList& sl, i
     if (n_split > 1) {
         if (copies) CKV_ATTN_D(false, true, false, true, no_dbg);
         else CKV_ATTN_D(false, true, false, false, no_dbg);
-        if (g.d == 128)
-            hipLaunchKernelGGL(attn_merge_kernel<128>, dim3((g.G * Q + 7) / 8, g.B * g.Hkv), dim3(kMergeThreads), 0, s, g, Q, tiles, n_split, BM,
-                               part_o, part_ml, (bf16_t*)out, b.lse, so);
-        else
-            hipLaunchKernelGGL(attn_merge_kernel<64>, dim3((g.G * Q + 15) / 16, g.B * g.Hkv), dim3(kMergeThreads), 0, s, g, Q, tiles, n_split, BM,
-                               part_o, part_ml, (bf16_t*)out, b.lse, so);
+#define CKV_MERGE(D, N)                                                                                                                            \
+    hipLaunchKernelGGL((attn_merge_kernel<D, N>), dim3((g.G * Q + 1024 / D - 1) / (1024 / D), g.B * g.Hkv), dim3(kMergeThreads), 0, s, g, Q, tiles, \
+                       n_split, BM, part_o, part_ml, (bf16_t*)out, b.lse, so)
+        if (g.d == 128) { if (n_split <= 2) CKV_MERGE(128, 2); else if (n_split <= 4) CKV_MERGE(128, 4); else CKV_MERGE(128, 8); }
+        else { if (n_split <= 2) CKV_MERGE(64, 2); else if (n_split <= 4) CKV_MERGE(64, 4); else CKV_MERGE(64, 8); }
+#undef CKV_MERGE
         return;
     }
 #ifdef CASCADE_KV_ATTN_PHASE_TIMING   // development builds only: per-phase cycle counts of one workgroup

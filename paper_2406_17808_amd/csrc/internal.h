@@ -78,6 +78,7 @@ struct SegList {
     int qrot0[kMaxQueryRotations];   // rotation index of chunk row 0 for query copy v (row i uses qrot0 + i)
     Seg s[kMaxSegments];
     int pad[kMaxSegments];           // packed tiles: the first tile of a segment starts this many rows (0 .. 63) before it
+    int tile0[kMaxSegments];         // packed tiles: the first tile of segment i; INT32_MAX from entry n on
 };
 
 // ------------------------------------------------------------------ structure of one cache update
@@ -151,7 +152,7 @@ struct TileRuns {
     int n;                       // runs
     int total;                   // tiles in all runs
     int first[kMaxTileRuns];     // first tile of run i
-    int ahead[kMaxTileRuns];     // tiles in the runs before run i
+    int ahead[kMaxTileRuns];     // tiles in the runs before run i; INT32_MAX from entry n on (set by the launcher)
 };
 
 // scratch index space of the update: refs < slots name a physical slot, refs >= slots a chunk token

@@ -38,25 +38,17 @@ template <int D> struct ScoreSwz {   // permutation of the 16-byte pieces of a s
     __device__ static int of(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
 };
 
-// The segment a block of `keys` keys of the segment list belongs to, and its number inside it.
-__device__ inline int score_tile_segment(const SegList& sl, int keys, int tile, int* within)
-{
-    int si = 0;
-    while (si < sl.n) {
-        const int nt = (sl.s[si].len + keys - 1) / keys;
-        if (tile < nt) break;
-        tile -= nt;
-        ++si;
-    }
-    *within = tile;
-    return si;
-}
+// The segments cut into blocks of the keys a workgroup takes: first block of every segment (INT32_MAX behind the last).
+struct KeyBlocks {
+    int total;
+    int first[kMaxSegments];
+};
 
 // NKB: 32-key blocks per wave.  Two halve the LDS reads per MFMA; one gives twice as many
 // workgroups, for launches that would otherwise leave compute units without work.
 template <int D, int NKB>
 __global__ __launch_bounds__(kScoreThreads, 3) void score_stream_kernel(
-    Geom g, SegList sl, int Q, int qstride, int tail, int qpad, int n_tiles, int row_parts, float decay, const bf16_t* __restrict__ Qr,
+    Geom g, SegList sl, KeyBlocks kbs, int Q, int qstride, int tail, int qpad, int row_parts, float decay, const bf16_t* __restrict__ Qr,
     const bf16_t* __restrict__ Kr, const bf16_t* __restrict__ Krc, const float* __restrict__ negt,
     float* __restrict__ mu, float* __restrict__ mu_chunk, float* __restrict__ sums)
 {
@@ -69,13 +61,11 @@ __global__ __launch_bounds__(kScoreThreads, 3) void score_stream_kernel(
     constexpr int NOPS = NCW + 1;                    // vector memory operations per wave and stage
     __shared__ __attribute__((aligned(1024))) unsigned char ring[kStStages][kStageBytes];
     __shared__ __attribute__((aligned(256))) float tneg[kStStages][4][kStRows];   // every wave keeps its own copy
-    const int BH = g.B * g.Hkv;
+    const int BH = g.B * g.Hkv, n_tiles = kbs.total;
     const int bh = blockIdx.x % BH;
     const int list_tile = (blockIdx.x / BH) % n_tiles, part = blockIdx.x / BH / n_tiles;
-    int tile;
     const int b = bh / g.Hkv, hk = bh % g.Hkv;
-    const int si = score_tile_segment(sl, kScoreKeys, list_tile, &tile);
-    if (si >= sl.n) return;       // uniform for the workgroup
+    const int si = table_entry(kbs.first, list_tile), tile = list_tile - kbs.first[si];
     const Seg sg = sl.s[si];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l32 = l & 31, half = l >> 5;
     const int wave_k0 = tile * kScoreKeys + wave * kWaveKeys;   // first key of this wave inside the segment
@@ -283,14 +273,12 @@ __global__ __launch_bounds__(kScoreThreads, 3) void score_stream_kernel(
 
 // The parts' column sums of every key added up in a fixed order, the query heads of the group reduced, and the
 // EMA step taken (one thread per key).
-__global__ __launch_bounds__(2 * kScoreKeysPerBlock) void score_merge_kernel(Geom g, SegList sl, int qstride, int n_tiles, int row_parts, float decay,
+__global__ __launch_bounds__(2 * kScoreKeysPerBlock) void score_merge_kernel(Geom g, SegList sl, KeyBlocks kbs, int qstride, int row_parts, float decay,
                                                                              const float* __restrict__ sums, float* __restrict__ mu,
                                                                              float* __restrict__ mu_chunk)
 {
-    const int keys = blockDim.x, bh = blockIdx.y;
-    int tile;
-    const int si = score_tile_segment(sl, keys, blockIdx.x, &tile);
-    if (si >= sl.n) return;
+    const int keys = blockDim.x, bh = blockIdx.y, n_tiles = kbs.total;
+    const int si = table_entry(kbs.first, (int)blockIdx.x), tile = (int)blockIdx.x - kbs.first[si];
     const Seg sg = sl.s[si];
     const int k = tile * keys + threadIdx.x;
     if (k >= sg.len) return;
@@ -338,16 +326,22 @@ void launch_score_mfma(const Geom& g, const DevBuffers& b, const SegList& sl, in
     const int keys = narrow ? kScoreKeysPerBlock : 2 * kScoreKeysPerBlock, n_tiles = tiles_of(keys);
     // the parts' sums lie where a split attention launch keeps its partial results
     while (row_parts > 0 && (size_t)BH * g.G * row_parts * n_tiles * keys > (size_t)kAttnPartRows * (g.d + 2)) --row_parts;
+    KeyBlocks kbs;
+    kbs.total = n_tiles;
+    for (int i = 0, n = 0; i < kMaxSegments; ++i) {
+        kbs.first[i] = i < sl.n ? n : INT32_MAX;
+        if (i < sl.n) n += (sl.s[i].len + keys - 1) / keys;
+    }
     const dim3 grid(n_tiles * BH * (row_parts ? g.G * row_parts : 1)), block(kScoreThreads);
     const int qpad = max_chunk + kStRows;   // the attention launch left the offsets of this chunk's rows in b.negt
 #define CKV_SCORE(D, NKB)                                                                                              \
-    hipLaunchKernelGGL((score_stream_kernel<D, NKB>), grid, block, 0, s, g, sl, Q, max_chunk, tail_rows, qpad, n_tiles, row_parts, decay, \
+    hipLaunchKernelGGL((score_stream_kernel<D, NKB>), grid, block, 0, s, g, sl, kbs, Q, max_chunk, tail_rows, qpad, row_parts, decay, \
                        (const bf16_t*)b.Qr, (const bf16_t*)b.Kr, (const bf16_t*)b.Krc, b.negt, b.mu, b.mu_chunk, b.attn_part)
     if (g.d == 128) { if (narrow) CKV_SCORE(128, 1); else CKV_SCORE(128, 2); }
     else { if (narrow) CKV_SCORE(64, 1); else CKV_SCORE(64, 2); }
 #undef CKV_SCORE
     if (row_parts)
-        hipLaunchKernelGGL(score_merge_kernel, dim3(n_tiles, BH), dim3(keys), 0, s, g, sl, max_chunk, n_tiles, row_parts, decay, b.attn_part, b.mu,
+        hipLaunchKernelGGL(score_merge_kernel, dim3(n_tiles, BH), dim3(keys), 0, s, g, sl, kbs, max_chunk, row_parts, decay, b.attn_part, b.mu,
                            b.mu_chunk);
 }
 

@@ -187,6 +187,11 @@ void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, 
         rank += cnt;
     }
     if (with_chunk) add(0, Q, n, 1);                 // chunk key i is rotated to i and sits at n + i
+    int tiles = 0;
+    for (int i = 0; i < kMaxSegments; ++i) {
+        out.tile0[i] = i < out.n ? tiles : INT32_MAX;
+        if (i < out.n) tiles += (out.s[i].len + out.pad[i] + 63) / 64;
+    }
 }
 
 void plan_insert(const Geom& g, const UpdatePlan& plan, DecodeInsert& out)
