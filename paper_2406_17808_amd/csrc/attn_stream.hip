@@ -189,9 +189,7 @@ __device__ inline void write_score_offset(const ScoreOffsets& so, size_t head, i
 // to part_o / part_ml, and attn_merge_kernel combines them.
 // SP: single-pass scores (needs Q % 256 == 0 and no SPLIT: a row block is one head's 256 tokens; and
 // every row of the chunk carrying EMA weight, so that every row block takes part).
-// QC: the rotated copies of the queries that the exact score pass reads exist for every row of the
-// chunk (all of them carry EMA weight): the kernel reads its queries there.
-template <int D, bool DBG, bool SPLIT, bool SP, bool QC>
+template <int D, bool DBG, bool SPLIT, bool SP>
 __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     Geom g, SegList sl, int Q, int tiles_per_bh, const bf16_t* __restrict__ q, const bf16_t* __restrict__ Qr, const float4* __restrict__ rope_t,
     int rope_rows, float qscale, const bf16_t* __restrict__ Kt, const bf16_t* __restrict__ Vt, bf16_t* __restrict__ out, float* __restrict__ lse,
@@ -213,9 +211,9 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
 
     const int BH = g.B * g.Hkv;
     // consecutive workgroups: different KV heads; row blocks that see more of the chunk (longer loops) start first
-    const int n_tiles = (int)(gridDim.x / BH) / (SPLIT ? n_split : 1);
-    const int rest = (int)(blockIdx.x / BH);
-    const int bh = blockIdx.x % BH, split = SPLIT ? rest % n_split : 0, tile = n_tiles - 1 - (SPLIT ? rest / n_split : rest);
+    const uint32_t rest = blockIdx.x / (uint32_t)BH;
+    const int n_tiles = (int)(gridDim.x / (uint32_t)BH), tile = n_tiles - 1 - (int)rest, bh = (int)(blockIdx.x - rest * (uint32_t)BH);
+    const int split = SPLIT ? (int)blockIdx.y : 0;
     const int b = bh / g.Hkv, hk = bh % g.Hkv;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l32 = l & 31, half = l >> 5;
     const int GQ = g.G * Q;
@@ -227,13 +225,14 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     const bool qvalid = r_row < GQ;
     const int rc = min(r_row, GQ - 1);
     const int qh = hk * g.G + rc / Q, qi = rc % Q;
-    int wave_imax, wave_imin, wg_imax;
+    int wave_imax, wave_imin, wg_imax, wg_imin;
     {
         const int r_lo = min(tile * BM + wave * 32, GQ - 1), r_hi = min(tile * BM + wave * 32 + 31, GQ - 1);
         if (r_lo / Q == r_hi / Q) { wave_imin = r_lo % Q; wave_imax = r_hi % Q; }
         else { wave_imin = 0; wave_imax = Q - 1; }
         const int w_lo = min(tile * BM, GQ - 1), w_hi = min(tile * BM + BM - 1, GQ - 1);
         wg_imax = (w_lo / Q == w_hi / Q) ? w_hi % Q : Q - 1;
+        wg_imin = (w_lo / Q == w_hi / Q) ? w_lo % Q : 0;
     }
 
     f32x16_t o[DB];
@@ -283,14 +282,17 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     // rotary partners (element + D/2) are the fragment of step ks + KS/2 of the same lane.  The
     // arithmetic is that of rotate_queries (scale first, then the rotation, then one rounding), which
     // writes the same values for the rows the score kernel reads.
+    // Row blocks whose rows all carry EMA weight find them rotated, among the copies that kv_pack_kernel wrote for the
+    // exact score pass: the last rows of a chunk, whose workgroups have the most tiles.
+    const bool copies = !SP && wg_imin >= Q - so.tail;
     Frag qf[KS];
     float qn2 = 0.f;      // this lane's half of the squared norm of its (scaled) query, summed by the first load_q
     auto load_q = [&](const Seg& sg) {
         qn2 = 0.f;
-        if constexpr (QC) {
+        if (copies) {
             // 8 loads a reload instead of 24 and no arithmetic: the 16 loads of (cos, sin) are most of what a
-            // reload costs, with all eight waves of the workgroup stopped.  4096 tokens against 16K slots: 1034 ->
-            // 1016 us; 512 against 8K, whose workgroups have 34 tiles each: 78.5 -> 74.1.
+            // reload costs, with all eight waves of the workgroup stopped (2.0 us, 1.0 to 1.3 so).  4096 tokens against 16K slots:
+            // 1034 -> 1016 us; 512 against 8K, whose workgroups have 34 tiles each: 78.5 -> 74.1.
             const bf16_t* qsrc = Qr + ((((size_t)sg.qvar * g.B + b) * g.Hq + qh) * Q + qi) * D + half * 8;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) qf[ks].u = *reinterpret_cast<const u32x4_t*>(qsrc + ks * 16);
@@ -491,7 +493,7 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     // this lane's row of the partial results
     const size_t prow = ((((size_t)split * BH + bh) * n_tiles + tile) * BM) + wave * 32 + l32;
     if (SPLIT) {
-        const int tb = (int)((long long)NT * split / n_split), te = (int)((long long)NT * (split + 1) / n_split);
+        const int tb = (int)((uint32_t)(NT * split) / (uint32_t)n_split), te = (int)((uint32_t)(NT * (split + 1)) / (uint32_t)n_split);   // (at most 2^22 tiles, 256 splits)
         if (tb == te) {                  // nothing to do (uniform for the workgroup): an empty partial result
             if (half == 0) { part_ml[prow * 2] = 0.f; part_ml[prow * 2 + 1] = 0.f; }
             return;
@@ -539,12 +541,10 @@ __global__ __launch_bounds__(kSWaves * 64, 1) void attn_stream_kernel(
     // first: with everything in front of them, a workgroup began its first product 8 to 11 us after its start.
     copy_tile(kt_bh, lds_k, 0, 0);
     // the largest squared key norm among the tiles of this workgroup
-    float kn2 = 0.f;
-    {
-        const float* kn = Knorm2 + (size_t)bh * tiles_per_bh + (SPLIT ? tile_first : 0);
-        for (int i = tid; i < NT; i += kSWaves * 64) kn2 = fmaxf(kn2, kn[i]);
-    }
+    const float* kn = Knorm2 + (size_t)bh * tiles_per_bh + (SPLIT ? tile_first : 0);
+    float kn2 = kn[min(tid, NT - 1)];
     load_q(it1.sg);
+    for (int i = tid + kSWaves * 64; i < NT; i += kSWaves * 64) kn2 = fmaxf(kn2, kn[i]);
     int q_var = it1.sg.qvar;   // the rotation the query fragments hold (two segments may share one)
     wait_vm<0>();
     __builtin_amdgcn_sched_barrier(0);
@@ -940,23 +940,20 @@ void launch_attn_stream(const Geom& g, const DevBuffers& b, const SegList& sl, i
     constexpr int BM = kSWaves * 32;
     const int tiles = (g.G * Q + BM - 1) / BM;
     const int n_split = attn_splits(g, Q, b.opt_attn_splits, packed_tiles(sl));
-    const dim3 grid(tiles * g.B * g.Hkv * n_split), block(kSWaves * 64);
+    const dim3 grid(tiles * g.B * g.Hkv, n_split), block(kSWaves * 64);
     float* part_o = b.attn_part;
     float* part_ml = b.attn_part + (size_t)kAttnPartRows * g.d;
-    // kv_pack_kernel wrote rotated copies of the last tail_rows rows, for the exact score pass
-    const bool copies = !single_pass && tail_rows >= Q;
-#define CKV_ATTN(D, DBG, SPLIT, SP, QC, dbg)                                                                                                  \
-    hipLaunchKernelGGL((attn_stream_kernel<D, DBG, SPLIT, SP, QC>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q,               \
+#define CKV_ATTN(D, DBG, SPLIT, SP, dbg)                                                                                                  \
+    hipLaunchKernelGGL((attn_stream_kernel<D, DBG, SPLIT, SP>), grid, block, 0, s, g, sl, Q, tiles_per_bh, (const bf16_t*)q,               \
                        (const bf16_t*)b.Qr, (const float4*)b.rope_t, b.rope_rows, qscale, (const bf16_t*)b.Kt, (const bf16_t*)b.Vt, (bf16_t*)out, \
                        b.lse, dbg, n_split, part_o, part_ml, b.knorm2, so, sp)
-#define CKV_ATTN_D(DBG, SPLIT, SP, QC, dbg)                                                            \
+#define CKV_ATTN_D(DBG, SPLIT, SP, dbg)                                                            \
     do {                                                                                               \
-        if (g.d == 128) CKV_ATTN(128, DBG, SPLIT, SP, QC, dbg); else CKV_ATTN(64, DBG, SPLIT, SP, QC, dbg); \
+        if (g.d == 128) CKV_ATTN(128, DBG, SPLIT, SP, dbg); else CKV_ATTN(64, DBG, SPLIT, SP, dbg); \
     } while (0)
     long long* const no_dbg = nullptr;
     if (n_split > 1) {
-        if (copies) CKV_ATTN_D(false, true, false, true, no_dbg);
-        else CKV_ATTN_D(false, true, false, false, no_dbg);
+        CKV_ATTN_D(false, true, false, no_dbg);
 #define CKV_MERGE(D, N)                                                                                                                            \
     hipLaunchKernelGGL((attn_merge_kernel<D, N>), dim3((g.G * Q + 1024 / D - 1) / (1024 / D), g.B * g.Hkv), dim3(kMergeThreads), 0, s, g, Q, tiles, \
                        n_split, BM, part_o, part_ml, (bf16_t*)out, b.lse, so)
@@ -968,9 +965,8 @@ void launch_attn_stream(const Geom& g, const DevBuffers& b, const SegList& sl, i
 #ifdef CASCADE_KV_ATTN_PHASE_TIMING   // development builds only: per-phase cycle counts of one workgroup
     if (g.d == 128) {
         long long* dbg = (long long*)b.move_stage;
-        if (single_pass) CKV_ATTN(128, true, false, true, false, dbg);
-        else if (copies) CKV_ATTN(128, true, false, false, true, dbg);
-        else CKV_ATTN(128, true, false, false, false, dbg);
+        if (single_pass) CKV_ATTN(128, true, false, true, dbg);
+        else CKV_ATTN(128, true, false, false, dbg);
         long long h[16];
         (void)hipStreamSynchronize(s);
         (void)hipMemcpy(h, dbg, sizeof(h), hipMemcpyDeviceToHost);
@@ -981,9 +977,8 @@ void launch_attn_stream(const Geom& g, const DevBuffers& b, const SegList& sl, i
         return;
     }
 #endif
-    if (single_pass) CKV_ATTN_D(false, false, true, false, no_dbg);      // (the caller has checked attn_single_pass_ok)
-    else if (copies) CKV_ATTN_D(false, false, false, true, no_dbg);
-    else CKV_ATTN_D(false, false, false, false, no_dbg);
+    if (single_pass) CKV_ATTN_D(false, false, true, no_dbg);      // (the caller has checked attn_single_pass_ok)
+    else CKV_ATTN_D(false, false, false, no_dbg);
 #undef CKV_ATTN_D
 #undef CKV_ATTN
 }
