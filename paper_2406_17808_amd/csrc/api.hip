@@ -128,6 +128,7 @@ static WorkspaceBytes carve(const cascade_config* c, const Geom& g, char* state_
         b.opart = (float*)take(BHq * (size_t)splits * g.d * 4);
     }
     off = std::max(off, prefill_end);
+    const size_t behind_prefill = off - prefill_end;
     b.knorm2 = (float*)take(BH * (size_t)vt_tiles * 4);
     b.lse = (float*)take(BHq * mc * 4);
     b.mu_chunk = (float*)take(BH * mc * 4);
@@ -143,6 +144,9 @@ static WorkspaceBytes carve(const cascade_config* c, const Geom& g, char* state_
     const int move_stage_rows = (g.N + 1) * ((int)mc + 1);    // every cascade and the sinks: at most max_chunk + 1 entries each
     b.move_stage = take(g.d % 16 == 0 ? BH * (size_t)move_stage_rows * (2 * g.d * elem + 8) : 0);
     bytes.shared = off;
+    const size_t stage_bytes = g.d % 16 == 0 ? BH * (size_t)move_stage_rows * (2 * g.d * elem + 8) : 0;
+    b.f32_part = (float*)(stage_bytes >= behind_prefill ? b.move_stage : base ? base + prefill_end : nullptr);
+    b.f32_part_floats = std::max(stage_bytes, behind_prefill) / 4;
     b.rope_rows = rope_rows;
     b.dec_splits = splits;
     b.vt_tiles = vt_tiles;

@@ -40,6 +40,8 @@ struct DevBuffers {
     int32_t* winners;// [B,Hkv,N,max_chunk+1]
     void* move_stage;// [B,Hkv,move_stage_rows] x (K row, V row, score, id): sources of the update's moves, gathered before any is overwritten
     int move_stage_rows;
+    float* f32_part; // [f32_part_floats] fp32 MFMA path: partial results of a split attention launch, in memory that nothing uses at that
+    size_t f32_part_floats; // time: the staging rows of the update, or the decode scratch behind the prefill scratch
     // decode scratch (in the memory of the per-call scratch of the prefill path)
     float* logits;   // [B,Hkv,decode_max_tiles,32,decode_logit_heads] (the stride is the number of tiles of the step)
     float* part;     // [B,Hq,dec_splits+1,2] (max, sum) of every split, and the own logit

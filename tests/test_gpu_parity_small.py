@@ -740,6 +740,55 @@ def test_f32_matrix_kernels(oracle_mod, d, G, Hkv, sizes, reduce_mean, chunks):
     run.close()
 
 
+@pytest.mark.parametrize("d,G,max_chunk,chunks", [(64, 1, 64, [64, 1, 17, 33]), (64, 4, 4, [4, 1, 3]), (128, 1, 4, [4, 1, 3]), (128, 2, 64, [64, 1, 17, 33])])
+def test_f32_split_attention(oracle_mod, d, G, max_chunk, chunks):
+    """fp32 launches whose tiles are shared by several workgroups, at the edges of 16-row blocks and 16-key tiles; the partial
+    results lie in the staging rows of the update (chunks of 64) or behind the prefill scratch (chunks of 4)."""
+    import torch
+    from gpu_harness import ParityRun
+    cfg = B.make_config(batch=1, n_q_heads=2 * G, n_kv_heads=2, head_dim=d, dtype=B.CASCADE_F32, n_sink=5, cascade_sizes=[1101, 300],
+                        ema_beta=0.95, rope_base=10000.0, max_chunk=max_chunk, keep_update_scores=1)
+    run = ParityRun(cfg, one_step_ahead=True)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(d + G)
+    for _ in range(2000 // max_chunk):
+        run.advance_gpu_only(*(torch.randn((1, max_chunk, h, d), generator=gen, device="cuda:0") for h in (2 * G, 2, 2)))
+    run.sync_oracle_from_gpu()
+    rng = np.random.default_rng(d + G)
+    out_tol, score_tol = _tolerances(cfg)
+    for step, n in enumerate(chunks):
+        rep = run.step(*_inputs(rng, cfg, n))
+        assert rep.replay_exact, step
+        assert rep.out_err <= out_tol and rep.score_err <= score_tol, (step, rep)
+    run.close()
+
+
+@pytest.mark.parametrize("d,at,value", [(64, 5, float("inf")), (128, 30, float("nan"))])
+def test_f32_split_rows_do_not_see_later_values(d, at, value):
+    """The same launches: a value that is not finite in a token of the chunk reaches the rows that see it and no other."""
+    import torch
+    from paper_2406_17808_amd.cache import CascadeKVCache
+    cfg = B.make_config(batch=1, n_q_heads=2, n_kv_heads=2, head_dim=d, dtype=B.CASCADE_F32, n_sink=5, cascade_sizes=[1101, 300],
+                        ema_beta=0.95, rope_base=10000.0, max_chunk=64)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(at)
+    q, k, v = (torch.randn((1, 40, 2, d), generator=gen, device="cuda:0") for _ in range(3))
+    odd = v.clone()
+    odd[:, at, 1, 3] = value
+    fill = [torch.randn((3, 1, 64, 2, d), generator=gen, device="cuda:0") for _ in range(24)]
+    outs = []
+    for x in (v, odd):
+        c = CascadeKVCache(cfg)
+        for f in fill:
+            c.prefill_chunk(f[0], f[1], f[2])
+        outs.append(c.prefill_chunk(q, k, x))
+        c.close()
+    sees = torch.zeros_like(outs[0], dtype=torch.bool)
+    sees[:, at:, 1, 3] = True
+    assert torch.isfinite(outs[0]).all() and not torch.isfinite(outs[1][sees]).any()
+    assert (outs[1][~sees] - outs[0][~sees]).abs().max() <= 40 * 2.0 ** -24 * v.abs().max()
+
+
 @pytest.mark.parametrize("d,G,at,value", [(64, 1, 5, float("inf")), (64, 3, 16, float("nan")), (128, 2, 30, float("-inf")), (128, 1, 39, float("nan"))])
 def test_f32_chunk_rows_do_not_see_later_values(d, G, at, value):
     """An infinite or undefined value in a token of the chunk reaches the rows that see the token and no other: the rows
