@@ -88,7 +88,7 @@ static const char* pack(const Geom& g, const HostState& st, int Q, const PackedC
         if (runs.first[r] < 0 || runs.first[r] + (r + 1 < runs.n ? runs.ahead[r + 1] : runs.total) - runs.ahead[r] > n) wrong = "a run names tiles that do not exist";
     if (total > runs.total) wrong = "the runs hold fewer tiles than they name";
     if (rows != st.n_cached(g)) wrong = "the segments do not hold all cached rows";
-    if (lay.full && n != lay.cache_tiles + (Q + 63) / 64) wrong = "the segments do not have the tiles of the layout";
+    if (lay.settled && n != lay.cache_tiles + (Q + 63) / 64) wrong = "the segments do not have the tiles of the layout";
     if (n > max_tiles) wrong = "more tiles than the workspace holds";
     *tiles_packed += runs.total;
     return wrong;
@@ -124,7 +124,7 @@ static int packing_case(int seed, int kind, long* tiles_packed)
     HostState st;
     PackedCopies pc;
     pc.own = kind != 1;
-    pc.may_fix = kind != 2;
+    pc.any_order = kind != 2;
     std::vector<std::vector<int>> packed;
     const int max_tiles = (g.slots + cfg.max_chunk) / 64 + kMaxSegments;
     int left = (largest << g.N) + 700;
