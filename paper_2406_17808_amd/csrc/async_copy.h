@@ -50,6 +50,15 @@ __device__ inline void counted_store_f32(void* base, uint32_t voff, float value)
     asm volatile("global_store_dword %0, %1, %2" : : "v"(voff), "v"(value), "s"(base) : "memory");
 }
 
+// A 16-byte store, one of the same sequence, that does not stay in the L2 as a changed line: what is written beside a
+// stream of reads reaches memory in the order of the stores, not in that of the evictions.  (The s_nop keeps a vector
+// instruction that follows from overwriting value: the compiler looks for that hazard only behind its own stores.)
+typedef __attribute__((ext_vector_type(4))) float store_f32x4_t;
+__device__ inline void store_16_through(void* p, store_f32x4_t value)
+{
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(value) : "memory");
+}
+
 template <int N> __device__ inline void wait_vm()   // at most N vector memory operations outstanding
 {
     static_assert(N >= 0 && N < 64, "vmcnt range");

@@ -182,7 +182,17 @@ struct OwnLogits {
 // workgroup ended 10.0 us after it began: 3.4 until its last copy was issued (a scalar load for every run in the list, two
 // 64-bit divisions), 1.5 for queries that came behind the tiles, 2.2 for the second tile, 2.0 where a wave had a third;
 // now 6.0, in the splits with a tile more 7.1.  us a step with decode_finish, before and after: 8K slots 19.1 -> 14.2, a layer of
-// 4K slots 16.2 -> 11.9 (where the host's calls are the limit), 8 sequences of 16K slots 109.6 -> 103.8, 32 of 65K 1655 -> 1656.
+// 4K slots 16.2 -> 11.9 (where the host's calls are the limit), 8 sequences of 16K slots 109.6 -> 103.8.
+//
+// On a large cache the logits cost far more than their bytes: without their stores (a sixteenth of the bytes read,
+// for groups of 4) a step of 32 sequences of 65K slots took 1312 us, with them 1660: memory turns round for every
+// few of them.  So a wave keeps the logits of HOLD tiles in registers and writes them at once, past the L2, which would put
+// the lines out one by one later on: 8 tiles 1607, 16 tiles 1565, 32 tiles (R = 8) 1520, 40 to 48 the same; 32 tiles by way
+// of the L2 1623.  8 sequences of 16K slots 105.4 -> 95.5.  No lane is moved for it: the queries stand in all column groups of
+// the product, so each group of MAXG columns keeps the tile that is its turn.  Where no wave has more tiles than one
+// register holds, R = 1 does it, which is 0.4 to 0.8 us less (8K slots 13.9 -> 13.2, before 13.1; 32 sequences, 40
+// tiles a workgroup, one head a KV head 35.4 -> 34.3); its few stores go through the L2 but for groups of 8 (one head 34.2 us
+// against 34.7 past it, 8 heads 47.6 against 46.8).
 //
 // The piece permutations (16-byte pieces of a staged row): the 16 rows of a K fragment read, and the
 // 8 rows one half of a wave reads in a transposing read, fall into different banks.
@@ -246,7 +256,7 @@ constexpr float kDecRescale = 8.f;
 constexpr int kAttendThreads = 512;
 constexpr int kAttendWaves = kAttendThreads / 64;
 
-template <int D, int MAXG>
+template <int D, int MAXG, int R>
 __global__ __launch_bounds__(kAttendThreads, 1) void decode_attend_kernel(
     Geom g, DecodeRuns runs, Splits sp, float qscale, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k_new,
     const bf16_t* __restrict__ Kr, const bf16_t* __restrict__ Vc, const float2* __restrict__ rope, float* __restrict__ logits,
@@ -258,7 +268,9 @@ __global__ __launch_bounds__(kAttendThreads, 1) void decode_attend_kernel(
     constexpr int RPI = 64 / PPR;                  // rows per copy instruction
     constexpr int kStage = kDecRows * D * 2;       // bytes of a staged K or V tile
     constexpr int NC = kStage / 1024;              // copies per stage
-    constexpr int NS = 2;                          // stores of logits per tile
+    constexpr int P = 16 / MAXG, HOLD = P * R;         // tiles whose logits share a register, tiles a wave holds
+    constexpr int NS = 2 * R;                      // stores when all of them leave
+    constexpr bool kThrough = R > 1 || MAXG == 8;  // whether they pass the L2 by
     constexpr int NQ = (MAXG * D * 2 + 1023) / 1024;   // copies that bring the group's queries
     constexpr int W = kAttendWaves, DEPTH = 8192 / kStage;
     constexpr int kLds = 160 * 1024, kFixed = W * DEPTH * 2 * kStage + W * (NQ * 1024 + D * 4) + W * 16 * 8;
@@ -355,8 +367,10 @@ __global__ __launch_bounds__(kAttendThreads, 1) void decode_attend_kernel(
     float m = -INFINITY, lsum = 0.f;               // maximum of head n; this lane's part of its sum
     DFrag qf[KS];
     int q_rot = -1;
-    float* lbase = logits + (size_t)bh * n_tiles * (kDecRows * MAXG) + (n * 4 + c) * 4;
+    const int nh = n % MAXG, np = n / MAXG;        // head of this lane; which of the P tiles in a register is its own
+    df32x4_t held[R][2];                           // logits of the tiles since the last stores
     int done = 0;
+    float* lbase = logits + ((size_t)bh * n_tiles + np * W) * (kDecRows * MAXG) + (nh * 4 + c) * 4;
 #pragma nounroll                                   // (nor peeled: a second copy of the loop is fetched with a cold cache)
     while (cons.tile < t_end) {
         const bool in_spare = has_spare && done == DEPTH;
@@ -372,7 +386,7 @@ __global__ __launch_bounds__(kAttendThreads, 1) void decode_attend_kernel(
             if (done == 0) { if (next1) wait_vm_fenced<4 * NC>(); else wait_vm_fenced<2 * NC>(); }
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) qf[ks].u = du32x4_t{0u, 0u, 0u, 0u};
-            if (n < g.G) {
+            if (nh < g.G) {
                 float4 w[KS / 2][4];               // (cos, sin) of 8 rotary pairs per step
                 if (done == 0) {
                     const float* cs = reinterpret_cast<const float*>(&csbuf[wave][0]);
@@ -387,7 +401,7 @@ __global__ __launch_bounds__(kAttendThreads, 1) void decode_attend_kernel(
 #pragma unroll
                         for (int x = 0; x < 4; ++x) w[ks][x] = *reinterpret_cast<const float4*>(cs + ks * 32 + c * 8 + 2 * x);
                 }
-                const bf16_t* qh = reinterpret_cast<const bf16_t*>(&qbuf[wave][0]) + n * D;
+                const bf16_t* qh = reinterpret_cast<const bf16_t*>(&qbuf[wave][0]) + nh * D;
 #pragma unroll
                 for (int ks = 0; ks < KS / 2; ++ks) {
                     const int e = ks * 32 + c * 8;
@@ -408,10 +422,11 @@ __global__ __launch_bounds__(kAttendThreads, 1) void decode_attend_kernel(
                 }
             }
         }
-        // K of this tile has landed.  Issued after it: V of this tile, K and V of the tiles on their way, and (once
-        // a stage has been filled again) the stores of DEPTH tiles.  Counting fewer than are outstanding only waits longer.
-        if (done >= DEPTH) { if (next1) wait_vm_fenced<3 * NC + DEPTH * NS>(); else wait_vm_fenced<NC + DEPTH * NS>(); }
-        else               { if (next1) wait_vm_fenced<3 * NC>(); else wait_vm_fenced<NC>(); }
+        // K of this tile has landed.  Issued after it: V of this tile, K and V of the tiles on their way, and (while
+        // these are the copies that were on their way then) the stores.  Counting fewer than are outstanding only waits longer.
+        const bool stored = done >= HOLD && done % HOLD < DEPTH;
+        if (stored) { if (next1) wait_vm_fenced<3 * NC + NS>(); else wait_vm_fenced<NC + NS>(); }
+        else        { if (next1) wait_vm_fenced<3 * NC>(); else wait_vm_fenced<NC>(); }
         const unsigned char* kp = in_spare ? &spare[0][0] : ring_w + 2 * stage * kStage;
         // (all fragments of a product are read before it starts: read two ahead, as the compiler would, a tile takes twice as long)
         DFrag kf[2][KS];
@@ -427,11 +442,22 @@ __global__ __launch_bounds__(kAttendThreads, 1) void decode_attend_kernel(
 #pragma unroll
             for (int gi = 0; gi < 2; ++gi) s[gi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[gi][ks].v, qf[ks].v, s[gi], 0, 0, 0);
         if (more) issue(kbh, k_off, prod, ring_lds + 2 * stage * kStage);
-        // the logits leave (lane 0 always stores: the counts above and below rely on NS stores per tile)
-        if (n < MAXG) {
-            float* lt = lbase + (size_t)cons.tile * (kDecRows * MAXG);
+        // The logits wait in registers (every column group has the products of all heads) and leave together: all NS stores of
+        // HOLD tiles, or, behind the last tile, those that there are (two at least).
 #pragma unroll
-            for (int gi = 0; gi < 2; ++gi) *reinterpret_cast<df32x4_t*>(lt + gi * (16 * MAXG)) = s[gi];
+        for (int r = 0; r < R; ++r)
+            if (done / P % R == r && done % P == np) { held[r][0] = s[0]; held[r][1] = s[1]; }
+        const bool full = done % HOLD == HOLD - 1;
+        if (full || cons.tile + W >= t_end) {
+            float* lt = lbase + (ptrdiff_t)(cons.tile - done % HOLD * W) * (kDecRows * MAXG);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (r * P <= done % HOLD && r * P + np <= done % HOLD)
+#pragma unroll
+                    for (int gi = 0; gi < 2; ++gi) {
+                        float* to = lt + r * P * W * (kDecRows * MAXG) + gi * (16 * MAXG);
+                        if (kThrough) store_16_through(to, held[r][gi]); else *reinterpret_cast<df32x4_t*>(to) = held[r][gi];
+                    }
         }
         if (cons.nvalid < kDecRows) {
 #pragma unroll
@@ -461,14 +487,12 @@ __global__ __launch_bounds__(kAttendThreads, 1) void decode_attend_kernel(
                 lsum += p0 + p1;
                 pf.u[2 * gi + x] = dec_pack_bf16(p0, p1);
             }
-        // V of this tile has landed.  Issued after it: K and V of the tiles on their way, K of the one that takes this
-        // stage, the stores of DEPTH tiles (of this one at least)
-        if (done >= DEPTH - 1) {
-            if (more) wait_vm_fenced<(2 * DEPTH - 1) * NC + DEPTH * NS>();
-            else if (next1) wait_vm_fenced<2 * NC + DEPTH * NS>();
-            else wait_vm_fenced<DEPTH * NS>();
-        } else {
+        // V of this tile has landed.  Issued after it: K and V of the tiles on their way, K of the one that takes this stage, the
+        // stores of the last DEPTH tiles and this one
+        if (done + 1 >= HOLD && (done + 1) % HOLD < DEPTH) {
             if (more) wait_vm_fenced<(2 * DEPTH - 1) * NC + NS>(); else if (next1) wait_vm_fenced<2 * NC + NS>(); else wait_vm_fenced<NS>();
+        } else {
+            if (more) wait_vm_fenced<(2 * DEPTH - 1) * NC>(); else if (next1) wait_vm_fenced<2 * NC>(); else wait_vm_fenced<2>();
         }
         const unsigned char* vp = in_spare ? &spare[kSpare ? 1 : 0][0] : ring_w + (2 * stage + 1) * kStage;
         DFrag vf[DB];
@@ -491,7 +515,6 @@ __global__ __launch_bounds__(kAttendThreads, 1) void decode_attend_kernel(
         ++done;
         cons.advance(lr, W);
     }
-    wait_vm_fenced<0>();
     if (split == 0) own.finish(g, b, hk, qscale, part, n_splits);
     lsum = sum_groups(lsum);
     // The waves' results meet in LDS once: every wave leaves its sums as they are in its own ring (nothing is on its way there
@@ -996,9 +1019,13 @@ void launch_decode_attend(const Geom& g, int dtype, const DevBuffers& b, const S
 #define CKV_ATTEND_F32(T, D, MG)                                                                                          \
     hipLaunchKernelGGL((decode_attend_f32_kernel<D, MG>), grid, block, 0, s, g, runs, sp, qscale, (const T*)q, \
                        (const T*)k, (const T*)b.Kr, (const T*)b.Vc, b.rope, b.logits, b.part, b.opart)
-#define CKV_ATTEND_MFMA(T, D, MG)                                                                                         \
-    hipLaunchKernelGGL((decode_attend_kernel<D, MG>), grid, dim3(kAttendThreads), 0, s, g, runs, sp, qscale, (const T*)q,     \
+    // Eight registers' worth of logits are held where some wave has more tiles than fit in one; both sides are measured at
+    // decode_attend_kernel
+    const bool hold = sp.each + (sp.more > 0) > kAttendWaves * (16 / decode_logit_heads(g));
+#define CKV_ATTEND_MFMA_R(T, D, MG, R)                                                                                    \
+    hipLaunchKernelGGL((decode_attend_kernel<D, MG, R>), grid, dim3(kAttendThreads), 0, s, g, runs, sp, qscale, (const T*)q,  \
                        (const T*)k, (const T*)b.Kr, (const T*)b.Vc, b.rope, b.logits, b.part, b.opart)
+#define CKV_ATTEND_MFMA(T, D, MG) if (hold) CKV_ATTEND_MFMA_R(T, D, MG, 8); else CKV_ATTEND_MFMA_R(T, D, MG, 1)
     if (dtype == CASCADE_F32) {
         if (g.d == 128) { CKV_DECODE_G(CKV_ATTEND_F32, float, 128) } else { CKV_DECODE_G(CKV_ATTEND_F32, float, 64) }
     } else {
@@ -1006,6 +1033,7 @@ void launch_decode_attend(const Geom& g, int dtype, const DevBuffers& b, const S
     }
 #undef CKV_ATTEND_F32
 #undef CKV_ATTEND_MFMA
+#undef CKV_ATTEND_MFMA_R
 }
 
 void launch_decode_finish(const Geom& g, int dtype, const DevBuffers& b, const SegList& sl, const DecodeInsert& ins, int n_splits, bool scores,

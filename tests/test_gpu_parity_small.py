@@ -673,6 +673,15 @@ def test_decode_waves_refill_their_ring(oracle_mod, d, G):
     _decode_after_fill(cfg, [512, 512, 512], 5, seqs=[0, 41])
 
 
+@pytest.mark.parametrize("d,G,sizes", [(128, 4, [650, 400, 200]), (64, 8, [2100, 1300, 900]), (128, 8, [2100, 1300, 900])])
+def test_decode_waves_hold_their_logits(oracle_mod, d, G, sizes):
+    """One split for each of 256 pairs, of about 40 or 137 tiles: more than eight waves hold in one register, or than 16 tiles a wave
+    that it holds at most for 8 heads (its logits then leave while copies are in flight, and the rest behind the last tile)."""
+    cfg = B.make_config(batch=64, n_q_heads=4 * G, n_kv_heads=4, head_dim=d, dtype=B.CASCADE_BF16, n_sink=5, cascade_sizes=sizes,
+                        ema_beta=0.9, rope_base=10000.0, max_chunk=512, keep_update_scores=1)
+    _decode_after_fill(cfg, [512] * (sum(c << i for i, c in enumerate(sizes)) // 512 + 1), 3, seqs=[0, 41])
+
+
 @pytest.mark.parametrize("d,G,sizes", [(128, 1, [130, 60]), (128, 4, [130, 60]), (128, 8, [130, 60]), (64, 4, [300, 150])])
 def test_decode_splits_of_one_tile_more_than_stages(oracle_mod, d, G, sizes):
     """One split for each of 256 pairs, of 8, 9 or 10 tiles at head size 128 and of 16, 17 or 18 at 64 as the ring heads move: as
