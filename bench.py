@@ -153,7 +153,7 @@ def prefill_bench(args, torch, B, wl):
                      "traffic_source": "profiles/attn_stream_kernel_prefill_1m_hbm_traffic.json (rocprofv3 --pmc runs, not this run)",
                      "flop_per_launch": sum(flops) / K, "avg_launch_ms": avg_s * 1e3},
         "end_to_end_mfma_frac": (sum(flops) / seconds) / MFMA_BF16_PEAK,
-        "roofline_update": {"bound": "hbm", "kernel": "gather_direct_kernel + scatter_kernel (plan_kernel + gather_kernel + scatter_kernel when a ring turns over within one chunk)",
+        "roofline_update": {"bound": "hbm", "kernel": "move_trees_kernel (gather_direct_kernel + scatter_kernel for trees of more than 256 slots, plan_kernel + gather_kernel + scatter_kernel when a ring turns over within one chunk)",
                             "achieved": upd_rate / 1e9, "peak": HBM_PEAK / 1e9, "unit": "GB/s", "frac": upd_rate / HBM_PEAK,
                             "basis": f"rows moved x {row_bytes} B (K, V, score, id) read once and written once",
                             "achieved_incl_rotated_copy": upd_rate_incl / 1e9,

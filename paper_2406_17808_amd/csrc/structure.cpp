@@ -242,7 +242,8 @@ void plan_trees(const UpdatePlan& plan, int capacity, MoveTrees& out)
 // 17.8 / 18.0; 64 of 16K 104.8 / 104.2; 256 of 8K 221 / 211 (5); d = 64, 8 heads of 16K 13.1 / 12.5, 64 of 16K 61.2 / 59.1.
 // fp32 (four tiles at a time): d = 128, 8 heads of 4K 46.7 / 46.4, 64 of 4K 117 / 126, 256 of 2K 267 / 280; d = 64, 8 of 4K
 // 31.9 / 31.7, but 64 of 4K 84.6 / 58.3 (11 splits).
-// Where even then there are hundreds of tiles for each of four waves, more rounds even out the CUs (256 x 65K slots: 8 splits 1656, 1 split 1676).
+// Where even then there are hundreds of tiles for each of four waves, more rounds even out the CUs (256 x 65K slots: 8 splits 1656, 1 split 1676; all
+// these before the attend kernel held its logits back, which takes up to a tenth off the large ones).
 // For a given number of rounds the cost falls with every split, so only the most splits of each number of
 // rounds are looked at: nine at most, 0.05 us of host time a step (all of up to 2048 split counts: 9.7).
 int decode_split_count(int pairs, int most, int n_tiles)
