@@ -232,7 +232,7 @@ static int init_context(const char* who, const cascade_config* cfg, const Geom& 
     ctx->f32_mfma = attn_f32_ok(g, cfg->dtype);
     if (const char* e = getenv("CASCADE_KV_SCALAR_ATTENTION")) if (e[0] == '1') ctx->mfma = ctx->f32_mfma = false;
     if (const char* e = getenv("CASCADE_KV_PACK_REUSE")) ctx->packed.reuse = e[0] != '0';   // 0: pack every tile for every chunk
-    ctx->packed.any_order = cfg->score_mode == CASCADE_SCORES_EXACT;
+    ctx->packed.may_fix = cfg->score_mode == CASCADE_SCORES_EXACT;
     ctx->buf.opt_attn_splits = 0;
     if (const char* e = getenv("CASCADE_KV_ATTN_SPLITS")) ctx->buf.opt_attn_splits = atoi(e);
     ctx->buf.opt_score_narrow = -1;
@@ -496,7 +496,7 @@ extern "C" int cascade_prefill_chunk(cascade_ctx* ctx, const void* dev_q, const 
         // scores); the attention kernel reads them where they cover the chunk, and otherwise rotates its queries itself
         if (!ctx->mfma) launch_prep(g, ctx->dtype, ctx->buf, sl, Q, qscale, dev_q, dev_k, dev_v, s);
         else {
-            if (lay.settled && packed_tiles_of(sl) != lay.cache_tiles + (Q + 63) / 64)
+            if (lay.full && packed_tiles_of(sl) != lay.cache_tiles + (Q + 63) / 64)
                 return fail(ctx, CASCADE_E_INTERNAL, "cascade_prefill_chunk: the segment list does not have the tiles of the packed layout");
             ctx->packed.valid = false;   // until this call has gone through
             if (!launch_kv_pack(g, ctx->buf, sl, runs, Q, qscale, single_pass ? Q : Q - tail, dev_q, dev_k, dev_v, s))

@@ -144,11 +144,11 @@ static int cut_of(int cap, int xi) { return std::min(32, (cap - xi) / 2); }
 // "Positional Encoding": the index inside the cache).  Stored keys are rotated to their
 // physical slot index, so within a run where (cache index - slot index) is constant the
 // queries need one rotation: by (own index) - (that constant).  The segments are listed in
-// physical order (the wrapped part of a ring before its oldest part) or, by_cascade, ring by ring from the first cascade
-// on: attention does not care in which order it meets the keys (single-pass scores do).  The
+// physical order (the wrapped part of a ring before its oldest part): attention does not care
+// in which order it meets the keys, and a full cache then always reads front to back.  The
 // wrapped part of a full ring is listed as [0, o) and [o, xi), o = xi mod 64, which fixes the
 // place of every 64-row tile of the ring (see PackedLayout, also for the other cut).
-void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, SegList& out, bool fixed, bool by_cascade)
+void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, SegList& out, bool fixed)
 {
     out.n = 0;
     out.n_qvar = 0;
@@ -165,24 +165,26 @@ void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, 
         s.start = start; s.len = len; s.qvar = v; s.chunk = chunk;
     };
     add(0, st.sink_fill, 0, 0);
-    int ranks[kMaxCascades];                         // cache index of the oldest item of every cascade
-    for (int c = g.N - 1, rank = st.sink_fill; c >= 0; rank += st.count[c--]) ranks[c] = rank;
-    for (int x = 0; x < g.N; ++x) {
-        const int c = by_cascade ? x : g.N - 1 - x;
-        const int rank = ranks[c], cnt = st.count[c], cap = g.cap[c], xi = st.xi[c], base = g.base[c];
+    int rank = st.sink_fill;                         // cache index of the oldest item of the cascade
+    for (int c = g.N - 1; c >= 0; --c) {
+        const int cnt = st.count[c], cap = g.cap[c], xi = st.xi[c], base = g.base[c];
         if (cnt < cap) {
             add(base, cnt, rank - base, 0);
-        } else if (fixed) {
-            const int o = xi % 64, cut = o ? 0 : cut_of(cap, xi), oldest = rank - (base + xi);
-            add(base, xi, rank + (cap - xi) - base, 0);
-            add(base + xi, cut, oldest, 0);
-            add(base + xi + cut, cap - xi - cut, oldest, 0, o + cut);
         } else {
+            if (fixed) {
+                const int o = xi % 64, cut = o ? 0 : cut_of(cap, xi), oldest = rank - (base + xi);
+                add(base, xi, rank + (cap - xi) - base, 0);
+                add(base + xi, cut, oldest, 0);
+                add(base + xi + cut, cap - xi - cut, oldest, 0, o + cut);
+                rank += cnt;
+                continue;
+            }
             const int o = with_chunk ? xi % 64 : 0, wrapped = rank + (cap - xi) - base;
             add(base, o, wrapped, 0);                                 // wrapped part: ring [0, xi), in two pieces (packed tiles only)
             add(base + o, xi - o, wrapped, 0);
             add(base + xi, cap - xi, rank - (base + xi), 0);          // oldest part: ring [xi, cap)
         }
+        rank += cnt;
     }
     if (with_chunk) add(0, Q, n, 1);                 // chunk key i is rotated to i and sits at n + i
     int tiles = 0;
@@ -266,35 +268,24 @@ int decode_split_count(int pairs, int most, int n_tiles)
     return best;
 }
 
-void packed_layout(const Geom& g, const HostState& st, PackedLayout& out, bool fixed, bool by_cascade)
+void packed_layout(const Geom& g, const HostState& st, PackedLayout& out, bool fixed)
 {
     out.fixed = fixed;
-    out.settled = st.sink_fill == g.n_sink;
+    out.full = st.sink_fill == g.n_sink;
     int tiles = (g.n_sink + 63) / 64;
-    bool filling = false;
-    for (int x = 0; x < g.N; ++x) {
-        const int c = by_cascade ? x : g.N - 1 - x;
-        const int cap = g.cap[c], cnt = st.count[c], o = cnt == cap ? st.xi[c] % 64 : 0;
-        if (cnt > 0 && filling) out.settled = false;             // a ring behind one that still grows has no fixed place
-        filling = filling || cnt < cap;
+    for (int c = g.N - 1; c >= 0; --c) {             // physical order: the last cascade first
+        if (st.count[c] != g.cap[c]) out.full = false;
+        const int o = st.xi[c] % 64;
         out.off[c] = o;
         out.tile0[c] = tiles;
-        if (cnt < cap) tiles += (cnt + 63) / 64;
-        else tiles += fixed ? 1 + (cap + 63) / 64 : (o > 0 ? 1 : 0) + (cap - o + 63) / 64;
+        tiles += fixed ? 1 + (g.cap[c] + 63) / 64 : (o > 0 ? 1 : 0) + (g.cap[c] - o + 63) / 64;
     }
-    if (!by_cascade && filling) out.settled = false;
     out.cache_tiles = tiles;
 }
 
 bool same_offsets(const Geom& g, const PackedLayout& a, const PackedLayout& b)
 {
     for (int c = 0; c < g.N; ++c) if (a.off[c] != b.off[c]) return false;
-    return true;
-}
-
-static bool all_full(const Geom& g, const HostState& st)
-{
-    for (int c = 0; c < g.N; ++c) if (st.count[c] < g.cap[c]) return false;
     return true;
 }
 
@@ -305,18 +296,13 @@ static bool all_full(const Geom& g, const HostState& st)
 // (a decode step, an update that was not followed) makes the copies invalid.  The cut does not depend on whether the
 // copies can be kept at all: contexts that share them (the layers of one workspace) follow the same rule and get the
 // same sums, but pack everything for every chunk either way.
-// Rings fill one after the other, the first cascade first, so in that order the tiles of a cache that is still filling keep
-// their places, too (40000 tokens in chunks of 512 through rings of 2K 11530 -> 11380 us; 2048 tokens on eight rings of 2K, five of
-// them full: packing 41 -> 25, where the fixed tiles cost the attention 8).  Full caches keep the physical order: the other one
-// took the calls on them 0.1 to 0.5 % longer.
 void plan_packing(const Geom& g, const HostState& st, int Q, const PackedCopies& pc, SegList& sl, PackedLayout& lay, TileRuns& runs)
 {
-    const bool by_cascade = pc.any_order && !all_full(g, st);
-    packed_layout(g, st, lay, false, by_cascade);
+    packed_layout(g, st, lay, false);
     bool partial = false;
-    if (lay.settled) {
-        bool possible = pc.any_order;    // (a last row that begins a tile cannot be cut)
-        for (int c = 0; c < g.N; ++c) possible = possible && (st.count[c] < g.cap[c] || st.xi[c] % 64 != 0 || cut_of(g.cap[c], st.xi[c]) > 0);
+    if (lay.full) {
+        bool possible = pc.may_fix;      // (a last row that begins a tile cannot be cut)
+        for (int c = 0; c < g.N; ++c) possible = possible && (st.xi[c] % 64 != 0 || cut_of(g.cap[c], st.xi[c]) > 0);
         if (pc.valid && !pc.lay.fixed && same_offsets(g, lay, pc.lay)) partial = true;
         else if (possible) {
             bool fixed = pc.valid && pc.lay.fixed;
@@ -326,13 +312,13 @@ void plan_packing(const Geom& g, const HostState& st, int Q, const PackedCopies&
                 UpdatePlan pl;
                 PackedLayout after;
                 plan_update(g, next, Q, pl);
-                packed_layout(g, next, after, false, by_cascade);
+                packed_layout(g, next, after, false);
                 fixed = !same_offsets(g, lay, after);
             }
-            if (fixed) packed_layout(g, st, lay, true, by_cascade);
+            if (fixed) packed_layout(g, st, lay, true);
         }
     }
-    build_segments(g, st, true, Q, sl, lay.fixed, by_cascade);
+    build_segments(g, st, true, Q, sl, lay.fixed);
     const int chunk_tiles = (Q + 63) / 64;
     if (partial && pc.own && pc.reuse) {
         runs = pc.stale;
@@ -348,31 +334,27 @@ void plan_packing(const Geom& g, const HostState& st, int Q, const PackedCopies&
 void packed_after_update(const Geom& g, const PackedLayout& lay, const HostState& before, const HostState& after, const UpdatePlan& pl, PackedCopies& pc)
 {
     pc.valid = false;
-    const bool by_cascade = pc.any_order && !all_full(g, before);
-    if (!lay.settled || by_cascade != (pc.any_order && !all_full(g, after))) return;
+    if (!lay.full) return;
+    pc.lay = lay;
     pc.stale.n = 0;
     pc.stale.total = 0;
-    packed_layout(g, after, pc.lay, lay.fixed, by_cascade);      // (a ring that begins to fill finds its place only now)
+    pc.valid = true;
     if (!lay.fixed) {
-        pc.valid = same_offsets(g, lay, pc.lay) && add_touched_tiles(g, pc.lay, pl, pc.stale);
+        pc.valid = add_touched_tiles(g, lay, pl, pc.stale);
         return;
     }
-    pc.valid = true;
     for (int c = 0; c < pl.N && pl.c[c].M > 0; ++c) {
         const CascStep& cs = pl.c[c];
-        const int xi = before.xi[c];
+        const int xi = before.xi[c], tiles = 1 + (cs.cap + 63) / 64;
         if (cs.J + cs.pre == 0) continue;
         // from the first row written to the tile the ring head now stands in, second listing included; a ring
-        // that starts over or has just become full, or whose newest item is its last row, is packed anew
-        int first = 0, last = (cs.cap + 63) / 64;
-        if (after.count[c] < cs.cap) {
-            first = before.count[c] / 64;
-            last = (after.count[c] - 1) / 64;
-        } else if (before.count[c] == cs.cap && !(xi + cs.J >= cs.cap || (cs.pre && xi == 0))) {
+        // that starts over, or whose newest item is its last row, is packed anew
+        int first = 0, last = tiles - 1;
+        if (!(xi + cs.J >= cs.cap || (cs.pre && xi == 0))) {
             first = (xi - cs.pre) / 64;
             last = std::min(last, after.xi[c] / 64 + 1);
         }
-        pc.valid = pc.valid && add_tile_run(pc.stale, pc.lay.tile0[c] + first, last - first + 1);
+        pc.valid = pc.valid && add_tile_run(pc.stale, lay.tile0[c] + first, last - first + 1);
     }
 }
 

@@ -54,14 +54,10 @@ void plan_trees(const UpdatePlan& plan, int capacity, MoveTrees& out);
 int decode_split_count(int pairs, int most, int n_tiles);
 
 // Runs of physical rows that share one query rotation, for the state BEFORE a chunk of Q tokens.
-// with_chunk: append the segment of the chunk's own keys.  fixed: cut for the fixed tiles of PackedLayout.  by_cascade: the
-// first cascade's runs first (otherwise in physical order, the last cascade's first).
-void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, SegList& out, bool fixed = false, bool by_cascade = false);
+// with_chunk: append the segment of the chunk's own keys.  fixed: cut for the fixed tiles of PackedLayout.
+void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, SegList& out, bool fixed = false);
 
-// Where the 64-row tiles of the packed K / V copies sit.  Once every ring is full they are listed in physical order; before
-// that, where the order is free, ring by ring from the first cascade on: a ring grows only when all before it are full and
-// all behind it are empty (an initial state may differ: it is not `settled`), so that every tile has its place as soon
-// as the sinks are full; those of the growing ring are rows 64k .. 64k + 63.  Two ways to cut a full ring:
+// Where the 64-row tiles of the packed K / V copies sit when every ring is full.  Two ways to cut a ring:
 //   by offset  build_segments lists it as [0, o), [o, xi), [xi, cap) with o = xi mod 64, so ring rows o + 64k ..
 //              o + 64k + 63 always form tile (o > 0) + k of the ring whatever xi is: as long as no o changes, a
 //              tile keeps its place and its content from chunk to chunk until one of its rows is written;
@@ -71,20 +67,20 @@ void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, 
 //              the ring has the same number of tiles.)  As xi moves on, tiles change place only where
 //              rows were written, and all of a ring's once it starts over.
 struct PackedLayout {
-    bool settled;
+    bool full;                    // sinks and every ring are full
     bool fixed;
     int off[kMaxCascades];        // o of every ring
     int tile0[kMaxCascades];      // first tile of every ring
     int cache_tiles;              // tiles of all cached rows; the chunk's tiles follow
 };
-void packed_layout(const Geom& g, const HostState& st, PackedLayout& out, bool fixed, bool by_cascade);
+void packed_layout(const Geom& g, const HostState& st, PackedLayout& out, bool fixed);
 bool same_offsets(const Geom& g, const PackedLayout& a, const PackedLayout& b);
 
 // What the packed copies hold from call to call, and what a chunk has to pack.
 struct PackedCopies {
     bool own = true;              // the copies belong to one context (if not, another layer overwrites them: everything is packed)
     bool reuse = true;            // tiles that are still valid are not packed again
-    bool any_order = true;        // single-pass scores depend on the order of visits: physical order, no fixed tiles
+    bool may_fix = true;          // fixed tiles may be used (single-pass scores depend on the order of visits: not there)
     bool valid = false;           // they hold every cache tile where `lay` puts it, except those named by `stale`
     PackedLayout lay;
     TileRuns stale;

@@ -246,7 +246,8 @@ def test_packed_tiles_hold_the_rows_of_their_segments(host_rules, seed):
     """Which tiles of the packed K / V copies a chunk packs again is decided from the structure alone.  The replay
     packs token numbers in their place and fails if a cached row is not where the attention kernel reads
     it: ring sizes on and off the tile grid, with and without sinks, rings that start over, chunks of any length; copies
-    of one context, shared between layers, of single-pass scores, and with decode steps between the chunks."""
+    of one context, shared between layers, of single-pass scores, and with decode steps between the chunks.  The
+    rows are listed in the order of their slots, in caches that fill, too."""
     res = subprocess.run([host_rules, "packing", str(seed)], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0, res.stderr
 
