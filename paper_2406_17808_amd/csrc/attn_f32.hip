@@ -9,6 +9,7 @@
 
 #include "launch.h"
 #include "mfma_util.h"
+#include "plan_core.h"
 
 namespace ckv {
 
@@ -104,8 +105,8 @@ __global__ __launch_bounds__(WAVES * 64, D == 64 ? 4 : 2) void attn_f32_kernel(G
     int t0 = 0, t1 = ft.first[sl.n - 1] + imax / kF32Keys + 1;               // tiles of this row block (the chunk is the last segment), of this split
     if (SPLIT) {
         const int all = t1;
-        t0 = (int)((uint32_t)(all * (int)blockIdx.z) / (uint32_t)n_split);
-        t1 = (int)((uint32_t)(all * (int)(blockIdx.z + 1)) / (uint32_t)n_split);
+        t0 = share_begin(all, (int)blockIdx.z, n_split);
+        t1 = share_begin(all, (int)blockIdx.z + 1, n_split);
     }
 
     f32x4_t o[DB];

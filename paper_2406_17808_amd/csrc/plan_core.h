@@ -12,6 +12,14 @@
 
 namespace ckv {
 
+// First of `all` tiles of share z when n workgroups divide them (z = n: all): floor(all z / n), without that product, which
+// 32 bits do not hold for fp32 caches of 2^27 slots (2^23 tiles) in 256 shares.
+__host__ __device__ inline int share_begin(int all, int z, int n)
+{
+    const uint32_t each = (uint32_t)all / (uint32_t)n, rest = (uint32_t)all - each * (uint32_t)n;
+    return (int)(each * (uint32_t)z + rest * (uint32_t)z / (uint32_t)n);
+}
+
 __host__ __device__ inline float ref_score(int ref, int slots, const float* mu, const float* mu_chunk)
 {
     return ref < slots ? mu[ref] : mu_chunk[ref - slots];

@@ -3,6 +3,7 @@
 //                  packs token numbers in the place of rows.  Exit code 0 = every row is where it is read.
 //   trees SEED     the update of a chunk in trees: workgroup after workgroup in a drawn order, each reading its slots' new
 //                  rows from the cache as it then is and writing them, against Alg. 2 token by token.
+//   shares         where the shares of workgroups that divide the tiles of a row block begin, against 64-bit arithmetic.
 //   splits         the split count of a decode step against the same costs looked at for every count, and its time.
 #include <stdio.h>
 #include <stdlib.h>
@@ -249,6 +250,20 @@ static int trees_case(int seed, long* updates, long* refused)
     return 0;
 }
 
+// ------------------------------------------------------------------ shares of a row block's tiles
+
+static int wrong_shares()
+{
+    const int most = (1 << 28) / 16 + 4096;          // 16-key tiles of the largest cache check_config accepts, and a chunk
+    int bad = 0;
+    for (int n = 1; n <= 256; ++n)
+        for (int x : {1, 2, n - 1, n, n + 1, 2 * n + 1, 1000, (1 << 22) + 1, (1 << 23) - 1, 1 << 23, (1 << 23) + 77, 1 << 24, most - 1, most}) {
+            if (x < 1) continue;
+            for (int z = 0; z <= n; ++z) bad += share_begin(x, z, n) != (int)((int64_t)x * z / n);
+        }
+    return bad;
+}
+
 // ------------------------------------------------------------------ splits of a decode step
 
 static int best_of_all_splits(int pairs, int most, int n_tiles)
@@ -306,6 +321,11 @@ int main(int argc, char** argv)
         printf("%ld updates in trees, %ld not\n", updates, refused);
         return bad || updates < refused / 4 ? 1 : 0;
     }
-    fprintf(stderr, "usage: host_rules packing SEED | trees SEED | splits\n");
+    if (argc == 2 && !strcmp(argv[1], "shares")) {
+        const int bad = wrong_shares();
+        printf("%d shares begin elsewhere\n", bad);
+        return bad ? 1 : 0;
+    }
+    fprintf(stderr, "usage: host_rules packing SEED | trees SEED | shares | splits\n");
     return 2;
 }

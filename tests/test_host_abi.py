@@ -261,6 +261,12 @@ def test_update_trees_are_independent(host_rules, seed):
     assert res.returncode == 0, res.stdout + res.stderr
 
 
+def test_shares_of_the_largest_caches(host_rules):
+    """The tiles of a row block divided over up to 256 workgroups: whole ranges, for as many tiles as a cache can have."""
+    res = subprocess.run([host_rules, "shares"], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
 def test_decode_split_count(host_rules):
     """Few split counts of a decode step are looked at; they give what looking at all of them gives, in little host time."""
     res = subprocess.run([host_rules, "splits"], capture_output=True, text=True, timeout=300)
