@@ -3,6 +3,7 @@
 //                  packs token numbers in the place of rows.  Exit code 0 = every row is where it is read.
 //   trees SEED     the update of a chunk in trees: workgroup after workgroup in a drawn order, each reading its slots' new
 //                  rows from the cache as it then is and writing them, against Alg. 2 token by token.
+//   large D CHUNK SIZE:PERIOD ...   how many updates of full chunks on a full cache are direct, with trees larger than any workgroup takes.
 //   shares         where the shares of workgroups that divide the tiles of a row block begin, against 64-bit arithmetic.
 //   splits         the split count of a decode step against the same costs looked at for every count, and its time.
 #include <stdio.h>
@@ -250,6 +251,33 @@ static int trees_case(int seed, long* updates, long* refused)
     return 0;
 }
 
+// Exit code 0: every one of 40 updates is direct and its trees are too large for 1024 threads, d / 16 for two slots.
+static int large_trees(int argc, char** argv)
+{
+    cascade_config cfg;
+    memset(&cfg, 0, sizeof(cfg));
+    cfg.batch = 1; cfg.n_q_heads = 1; cfg.n_kv_heads = 1; cfg.head_dim = atoi(argv[2]); cfg.dtype = CASCADE_F32;
+    cfg.n_sink = 3; cfg.max_chunk = atoi(argv[3]); cfg.ema_beta = 0.9f; cfg.rope_base = 10000.f; cfg.token_selection = 1;
+    for (int i = 4; i < argc; ++i, ++cfg.n_cascades)
+        if (sscanf(argv[i], "%d:%d", &cfg.cascade_sizes[cfg.n_cascades], &cfg.accept_period[cfg.n_cascades]) != 2) return 2;
+    std::string why;
+    if (check_config(&cfg, why) != CASCADE_OK) { fprintf(stderr, "%s\n", why.c_str()); return 1; }
+    Geom g;
+    make_geom(&cfg, g);
+    HostState st;
+    UpdatePlan pl;
+    while (st.n_cached(g) < g.slots) plan_update(g, st, cfg.max_chunk, pl);
+    int large = 0;
+    for (int i = 0; i < 40; ++i) {
+        plan_update(g, st, cfg.max_chunk, pl);
+        MoveTrees mt;
+        plan_trees(pl, 1024 / (g.d / 16) * 2, mt);
+        large += plan_is_direct(pl) && mt.wgs == 0;
+    }
+    printf("%d of 40 updates\n", large);
+    return large == 40 ? 0 : 1;
+}
+
 // ------------------------------------------------------------------ shares of a row block's tiles
 
 static int wrong_shares()
@@ -321,11 +349,12 @@ int main(int argc, char** argv)
         printf("%ld updates in trees, %ld not\n", updates, refused);
         return bad || updates < refused / 4 ? 1 : 0;
     }
+    if (argc >= 5 && argc <= 4 + CASCADE_MAX_CASCADES && !strcmp(argv[1], "large")) return large_trees(argc, argv);
     if (argc == 2 && !strcmp(argv[1], "shares")) {
         const int bad = wrong_shares();
         printf("%d shares begin elsewhere\n", bad);
         return bad ? 1 : 0;
     }
-    fprintf(stderr, "usage: host_rules packing SEED | trees SEED | shares | splits\n");
+    fprintf(stderr, "usage: host_rules packing SEED | trees SEED | large D CHUNK SIZE:PERIOD .. | shares | splits\n");
     return 2;
 }

@@ -649,6 +649,44 @@ def test_update_trees_of_many_cascades(oracle_mod, dtype, d, n_cascades):
     run.close()
 
 
+# Updates with a tree of more slots than a workgroup of 1024 threads moves (two slots for every d / 16 threads): dtype, d, sizes, periods, chunk
+LARGE_TREES = [(B.CASCADE_F32, 256, [130] * 8, None, 128), (B.CASCADE_BF16, 128, [512, 130, 130], [1, 20, 400], 500),
+               (B.CASCADE_BF16, 64, [1024, 130, 130], [1, 30, 900], 950)]
+
+
+@pytest.mark.parametrize("dtype,d,sizes,periods,chunk", LARGE_TREES)
+@pytest.mark.parametrize("token_selection", [1, 0])
+def test_update_trees_too_large_for_a_workgroup(oracle_mod, dtype, d, sizes, periods, chunk, token_selection):
+    """Direct updates that go through the staging array because their trees are too large: rows, scores, membership and the
+    counters of replaced items are those of Alg. 2 with the library's own scores."""
+    import torch
+    from gpu_harness import ParityRun, gpu_decision_scores, replay_is_exact
+    cfg = B.make_config(batch=1, n_q_heads=2, n_kv_heads=2, head_dim=d, dtype=dtype, n_sink=3, cascade_sizes=sizes, ema_beta=0.99,
+                        rope_base=10000.0, max_chunk=chunk, accept_period=periods, token_selection=token_selection, keep_update_scores=1)
+    run = ParityRun(cfg, one_step_ahead=True)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(d)
+    full = (130 << 8 if periods is None else 130 * periods[2] + 130 * periods[1] + sizes[0]) // chunk
+    for n in [41] + [chunk] * full:
+        run.advance_gpu_only(*(torch.randn((1, n, 2, d), generator=gen, device="cuda:0").to(run.gpu.torch_dtype) for _ in range(3)))
+    run.sync_oracle_from_gpu()
+    assert run.prev.count == 3 + sum(sizes)
+    rng = np.random.default_rng(d)
+    replaced = 0
+    for step, n in enumerate([chunk, chunk - 51, chunk]):
+        before = run.prev
+        rep = run.step(*_inputs(rng, cfg, n))
+        assert rep.replay_exact, step
+        for g in range(2):
+            after = []
+            replay_is_exact(cfg, before, run.prev, 0, g, gpu_decision_scores(run.prev, 0, g, before.count, n), state_out=after)
+            swaps = run.prev.swaps[0, g] - before.swaps[0, g]
+            assert np.array_equal(swaps, after[0].stats[:, 1]), (step, g)
+            replaced += int(swaps.sum())
+    assert (replaced > 0) == bool(token_selection)
+    run.close()
+
+
 @pytest.mark.parametrize("d", [48, 80, 96])
 def test_update_with_head_sizes_that_do_not_divide_a_wave(oracle_mod, d):
     """d / 16 threads move a row: three, five or six of them do not divide a wave, so the offers are not compared inside one."""
@@ -673,13 +711,51 @@ def test_decode_waves_refill_their_ring(oracle_mod, d, G):
     _decode_after_fill(cfg, [512, 512, 512], 5, seqs=[0, 41])
 
 
-@pytest.mark.parametrize("d,G,sizes", [(128, 4, [650, 400, 200]), (64, 8, [2100, 1300, 900]), (128, 8, [2100, 1300, 900])])
+@pytest.mark.parametrize("d,G,sizes", [
+    (128, 4, [650, 400, 200]), (64, 8, [2100, 1300, 900]), (128, 8, [2100, 1300, 900]), (128, 1, [2100, 1300, 900]), (128, 2, [2100, 1300, 900]),
+    (64, 1, [2100, 1300, 900]), (64, 2, [2100, 1300, 900]), (64, 4, [5000, 2500, 1500]), (128, 4, [5000, 2500, 1500]),
+])
 def test_decode_waves_hold_their_logits(oracle_mod, d, G, sizes):
-    """One split for each of 256 pairs, of about 40 or 137 tiles: more than eight waves hold in one register, or than 16 tiles a wave
-    that it holds at most for 8 heads (its logits then leave while copies are in flight, and the rest behind the last tile)."""
+    """One split for each of 256 pairs, of about 40, 137 or 283 tiles: more than eight waves hold in one register, in every form of the
+    kernel.  With 137 tiles for groups of 8 and 283 for groups of 4 a wave has one or more beyond the 16 or 32 that it holds (its
+    logits then leave while copies are in flight, and the rest behind the last tile)."""
     cfg = B.make_config(batch=64, n_q_heads=4 * G, n_kv_heads=4, head_dim=d, dtype=B.CASCADE_BF16, n_sink=5, cascade_sizes=sizes,
                         ema_beta=0.9, rope_base=10000.0, max_chunk=512, keep_update_scores=1)
     _decode_after_fill(cfg, [512] * (sum(c << i for i, c in enumerate(sizes)) // 512 + 1), 3, seqs=[0, 41])
+
+
+@pytest.mark.parametrize("G,size", [(2, 8400), (1, 16700)])
+def test_decode_waves_hold_many_logits(oracle_mod, G, size):
+    """The same for groups of 2 and 1, whose waves hold 64 and 128 tiles: one split for each of 2048 pairs, of 66 or 131 tiles a wave."""
+    import torch
+    from gpu_harness import ParityRun
+    d, dev = 64, "cuda:0"
+    cfg = B.make_config(batch=512, n_q_heads=4 * G, n_kv_heads=4, head_dim=d, dtype=B.CASCADE_BF16, n_sink=5, cascade_sizes=[size, size],
+                        ema_beta=0.9, rope_base=10000.0, max_chunk=1, keep_update_scores=1)
+    slots, total = 5 + 2 * size, 4 * size
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(G)
+    k, v = (torch.randn((512, 4, slots, d), generator=gen, device=dev, dtype=torch.bfloat16) for _ in range(2))
+    mu = torch.rand((512, 4, slots), generator=gen, device=dev) * (2.0 / slots)
+    row = torch.cat([torch.arange(5), torch.arange(total - 2 * size, total)]).to(torch.int32)
+    ids = row.to(dev).expand(512, 4, slots).contiguous()
+    st = B.cascade_init_state()
+    st.dev_k, st.dev_v, st.dev_mu, st.dev_ids = k.data_ptr(), v.data_ptr(), mu.data_ptr(), ids.data_ptr()
+    for i, n in enumerate([5, size, size]):
+        st.counts[i] = n
+    st.t, st.n_seen = total - 5, total
+    seqs = [0, 301]
+    run = ParityRun(cfg, one_step_ahead=True, init_state=st, seqs=seqs)
+    run.fed.add_initial(row.numpy(), *({(b, g): x[b, g].float().cpu().numpy() for b in seqs for g in range(4)} for x in (k, v)))
+    del k, v, mu, ids
+    run.sync_oracle_from_gpu()
+    rng = np.random.default_rng(G)
+    tol_out, tol_score = _tolerances(cfg)
+    for step in range(3):
+        rep = run.step(*_inputs(rng, cfg, 1), decode=True)
+        assert rep.replay_exact, step
+        assert rep.out_err <= tol_out and rep.score_err <= tol_score, (step, rep)
+    run.close()
 
 
 @pytest.mark.parametrize("d,G,sizes", [(128, 1, [130, 60]), (128, 4, [130, 60]), (128, 8, [130, 60]), (64, 4, [300, 150])])
@@ -740,6 +816,24 @@ def test_f32_matrix_kernels(oracle_mod, d, G, Hkv, sizes, reduce_mean, chunks):
                         ema_beta=0.95, rope_base=10000.0, max_chunk=64, keep_update_scores=1,
                         head_reduce=B.CASCADE_REDUCE_MEAN if reduce_mean else B.CASCADE_REDUCE_MAX)
     rng = np.random.default_rng(d + G)
+    run = ParityRun(cfg, one_step_ahead=True)
+    out_tol, score_tol = _tolerances(cfg)
+    for step, n in enumerate(chunks):
+        rep = run.step(*_inputs(rng, cfg, n))
+        assert rep.replay_exact, step
+        assert rep.out_err <= out_tol and rep.score_err <= score_tol, (step, rep)
+    run.close()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("chunks", [[128, 128, 128], [129, 160, 129]])
+def test_f32_launches_of_256_and_more_row_blocks(oracle_mod, d, chunks):
+    """16 pairs of two query heads: 128 tokens are 256 blocks of 16 rows, the most that take sixteen waves a block at head size 64, 129
+    tokens are 272 blocks and 160 are 320, which take eight; a small cache whose runs end inside tiles."""
+    from gpu_harness import ParityRun
+    cfg = B.make_config(batch=2, n_q_heads=16, n_kv_heads=8, head_dim=d, dtype=B.CASCADE_F32, n_sink=3, cascade_sizes=[170, 61],
+                        ema_beta=0.95, rope_base=10000.0, max_chunk=160, keep_update_scores=1)
+    rng = np.random.default_rng(d + chunks[0])
     run = ParityRun(cfg, one_step_ahead=True)
     out_tol, score_tol = _tolerances(cfg)
     for step, n in enumerate(chunks):

@@ -261,6 +261,15 @@ def test_update_trees_are_independent(host_rules, seed):
     assert res.returncode == 0, res.stdout + res.stderr
 
 
+def test_trees_too_large_for_a_workgroup(host_rules):
+    """The updates that the device test of oversized trees makes are direct, and no workgroup takes their trees."""
+    from test_gpu_parity_small import LARGE_TREES
+    for _, d, sizes, periods, chunk in LARGE_TREES:
+        rings = [f"{n}:{p}" for n, p in zip(sizes, periods or [1 << i for i in range(len(sizes))])]
+        res = subprocess.run([host_rules, "large", str(d), str(chunk)] + rings, capture_output=True, text=True, timeout=120)
+        assert res.returncode == 0, (d, res.stdout + res.stderr)
+
+
 def test_shares_of_the_largest_caches(host_rules):
     """The tiles of a row block divided over up to 256 workgroups: whole ranges, for as many tiles as a cache can have."""
     res = subprocess.run([host_rules, "shares"], capture_output=True, text=True, timeout=120)
