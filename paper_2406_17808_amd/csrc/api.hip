@@ -69,8 +69,8 @@ static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 static int decode_splits(const Geom& g, bool f32)
 {
     // the most a step may be split into: enough workgroups to fill 256 compute units several times over, at
-    // least 128 rows (a tile per wave of the MFMA kernel; fp32: 256) each; decode_split_count takes what suits the
-    // rows cached
+    // least 128 rows each (four tiles: half of the eight waves of the bf16 kernel have one; fp32: 256, two rounds of four);
+    // decode_split_count takes what suits the rows cached.  (Smaller shares were not measured.)
     int s = (2048 + g.B * g.Hkv - 1) / (g.B * g.Hkv);
     const int max_s = f32 ? (g.slots + 255) / 256 : (g.slots + 127) / 128;
     if (s > max_s) s = max_s;
@@ -493,7 +493,7 @@ extern "C" int cascade_prefill_chunk(cascade_ctx* ctx, const void* dev_q, const 
     {
         Timed t(ctx, CASCADE_K_PREP, s);
         // bf16: rotated query copies are written for the rows the exact score pass reads (none with single-pass
-        // scores); the attention kernel reads them where they cover the chunk, and otherwise rotates its queries itself
+        // scores); the attention kernel reads them for row blocks whose rows all have copies, and otherwise rotates its queries itself
         if (!ctx->mfma) launch_prep(g, ctx->dtype, ctx->buf, sl, Q, qscale, dev_q, dev_k, dev_v, s);
         else {
             if (lay.full && packed_tiles_of(sl) != lay.cache_tiles + (Q + 63) / 64)

@@ -75,6 +75,9 @@ __device__ inline void add_visible(const float* __restrict__ vbase, int k0, int 
 // with a partial result that merge_f32_kernel combines.  Against one workgroup a row block, V element by element and the segments
 // read one after the other, us a call: d = 64, one head, chunks of 32: 260 slots 30.1 -> 25.7 (with the update in one launch), 16K slots
 // 271 -> 52; d = 128, one head, one row on 16K slots 554 -> 53; 128 rows of 32 heads on 1K slots 130 -> 123.  67 forms: 1.005 at least, 1.58 in the median.
+// The bound on registers (128 at d = 64) lets a CU hold two workgroups of eight waves.  It spills four to six registers, outside the
+// loop over the tiles; with 138 registers, none spilled and one workgroup a CU, 320 row blocks on 192 slots took 63.7 us a call
+// instead of 60.1, 1024 on 128 slots 88.5 instead of 80.2.
 
 // The segments cut into 16-key tiles: first tile of every segment (INT32_MAX behind the last, which is the chunk).
 struct F32Tiles {

@@ -734,9 +734,9 @@ bool update_is_direct(const Geom& g, const DevBuffers& b, const UpdatePlan& pl)
     return total <= b.move_stage_rows;
 }
 
-// `direct`: no plan_kernel has run; the gather launch decides the segments itself (update_is_direct)
-// A direct update whose trees fit workgroups: as few threads as hold the largest tree (four cascades with the default
-// periods: 15 slots).  Larger ones (more than eight cascades at d = 128) go through the staging array.
+// A direct update whose trees fit workgroups: as few threads as hold the largest tree.  The trees of N cascades with the default
+// periods have up to 2^N - 1 slots; false where a tree has more than 1024 threads hold, d / 16 of them for two slots (from ten
+// cascades on at d = 64, nine at 128, eight at 256, fewer with long periods): such updates go through the staging array.
 template <typename T>
 static bool moves_of_trees(const Geom& g, const DevBuffers& b, const UpdatePlan& pl, int max_chunk, const void* k, const void* v, int k_token_stride,
                            int k_batch_stride, hipStream_t s)
@@ -759,6 +759,7 @@ static bool moves_of_trees(const Geom& g, const DevBuffers& b, const UpdatePlan&
     return false;
 }
 
+// `direct`: no plan_kernel has run; the launches decide the segments themselves (update_is_direct)
 void launch_moves(const Geom& g, int dtype, const DevBuffers& b, const UpdatePlan& pl, int max_chunk,
                   const void* k, const void* v, int k_token_stride, int k_batch_stride, bool direct, hipStream_t s)
 {

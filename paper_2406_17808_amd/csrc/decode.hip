@@ -181,14 +181,16 @@ struct OwnLogits {
 // Bound by memory where the cache is large, by the latency of one tile where it is small.  At 8K slots and 8 KV heads a
 // workgroup ended 10.0 us after it began: 3.4 until its last copy was issued (a scalar load for every run in the list, two
 // 64-bit divisions), 1.5 for queries that came behind the tiles, 2.2 for the second tile, 2.0 where a wave had a third;
-// now 6.0, in the splits with a tile more 7.1.  us a step with decode_finish, before and after: 8K slots 19.1 -> 14.2, a layer of
-// 4K slots 16.2 -> 11.9 (where the host's calls are the limit), 8 sequences of 16K slots 109.6 -> 103.8.
+// now 6.0, in the splits with a tile more 7.1.  us a step with decode_finish, timed as calls of a program, before and after: 8K
+// slots 19.1 -> 14.2, a layer of 4K slots 16.2 -> 11.9 (where the host's calls are the limit), 8 sequences of 16K slots 109.6 ->
+// 103.8 (with the logits written tile by tile).
 //
 // On a large cache the logits cost far more than their bytes: without their stores (a sixteenth of the bytes read,
 // for groups of 4) a step of 32 sequences of 65K slots took 1312 us, with them 1660: memory turns round for every
 // few of them.  So a wave keeps the logits of HOLD tiles in registers and writes them at once, past the L2, which would put
 // the lines out one by one later on: 8 tiles 1607, 16 tiles 1565, 32 tiles (R = 8) 1520, 40 to 48 the same; 32 tiles by way
-// of the L2 1623.  8 sequences of 16K slots 105.4 -> 95.5.  No lane is moved for it: the queries stand in all column groups of
+// of the L2 1623 (groups of 4; R = 8 holds 128, 64 and 16 tiles for groups of 1, 2 and 8).  8 sequences of 16K slots 105.4 -> 95.5.
+// (These are steps in a stream of steps; calls of a program with 8K slots take 1 us more.)  No lane is moved for it: the queries stand in all column groups of
 // the product, so each group of MAXG columns keeps the tile that is its turn.  Where no wave has more tiles than one
 // register holds, R = 1 does it, which is 0.4 to 0.8 us less (8K slots 13.9 -> 13.2, before 13.1; 32 sequences, 40
 // tiles a workgroup, one head a KV head 35.4 -> 34.3); its few stores go through the L2 but for groups of 8 (one head 34.2 us

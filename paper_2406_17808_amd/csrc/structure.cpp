@@ -145,7 +145,7 @@ static int cut_of(int cap, int xi) { return std::min(32, (cap - xi) / 2); }
 // physical slot index, so within a run where (cache index - slot index) is constant the
 // queries need one rotation: by (own index) - (that constant).  The segments are listed in
 // physical order (the wrapped part of a ring before its oldest part): attention does not care
-// in which order it meets the keys, and a full cache then always reads front to back.  The
+// in which order it meets the keys, but for the rounding of its sums, and a full cache then always reads front to back.  The
 // wrapped part of a full ring is listed as [0, o) and [o, xi), o = xi mod 64, which fixes the
 // place of every 64-row tile of the ring (see PackedLayout, also for the other cut).
 void build_segments(const Geom& g, const HostState& st, bool with_chunk, int Q, SegList& out, bool fixed)
@@ -239,18 +239,21 @@ void plan_trees(const UpdatePlan& plan, int capacity, MoveTrees& out)
 
 // Splits of a decode step: as many as make the busiest compute unit finish first.  A CU holds one workgroup of
 // the bf16 kernels (their rings fill the LDS); a workgroup costs about as much as two rounds of four tiles besides (first
-// copies, queries, epilogue).  Where the shares differ by a tile, half a tile is charged.  The rule's count / the best of up to 29,
-// us a step: bf16, d = 128, 8 KV heads: 8K slots 13.4 / 12.8 (24 splits), 16K 16.9 / 17.0, 64K 53.1 / 51.9 (24); 16 heads of 8K
-// 17.8 / 18.0; 64 of 16K 104.8 / 104.2; 256 of 8K 221 / 211 (5); d = 64, 8 heads of 16K 13.1 / 12.5, 64 of 16K 61.2 / 59.1.
-// fp32 (four tiles at a time): d = 128, 8 heads of 4K 46.7 / 46.4, 64 of 4K 117 / 126, 256 of 2K 267 / 280; d = 64, 8 of 4K
-// 31.9 / 31.7, but 64 of 4K 84.6 / 58.3 (11 splits).
-// Where even then there are hundreds of tiles for each of four waves, more rounds even out the CUs (256 x 65K slots: 8 splits 1656, 1 split 1676; all
-// these before the attend kernel held its logits back, which takes up to a tenth off the large ones).
+// copies, queries, epilogue).  Where the shares differ by a tile, half a tile is charged.  Where even then there are hundreds
+// of tiles for each of four waves, more rounds even out the CUs.  All of this was fitted to kernels of four waves, which the bf16
+// ones no longer are.  With the present kernels, the rule's count / the best of up to 22, us a step in a stream of steps (in
+// brackets the best count where the rule is off by more than 2 %):
+// bf16, d = 128, 4 query heads: 8 KV heads: 4K slots 11.0 / 11.2, 8K 13.3 / 12.8 (24), 16K 16.8 / 16.9, 64K 51.5 / 49.2 (24); 16 heads
+// of 8K 17.8 / 17.7; 64 of 16K 96.2 / 93.7 (3); 128 of 4K 52.2 / 52.0; 256 of 2K 55.9 / 56.4, of 8K 198 / 197, of 64K 1526 / 1523 (one
+// split 1530); one head of 64K 21.4 / 16.7 (128).  One query head: 64 of 16K 88.0 / 87.9, 256 of 8K 189 / 183 (6).  Eight: 102.2 / 102.0,
+// 217 / 212 (3).  d = 64: 8 heads of 16K 13.2 / 12.7 (28), 64 of 16K 57.2 / 54.5 (3), 128 of 4K 30.7 / 30.5, 512 of 4K 119 / 120.
+// fp32 (four tiles at a time): d = 128: 8 heads of 4K 42.4 / 42.0, of 16K 33.2 / 33.5 (one query head), 64 of 4K 105 / 109, 256 of 2K
+// 248 / 253; d = 64: 8 of 4K 27.7 / 27.7, 64 of 4K 76.3 / 52.2 (12), 256 of 2K 167 / 98 (3).
 // For a given number of rounds the cost falls with every split, so only the most splits of each number of
 // rounds are looked at: nine at most, 0.05 us of host time a step (all of up to 2048 split counts: 9.7).
 int decode_split_count(int pairs, int most, int n_tiles)
 {
-    constexpr int kWaves = 4, kCus = 256;     // (a tile of four waves at a time: fp32; the bf16 kernels have eight)
+    constexpr int kWaves = 4, kCus = 256;     // (four tiles at a time, as in fp32; the bf16 kernels take eight)
     if (n_tiles == 0) return 1;
     int best = 1;
     float best_cost = -1.f;
